@@ -213,10 +213,10 @@ int tc_fmm_get_pairs(tc_ctx *ctx, int32_t *m2l, int32_t *p2p);
 
 /* How a group's walk is spread over waves, for sizes with fewer walk groups
  * than the GPU keeps waves resident, where one wave per group leaves a lone,
- * latency-bound walk per SIMD.  mode 1 (the default): for n <= 163840 a
- * block of 4 waves shares each group's walk (the cells of one level, 5 to 7
- * by n and dim, dealt out among them) and adds their FP32 partial sums in
- * FP64 in wave order.  mode 2: for n <= 12288 in 3D and n <= 24576 in 2D
+ * latency-bound walk per SIMD.  mode 1 (the default): for n <= 524288 in 3D
+ * and n <= 163840 in 2D a block of 2 to 8 waves (by n and dim) shares each
+ * group's walk and list and adds their FP32 partial sums in FP64 in wave
+ * order.  mode 2: for n <= 12288 in 3D and n <= 24576 in 2D
  * each group's walk is cut into one task per (level-1 cell, child) (64 in
  * 3D, 16 in 2D) whose FP32 partial sums are added in FP64 in a fixed order,
  * and above that as mode 1.  mode 0: one wave per group at any n.  The

@@ -472,8 +472,7 @@ int do_forces(tc_ctx* ctx, double G, double eps) {
                                       (float)G, (float)(eps * eps), ctx->prm(), ctx->at<float>(l.off_acc),
                                       ctx->at<float>(l.off_pot), ctx->at<int64_t>(l.off_m2p),
                                       ctx->at<int64_t>(l.off_p2p), ctx->at<int64_t>(l.off_tests), ctx->plain_acc,
-                                      ctx->split != 0,
-                                      ctx->at<uint32_t>(l.off_lvl_off), ctx->stream));
+                                      ctx->split != 0, ctx->stream));
     }
     if (ctx->timing) {
         TC_HIP(ctx, hipEventRecord(e1, ctx->stream));

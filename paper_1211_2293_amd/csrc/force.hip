@@ -29,6 +29,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <atomic>
 
 namespace tc {
 namespace {
@@ -40,21 +41,14 @@ constexpr int kWavesPerBlock = 4;
 // root alone for a whole walk) and sum its list into a, counting the cell
 // entries in nm2p and the body entries in np2p.  The group's box is
 // [lo, hi], its FP32 origin (rx, ry, rz), this lane's body (xi, yi, zi).
-// With NP > 1 (a walk from the root shared by NP waves) this wave walks
-// part `part` of it: the cells above the deal level (level-order indices
-// below deal_lo) are tested by every part but their entries kept by part 0
-// only; the cells of the deal level ([deal_lo, deal_hi) in level order) are
-// dealt out by index modulo NP; everything deeper follows its ancestor at
-// the deal level.  The parts' lists together are the whole walk's.
-// STAGED: the list sums in staged batches (flush).
-template <int D, bool PLAIN, bool QUAD, int NP = 1, bool STAGED = false, int STEP = 8>
+template <int D, bool PLAIN, bool QUAD, int STEP = 8>
 __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, const float4* __restrict__ walkq,
                                            const Body* __restrict__ bodies, const float4* __restrict__ bodies32,
                                            float4* L, uint32_t* S, float4* LQ, int lpl_log2, float eps2,
                                            double lox, double hix, double loy, double hiy, double loz, double hiz,
                                            double rx, double ry, double rz, float xi, float yi, float zi,
                                            uint32_t first, int first_len, Acc& a, int64_t& nm2p, int64_t& np2p,
-                                           int64_t& ntest, int part = 0, uint32_t deal_lo = 0, uint32_t deal_hi = 0) {
+                                           int64_t& ntest) {
     constexpr int R = D == 3 ? 8 : 4;                    // lanes (cells) per popped range
     constexpr int RP = kWave / R;                        // ranges per full round
     constexpr int kReserve = (R - 1) * (D == 3 ? 21 : 31) + R;
@@ -71,7 +65,6 @@ __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, co
         // memory round trips of a round overlap.
         int top = 0;
         bool vc = lane < first_len;
-        uint32_t cidx = first + (uint32_t)lane;              // level-order index of the tested cell
         WalkCell wc = load_cell(walk, first + (uint32_t)lane, vc);
         float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0;   // quadrupole of the tested cell
         if (QUAD && vc) {
@@ -88,14 +81,11 @@ __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, co
                 const double dzm = fmax(fmax(loz - wc.cz, 0.0), wc.cz - hiz);
                 d2 = d2 + dzm * dzm;
             }
-            const bool own = vc && (NP == 1 || cidx < deal_lo || cidx >= deal_hi || (int)(cidx % NP) == part);
-            const bool emit = NP == 1 || cidx >= deal_lo || part == 0;
-            const bool leaf = own && wc.b < 0;
-            const bool acc0 = own && d2 > wc.rcrit2;
-            const bool opened = own && !acc0 && !leaf;
-            const bool accept = acc0 && emit;
-            const bool direct = leaf && !acc0 && emit;
-            ntest += __popcll(__ballot(own && emit));    // each tested cell once over the parts
+            const bool leaf = vc && wc.b < 0;
+            const bool accept = vc && d2 > wc.rcrit2;
+            const bool opened = vc && !accept && !leaf;
+            const bool direct = leaf && !accept;
+            ntest += __popcll(__ballot(vc));
 
             // push the children ranges of opened cells
             const uint64_t O = __ballot(opened);
@@ -107,7 +97,6 @@ __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, co
             // reserve is free) and start loading its cells
             more = top > 0;
             bool vcn = false;
-            uint32_t cidxn = 0;
             WalkCell wcn;
             float4 q0n = make_float4(0.f, 0.f, 0.f, 0.f), q1n = q0n;
             if (more) {
@@ -118,7 +107,6 @@ __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, co
                 top -= nr;
                 const int rlen = (int)(packed & 7u) + 1;
                 vcn = rr < nr && j < rlen;
-                cidxn = (packed >> 3) + j;
                 wcn = load_cell(walk, (packed >> 3) + j, vcn);
                 if (QUAD && vcn) {
                     const uint32_t bq = (packed >> 3) + j;
@@ -147,7 +135,7 @@ __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, co
                 nm2p += na;
             } else if (na) {
                 if (len + na > kListCap) {
-                    flush<D, PLAIN, STAGED, STEP>(L, len, xi, yi, zi, eps2, a);
+                    flush<D, PLAIN, false, STEP>(L, len, xi, yi, zi, eps2, a);
                     len = 0;
                 }
                 if (accept)
@@ -178,7 +166,7 @@ __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, co
                         tot += cl;
                     }
                     if (len + tot > kListCap) {
-                        flush<D, PLAIN, STAGED, STEP>(L, len, xi, yi, zi, eps2, a);
+                        flush<D, PLAIN, false, STEP>(L, len, xi, yi, zi, eps2, a);
                         len = 0;
                     }
                     if (jj < my_cnt)
@@ -195,7 +183,7 @@ __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, co
                     for (int o = 0; o < cl; o += kWave) {
                         const int m = min(kWave, cl - o);
                         if (len + m > kListCap) {
-                            flush<D, PLAIN, STAGED, STEP>(L, len, xi, yi, zi, eps2, a);
+                            flush<D, PLAIN, false, STEP>(L, len, xi, yi, zi, eps2, a);
                             len = 0;
                         }
                         if (lane < m) L[len + lane] = body_entry(bodies, bodies32, bl + o + lane, rx, ry, rz);
@@ -207,13 +195,12 @@ __device__ __forceinline__ void walk_group(const WalkCell* __restrict__ walk, co
             wave_lds_sync();
             wc = wcn;
             vc = vcn;
-            cidx = cidxn;
             if (QUAD) {
                 q0 = q0n;
                 q1 = q1n;
             }
         }
-        flush<D, PLAIN, STAGED, STEP>(L, len, xi, yi, zi, eps2, a);
+        flush<D, PLAIN, false, STEP>(L, len, xi, yi, zi, eps2, a);
         if (QUAD) flush_quad<PLAIN>(LQ, qlen, xi, yi, zi, eps2, a);
 }
 
@@ -268,7 +255,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
 
             Acc a = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             int64_t nm2p = 0, np2p = 0, ntest = 0;
-            walk_group<D, PLAIN, QUAD, 1, false, STEP>(walk, walkq, bodies, bodies32, L, S, LQ, lpl_log2, eps2, lox,
+            walk_group<D, PLAIN, QUAD, STEP>(walk, walkq, bodies, bodies32, L, S, LQ, lpl_log2, eps2, lox,
                                                        hix, loy, hiy, loz, hiz, rx, ry, rz, xi, yi, zi, 0u, 1, a, nm2p,
                                                        np2p, ntest);
 
@@ -300,100 +287,280 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
 
 // Small and mid-size problems: with fewer groups than resident waves, every
 // wave walks its group alone on its SIMD and the walk's latency sets the
-// time.  Here a block of NW waves takes one group at a time
-// (positions of the cost order of k_group_order, strided by the grid):
-// each wave walks its part of the tree (walk_group with NP parts, the cells
-// of level `deal` dealt out) and sums its own list, and the parts' FP32 sums
-// are added in FP64 in wave order.  The interactions and counts are those
-// of the one-wave walk; only the summation order differs.  The near field,
-// where most of a group's list comes from, lies in a few cells around the
-// group, so a shallow deal level leaves one part with most of the work
-// (3D Plummer, 65,536 bodies: 1.15x over one wave dealing level 3, 1.7x
-// dealing level 5 or 6); one too deep leaves the parts repeating the walk
-// above it.  coop_deal_level holds the measured choice, coop_waves the
-// number of waves (NW) per group.
-template <int D, bool PLAIN, bool QUAD, int NW>
-__global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(QUAD ? 4 : 5, 8))) k_walk_force_coop(
+// time.  Here a block of NW waves takes one group at a time and shares both
+// halves of its work evenly: the walk goes breadth first with one lane per
+// cell over the whole block (NW 64 cells a round, from one LDS stack of
+// ranges), and what it finds goes to one LDS list (cells at once, unaccepted
+// leaves to a queue whose bodies are copied together), which the waves sum
+// in equal contiguous parts whenever it is full.  Places come from prefix
+// sums over the lanes and waves, so the list's order, and with it every sum,
+// is the same in each run; the waves' FP32 sums are added in FP64 in wave
+// order.  The interactions and counts are those of the one-wave walk; only
+// the summation order differs.
+// What bounds it: about a dozen dependent rounds (the tree's depth; a cell
+// load and two barriers each) and then the list's arithmetic.  Dealing the
+// cells of one level among waves that each walk and sum alone instead left
+// the parts unequal, the near field lying in a few cells around the group
+// (3D Plummer, theta 0.5, whole force evaluation: 110 us at 10,000 bodies,
+// 239 at 50,000, 334 at 100,000 and 510 at 160,000 so; 61, 149, 219 and 345
+// shared evenly).  coop_shape holds the measured NW and H.
+template <int D, bool QUAD, int NW>
+struct BlockWalk {
+    static constexpr int kThreads = NW * kWave;
+    static constexpr int R = D == 3 ? 8 : 4;                          // cells per range
+    static constexpr int kReserve = (R - 1) * (D == 3 ? 21 : 31) + R;
+    static constexpr int kStack = NW <= 2 ? 512 : 4 * kThreads;       // ranges
+    static constexpr int kList = NW <= 2 || (QUAD && NW <= 4) ? 512 : NW <= 4 || QUAD ? 1024 : 2048;   // entries (16 B)
+    static constexpr int kQuad = QUAD ? kThreads : 0;                 // entries with quadrupole (48 B)
+    static_assert(kStack > kReserve + kThreads, "stack too small for its bound");
+    static_assert(kList >= kThreads && kList % 8 == 0, "a round's cells must fit the list");
+    static_assert(kList * sizeof(float4) >= NW * 4 * kWave * sizeof(double), "the waves' sums reuse the list");
+};
+
+template <int D, bool PLAIN, bool QUAD, int NW, int H>
+__global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW <= 4 ? 5 : 4, 8))) k_walk_force_coop(
     const WalkCell* __restrict__ walk, const float4* __restrict__ walkq, const Body* __restrict__ bodies,
     const float4* __restrict__ bodies32, const uint32_t* __restrict__ perm, const int32_t* __restrict__ gbeg,
-    const int32_t* __restrict__ gcnt, const uint32_t* __restrict__ order, uint32_t* __restrict__ bcost,
-    const uint32_t* __restrict__ lvl_off, int deal, int lpl_log2, float G, float eps2,
-    const DevParams* __restrict__ prm,
+    const int32_t* __restrict__ gcnt, const uint32_t* __restrict__ order, uint32_t* queue,
+    uint32_t* __restrict__ bcost, int lpl_log2, float G, float eps2, const DevParams* __restrict__ prm,
     float* __restrict__ acc, float* __restrict__ pot, int64_t* __restrict__ m2p_out, int64_t* __restrict__ p2p_out,
     int64_t* __restrict__ tst_out) {
-    constexpr int kCoopParts = NW;
-    __shared__ float4 s_list[NW][kListCap];
-    __shared__ uint32_t s_stack[NW][kStackCap];
-    __shared__ float4 s_qlist[NW][QUAD ? 3 * kQuadCap : 1];
-    __shared__ double s_part[NW - 1][4][kWave];
-    __shared__ int64_t s_cnt[NW - 1][3];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
-    const uint32_t deal_lo = lvl_off[deal], deal_hi = lvl_off[deal + 1];   // the cells dealt out
-    // blocks take the positions of order in strides of the grid
-    for (uint32_t pos = blockIdx.x; pos < prm->ngroups; pos += gridDim.x) {
-        const uint32_t g = order[pos];
-        const int64_t i0 = gbeg[g];
-        const int gn = gcnt[g];
-        const int64_t i = i0 + lane;
-        const bool valid = lane < gn;
-        const Body me = bodies[valid ? i : i0];
-        const double lox = uniform(wave_min(me.x)), hix = uniform(wave_max(me.x));
-        const double loy = uniform(wave_min(me.y)), hiy = uniform(wave_max(me.y));
-        const double loz = D == 3 ? uniform(wave_min(me.z)) : 0.0;
-        const double hiz = D == 3 ? uniform(wave_max(me.z)) : 0.0;
-        const double rx = (lox + hix) * 0.5, ry = (loy + hiy) * 0.5, rz = (loz + hiz) * 0.5;
-        const float xi = (float)(me.x - rx), yi = (float)(me.y - ry), zi = (float)(me.z - rz);
+    using B = BlockWalk<D, QUAD, NW>;
+    constexpr int R = B::R, T = B::kThreads;
+    __shared__ float4 L[B::kList];
+    __shared__ uint32_t S[B::kStack];
+    __shared__ float4 LQ[QUAD ? 3 * B::kQuad : 1];
+    __shared__ int2 s_leaf[T];                       // queued leaves: first body, count
+    __shared__ uint32_t s_loff[T];                   // their first places
+    __shared__ uint64_t s_cnt[NW];
+    __shared__ uint32_t s_sum[NW];
+    __shared__ uint32_t s_next;
+    const int t = (int)threadIdx.x, lane = t & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+    const int lpl = 1 << lpl_log2, slot = t >> lpl_log2, jj = t & (lpl - 1), slots = T >> lpl_log2;
 
-        Acc a = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        int64_t nm2p = 0, np2p = 0, ntest = 0;
-        walk_group<D, PLAIN, QUAD, kCoopParts, true>(walk, walkq, bodies, bodies32, s_list[wv], s_stack[wv], s_qlist[wv],
-                                               lpl_log2, eps2, lox, hix, loy, hiy, loz, hiz, rx, ry, rz, xi, yi, zi,
-                                               0u, 1, a, nm2p, np2p, ntest, wv, deal_lo, deal_hi);
-        double px = (double)a.sx + (double)a.cx, py = (double)a.sy + (double)a.cy;
-        double pz = (double)a.sz + (double)a.cz, pp = (double)a.sp + (double)a.cp;
-        if (wv > 0) {
-            s_part[wv - 1][0][lane] = px;
-            s_part[wv - 1][1][lane] = py;
-            s_part[wv - 1][2][lane] = pz;
-            s_part[wv - 1][3][lane] = pp;
-            if (lane == 0) {
-                s_cnt[wv - 1][0] = nm2p;
-                s_cnt[wv - 1][1] = np2p;
-                s_cnt[wv - 1][2] = ntest;
-            }
+    // Blocks are scheduled like the one-wave kernel's waves (GroupSched over
+    // the positions of order, longest walks first in each XCD's share).
+    // With H > 1 a group is H tasks of 64 / H bodies each: every task walks
+    // for the whole group, and each of a wave's H lane parts sums its share
+    // of the list for the task's bodies.
+    const GroupSched sched{queue, prm->ngroups * (uint32_t)H, blockIdx.x / kXcd, (int)(blockIdx.x % kXcd), 1};
+    // Without an order the tasks are dealt out in strides of the grid.
+    constexpr int kBodies = kWave / H;
+    for (int hop = 0; hop < (order ? kXcd : 1); ++hop) {
+        const int xq = (sched.home + hop) % kXcd;
+        const uint32_t g_hi = order ? sched.share_lo(xq + 1) : sched.ng;
+        if (wv == 0) {
+            const uint32_t f = order ? sched.first(xq, hop) : blockIdx.x;
+            if (lane == 0) s_next = f;
         }
         __syncthreads();
-        if (wv == 0) {
-            for (int w = 0; w < kCoopParts - 1; ++w) {
-                px += s_part[w][0][lane];
-                py += s_part[w][1][lane];
-                pz += s_part[w][2][lane];
-                pp += s_part[w][3][lane];
-                nm2p += s_cnt[w][0];
-                np2p += s_cnt[w][1];
-                ntest += s_cnt[w][2];
+        uint32_t pos = s_next;
+        while (pos < g_hi) {
+            const uint32_t g = order ? order[pos / H] : pos / H;
+            const int64_t i0 = gbeg[g];
+            const int gn = gcnt[g];
+            const Body me = bodies[lane < gn ? i0 + lane : i0];
+            const double lox = uniform(wave_min(me.x)), hix = uniform(wave_max(me.x));
+            const double loy = uniform(wave_min(me.y)), hiy = uniform(wave_max(me.y));
+            const double loz = D == 3 ? uniform(wave_min(me.z)) : 0.0;
+            const double hiz = D == 3 ? uniform(wave_max(me.z)) : 0.0;
+            const double rx = (lox + hix) * 0.5, ry = (loy + hiy) * 0.5, rz = (loz + hiz) * 0.5;
+            // the body this lane sums for, and whether it is the one to store it
+            const int own = (int)(pos % H) * kBodies + lane % kBodies;
+            const bool valid = own < gn && lane < kBodies;
+            float xi = (float)(me.x - rx), yi = (float)(me.y - ry), zi = (float)(me.z - rz);
+            if (H > 1) {
+                xi = __shfl(xi, own, kWave);
+                yi = __shfl(yi, own, kWave);
+                zi = __shfl(zi, own, kWave);
             }
-            if (valid) {
-                // the body met itself once as a direct entry (in one of the
-                // parts): its -m/eps potential term is removed as in the
-                // one-wave kernel
-                const float mself = (float)me.m;
-                pp += (double)(mself * __builtin_amdgcn_rsqf(eps2));
-                const int64_t o = perm[i];
-                acc[o * D + 0] = (float)((double)G * px);
-                acc[o * D + 1] = (float)((double)G * py);
-                if (D == 3) acc[o * D + 2] = (float)((double)G * pz);
-                pot[o] = (float)((double)G * pp);
-                const int64_t lc = nm2p + np2p;
-                bcost[o] = lc > 0xffffffffll ? 0xffffffffu : (uint32_t)lc;
+
+            Acc a = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            int64_t nm2p = 0, np2p = 0, ntest = 0;
+            int len = 0, qlen = 0, nleaf = 0, top = 1;
+
+            bool drain = false;                      // the list or the leaf queue is full
+
+            if (t == 0) S[0] = 0u;                   // the root alone
+            __syncthreads();
+            for (;;) {
+                if (drain || top == 0) {
+                    // the queued leaves' bodies into the list: lpl lanes per
+                    // leaf, places from the scanned counts, in windows that
+                    // fit the list; each window is summed with what is there
+                    const uint32_t c = t < nleaf ? (uint32_t)s_leaf[t].y : 0u;
+                    uint32_t x = c;
+#pragma unroll
+                    for (int o = 1; o < kWave; o <<= 1) {
+                        const uint32_t y = __shfl_up(x, o, kWave);
+                        if (lane >= o) x += y;
+                    }
+                    if (lane == kWave - 1) s_sum[wv] = x;
+                    __syncthreads();
+                    uint32_t before = 0, total = 0, done = 0;
+                    for (int w = 0; w < NW; ++w) {
+                        const uint32_t v = s_sum[w];
+                        if (w < wv) before += v;
+                        total += v;
+                    }
+                    s_loff[t] = before + x - c;
+                    __syncthreads();
+                    do {
+                        const uint32_t end = min(total, done + (uint32_t)(B::kList - len));
+                        for (int s0 = slot; s0 < nleaf; s0 += 2 * slots) {
+                            int32_t from[2], to[2], at[2];
+                            float4 e[2];
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) {
+                                const int s = s0 + u * slots;
+                                const int2 lf = s < nleaf ? s_leaf[s] : make_int2(0, 0);
+                                const int32_t o = s < nleaf ? (int32_t)s_loff[s] : 0;
+                                const int32_t k0 = max(0, (int32_t)done - o);
+                                from[u] = lf.x + k0 + jj;
+                                to[u] = lf.x + min(lf.y, (int32_t)end - o);
+                                at[u] = len + o + k0 + jj - (int32_t)done;
+                            }
+#pragma unroll
+                            for (int u = 0; u < 2; ++u)
+                                if (from[u] < to[u]) e[u] = body_entry(bodies, bodies32, from[u], rx, ry, rz);
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) {
+                                if (from[u] < to[u]) L[at[u]] = e[u];
+                                // leaves larger than lpl
+                                for (int32_t j = from[u] + lpl, p = at[u] + lpl; j < to[u]; j += lpl, p += lpl)
+                                    L[p] = body_entry(bodies, bodies32, j, rx, ry, rz);
+                            }
+                        }
+                        len += (int)(end - done);
+                        done = end;
+                        __syncthreads();
+                        // the waves' parts of the list: contiguous, equal, whole rounds of 8 H
+                        const int per = ((len + NW - 1) / NW + 8 * H - 1) & ~(8 * H - 1);
+                        const int cnt = min(per, len - wv * per);
+                        if (cnt > 0) flush<D, PLAIN, true, 8, H>(L + wv * per, cnt, xi, yi, zi, eps2, a);
+                        len = 0;
+                        __syncthreads();
+                    } while (done < total);
+                    np2p += total;
+                    nleaf = 0;
+                    if (QUAD) {
+                        const int per = ((qlen + NW - 1) / NW + 8 * H - 1) & ~(8 * H - 1);
+                        const int cnt = min(per, qlen - wv * per);
+                        if (cnt > 0) flush_quad<PLAIN, H>(LQ + 3 * wv * per, cnt, xi, yi, zi, eps2, a);
+                        qlen = 0;
+                        __syncthreads();
+                    }
+                    drain = false;
+                    if (top == 0) break;
+                }
+                // pop as many ranges as the stack's depth-first reserve allows
+                const int fit = (B::kStack - B::kReserve - top) / (R - 1);
+                const int nr = max(1, min(min(top, T / R), fit));
+                const int rr = t / R, j = t % R;
+                uint32_t packed = 0;
+                if (rr < nr) packed = S[top - 1 - rr];
+                const bool vc = rr < nr && j < (int)(packed & 7u) + 1;
+                const uint32_t cidx = (packed >> 3) + (uint32_t)j;
+                const WalkCell wc = load_cell(walk, cidx, vc);
+                // opening test: squared distance from the centre of mass to the box
+                const double dxm = fmax(fmax(lox - wc.cx, 0.0), wc.cx - hix);
+                const double dym = fmax(fmax(loy - wc.cy, 0.0), wc.cy - hiy);
+                double d2 = dxm * dxm + dym * dym;
+                if (D == 3) {
+                    const double dzm = fmax(fmax(loz - wc.cz, 0.0), wc.cz - hiz);
+                    d2 = d2 + dzm * dzm;
+                }
+                const bool leaf = vc && wc.b < 0;
+                const bool accept = vc && d2 > wc.rcrit2;
+                const bool opened = vc && !accept && !leaf;
+                const bool direct = leaf && !accept;
+                const uint64_t O = __ballot(opened), A = __ballot(accept), P = __ballot(direct), V = __ballot(vc);
+                // four counts of at most kThreads each, 16 bits apart
+                if (lane == 0)
+                    s_cnt[wv] = (uint64_t)__popcll(O) | (uint64_t)__popcll(A) << 16 | (uint64_t)__popcll(P) << 32 |
+                                (uint64_t)__popcll(V) << 48;
+                __syncthreads();
+                uint64_t before = 0, total = 0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    const uint64_t v = s_cnt[w];
+                    if (w < wv) before += v;
+                    total += v;
+                }
+                const int na = (int)(total >> 16 & 0xffffu), np = (int)(total >> 32 & 0xffffu);
+                if ((QUAD ? qlen + na > B::kQuad : len + na > B::kList) || nleaf + np > T) {
+                    drain = true;                    // make room, then this round again
+                    __syncthreads();
+                    continue;
+                }
+                top -= nr;
+                if (opened)
+                    S[top + (int)(before & 0xffffu) + __popcll(O & below)] =
+                        ((uint32_t)wc.a << 3) | (uint32_t)(wc.b - 1);
+                if (accept) {
+                    const int at = (int)(before >> 16 & 0xffffu) + __popcll(A & below);
+                    const float4 e =
+                        make_float4((float)(wc.cx - rx), (float)(wc.cy - ry), (float)(wc.cz - rz), wc.m);
+                    if (QUAD) {
+                        LQ[3 * (qlen + at)] = e;
+                        LQ[3 * (qlen + at) + 1] = walkq[2 * (size_t)cidx];
+                        LQ[3 * (qlen + at) + 2] = walkq[2 * (size_t)cidx + 1];
+                    } else {
+                        L[len + at] = e;
+                    }
+                }
+                if (direct)
+                    s_leaf[nleaf + (int)(before >> 32 & 0xffffu) + __popcll(P & below)] =
+                        make_int2(wc.a, wc.b & 0x7fffffff);
+                top += (int)(total & 0xffffu);
+                if (QUAD) qlen += na;
+                else len += na;
+                nleaf += np;
+                nm2p += na;
+                ntest += (int)(total >> 48);
+                __syncthreads();
             }
-            if (lane == 0) {
+
+            // the waves' sums, added in FP64 in wave order: one thread per
+            // body and component
+            double* part = reinterpret_cast<double*>(L);
+            part[(wv * 4 + 0) * kWave + lane] = (double)a.sx + (double)a.cx;
+            part[(wv * 4 + 1) * kWave + lane] = (double)a.sy + (double)a.cy;
+            part[(wv * 4 + 2) * kWave + lane] = (double)a.sz + (double)a.cz;
+            part[(wv * 4 + 3) * kWave + lane] = (double)a.sp + (double)a.cp;
+            if (wv == 0) {
+                const uint32_t nx = order ? sched.pop(xq) : pos + gridDim.x;
+                if (lane == 0) s_next = nx;
+            }
+            __syncthreads();
+            for (int c = wv; c < 4 && valid; c += NW) {
+                double v = 0.0;
+                for (int q = 0; q < H; ++q)
+                    for (int w = 0; w < NW; ++w) v += part[(w * 4 + c) * kWave + q * kBodies + lane];
+                const int64_t o = perm[i0 + own];
+                if (c < 3) {
+                    if (c < D) acc[o * D + c] = (float)((double)G * v);
+                } else {
+                    // the body met itself once as a direct entry: its -m/eps
+                    // potential term is removed as in the one-wave kernel
+                    const float mself = (float)bodies[i0 + own].m;
+                    v += (double)(mself * __builtin_amdgcn_rsqf(eps2));
+                    pot[o] = (float)((double)G * v);
+                    const int64_t lc = nm2p + np2p;
+                    bcost[o] = lc > 0xffffffffll ? 0xffffffffu : (uint32_t)lc;
+                }
+            }
+            if (t == 0 && pos % H == 0) {
                 m2p_out[g] = nm2p;
                 p2p_out[g] = np2p;
                 tst_out[g] = ntest;
             }
+            pos = s_next;
+            __syncthreads();                         // the list is reused by the next group
         }
-        __syncthreads();                                  // s_part is reused by the next group
+        __syncthreads();                             // s_next is rewritten
     }
 }
 
@@ -688,13 +855,34 @@ hipError_t launch_walk_force_split(const WalkCell* walk, const float4* walkq, co
     return hipGetLastError();
 }
 
+// Blocks of a shared-walk kernel that can be resident at once, at most one
+// per group and at least one per XCD share (k_group_order's eight shares).
+template <auto kKernel>
+static hipError_t coop_blocks(int threads, int64_t gmax, unsigned* out) {
+    static std::atomic<int> resident{0};
+    int64_t want = resident.load(std::memory_order_relaxed);
+    if (want == 0) {
+        int dev = 0, cus = 0, per_cu = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kKernel, threads, 0);
+        if (e != hipSuccess) return e;
+        want = (int64_t)cus * (per_cu > 0 ? per_cu : 1);
+        resident.store((int)want, std::memory_order_relaxed);
+    }
+    if (want > gmax) want = gmax;
+    if (want < kXcd) want = kXcd;
+    *out = (unsigned)want;
+    return hipSuccess;
+}
+
 hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Body* bodies, const float4* bodies32,
                              const uint32_t* perm,
                              const int32_t* gbeg, const int32_t* gcnt, int64_t gmax, uint32_t* order,
                              uint32_t* queue, uint32_t* bcost,
                              int64_t n, int dim, int leaf_cap, float G, float eps2,
                              const DevParams* prm, float* acc, float* pot, int64_t* m2p,
-                             int64_t* p2p, int64_t* tests, bool plain, bool share, const uint32_t* lvl_off,
+                             int64_t* p2p, int64_t* tests, bool plain, bool share,
                              hipStream_t s) {
     // as many blocks as can be resident at once (the waves are persistent)
     static int resident[3] = {0, 0, 0};                // 2D, 3D, 3D with quadrupoles
@@ -721,24 +909,36 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
     // (as the layout reserves), then the counting sort of each share
     uint32_t* gcost = order + gmax;
     uint16_t* ckey = reinterpret_cast<uint16_t*>(order + 2 * gmax);
-    hipLaunchKernelGGL(k_group_order, dim3(kXcd), dim3(kOrderThreads), 0, s, (const uint32_t*)bcost, perm, gbeg,
-                       gcnt, prm, gcost, ckey, order, queue, (uint32_t)(nb * kWavesPerBlock));
+    auto make_order = [&]() {
+        hipLaunchKernelGGL(k_group_order, dim3(kXcd), dim3(kOrderThreads), 0, s, (const uint32_t*)bcost, perm, gbeg,
+                           gcnt, prm, gcost, ckey, order, queue, (uint32_t)(nb * kWavesPerBlock));
+    };
     if (share && n <= coop_max_n(dim)) {
-        // one block per group at a time, as many blocks as can be resident
-        const int deal = coop_deal_level(n, dim);
-        const int nw = coop_waves(n, dim);
-#define TC_LAUNCH_COOP_NW(DIM, PL, QU, NW)                                                                          \
-    hipLaunchKernelGGL((k_walk_force_coop<DIM, PL, QU, NW>), dim3(nb), dim3(NW * kWave), 0, s, walk, walkq, bodies,  \
-                       bodies32, perm, gbeg, gcnt, order, bcost, lvl_off, deal, lpl_log2, G, eps2, prm, acc, pot,  \
-                       m2p, p2p, tests)
+        // one block per task at a time, as many blocks as can be resident;
+        // with about one task per block (coop_shape) no order is made: it
+        // would cost its launch and change nothing
+        const CoopShape shape = coop_shape(n, dim);
+        if (shape.ordered) make_order();
+        const uint32_t* places = shape.ordered ? order : nullptr;
+        unsigned cb = 0;
+#define TC_LAUNCH_COOP_NW(DIM, PL, QU, NW, H)                                                                       \
+    do {                                                                                                            \
+        const hipError_t e_ = coop_blocks<k_walk_force_coop<DIM, PL, QU, NW, H>>(NW * kWave, gmax * H, &cb);        \
+        if (e_ != hipSuccess) return e_;                                                                            \
+        hipLaunchKernelGGL((k_walk_force_coop<DIM, PL, QU, NW, H>), dim3(cb), dim3(NW * kWave), 0, s, walk, walkq,  \
+                           bodies, bodies32, perm, gbeg, gcnt, places, queue, bcost, lpl_log2, G, eps2, prm, acc,   \
+                           pot, m2p, p2p, tests);                                                                   \
+    } while (0)
 #define TC_LAUNCH_COOP(DIM, PL, QU)                                                                                 \
     do {                                                                                                            \
-        if (nw == 8) TC_LAUNCH_COOP_NW(DIM, PL, QU, 8);                                                             \
-        else TC_LAUNCH_COOP_NW(DIM, PL, QU, 4);                                                                     \
+        if (DIM == 3 && shape.parts == 2) TC_LAUNCH_COOP_NW(3, PL, QU, 8, 2);                                       \
+        else if (shape.waves == 8) TC_LAUNCH_COOP_NW(DIM, PL, QU, 8, 1);                                            \
+        else if (DIM == 3 || shape.waves == 4) TC_LAUNCH_COOP_NW(DIM, PL, QU, 4, 1);                                \
+        else TC_LAUNCH_COOP_NW(2, PL, false, 2, 1);                                                                 \
     } while (0)
-        if (dim == 3 && walkq) {    // quadrupole lists: four waves (eight would take 82 KB of LDS)
-            if (plain) TC_LAUNCH_COOP_NW(3, true, true, 4);
-            else TC_LAUNCH_COOP_NW(3, false, true, 4);
+        if (dim == 3 && walkq) {
+            if (plain) TC_LAUNCH_COOP(3, true, true);
+            else TC_LAUNCH_COOP(3, false, true);
         } else if (dim == 3) {
             if (plain) TC_LAUNCH_COOP(3, true, false);
             else TC_LAUNCH_COOP(3, false, false);
@@ -750,6 +950,7 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
 #undef TC_LAUNCH_COOP_NW
         return hipGetLastError();
     }
+    make_order();
     // With two to four groups per resident wave (counting n/64 groups) the
     // list sums go in rounds of 4 entries, else 8: the same sums either
     // way, and measured per force kernel (3D Plummer, rounds of 4 against

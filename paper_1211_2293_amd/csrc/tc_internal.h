@@ -156,7 +156,7 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
                              const int32_t* gbeg, const int32_t* gcnt, int64_t gmax, uint32_t* order,
                              uint32_t* queue, uint32_t* bcost, int64_t n, int dim, int leaf_cap, float G, float eps2,
                              const DevParams* prm, float* acc, float* pot, int64_t* m2p,
-                             int64_t* p2p, int64_t* tests, bool plain, bool share, const uint32_t* lvl_off,
+                             int64_t* p2p, int64_t* tests, bool plain, bool share,
                              hipStream_t s);
 hipError_t launch_scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* part, int64_t tiles,
                            hipStream_t s);
@@ -173,30 +173,37 @@ hipError_t launch_direct64(const Body* bodies, const uint32_t* inv_perm, int64_t
 constexpr int64_t kSplitMaxN3 = 12288;
 constexpr int64_t kSplitMaxN2 = 24576;
 inline int64_t split_max_n(int dim) { return dim == 3 ? kSplitMaxN3 : kSplitMaxN2; }
-// Up to coop_max_n(dim), one block of waves shares each group's walk
-// (k_walk_force_coop), dealing out the cells of level coop_deal_level;
-// beyond, one wave per group.  Measured (force evaluation, one wave / shared):
-// 3D Plummer 0.160 / 0.073 ms at 2,000 bodies, 0.402 / 0.168 at 10,000,
-// 0.473 / 0.278 at 65,536, 0.494 / 0.450 at 131,072, 0.663 / 0.807 at
-// 262,144; 2D disk 0.111 / 0.052 at 5,000, 0.098 / 0.049 at 32,768,
-// 0.118 / 0.103 at 131,072, 0.125 / 0.179 at 262,144.  tc_set_split(ctx, 0)
-// turns it off; tc_set_split(ctx, 2) uses the split walks (above) for
-// n <= split_max_n(dim) instead.
-constexpr int64_t kCoopMaxN3 = 163840;
+// Up to coop_max_n(dim), one block of waves shares each group's walk and
+// list (k_walk_force_coop); beyond, one wave per group.  Measured (force
+// evaluation, one wave / shared): 3D Plummer 425 / 61 us at 10,000 bodies,
+// 491 / 219 at 100,000, 506 / 371 at 200,000, 788 / 736 at 400,000 and
+// 1,830 / 1,874 at 1,048,576; 2D disk 96 / 43 us at 50,000, 121 / 90 at
+// 160,000, 115 / 143 at 262,144.  tc_set_split(ctx, 0) turns it off;
+// tc_set_split(ctx, 2) uses the split walks (above) for n <=
+// split_max_n(dim) instead.
+constexpr int64_t kCoopMaxN3 = 524288;
 constexpr int64_t kCoopMaxN2 = 163840;
 inline int64_t coop_max_n(int dim) { return dim == 3 ? kCoopMaxN3 : kCoopMaxN2; }
-// Waves sharing each group's walk: eight for the smaller systems, where
-// even a block per group leaves most of the GPU idle, else four.  Measured
-// (force kernel, four / eight waves): 3D Plummer 0.175 / 0.123 ms at 10,000
-// bodies, 0.196 / 0.147 at 20,000, 0.213 / 0.183 at 30,000, 0.238 / 0.258
-// at 50,000, 0.536 / 0.690 at 163,840; 2D disk 0.046 / 0.038 at 20,000,
-// 0.048 / 0.044 at 30,000, 0.063 / 0.063 at 50,000, 0.121 / 0.159 at
-// 163,840.  Walks with quadrupole lists always use four (eight would need
-// 82 KB of LDS).
-inline int coop_waves(int64_t n, int dim) { return n <= 36000 ? 8 : 4; }
-inline int coop_deal_level(int64_t n, int dim) {
-    if (dim == 3) return n < 8192 ? 5 : 6;
-    return n < 8192 ? 5 : n < 65536 ? 6 : 7;
+// How a block shares a group: its waves, the tasks (of 64 / parts bodies) a
+// group is cut into, and whether the longest walks are sent first
+// (k_group_order).  More waves shorten one group's walk and sums, where the
+// chip has blocks to spare; fewer let more blocks share a CU, whose walks
+// and sums then overlap.  Measured (force evaluation in us, 3D Plummer):
+// 10,000 bodies, 8 waves x 2 parts 61, 8 x 1 78, 8 x 4 83, 4 x 1 113, 16 x
+// 1 77; 20,000: 8 x 1 86, 4 x 2 100, 8 x 2 107, 4 x 1 108; 35,000: 8 x 1
+// 108, 4 x 1 122; 50,000: 4 x 1 149, 8 x 1 160, 2 x 1 208; 100,000: 219,
+// 267, 276.  2D disk: 20,000: 8 waves 34, 4 waves 39; 50,000: 4 waves 43,
+// 2 waves 55, 8 waves 57; 160,000: 2 waves 90, 4 waves 103.  Up to 12,288
+// bodies about every task has a block of its own, and skipping the order
+// takes 4,096 bodies (8 x 2) from 31 to 24 us.
+struct CoopShape {
+    int waves, parts;
+    bool ordered;
+};
+inline CoopShape coop_shape(int64_t n, int dim) {
+    if (n <= 12288) return {8, dim == 3 ? 2 : 1, false};
+    if (dim == 3) return n <= 40000 ? CoopShape{8, 1, true} : CoopShape{4, 1, true};
+    return n <= 30000 ? CoopShape{8, 1, true} : n <= 100000 ? CoopShape{4, 1, true} : CoopShape{2, 1, true};
 }
 hipError_t launch_walk_force_split(const WalkCell* walk, const float4* walkq, const Body* bodies,
                                    const float4* bodies32, const uint32_t* perm, const int32_t* gbeg,

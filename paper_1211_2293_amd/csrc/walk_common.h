@@ -68,7 +68,10 @@ struct Acc {
 // (8% at 50,000 bodies); with one wave per group the compiler then issues
 // four list reads at a time instead of eight, and that kernel ran as fast at
 // 1M bodies and 1.8% slower at 4M.
-template <int D, bool PLAIN = false, bool STAGED = false, int STEP = 8>
+//
+// With H > 1 the wave's lanes are H parts of 64 / H bodies each, and part p
+// sums the entries p, p + H, ... (padded to 8 H).
+template <int D, bool PLAIN = false, bool STAGED = false, int STEP = 8, int H = 1>
 static __device__ __forceinline__ void flush(float4* L, int cnt, float xi, float yi, float zi, float eps2, Acc& a) {
     // entries per unrolled round: the staged form takes batches of 8; the
     // order of the sums is the same for any STEP
@@ -76,9 +79,13 @@ static __device__ __forceinline__ void flush(float4* L, int cnt, float xi, float
     static_assert(8 % kStep == 0, "rounds of 1, 2, 4 or 8 entries");
     const int lane = threadIdx.x & (kWave - 1);
     // zero entries pad the list to whole rounds (they add exact zeros)
-    const int padded = (cnt + kStep - 1) & ~(kStep - 1);
+    int padded = (cnt + kStep * H - 1) & ~(kStep * H - 1);
     for (int j = cnt + lane; j < padded; j += kWave) L[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     wave_lds_sync();
+    if (H > 1) {
+        L += lane / (kWave / H);
+        padded /= H;
+    }
     for (int e = 0; e < padded; e += kWave) {
         const int lim = min(kWave, padded - e);
         float ax = 0.f, ay = 0.f, az = 0.f, ap = 0.f;
@@ -95,7 +102,7 @@ static __device__ __forceinline__ void flush(float4* L, int cnt, float xi, float
                     float dx[4], dy[4], dz[4], m[4], s[4];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        const float4 p = L[e + k + h4 + u];
+                        const float4 p = L[(e + k + h4 + u) * H];
                         dx[u] = p.x - xi;
                         dy[u] = p.y - yi;
                         m[u] = p.w;
@@ -124,7 +131,7 @@ static __device__ __forceinline__ void flush(float4* L, int cnt, float xi, float
             }
 #pragma unroll
             for (int u = 0; u < kStep; ++u) {
-                const float4 p = L[e + k + u];
+                const float4 p = L[(e + k + u) * H];
                 const float dx = p.x - xi, dy = p.y - yi;
                 float r2, dz = 0.f;
                 if (D == 3) {
@@ -163,17 +170,21 @@ static __device__ __forceinline__ void flush(float4* L, int cnt, float xi, float
 // body: the monopole term plus, with d the entry's offset from the body and
 // s = (|d|^2 + eps^2)^{-1/2}, a += -Q d s^5 + (5/2) (d.Q d) d s^7 and
 // phi -= (1/2) (d.Q d) s^5.  Padded to a multiple of 8 with zero entries.
-template <bool PLAIN = false>
+template <bool PLAIN = false, int H = 1>
 static __device__ __forceinline__ void flush_quad(float4* LQ, int cnt, float xi, float yi, float zi, float eps2,
                                                   Acc& a) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int padded = (cnt + 7) & ~7;
+    int padded = (cnt + 8 * H - 1) & ~(8 * H - 1);
     for (int j = cnt + lane; j < padded; j += kWave) {
         LQ[3 * j] = make_float4(0.f, 0.f, 0.f, 0.f);
         LQ[3 * j + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
         LQ[3 * j + 2] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     wave_lds_sync();
+    if (H > 1) {
+        LQ += 3 * (lane / (kWave / H));
+        padded /= H;
+    }
     for (int e = 0; e < padded; e += kWave) {
         const int lim = min(kWave, padded - e);
         float ax = 0.f, ay = 0.f, az = 0.f, ap = 0.f;
@@ -186,9 +197,9 @@ static __device__ __forceinline__ void flush_quad(float4* LQ, int cnt, float xi,
         for (int k = 0; k < lim; k += 4) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float4 p = LQ[3 * (e + k + u)];
-                const float4 qa = LQ[3 * (e + k + u) + 1];
-                const float4 qb = LQ[3 * (e + k + u) + 2];
+                const float4 p = LQ[3 * H * (e + k + u)];
+                const float4 qa = LQ[3 * H * (e + k + u) + 1];
+                const float4 qb = LQ[3 * H * (e + k + u) + 2];
                 const float dx = p.x - xi, dy = p.y - yi, dz = p.z - zi;
                 const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
                 const float s = __builtin_amdgcn_rsqf(r2);

@@ -298,3 +298,34 @@ def test_shared_walk_at_its_largest_size():
     within the parity bound."""
     w = workloads.plummer_sphere(163840, seed=86)
     _check_against_oracle(w.pos, w.mass, 16, 0.5, w.eps)
+
+
+@pytest.mark.parametrize("dim,n,lc,theta,order", [
+    (3, 12288, 16, 0.5, 1), (3, 12289, 16, 0.5, 1), (3, 40000, 8, 0.5, 1), (3, 40001, 8, 0.5, 1),
+    (3, 200001, 16, 0.6, 1), (3, 524288, 16, 0.7, 1), (3, 12288, 32, 0.5, 2), (3, 12289, 16, 0.6, 2),
+    (2, 12288, 16, 0.5, 1), (2, 30001, 16, 0.5, 1), (2, 100001, 8, 0.6, 1),
+    # every cell opened: the list is all bodies, in many windows, and the stack is at its bound
+    (3, 9000, 4, 0.0, 1), (3, 20000, 100, 0.0, 1), (2, 14000, 1, 0.0, 1)])
+def test_shared_walk_shapes(dim, n, lc, theta, order):
+    """Each shape of the shared walk (waves per block, parts per group) on
+    both sides of its sizes, against one wave per group: equal interactions,
+    counts and tested cells, forces to summation order."""
+    from paper_1211_2293_amd import treecode
+    from tests.gpu_util import to_dev
+    w = workloads.plummer_sphere(n, seed=91) if dim == 3 else workloads.gaussian_disk(n, seed=92)
+    tc = treecode.Treecode(dim, leaf_cap=lc)
+    keep = (to_dev(w.pos), to_dev(w.mass))
+    tc.build(*keep)
+    tc.moments()
+    tc.walk(theta)
+    tc.set_multipole(order)
+    out = {}
+    for mode in (0, 1):
+        tc.set_split(mode)
+        acc, pot = tc.forces(1.0, 1e-2)
+        out[mode] = [v.cpu().numpy() for v in (acc, pot, *tc.counts(), tc.tests())]
+    for k in (2, 3, 4):
+        np.testing.assert_array_equal(out[1][k], out[0][k])
+    # both sum chunks of 64 entries in FP32 (at most 64 x 2^-24 of a chunk,
+    # of either sign) and fold them with compensation: 2^-20 covers the two
+    assert oracle.rel_l2(out[1][0], out[0][0]) < 2.0 ** -20 and oracle.rel_l2(out[1][1], out[0][1]) < 2.0 ** -20
