@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtc.so")
-SOURCES = ["api.hip", "build.hip", "force.hip", "step.hip", "closure.hip", "learned.hip", "direct.hip", "perbody.hip", "fmm.hip"]
+SOURCES = ["api.hip", "build.hip", "bodysort.hip", "force.hip", "step.hip", "closure.hip", "learned.hip", "direct.hip", "perbody.hip", "fmm.hip"]
 # a benchmark program beside the library: the force loop's own throughput
 PROBE_SRC = "loop_probe.hip"
 PROBE = os.path.join(HERE, "loop_probe")

@@ -288,29 +288,60 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
     const Layout& l = ctx->lay;
     const int f64 = dtype == TC_F64;
     DevParams* prm = ctx->prm();
+    // the records on their way to key order live in the moments pass's
+    // level-order buffer (at least 112 B per body, unused until the moments pass)
+    const bool buckets = n < kBucketMaxN;
+    char* packed = buckets ? nullptr : ctx->at<char>(l.off_mom_lvl);
     {
         StageScope st_(ctx, TC_STAGE_BBOX, s);
-        // the packed records live in the moments pass's level-order buffer
-        // (at least 112 B per body, unused until the moments pass)
-        TC_HIP(ctx, launch_bbox(pos, mass, n, dim, f64, ctx->at<double>(l.off_bbox_part),
-                                ctx->at<char>(l.off_mom_lvl), prm, s));
+        TC_HIP(ctx, launch_bbox(pos, mass, n, dim, f64, ctx->at<double>(l.off_bbox_part), packed, prm, s));
     }
-    {
-        StageScope st_(ctx, TC_STAGE_KEYS, s);
-        TC_HIP(ctx, launch_keys(pos, n, dim, f64, prm, ctx->at<uint64_t>(l.off_keys_a),
-                                ctx->at<uint32_t>(l.off_idx_a), s));
-    }
-    {
-        StageScope st_(ctx, TC_STAGE_SORT, s);
-        TC_HIP(ctx, launch_sort(ctx->at<uint64_t>(l.off_keys_a), ctx->at<uint32_t>(l.off_idx_a),
-                                ctx->at<uint64_t>(l.off_keys_b), ctx->at<uint32_t>(l.off_idx_b), n,
-                                dim * levels_for(dim), ctx->at<uint32_t>(l.off_hist),
-                                ctx->at<uint32_t>(l.off_digit_tot), s));
-    }
-    {
+    if (buckets) {
+        // the bucket numbers, splitters, totals and starts take the place of
+        // what the topology writes later
+        char* nper = ctx->at<char>(l.off_nper);
+        BodySort a;
+        a.keys_a = ctx->at<uint64_t>(l.off_keys_a);
+        a.keys_b = ctx->at<uint64_t>(l.off_keys_b);
+        a.idx_a = ctx->at<uint32_t>(l.off_idx_a);
+        a.idx_b = ctx->at<uint32_t>(l.off_idx_b);
+        a.bucket = ctx->at<uint16_t>(l.off_range);
+        a.hist = ctx->at<uint32_t>(l.off_hist);
+        a.recs = ctx->at<char>(l.off_mom_lvl);
+        const int nb = body_buckets(n);
+        a.split_key = reinterpret_cast<uint64_t*>(nper);
+        a.split_idx = reinterpret_cast<uint32_t*>(nper + 8 * (size_t)nb);
+        a.total = a.split_idx + nb;
+        a.start = a.total + nb;
+        const double* part = ctx->at<double>(l.off_bbox_part);
+        const int parts = bbox_parts(n);
+        {
+            StageScope st_(ctx, TC_STAGE_KEYS, s);
+            TC_HIP(ctx, launch_body_keys(pos, n, dim, f64, part, parts, prm, a, s));
+        }
+        {
+            StageScope st_(ctx, TC_STAGE_SORT, s);
+            TC_HIP(ctx, launch_body_scatter(pos, mass, n, dim, f64, prm, a, s));
+        }
         StageScope st_(ctx, TC_STAGE_GATHER, s);
-        TC_HIP(ctx, launch_gather(ctx->at<char>(l.off_mom_lvl), ctx->at<uint32_t>(l.off_idx_a), n, f64,
-                                  ctx->at<Body>(l.off_bodies), ctx->at<float4>(l.off_bodies32), s));
+        TC_HIP(ctx, launch_body_sort(pos, mass, n, dim, f64, part, parts, prm, a, ctx->at<Body>(l.off_bodies),
+                                     ctx->at<float4>(l.off_bodies32), s));
+    } else {
+        {
+            StageScope st_(ctx, TC_STAGE_KEYS, s);
+            TC_HIP(ctx, launch_keys(pos, n, dim, f64, prm, ctx->at<uint64_t>(l.off_keys_a),
+                                    ctx->at<uint32_t>(l.off_idx_a), s));
+        }
+        {
+            StageScope st_(ctx, TC_STAGE_SORT, s);
+            TC_HIP(ctx, launch_sort(ctx->at<uint64_t>(l.off_keys_a), ctx->at<uint32_t>(l.off_idx_a),
+                                    ctx->at<uint64_t>(l.off_keys_b), ctx->at<uint32_t>(l.off_idx_b), n,
+                                    dim * levels_for(dim), ctx->at<uint32_t>(l.off_hist),
+                                    ctx->at<uint32_t>(l.off_digit_tot), s));
+        }
+        StageScope st_(ctx, TC_STAGE_GATHER, s);
+        TC_HIP(ctx, launch_gather(packed, ctx->at<uint32_t>(l.off_idx_a), n, f64, ctx->at<Body>(l.off_bodies),
+                                  ctx->at<float4>(l.off_bodies32), s));
     }
     {
         StageScope st_(ctx, TC_STAGE_TOPOLOGY, s);

@@ -6,8 +6,10 @@
 //   bbox     root cube: per-axis minimum corner, power-of-two side (FP64);
 //            the same pass packs the input as (x, y, z, m) records
 //   keys     Morton key of FP64-quantised coordinates, index iota
-//   sort     stable LSD radix sort of (key, index), 8 bits per pass (large
-//            sorts rank each tile in LDS before writing it out)
+//   sort     from kBucketMaxN bodies a stable LSD radix sort of (key,
+//            index), 8 bits per pass (each tile ranked in LDS before it is
+//            written out); keys, sort and gather of smaller systems are in
+//            bodysort.hip
 //   gather   bodies into key order, FP64, one packed record per body
 //   topology all cells at once from the sorted keys (no per-level launches):
 //            body i starts the cells of levels a_i..l*_i, where a_i is one
@@ -26,22 +28,18 @@
 // Every expression that decides an integer (keys, topology, opening radii)
 // is compiled without floating-point contraction.
 #include "tc_internal.h"
+#include "keys.h"
 
 #include <math.h>
 
 namespace tc {
 namespace {
 
+using namespace keys;
+
 __device__ __forceinline__ int wave_lane() { return threadIdx.x & (kWave - 1); }
 
 // ---------------------------------------------------------------- bbox ----
-
-// The input's bodies packed four values to a record, (x, y, z, m) with z = 0
-// in 2D, in the input's order: the gather then reads one record per body
-// instead of a position and a mass from two places.
-template <typename T> struct Packed;
-template <> struct Packed<float> { using type = float4; };
-template <> struct Packed<double> { using type = double4; };
 
 template <typename T, int D>
 __global__ void __launch_bounds__(256) k_bbox_part(const T* __restrict__ pos, const T* __restrict__ mass,
@@ -63,12 +61,14 @@ __global__ void __launch_bounds__(256) k_bbox_part(const T* __restrict__ pos, co
         const T mt = mass[i];
         const double m = (double)mt;
         if (!(isfinite(m) && m > 0.0)) bad = 1;
-        typename Packed<T>::type r;
-        r.x = c[0];
-        r.y = c[1];
-        r.z = c[2];
-        r.w = mt;
-        packed[i] = r;
+        if (packed) {
+            typename Packed<T>::type r;
+            r.x = c[0];
+            r.y = c[1];
+            r.z = c[2];
+            r.w = mt;
+            packed[i] = r;
+        }
     }
     __shared__ double s_lo[3][256], s_hi[3][256];
     __shared__ int s_bad[256];
@@ -123,82 +123,22 @@ __global__ void __launch_bounds__(256) k_bbox_final(const double* __restrict__ p
         __syncthreads();
     }
     if (t == 0) {
-        const int L = dim == 3 ? 21 : 31;
-        double ext = 0.0;
-        for (int a = 0; a < dim; ++a) {
-            double l = s_lo[a][0];
-            if (!isfinite(l)) l = 0.0;            // no finite coordinate on this axis
-            prm->lo[a] = l;
-            const double e = s_hi[a][0] - s_lo[a][0];
-            if (e > ext) ext = e;
-        }
-        for (int a = dim; a < 3; ++a) prm->lo[a] = 0.0;
-        double size = 1.0;
-        if (ext > 0.0 && isfinite(ext)) {
-            int e2;
-            const double f = frexp(ext, &e2);     // ext = f 2^e2, f in [0.5, 1)
-            size = (f == 0.5) ? ext : ldexp(1.0, e2);
-        }
-        int e2;
-        frexp(size, &e2);                         // size = 2^(e2-1)
-        prm->size = size;
-        prm->scale = ldexp(1.0, L - (e2 - 1));
-        prm->status = s_bad[0] ? kFlagNonFinite : 0u;
-        prm->ncells = 0;
+        const double l[3] = {s_lo[0][0], s_lo[1][0], s_lo[2][0]}, h[3] = {s_hi[0][0], s_hi[1][0], s_hi[2][0]};
+        store_cube(make_cube(l, h, dim), s_bad[0] != 0, prm);
     }
 }
 
 // ---------------------------------------------------------------- keys ----
 
-__device__ __forceinline__ uint64_t spread3(uint64_t x) {   // bit b -> bit 3b (21 bits)
-    x &= 0x1fffffull;
-    x = (x | x << 32) & 0x1f00000000ffffull;
-    x = (x | x << 16) & 0x1f0000ff0000ffull;
-    x = (x | x << 8) & 0x100f00f00f00f00full;
-    x = (x | x << 4) & 0x10c30c30c30c30c3ull;
-    x = (x | x << 2) & 0x1249249249249249ull;
-    return x;
-}
-
-__device__ __forceinline__ uint64_t spread2(uint64_t x) {   // bit b -> bit 2b (32 bits)
-    x &= 0xffffffffull;
-    x = (x | x << 16) & 0x0000ffff0000ffffull;
-    x = (x | x << 8) & 0x00ff00ff00ff00ffull;
-    x = (x | x << 4) & 0x0f0f0f0f0f0f0f0full;
-    x = (x | x << 2) & 0x3333333333333333ull;
-    x = (x | x << 1) & 0x5555555555555555ull;
-    return x;
-}
-
-template <int D>
-__device__ __forceinline__ uint64_t quantise(double x, double lo, double scale) {
-    constexpr int L = D == 3 ? 21 : 31;
-    const double top = (double)((1ull << L) - 1ull);
-    double f = floor((x - lo) * scale);
-    if (!(f >= 0.0)) f = 0.0;                     // also catches NaN
-    if (f > top) f = top;
-    return (uint64_t)f;
-}
-
 template <typename T, int D>
 __global__ void __launch_bounds__(256) k_keys(const T* __restrict__ pos, int64_t n,
                                               const DevParams* __restrict__ prm,
                                               uint64_t* __restrict__ keys, uint32_t* __restrict__ idx) {
-    const double scale = prm->scale;
-    const double lo0 = prm->lo[0], lo1 = prm->lo[1], lo2 = prm->lo[2];
+    const double scale = prm->scale, lo[3] = {prm->lo[0], prm->lo[1], prm->lo[2]};
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        uint64_t key;
-        if (D == 3) {
-            const uint64_t qx = quantise<3>((double)pos[i * 3 + 0], lo0, scale);
-            const uint64_t qy = quantise<3>((double)pos[i * 3 + 1], lo1, scale);
-            const uint64_t qz = quantise<3>((double)pos[i * 3 + 2], lo2, scale);
-            key = (spread3(qx) << 2) | (spread3(qy) << 1) | spread3(qz);
-        } else {
-            const uint64_t qx = quantise<2>((double)pos[i * 2 + 0], lo0, scale);
-            const uint64_t qy = quantise<2>((double)pos[i * 2 + 1], lo1, scale);
-            key = (spread2(qx) << 1) | spread2(qy);
-        }
+        const uint64_t key = morton<D>((double)pos[i * D], (double)pos[i * D + 1],
+                                       D == 3 ? (double)pos[i * D + D - 1] : 0.0, lo, scale);
         keys[i] = key;
         idx[i] = (uint32_t)i;
     }
@@ -1210,9 +1150,11 @@ __global__ void __launch_bounds__(256) k_export(const Cell* __restrict__ cells, 
 
 // ------------------------------------------------------------ launchers ----
 
+int bbox_parts(int64_t n) { return (int)grid_for(n, 1024); }
+
 hipError_t launch_bbox(const void* pos, const void* mass, int64_t n, int dim, int f64,
                        double* part, void* packed, DevParams* prm, hipStream_t s) {
-    const unsigned nb = grid_for(n, 1024);
+    const unsigned nb = (unsigned)bbox_parts(n);
     if (f64) {
         if (dim == 3) hipLaunchKernelGGL((k_bbox_part<double, 3>), dim3(nb), dim3(256), 0, s, (const double*)pos, (const double*)mass, n, part, (double4*)packed);
         else hipLaunchKernelGGL((k_bbox_part<double, 2>), dim3(nb), dim3(256), 0, s, (const double*)pos, (const double*)mass, n, part, (double4*)packed);
@@ -1220,7 +1162,7 @@ hipError_t launch_bbox(const void* pos, const void* mass, int64_t n, int dim, in
         if (dim == 3) hipLaunchKernelGGL((k_bbox_part<float, 3>), dim3(nb), dim3(256), 0, s, (const float*)pos, (const float*)mass, n, part, (float4*)packed);
         else hipLaunchKernelGGL((k_bbox_part<float, 2>), dim3(nb), dim3(256), 0, s, (const float*)pos, (const float*)mass, n, part, (float4*)packed);
     }
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(256), 0, s, part, (int)nb, dim, prm);
+    if (packed) hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(256), 0, s, part, (int)nb, dim, prm);
     return hipGetLastError();
 }
 

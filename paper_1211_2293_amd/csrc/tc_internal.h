@@ -107,8 +107,11 @@ Layout make_layout(int64_t n, int dim, int leaf_cap);
 
 // ---- launchers (all enqueue on `s`, return hipSuccess or the launch error)
 // build.hip
-// Also packs the input into (x, y, z, m) records (float4, or double4 for FP64
-// input; n of them at `packed`) for launch_gather.
+// Partial boxes of the input, bbox_parts(n) of 7 doubles.  With `packed` it also
+// packs the input into (x, y, z, m) records (float4, or double4 for FP64
+// input; n of them) for launch_gather and reduces the boxes to the root cube;
+// without, the kernels of bodysort.hip do that.
+int bbox_parts(int64_t n);
 hipError_t launch_bbox(const void* pos, const void* mass, int64_t n, int dim, int f64,
                        double* part, void* packed, DevParams* prm, hipStream_t s);
 hipError_t launch_keys(const void* pos, int64_t n, int dim, int f64, const DevParams* prm,
@@ -120,6 +123,29 @@ hipError_t launch_sort(uint64_t* keys_a, uint32_t* idx_a, uint64_t* keys_b, uint
                        int64_t n, int key_bits, uint32_t* hist, uint32_t* digit_tot, hipStream_t s);
 hipError_t launch_gather(const void* packed, const uint32_t* perm, int64_t n, int f64, Body* bodies,
                          float4* bodies32, hipStream_t s);
+// bodysort.hip: keys, order and gather of fewer than kBucketMaxN bodies, from
+// the input and the partial boxes of launch_bbox (whose root cube it stores
+// in prm).  Three parts in this order; small systems do all in the last.
+// keys_a and idx_a receive the sorted keys and the permutation.
+constexpr int64_t kRankMaxN = 8192;
+constexpr int64_t kBucketMaxN = (int64_t)1 << 21;
+struct BodySort {
+    uint64_t *keys_a, *keys_b;   // [n]
+    uint32_t *idx_a, *idx_b;     // [n]
+    uint16_t* bucket;            // [n]
+    uint32_t* hist;              // tiles x buckets, at most 256 per 1024 bodies (rounded up)
+    void* recs;                  // 48 n bytes
+    uint64_t* split_key;         // [buckets]
+    uint32_t *split_idx, *total, *start;   // [buckets], [buckets], [buckets + 1]
+};
+int body_buckets(int64_t n);     // at most n / 32
+hipError_t launch_body_keys(const void* pos, int64_t n, int dim, int f64, const double* part, int parts,
+                            DevParams* prm, const BodySort& a, hipStream_t s);
+hipError_t launch_body_scatter(const void* pos, const void* mass, int64_t n, int dim, int f64, const DevParams* prm,
+                               const BodySort& a, hipStream_t s);
+hipError_t launch_body_sort(const void* pos, const void* mass, int64_t n, int dim, int f64, const double* part,
+                            int parts, DevParams* prm, const BodySort& a, Body* bodies, float4* bodies32,
+                            hipStream_t s);
 hipError_t launch_topology(const uint64_t* keys, int64_t n, int dim, int leaf_cap,
                            uint32_t* range, uint32_t* nper, uint32_t* cstart,
                            uint32_t* scan_part, int64_t scan_tiles, Cell* cells,

@@ -147,3 +147,81 @@ def test_context_reuse_when_the_top_levels_no_longer_fit_in_lds(dim):
         assert g["status"] == treecode.TC_OK
         t = oracle.Tree(pos.astype(np.float64), mass.astype(np.float64), 16)
         assert_tree_equal(g, t)
+
+
+def _strata_draw(n, buckets, per):
+    """The bodies that the body sort samples: one at a hashed place of each of
+    buckets x per equal strata."""
+    S = buckets * per
+    j = np.arange(S, dtype=np.uint64)
+    lo, hi = j * n // S, (j + 1) * n // S
+    m32 = np.uint64(0xffffffff)
+    h = (j * np.uint64(2654435761)) & m32
+    h ^= h >> np.uint64(15)
+    h = (h * np.uint64(2246822519)) & m32
+    h ^= h >> np.uint64(13)
+    return (lo + h % (hi - lo)).astype(np.int64)
+
+
+def _missed_by_the_draw(n, buckets, per, dim):
+    """Bodies outside the sample all follow the sampled ones in key order, so
+    one bucket holds nearly all of them (more than a block sorts in LDS)."""
+    rng = np.random.default_rng(55)
+    pos = rng.uniform(0.75, 1.0, (n, dim))
+    pos[rng.permutation(n)[: n // 3]] = 0.875       # and many equal keys among them
+    at = _strata_draw(n, buckets, per)
+    pos[at] = rng.uniform(0.0, 0.25, (len(at), dim))
+    return pos.astype(np.float32)
+
+
+SORT_CASES = {
+    # the rank sort's own sizes: one block, a partial block, a chunk of keys
+    # and one more, its largest; then the first size with buckets
+    **{f"n{n}": (lambda n=n: workloads.plummer_sphere(n, seed=56).pos) for n in
+       (31, 32, 33, 4096, 4097, 8192, 8193, 16384, 16385, 65536, 65537, 262144, 262145, 524288, 1048577, 2097151)},
+    "f64-262145": lambda: workloads.plummer_sphere(262145, seed=57).pos.astype(np.float64) * 1.1,
+    "disk-300001": lambda: workloads.gaussian_disk(300001, seed=58).pos,
+    "sorted-input": lambda: np.sort(workloads.plummer_sphere(40001, seed=59).pos, axis=0),
+    "equal-30000": lambda: np.full((30000, 3), 0.5, np.float32),
+    "few-places": lambda: np.random.default_rng(60).integers(0, 3, (50000, 3)).astype(np.float32),
+    "missed-20000": lambda: _missed_by_the_draw(20000, 128, 4, 3),
+    "missed-2d": lambda: _missed_by_the_draw(60000, 256, 4, 2),
+}
+
+
+@pytest.mark.parametrize("name", list(SORT_CASES))
+def test_body_order_is_the_stable_order_of_the_keys(name):
+    """The order by (key, input index) on both sides of every size where the
+    body sort changes its shape, for equal keys and for inputs that its sample
+    misses: keys and permutation against numpy's stable sort of the oracle's
+    keys (equal whole numbers), and the bodies they gather."""
+    pos = SORT_CASES[name]()
+    n, dim = pos.shape
+    mass = np.random.default_rng(61).uniform(0.5, 2.0, n).astype(pos.dtype)
+    from paper_1211_2293_amd import treecode
+    from tests.gpu_util import to_dev
+    tc = treecode.Treecode(dim, leaf_cap=256)
+    keep = (to_dev(pos), to_dev(mass))
+    tc.build(*keep)
+    assert tc.status() == treecode.TC_OK
+    k, perm = tc.keys()
+    k, perm = k.cpu().numpy().view(np.uint64), perm.cpu().numpy().view(np.uint32)
+    lo, size = tc.root()
+    L = 21 if dim == 3 else 31
+    x = pos.astype(np.float64)
+    np.testing.assert_array_equal(lo, x.min(0))
+    q = np.minimum(np.floor((x - lo) * (2.0 ** L / size)), 2.0 ** L - 1).astype(np.uint64)
+    key = np.zeros(n, np.uint64)
+    for b in range(L):
+        for a in range(dim):
+            key |= ((q[:, a] >> np.uint64(b)) & np.uint64(1)) << np.uint64(dim * b + dim - 1 - a)
+    want = np.argsort(key, kind="stable")
+    np.testing.assert_array_equal(perm, want)
+    np.testing.assert_array_equal(k, key[want])
+    # the root's mass and centre are sums over the gathered bodies
+    tc.moments()
+    c = tc.cells()
+    m = mass.astype(np.float64)
+    assert abs(float(c["M"][0]) - m.sum()) <= 1e-12 * m.sum()
+    com = (m[:, None] * x).sum(0) / m.sum()
+    np.testing.assert_allclose(c["com"][0].cpu().numpy(), com, rtol=0, atol=1e-10 * np.abs(x).max())
