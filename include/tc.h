@@ -62,9 +62,8 @@ enum tc_dtype { TC_F32 = 0, TC_F64 = 1 };
 int tc_create(tc_ctx **out, int dim, void *hip_stream);
 
 /* Destroy a context (NULL is a no-op).  Does not touch the workspace.
- * Besides host memory, a context holds one event and 256 bytes of pinned
- * host memory, into which each tc_build copies its tree's level offsets
- * (the moments pass of later builds sizes its launches by that depth). */
+ * A context holds host memory, and events and a stream only for timing and
+ * graph replay. */
 void tc_destroy(tc_ctx *ctx);
 
 /* Bytes of device workspace needed for n bodies in dim dimensions with the

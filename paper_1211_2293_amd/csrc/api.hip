@@ -66,10 +66,12 @@ Layout make_layout(int64_t n, int dim, int leaf_cap) {
     l.off_cells = take(sizeof(Cell) * (size_t)l.cmax);
     l.off_mom = take(sizeof(Moments) * (size_t)l.cmax);
     l.off_walk = take(sizeof(WalkCell) * (size_t)l.cmax);
-    l.off_mom_lvl = take(sizeof(Moments) * (size_t)l.cmax);   // level-order copy for the moments pass
-    // ... and, earlier in each build, the packed input records (cmax > n)
-    static_assert(sizeof(Moments) >= sizeof(double4), "packed records must fit the level-order buffer");
-    l.off_kids = take(8 * (size_t)l.cmax);
+    // the bodies on their way to key order, or the packed input (cmax > n)
+    l.off_recs = take(sizeof(Moments) * (size_t)l.cmax);
+    static_assert(sizeof(Moments) >= sizeof(double4) && sizeof(Moments) >= 48, "the records must fit");
+    // the upper cells by level (BigList): at most 4 kLevels bytes per subtree_cells + 1 cells
+    l.off_big = take(8 * (size_t)l.cmax);
+    static_assert(4 * kLevels <= 8 * (kSubtreeMin + 1), "the lists must fit");
     l.off_acc = take(4 * (size_t)n * dim);
     l.off_pot = take(4 * (size_t)n);
     l.off_m2p = 0;   // placed after the group bound is known
@@ -156,16 +158,6 @@ struct tc_ctx {
     // the pre-force part of tc_leapfrog as a replayed graph (see tc_leapfrog)
     bool use_graph = false;
     bool capturing = false;    // inside the graph capture of the pre-force part
-    bool no_alloc = false;     // inside tc_forces_noalloc: no host copies that need pinned memory
-    // Level sizes of an earlier tree, for the moments pass: each build copies
-    // its level offsets to pinned host memory behind an event; a later call
-    // takes them once the event has completed.  Only launch shapes depend
-    // on them, never results.
-    uint32_t* lvl_host = nullptr;
-    hipEvent_t lvl_ev = nullptr;
-    bool lvl_pending = false;
-    bool have_hint = false;    // lvl_hint holds the last harvested build's level offsets
-    uint32_t lvl_hint[64] = {};
     bool plain_acc = false;    // uncompensated running sums (precision study)
     int mp_order = 1;          // 1: monopole cells, 2: with quadrupole terms (3D)
     int split = 1;             // 0: one wave per group; 1: shared walks (coop); 2: split walks up to split_max_n
@@ -271,27 +263,24 @@ struct StageScope {
     }
 };
 
-// Everything tc_build enqueues, after its checks.
-// Take the level offsets of the last build whose copy has arrived on the
-// host (never waits).
-void harvest_depth(tc_ctx* ctx) {
-    if (!ctx->lvl_pending || hipEventQuery(ctx->lvl_ev) != hipSuccess) return;
-    const int L = levels_for(ctx->dim);
-    for (int l = 0; l <= L + 1; ++l) ctx->lvl_hint[l] = ctx->lvl_host[l];
-    ctx->have_hint = true;
-    ctx->lvl_pending = false;
+// The upper cells' lists; their counters take the place of the partial boxes,
+// which nothing reads after the root cube.
+BigList big_list(tc_ctx* ctx) {
+    const Layout& l = ctx->lay;
+    static_assert(kLevels * BigList::kStride * 4 <= 7 * 8 * 1024, "the counters must fit the partial boxes");
+    const int sub = subtree_cells(l.cmax);
+    return {ctx->at<uint32_t>(l.off_bbox_part), ctx->at<uint32_t>(l.off_big), (uint32_t)(l.cmax / (sub + 1)), sub};
 }
 
+// Everything tc_build enqueues, after its checks.
 int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf_cap, int dtype, hipStream_t s) {
     const int dim = ctx->dim;
     ctx->lay = make_layout(n, dim, leaf_cap);
     const Layout& l = ctx->lay;
     const int f64 = dtype == TC_F64;
     DevParams* prm = ctx->prm();
-    // the records on their way to key order live in the moments pass's
-    // level-order buffer (at least 112 B per body, unused until the moments pass)
     const bool buckets = n < kBucketMaxN;
-    char* packed = buckets ? nullptr : ctx->at<char>(l.off_mom_lvl);
+    char* packed = buckets ? nullptr : ctx->at<char>(l.off_recs);
     {
         StageScope st_(ctx, TC_STAGE_BBOX, s);
         TC_HIP(ctx, launch_bbox(pos, mass, n, dim, f64, ctx->at<double>(l.off_bbox_part), packed, prm, s));
@@ -307,7 +296,7 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
         a.idx_b = ctx->at<uint32_t>(l.off_idx_b);
         a.bucket = ctx->at<uint16_t>(l.off_range);
         a.hist = ctx->at<uint32_t>(l.off_hist);
-        a.recs = ctx->at<char>(l.off_mom_lvl);
+        a.recs = ctx->at<char>(l.off_recs);
         const int nb = body_buckets(n);
         a.split_key = reinterpret_cast<uint64_t*>(nper);
         a.split_idx = reinterpret_cast<uint32_t*>(nper + 8 * (size_t)nb);
@@ -349,7 +338,7 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
                                     ctx->at<uint32_t>(l.off_range), ctx->at<uint32_t>(l.off_nper),
                                     ctx->at<uint32_t>(l.off_cstart), ctx->at<uint32_t>(l.off_scan_part),
                                     l.scan_tiles, ctx->at<Cell>(l.off_cells),
-                                    l.cmax, prm, s));
+                                    l.cmax, prm, big_list(ctx), s));
     }
     {
         StageScope st_(ctx, TC_STAGE_LEVELS, s);
@@ -360,17 +349,6 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
                                        ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_lvl_hist),
                                        ctx->at<uint32_t>(l.off_digit_tot), ctx->at<uint32_t>(l.off_pre2bfs),
                                        ctx->at<uint32_t>(l.off_lvl_off), s));
-    }
-    // the depth of this tree, for later moments passes (not inside a capture,
-    // and not where nothing may be allocated: the copy needs pinned memory)
-    if (!ctx->capturing && !ctx->no_alloc) {
-        harvest_depth(ctx);
-        if (!ctx->lvl_host) TC_HIP(ctx, hipHostMalloc((void**)&ctx->lvl_host, 4 * 64, hipHostMallocDefault));
-        if (!ctx->lvl_ev) TC_HIP(ctx, hipEventCreateWithFlags(&ctx->lvl_ev, hipEventDisableTiming));
-        TC_HIP(ctx, hipMemcpyAsync(ctx->lvl_host, ctx->at<uint32_t>(l.off_lvl_off),
-                                   4 * (size_t)(levels_for(dim) + 2), hipMemcpyDeviceToHost, s));
-        TC_HIP(ctx, hipEventRecord(ctx->lvl_ev, s));
-        ctx->lvl_pending = true;
     }
     {
         StageScope st_(ctx, TC_STAGE_GROUPS, s);
@@ -392,10 +370,8 @@ int do_moments(tc_ctx* ctx, hipStream_t s) {
     const Layout& l = ctx->lay;
     StageScope st_(ctx, TC_STAGE_MOMENTS, s);
     TC_HIP(ctx, launch_moments(ctx->at<Cell>(l.off_cells), ctx->at<Body>(l.off_bodies), ctx->dim, l.cmax,
-                               ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_pre2bfs),
-                               ctx->at<uint32_t>(l.off_lvl_off), ctx->prm(), ctx->at<Moments>(l.off_mom),
-                               ctx->at<Moments>(l.off_mom_lvl), ctx->at<uint2>(l.off_kids),
-                               ctx->at<WalkCell>(l.off_walk), ctx->have_hint ? ctx->lvl_hint : nullptr, s));
+                               ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_pre2bfs), big_list(ctx),
+                               ctx->prm(), ctx->at<Moments>(l.off_mom), ctx->at<WalkCell>(l.off_walk), s));
     ctx->state = kMoments;
     return TC_OK;
 }
@@ -835,9 +811,6 @@ int tc_create(tc_ctx** out, int dim, void* hip_stream) {
 
 void tc_destroy(tc_ctx* ctx) {
     if (!ctx) return;
-    if (ctx->lvl_ev) (void)hipEventSynchronize(ctx->lvl_ev);
-    if (ctx->lvl_ev) (void)hipEventDestroy(ctx->lvl_ev);
-    if (ctx->lvl_host) (void)hipHostFree(ctx->lvl_host);
     for (hipEvent_t e : ctx->ev_pending) (void)hipEventDestroy(e);
     for (const auto& e : ctx->st_pending) {
         (void)hipEventDestroy(e.a);
@@ -1200,13 +1173,11 @@ int tc_forces_noalloc(tc_ctx* ctx, const void* pos, const void* mass, int64_t n,
     // no events either: timing stays off for this call
     const bool timing = ctx->timing, stage_timing = ctx->stage_timing;
     ctx->timing = ctx->stage_timing = false;
-    ctx->no_alloc = true;
     hipStream_t s = ctx->stream;
     rc = do_build(ctx, pos, mass, n, leaf_cap, dtype, s);
     if (rc == TC_OK) rc = do_moments(ctx, s);
     if (rc == TC_OK) rc = do_walk(ctx, theta, s);
     if (rc == TC_OK) rc = do_forces(ctx, G, eps);
-    ctx->no_alloc = false;
     ctx->timing = timing;
     ctx->stage_timing = stage_timing;
     if (rc != TC_OK) return rc;

@@ -19,10 +19,9 @@
 //            exclusive scan is the depth-first pre-order index; the level
 //            order is one more radix pass, keyed by level, and the walk
 //            groups one more scan
-//   moments  FP64, leaves over bodies in order (one launch), then internal
-//            cells level by level from the deepest up, each over its
-//            children in digit order read from level-order copies (the top
-//            and the deepest levels each in one single-block launch)
+//   moments  FP64, leaves over bodies in order, internal cells over their
+//            children in digit order: small subtrees within a block each,
+//            the cells above them by one block
 //   mac      opening radius per cell for the current theta
 //
 // Every expression that decides an integer (keys, topology, opening radii)
@@ -31,6 +30,8 @@
 #include "keys.h"
 
 #include <math.h>
+
+#include <algorithm>
 
 namespace tc {
 namespace {
@@ -714,9 +715,10 @@ template <int D>
 __global__ void __launch_bounds__(256) k_topo_emit(const uint64_t* __restrict__ keys, int64_t n,
                                                    const uint32_t* __restrict__ range,
                                                    const uint32_t* __restrict__ cstart, Cell* __restrict__ cells,
-                                                   int64_t cmax, DevParams* prm) {
+                                                   int64_t cmax, DevParams* prm, BigList big) {
     constexpr int L = D == 3 ? 21 : 31;
     const uint32_t C = cstart[n];
+    if (blockIdx.x == 0 && threadIdx.x < kLevels) big.count[threadIdx.x * BigList::kStride] = 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         // C never exceeds the bound (internal cells are disjoint per level
         // and hold > leaf_cap bodies); clamp anyway so no reader can run off
@@ -783,24 +785,51 @@ __global__ void __launch_bounds__(256) k_topo_ends(const uint64_t* __restrict__ 
     }
 }
 
-__global__ void __launch_bounds__(256) k_topo_link(Cell* __restrict__ cells,
-                                                   const DevParams* __restrict__ prm, int64_t cmax) {
+// Parents and child counts: each internal cell walks over its children (the
+// next one starts where the last one's subtree ends).  Cells with subtrees of
+// more than big.sub cells also go on their level's list in `big` (BigList),
+// for the upper part of the moments pass: a block counts its own per level and takes
+// their places with one add per level (an add per cell would have thousands
+// of adds on one address wait for each other).
+constexpr int kLinkThreads = 1024;
+
+__global__ void __launch_bounds__(kLinkThreads) k_topo_link(Cell* __restrict__ cells,
+                                                            const DevParams* __restrict__ prm, int64_t cmax,
+                                                            BigList big) {
+    __shared__ uint32_t s_n[kLevels], s_at[kLevels];
     int64_t C = prm->ncells;
     if (C > cmax) C = cmax;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < C;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const Cell c = cells[k];
-        if (c.leaf_nch < 0) continue;          // leaf
-        int nch = 0;
-        int64_t ch = k + 1;
-        const int64_t end = c.skip < C ? c.skip : C;
-        while (ch < end) {
-            cells[ch].parent = (int32_t)k;
-            ++nch;
-            const int64_t nx = cells[ch].skip;
-            ch = nx > ch ? nx : end;           // defensive: the skip chain only moves forward
+    const int t = threadIdx.x;
+    for (int64_t k0 = blockIdx.x * (int64_t)kLinkThreads; k0 < C; k0 += (int64_t)gridDim.x * kLinkThreads) {
+        const int64_t k = k0 + t;
+        if (t < kLevels) s_n[t] = 0u;
+        __syncthreads();
+        int level = -1;
+        uint32_t at = 0;
+        if (k < C) {
+            const Cell c = cells[k];
+            if (c.leaf_nch >= 0) {
+                int nch = 0;
+                int64_t ch = k + 1;
+                const int64_t end = c.skip < C ? c.skip : C;
+                while (ch < end) {
+                    cells[ch].parent = (int32_t)k;
+                    ++nch;
+                    const int64_t nx = cells[ch].skip;
+                    ch = nx > ch ? nx : end;       // defensive: the skip chain only moves forward
+                }
+                cells[k].leaf_nch = nch;
+                if (c.skip - k > big.sub) {
+                    level = c.level;
+                    at = atomicAdd(&s_n[level], 1u);
+                }
+            }
         }
-        cells[k].leaf_nch = nch;
+        __syncthreads();
+        if (t < kLevels && s_n[t]) s_at[t] = atomicAdd(big.count + t * BigList::kStride, s_n[t]);
+        __syncthreads();
+        if (level >= 0 && s_at[level] + at < big.cap) big.cell[(size_t)level * big.cap + s_at[level] + at] = (uint32_t)k;
+        __syncthreads();                           // the counts are cleared for the next cells
     }
 }
 
@@ -839,197 +868,283 @@ __device__ void leaf_moments(const Cell& c, const Body* __restrict__ bodies, Mom
     mo.pad = 0.0;
 }
 
-// An internal cell's moments from its children's, in digit order.  The
-// children are contiguous in level order from the level-order index
-// `first`, and kid points at their level-order copies.
-template <int D>
-__device__ void internal_moments(const Moments* __restrict__ kid, int nch, Moments& mo) {
-    // fixed trip counts (predicated) let all children's loads issue together
-    double M = 0.0, S0 = 0.0, S1 = 0.0, S2 = 0.0;
+constexpr int kMomDoubles = 13;                  // M, S, com, Q
+
+// An internal cell's moments from its children's in LDS (kMomDoubles each), by
+// eight lanes: lane q sums M (q = 0) or one component of S (q = 1, 2, 3) into
+// `sum` and one component of Q (q < 6) into `quad`; all lanes get com.  place(i)
+// is where child i's moments are, or -1.  Children are added in digit order; a
+// lane reads all of them before it adds (the adds are selected, not branched
+// around).  One lane per cell instead waits on some 500 dependent FP64
+// operations: 2.2 us a level.
+template <int D, typename P>
+__device__ __forceinline__ void sum_children(const double (*sm)[kMomDoubles], P&& place, int q, double& sum,
+                                             double (&com)[3], double& quad) {
+    constexpr int N = 1 << D;
+    const int base = (threadIdx.x & (kWave - 1)) - q;
+    int at[N];
 #pragma unroll
-    for (int i = 0; i < (1 << D); ++i) {
-        if (i >= nch) continue;
-        M = M + kid[i].M;
-        S0 = S0 + kid[i].S[0];
-        S1 = S1 + kid[i].S[1];
-        if (D == 3) S2 = S2 + kid[i].S[2];
-    }
-    mo.M = M;
-    mo.S[0] = S0; mo.S[1] = S1; mo.S[2] = S2;
-    mo.com[0] = S0 / M; mo.com[1] = S1 / M; mo.com[2] = D == 3 ? S2 / M : 0.0;
-    double Q[6] = {0, 0, 0, 0, 0, 0};
+    for (int i = 0; i < N; ++i) at[i] = place(i);
+    double x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = sm[max(at[i], 0)][q < 4 ? q : 0];
+    double v = 0.0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v = at[i] >= 0 ? v + x[i] : v;
+    sum = v;
+    const double c = v / __shfl(v, base, kWave);
+    com[0] = __shfl(c, base + 1, kWave);
+    com[1] = __shfl(c, base + 2, kWave);
+    com[2] = D == 3 ? __shfl(c, base + 3, kWave) : 0.0;
+    quad = 0.0;
     if (D == 3) {
+        // component q: xx, yy, zz, xy, xz, yz
+        const int qa = q < 3 ? q : q == 5 ? 1 : 0, qb = q < 3 ? q : q == 3 ? 1 : 2;
 #pragma unroll
-        for (int i = 0; i < (1 << D); ++i) {
-            if (i >= nch) continue;
-            const double s0 = kid[i].com[0] - mo.com[0];
-            const double s1 = kid[i].com[1] - mo.com[1];
-            const double s2 = kid[i].com[2] - mo.com[2];
+        for (int i = 0; i < N; ++i) {
+            const double* k = sm[max(at[i], 0)];
+            const double s0 = k[4] - com[0];
+            const double s1 = k[5] - com[1];
+            const double s2 = k[6] - com[2];
             const double r2 = (s0 * s0 + s1 * s1) + s2 * s2;
-            const double Mc = kid[i].M;
-            Q[0] = Q[0] + (kid[i].Q[0] + Mc * ((3.0 * s0) * s0 - r2));
-            Q[1] = Q[1] + (kid[i].Q[1] + Mc * ((3.0 * s1) * s1 - r2));
-            Q[2] = Q[2] + (kid[i].Q[2] + Mc * ((3.0 * s2) * s2 - r2));
-            Q[3] = Q[3] + (kid[i].Q[3] + Mc * ((3.0 * s0) * s1));
-            Q[4] = Q[4] + (kid[i].Q[4] + Mc * ((3.0 * s0) * s2));
-            Q[5] = Q[5] + (kid[i].Q[5] + Mc * ((3.0 * s1) * s2));
+            const double sa = qa == 0 ? s0 : qa == 1 ? s1 : s2, sb = qb == 0 ? s0 : qb == 1 ? s1 : s2;
+            const double term = k[7 + min(q, 5)] + k[0] * ((3.0 * sa) * sb - (q < 3 ? r2 : 0.0));
+            quad = at[i] >= 0 ? quad + term : quad;
         }
     }
-    for (int q = 0; q < 6; ++q) mo.Q[q] = Q[q];
-    mo.pad = 0.0;
 }
 
+// The walk record of cell k, in level order.
 __device__ __forceinline__ void store_walk(WalkCell* walk, const uint32_t* __restrict__ pre2bfs, int64_t k,
-                                           const Cell& c, const Moments& mo) {
+                                           int32_t leaf_nch, int32_t begin, int32_t count, const Moments& mo) {
     WalkCell w;
     w.cx = mo.com[0];
     w.cy = mo.com[1];
     w.cz = mo.com[2];
     w.rcrit2 = INFINITY;
     w.m = (float)mo.M;
-    if (c.leaf_nch < 0) {
-        w.a = c.begin;
-        w.b = (c.count & 0x7fffffff) | (int32_t)0x80000000u;
+    if (leaf_nch < 0) {
+        w.a = begin;
+        w.b = (count & 0x7fffffff) | (int32_t)0x80000000u;
     } else {
         w.a = (int32_t)pre2bfs[k + 1];           // first child, pre-order k + 1
-        w.b = c.leaf_nch;
+        w.b = leaf_nch;
     }
     w.pad = 0;
     walk[pre2bfs[k]] = w;
 }
 
-// Leaves first, all levels in one launch (in pre-order, each leaf summing
-// its bodies in order), which also records every cell's children in level
-// order (first child, count; a leaf gets kLeafKids) and a level-order copy
-// of the leaves' moments.  Then one launch per level, deepest first, for
-// the internal cells: a cell's children sit one level below it and were
-// finished by an earlier launch, so no cross-block synchronisation is
-// needed, and with the level-order copies a cell waits on two dependent
-// loads (its children's range, then their moments) instead of five.
-// Internal cells sum their children in digit order: the result does not
-// depend on scheduling.  (Leaves inside the per-level launches and
-// children found through the pre-order arrays took 186 us per build of 1M
-// bodies; leaves first, 171 us.)
-constexpr uint32_t kLeafKids = 0xffffffffu;
+// The moments in two launches.  The maximal subtrees of at most SUB cells
+// are done in LDS: they are runs of cells in pre-order, so a block takes those
+// that start in its SUB cells (at most twice as many cells, a lane
+// each), sums the leaves over their bodies and follows the levels from the
+// deepest up, with nothing to wait for outside the block.  The few cells above
+// them (about C / 75 or C / 150) are done level by level by one block.  A launch per
+// level instead, each cell waiting on its children's moments in memory, took
+// 5 to 12 us a level, ten launches at 1M bodies.  Children are summed in digit
+// order, so the result does not depend on scheduling.
 
-template <int D>
-__global__ void __launch_bounds__(256) k_leaf_moments(const Cell* __restrict__ cells, const Body* __restrict__ bodies,
-                                                      const uint32_t* __restrict__ pre2bfs,
-                                                      const DevParams* __restrict__ prm, int64_t cmax,
-                                                      Moments* __restrict__ mom, Moments* __restrict__ mom_lvl,
-                                                      uint2* __restrict__ kids, WalkCell* __restrict__ walk) {
+template <int D, int SUB>
+__global__ void __launch_bounds__(2 * SUB) __attribute__((amdgpu_waves_per_eu(4, 8))) k_moments_low(const Cell* __restrict__ cells,
+                                                             const Body* __restrict__ bodies,
+                                                             const uint32_t* __restrict__ pre2bfs,
+                                                             const DevParams* __restrict__ prm, int64_t cmax,
+                                                             Moments* __restrict__ mom, WalkCell* __restrict__ walk) {
+    constexpr int N = 1 << D;
+    __shared__ double s_mom[(2 * SUB)][kMomDoubles];
+    __shared__ __align__(16) int16_t s_child[(2 * SUB)][N];   // a cell's children by digit, -1 where none
+    __shared__ uint16_t s_list[(2 * SUB)];                    // internal cells by level
+    __shared__ uint32_t s_lvl[kLevels + 1], s_next[kLevels];
+    __shared__ int s_first[2];
     int64_t C = prm->ncells;
     if (C > cmax) C = cmax;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < C; k += (int64_t)gridDim.x * blockDim.x) {
-        const Cell c = cells[k];
-        const uint32_t b = pre2bfs[k];
-        if (c.leaf_nch >= 0) {
-            kids[b] = make_uint2(pre2bfs[k + 1], (uint32_t)c.leaf_nch);   // first child: pre-order k + 1
-            continue;
-        }
-        kids[b] = make_uint2(0u, kLeafKids);
-        Moments mo;
-        leaf_moments<D>(c, bodies, mo);
-        mom[k] = mo;
-        mom_lvl[b] = mo;
-        store_walk(walk, pre2bfs, k, c, mo);
-    }
-}
-
-// The outputs of internal cell b (level order) with children kc.
-__device__ __forceinline__ void store_internal(int64_t b, uint2 kc, const Moments& mo,
-                                               const uint32_t* __restrict__ bfs2pre, Moments* mom,
-                                               Moments* mom_lvl, WalkCell* __restrict__ walk) {
-    mom_lvl[b] = mo;
-    mom[bfs2pre[b]] = mo;
-    WalkCell w;
-    w.cx = mo.com[0];
-    w.cy = mo.com[1];
-    w.cz = mo.com[2];
-    w.rcrit2 = INFINITY;
-    w.m = (float)mo.M;
-    w.a = (int32_t)kc.x;
-    w.b = (int32_t)kc.y;
-    w.pad = 0;
-    walk[b] = w;
-}
-
-// One internal cell of the level passes.
-template <int D>
-__device__ __forceinline__ void moments_of_internal(int64_t b, const uint32_t* __restrict__ bfs2pre,
-                                                    const uint2* __restrict__ kids, Moments* mom, Moments* mom_lvl,
-                                                    WalkCell* __restrict__ walk) {
-    const uint2 kc = kids[b];
-    if (kc.y == kLeafKids) return;
-    Moments mo;
-    internal_moments<D>(mom_lvl + kc.x, (int)kc.y, mo);
-    store_internal(b, kc, mo, bfs2pre, mom, mom_lvl, walk);
-}
-
-// Levels `deepest` down to top + 1, deepest first, in one block: a launch
-// costs a few microseconds even when its level is nearly empty, and most of
-// the deepest levels are.  Which levels come here follows from an earlier
-// tree, so they usually hold few cells; any cells they do hold are still
-// done (in order: a barrier separates the levels, and the block's waves
-// share one CU's L1).
-constexpr int kDeepThreads = 1024;
-
-template <int D>
-__global__ void __launch_bounds__(kDeepThreads) k_moments_deep(const uint32_t* __restrict__ bfs2pre,
-                                                               const uint32_t* __restrict__ lvl_off, int top,
-                                                               int deepest, const uint2* __restrict__ kids,
-                                                               Moments* mom, Moments* mom_lvl,
-                                                               WalkCell* __restrict__ walk) {
-    for (int l = deepest; l > top; --l) {
-        const int64_t b0 = lvl_off[l], b1 = lvl_off[l + 1];
-        for (int64_t b = b0 + threadIdx.x; b < b1; b += kDeepThreads)
-            moments_of_internal<D>(b, bfs2pre, kids, mom, mom_lvl, walk);
+    const int t = threadIdx.x;
+    for (int64_t b0 = blockIdx.x * (int64_t)SUB; b0 < C; b0 += (int64_t)gridDim.x * SUB) {
+        // the block's run: from the first cell of its SUB that starts a
+        // subtree or lies above them, to the next block's
+        if (t < 2) s_first[t] = SUB;
+        if (t < kLevels) s_next[t] = 0u;
+#pragma unroll
+        for (int i = 0; i < N; ++i) s_child[t][i] = -1;
         __syncthreads();
-    }
-}
-
-template <int D>
-__global__ void __launch_bounds__(256) k_moments_level(const uint32_t* __restrict__ bfs2pre,
-                                                       const uint32_t* __restrict__ lvl_off, int level,
-                                                       const uint2* __restrict__ kids, Moments* mom,
-                                                       Moments* mom_lvl, WalkCell* __restrict__ walk) {
-    const int64_t b0 = lvl_off[level], b1 = lvl_off[level + 1];
-    for (int64_t b = b0 + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < b1;
-         b += (int64_t)gridDim.x * blockDim.x)
-        moments_of_internal<D>(b, bfs2pre, kids, mom, mom_lvl, walk);
-}
-
-// Levels `head` down to 0 in one block, their moments kept in LDS: these
-// levels occupy level-order indices 0 .. lvl_off[head + 1] - 1, so a cell's
-// LDS slot is its level-order index, and each level reads its children from
-// LDS instead of going round through memory (the head level's children
-// come from the level below, done by an earlier launch).  Which levels come
-// here follows from an earlier tree; if the current one holds more than
-// kHeadCells cells in them, the block reads the children from memory
-// instead, as the per-level passes do.
-constexpr int kHeadCells = 512;
-
-template <int D>
-__global__ void __launch_bounds__(kDeepThreads) k_moments_head(const uint32_t* __restrict__ bfs2pre,
-                                                               const uint32_t* __restrict__ lvl_off, int head,
-                                                               const uint2* __restrict__ kids, Moments* mom,
-                                                               Moments* mom_lvl, WalkCell* __restrict__ walk) {
-    __shared__ Moments s_m[kHeadCells];
-    const bool fit = lvl_off[head + 1] <= (uint32_t)kHeadCells;
-    for (int l = head; l >= 0; --l) {
-        const int64_t b0 = lvl_off[l], b1 = lvl_off[l + 1];
-        for (int64_t b = b0 + threadIdx.x; b < b1; b += kDeepThreads) {
-            const uint2 kc = kids[b];
-            if (kc.y == kLeafKids) {
-                if (fit) s_m[b] = mom_lvl[b];
-                continue;
+        {
+            const int64_t k = b0 + t;
+            if (k < C) {
+                const Cell c = cells[k];
+                const bool starts = c.skip - k > SUB || c.parent < 0 ||
+                                    cells[c.parent].skip - c.parent > SUB;
+                if (starts) atomicMin(&s_first[t / SUB], t % SUB);
             }
-            Moments mo;
-            internal_moments<D>((fit && l < head ? s_m : mom_lvl) + kc.x, (int)kc.y, mo);
-            if (fit) s_m[b] = mo;
-            store_internal(b, kc, mo, bfs2pre, mom, mom_lvl, walk);
         }
         __syncthreads();
+        const int64_t k0 = b0 + s_first[0];
+        int64_t k1 = b0 + SUB + s_first[1];
+        if (k1 > C) k1 = C;
+        const int n = s_first[0] < SUB ? (int)(k1 - k0) : 0;
+        const int64_t k = k0 + t;
+        Cell c;
+        Moments mo;
+        bool internal = false, leaf = false;
+        uint32_t slot = 0;
+        if (t < n) {
+            c = cells[k];
+            leaf = c.leaf_nch < 0;
+            internal = !leaf && c.skip - k <= SUB;
+            if (c.parent >= k0) s_child[c.parent - k0][c.prefix & (N - 1)] = (int16_t)t;
+            if (internal) slot = atomicAdd(&s_next[c.level], 1u);
+            if (leaf) {
+                leaf_moments<D>(c, bodies, mo);
+                double* o = s_mom[t];
+                o[0] = mo.M;
+                for (int a = 0; a < 3; ++a) {
+                    o[1 + a] = mo.S[a];
+                    o[4 + a] = mo.com[a];
+                }
+                for (int a = 0; a < 6; ++a) o[7 + a] = mo.Q[a];
+            }
+        }
+        __syncthreads();
+        if (t < kLevels) {
+            uint32_t at = 0;
+            for (int l = 0; l < t; ++l) at += s_next[l];
+            s_lvl[t] = at;
+            if (t == kLevels - 1) s_lvl[kLevels] = at + s_next[t];
+        }
+        __syncthreads();
+        if (internal) s_list[s_lvl[c.level] + slot] = (uint16_t)t;
+        __syncthreads();
+        const int q = t & 7;
+        for (int l = kLevels - 1; l >= 0; --l) {
+            if (s_lvl[l] == s_lvl[l + 1]) continue;
+            for (uint32_t e = s_lvl[l] + t / 8; e < s_lvl[l + 1]; e += (2 * SUB) / 8) {
+                const int j = s_list[e];
+                double sum, com[3], quad;
+                sum_children<D>(s_mom, [&](int i) { return (int)s_child[j][i]; }, q, sum, com, quad);
+                if (q < 4) s_mom[j][q] = sum;
+                if (q < 3) s_mom[j][4 + q] = q == 0 ? com[0] : q == 1 ? com[1] : com[2];
+                if (q < 6) s_mom[j][7 + q] = quad;
+            }
+            __syncthreads();
+        }
+        if (leaf || internal) {
+            if (internal) {
+                const double* o = s_mom[t];
+                mo.M = o[0];
+                for (int a = 0; a < 3; ++a) {
+                    mo.S[a] = o[1 + a];
+                    mo.com[a] = o[4 + a];
+                }
+                for (int a = 0; a < 6; ++a) mo.Q[a] = o[7 + a];
+                mo.pad = 0.0;
+            }
+            mom[k] = mo;
+            store_walk(walk, pre2bfs, k, c.leaf_nch, c.begin, c.count, mo);
+        }
+        __syncthreads();                         // s_first and the rest are rewritten
+    }
+}
+
+// The cells above, levels hi down to lo, from their lists, in one block (a
+// barrier separates the levels, and the block's waves share one CU's L1), or
+// one level in any number of blocks.  A round takes up to kUpperCells cells of
+// a level: their children's moments are
+// brought to LDS eight lanes a child (one line per child; a lane per cell
+// reading its children itself spends 64 lines per load and took 5 us a level
+// of 170 cells), then eight lanes add up a cell.  What leads to the children
+// (the cell, its first child's place in level order, the children there) is
+// looked up for the first kUpperTable cells before the first round, so a
+// level waits on its children's moments only.
+constexpr int kUpperThreads = 1024;
+constexpr int kUpperCells = kUpperThreads / 8;
+constexpr int kUpperTable = 640;
+constexpr int64_t kUpperSplit = (int64_t)1 << 22;   // cell slots from which the levels get launches of their own
+
+template <int D>
+__global__ void __launch_bounds__(kUpperThreads) k_moments_upper(const Cell* __restrict__ cells,
+                                                                 const uint32_t* __restrict__ pre2bfs,
+                                                                 const uint32_t* __restrict__ bfs2pre, BigList big,
+                                                                 int hi, int lo, Moments* mom,
+                                                                 WalkCell* __restrict__ walk) {
+    constexpr int N = 1 << D;
+    __shared__ double s_mom[kUpperCells * N][kMomDoubles];
+    __shared__ uint32_t s_ch[kUpperTable][N];
+    __shared__ uint32_t s_k[kUpperTable], s_first[kUpperTable], s_at[kUpperTable];
+    __shared__ int32_t s_nch[kUpperTable];
+    __shared__ uint32_t s_n[kLevels];
+    const uint32_t t = threadIdx.x;
+    if (t < kLevels) s_n[t] = min(big.count[t * BigList::kStride], big.cap);
+    __syncthreads();
+    // cell i of level l into the table
+    auto look_up = [&](uint32_t slot, int l, uint32_t i) {
+        const uint32_t k = big.cell[(size_t)l * big.cap + i];
+        const int32_t nch = cells[k].leaf_nch;
+        const uint32_t first = pre2bfs[k + 1];
+        s_at[slot] = pre2bfs[k];
+        s_k[slot] = k;
+        s_first[slot] = first;
+        s_nch[slot] = nch;
+#pragma unroll
+        for (int c = 0; c < N; ++c) s_ch[slot][c] = bfs2pre[first + (c < nch ? c : 0)];
+    };
+    // one block: its first cells, in the order of the rounds
+    const uint32_t table = gridDim.x == 1 ? kUpperTable : 0u;
+    if (t < table) {
+        int l = hi;
+        uint32_t i = t;
+        while (l >= lo && i >= s_n[l]) i -= s_n[l--];
+        if (l >= lo) look_up(t, l, i);
+    }
+    __syncthreads();
+    uint32_t done = 0;                               // cells of the earlier rounds
+    for (int l = hi; l >= lo; --l) {
+        for (uint32_t i0 = blockIdx.x * kUpperCells; i0 < s_n[l]; i0 += gridDim.x * kUpperCells) {
+            const uint32_t m = min((uint32_t)kUpperCells, s_n[l] - i0);
+            uint32_t at = done;
+            if (at + m > table) {                    // not in the table: over its first, used places
+                at = 0;
+                if (t < m) look_up(t, l, i0 + t);
+                __syncthreads();
+            }
+            // the children's records, 16 bytes a lane (the last eighth of the
+            // eight lanes has none)
+            const double2* rec = reinterpret_cast<const double2*>(mom);
+#pragma unroll 8
+            for (uint32_t e = t / 8; e < m * N; e += kUpperThreads / 8) {
+                const uint32_t part = t & 7;
+                if (part < 7) {
+                    const double2 v = rec[(size_t)s_ch[at + e / N][e % N] * 7 + part];
+                    s_mom[e][2 * part] = v.x;
+                    if (part < 6) s_mom[e][2 * part + 1] = v.y;
+                }
+            }
+            __syncthreads();
+            const uint32_t j = t / 8;
+            const int q = (int)(t & 7);
+            if (j < m) {
+                const int nch = s_nch[at + j];
+                double sum, com[3], quad;
+                sum_children<D>(s_mom, [&](int i) { return i < nch ? (int)j * N + i : -1; }, q, sum, com, quad);
+                double* o = reinterpret_cast<double*>(&mom[s_k[at + j]]);
+                if (q < 4) o[q] = sum;
+                if (q < 3) o[4 + q] = q == 0 ? com[0] : q == 1 ? com[1] : com[2];
+                if (q < 7) o[7 + q] = q < 6 ? quad : 0.0;      // the last is the padding
+                if (q == 0) {
+                    WalkCell w;
+                    w.cx = com[0];
+                    w.cy = com[1];
+                    w.cz = com[2];
+                    w.rcrit2 = INFINITY;
+                    w.m = (float)sum;
+                    w.a = (int32_t)s_first[at + j];
+                    w.b = nch;
+                    w.pad = 0;
+                    walk[s_at[at + j]] = w;
+                }
+            }
+            done += m;
+            __threadfence_block();
+            __syncthreads();
+        }
     }
 }
 
@@ -1239,17 +1354,18 @@ hipError_t launch_scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_
 hipError_t launch_topology(const uint64_t* keys, int64_t n, int dim, int leaf_cap,
                            uint32_t* range, uint32_t* nper, uint32_t* cstart,
                            uint32_t* scan_part, int64_t scan_tiles, Cell* cells,
-                           int64_t cmax, DevParams* prm, hipStream_t s) {
+                           int64_t cmax, DevParams* prm, const BigList& big, hipStream_t s) {
     const unsigned nb = grid_for(n);
     if (dim == 3) hipLaunchKernelGGL(k_topo_count<3>, dim3(nb), dim3(256), 0, s, keys, n, leaf_cap, range, nper);
     else hipLaunchKernelGGL(k_topo_count<2>, dim3(nb), dim3(256), 0, s, keys, n, leaf_cap, range, nper);
     scan_u32(nper, n, nullptr, cstart, scan_part, scan_tiles, s);
-    if (dim == 3) hipLaunchKernelGGL(k_topo_emit<3>, dim3(nb), dim3(256), 0, s, keys, n, (const uint32_t*)range, (const uint32_t*)cstart, cells, cmax, prm);
-    else hipLaunchKernelGGL(k_topo_emit<2>, dim3(nb), dim3(256), 0, s, keys, n, (const uint32_t*)range, (const uint32_t*)cstart, cells, cmax, prm);
+    if (dim == 3) hipLaunchKernelGGL(k_topo_emit<3>, dim3(nb), dim3(256), 0, s, keys, n, (const uint32_t*)range, (const uint32_t*)cstart, cells, cmax, prm, big);
+    else hipLaunchKernelGGL(k_topo_emit<2>, dim3(nb), dim3(256), 0, s, keys, n, (const uint32_t*)range, (const uint32_t*)cstart, cells, cmax, prm, big);
     const unsigned nc = grid_for(cmax);
     if (dim == 3) hipLaunchKernelGGL(k_topo_ends<3>, dim3(nc), dim3(256), 0, s, keys, n, (const uint32_t*)cstart, cells, (const DevParams*)prm, cmax);
     else hipLaunchKernelGGL(k_topo_ends<2>, dim3(nc), dim3(256), 0, s, keys, n, (const uint32_t*)cstart, cells, (const DevParams*)prm, cmax);
-    hipLaunchKernelGGL(k_topo_link, dim3(nc), dim3(256), 0, s, cells, (const DevParams*)prm, cmax);
+    hipLaunchKernelGGL(k_topo_link, dim3(grid_for(cmax / 4)), dim3(kLinkThreads), 0, s, cells, (const DevParams*)prm,
+                       cmax, big);
     return hipGetLastError();
 }
 
@@ -1283,64 +1399,38 @@ hipError_t launch_groups(const Cell* cells, int64_t cmax, uint32_t* gper, uint32
     return hipGetLastError();
 }
 
-hipError_t launch_moments(const Cell* cells, const Body* bodies, int dim, int64_t cmax,
-                          const uint32_t* bfs2pre, const uint32_t* pre2bfs, const uint32_t* lvl_off,
-                          const DevParams* prm, Moments* mom, Moments* mom_lvl, uint2* kids, WalkCell* walk,
-                          const uint32_t* hint, hipStream_t s) {
-    const int L = levels_for(dim);
-    // levels L..top+1 go to one single-block launch, top..0 to one launch
-    // each.  (The top levels hold few cells too, but there one launch per
-    // level is the faster: a level's cost is a chain of dependent loads and
-    // stores either way, and the single block adds its barrier waits.)
-    int top = L;
-    int64_t cnt[66] = {};
-    if (hint) {
-        for (int l = 0; l <= L; ++l) cnt[l] = (int64_t)hint[l + 1] - (int64_t)hint[l];
-        top = 0;
-        for (int l = L; l > 0; --l)
-            if (cnt[l] > kDeepThreads) {
-                top = l;
-                break;
-            }
-    }
-    // levels head..0 (at most kHeadCells cells together, and at most down
-    // from top) go to one single-block launch with their moments in LDS
-    int head = -1;
-    if (hint)
-        while (head + 1 <= top && (int64_t)hint[head + 2] <= kHeadCells) ++head;
-    const unsigned nl = grid_for(cmax);
-    if (dim == 3)
-        hipLaunchKernelGGL(k_leaf_moments<3>, dim3(nl), dim3(256), 0, s, cells, bodies, pre2bfs, prm, cmax, mom,
-                           mom_lvl, kids, walk);
+template <int D>
+static void moments(const Cell* cells, const Body* bodies, int64_t cmax, const uint32_t* bfs2pre,
+                    const uint32_t* pre2bfs, const BigList& big, const DevParams* prm, Moments* mom, WalkCell* walk,
+                    hipStream_t s) {
+    constexpr int L = D == 3 ? 21 : 31;
+    const unsigned nb = (unsigned)std::min<int64_t>((cmax + big.sub - 1) / big.sub, 16384);
+    if (big.sub == 128)
+        hipLaunchKernelGGL((k_moments_low<D, 128>), dim3(nb), dim3(256), 0, s, cells, bodies, pre2bfs, prm, cmax, mom,
+                           walk);
     else
-        hipLaunchKernelGGL(k_leaf_moments<2>, dim3(nl), dim3(256), 0, s, cells, bodies, pre2bfs, prm, cmax, mom,
-                           mom_lvl, kids, walk);
-    if (top < L) {
-        if (dim == 3)
-            hipLaunchKernelGGL(k_moments_deep<3>, dim3(1), dim3(kDeepThreads), 0, s, bfs2pre, lvl_off, top, L,
-                               (const uint2*)kids, mom, mom_lvl, walk);
-        else
-            hipLaunchKernelGGL(k_moments_deep<2>, dim3(1), dim3(kDeepThreads), 0, s, bfs2pre, lvl_off, top, L,
-                               (const uint2*)kids, mom, mom_lvl, walk);
+        hipLaunchKernelGGL((k_moments_low<D, 256>), dim3(nb), dim3(512), 0, s, cells, bodies, pre2bfs, prm, cmax, mom,
+                           walk);
+    auto upper = [&](int hi, int lo, unsigned nb) {
+        hipLaunchKernelGGL(k_moments_upper<D>, dim3(nb), dim3(kUpperThreads), 0, s, cells, pre2bfs, bfs2pre, big, hi,
+                           lo, mom, walk);
+    };
+    if (cmax < kUpperSplit) {
+        upper(L, 0, 1);
+        return;
     }
-    for (int l = top; l > head; --l) {
-        // an earlier count plus a quarter: a grid-stride loop covers any more
-        const unsigned nb = hint ? grid_for(cnt[l] + cnt[l] / 4, 2048) : grid_for(cmax, 2048);
-        if (dim == 3)
-            hipLaunchKernelGGL(k_moments_level<3>, dim3(nb), dim3(256), 0, s, bfs2pre, lvl_off, l, kids, mom, mom_lvl,
-                               walk);
-        else
-            hipLaunchKernelGGL(k_moments_level<2>, dim3(nb), dim3(256), 0, s, bfs2pre, lvl_off, l, kids, mom, mom_lvl,
-                               walk);
-    }
-    if (head >= 0) {
-        if (dim == 3)
-            hipLaunchKernelGGL(k_moments_head<3>, dim3(1), dim3(kDeepThreads), 0, s, bfs2pre, lvl_off, head,
-                               (const uint2*)kids, mom, mom_lvl, walk);
-        else
-            hipLaunchKernelGGL(k_moments_head<2>, dim3(1), dim3(kDeepThreads), 0, s, bfs2pre, lvl_off, head,
-                               (const uint2*)kids, mom, mom_lvl, walk);
-    }
+    // large trees: the middle levels, which hold nearly all, by many blocks
+    constexpr int kTop = D == 3 ? 3 : 5, kDeep = D == 3 ? 13 : 17;
+    upper(L, kDeep, 1);
+    for (int l = kDeep - 1; l > kTop; --l) upper(l, l, (unsigned)std::min<int64_t>(256, big.cap / kUpperCells + 1));
+    upper(kTop, 0, 1);
+}
+
+hipError_t launch_moments(const Cell* cells, const Body* bodies, int dim, int64_t cmax, const uint32_t* bfs2pre,
+                          const uint32_t* pre2bfs, const BigList& big, const DevParams* prm, Moments* mom,
+                          WalkCell* walk, hipStream_t s) {
+    if (dim == 3) moments<3>(cells, bodies, cmax, bfs2pre, pre2bfs, big, prm, mom, walk, s);
+    else moments<2>(cells, bodies, cmax, bfs2pre, pre2bfs, big, prm, mom, walk, s);
     return hipGetLastError();
 }
 
