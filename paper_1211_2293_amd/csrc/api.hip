@@ -332,30 +332,52 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
         TC_HIP(ctx, launch_gather(packed, ctx->at<uint32_t>(l.off_idx_a), n, f64, ctx->at<Body>(l.off_bodies),
                                   ctx->at<float4>(l.off_bodies32), s));
     }
-    {
-        StageScope st_(ctx, TC_STAGE_TOPOLOGY, s);
-        TC_HIP(ctx, launch_topology(ctx->at<uint64_t>(l.off_keys_a), n, dim, leaf_cap,
-                                    ctx->at<uint32_t>(l.off_range), ctx->at<uint32_t>(l.off_nper),
-                                    ctx->at<uint32_t>(l.off_cstart), ctx->at<uint32_t>(l.off_scan_part),
-                                    l.scan_tiles, ctx->at<Cell>(l.off_cells),
-                                    l.cmax, prm, big_list(ctx), s));
-    }
-    {
-        StageScope st_(ctx, TC_STAGE_LEVELS, s);
-        // tiles sized for the cells a tree usually holds (about 4 per leaf_cap
-        // bodies), not for the slots
-        const int64_t cells_est = std::min<int64_t>(l.cmax, 4 * n / leaf_cap + 1);
-        TC_HIP(ctx, launch_level_order(ctx->at<Cell>(l.off_cells), l.cmax, cells_est, dim, prm,
-                                       ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_lvl_hist),
-                                       ctx->at<uint32_t>(l.off_digit_tot), ctx->at<uint32_t>(l.off_pre2bfs),
-                                       ctx->at<uint32_t>(l.off_lvl_off), s));
-    }
-    {
+    // the cells a tree usually holds: about 4 per leaf_cap bodies
+    const int64_t cells_est = std::min<int64_t>(l.cmax, 4 * n / leaf_cap + 1);
+    if (fused_tree(n, cells_est)) {
+        const BigList big = big_list(ctx);
+        const TreeScratch a{ctx->at<uint32_t>(l.off_idx_b), ctx->at<uint32_t>(l.off_lvl_hist),
+                            ctx->at<uint32_t>(l.off_goff)};
+        {
+            StageScope st_(ctx, TC_STAGE_TOPOLOGY, s);
+            TC_HIP(ctx, launch_tree_cells(ctx->at<uint64_t>(l.off_keys_a), n, dim, leaf_cap,
+                                          ctx->at<uint32_t>(l.off_range), ctx->at<uint32_t>(l.off_nper),
+                                          ctx->at<uint32_t>(l.off_cstart), ctx->at<Cell>(l.off_cells), l.cmax, prm,
+                                          big, a, s));
+        }
+        {
+            StageScope st_(ctx, TC_STAGE_LEVELS, s);
+            TC_HIP(ctx, launch_tree_link(ctx->at<Cell>(l.off_cells), l.cmax, dim, prm, big,
+                                         ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_pre2bfs),
+                                         ctx->at<uint32_t>(l.off_lvl_off), ctx->at<uint32_t>(l.off_gper), a, s));
+        }
         StageScope st_(ctx, TC_STAGE_GROUPS, s);
-        TC_HIP(ctx, launch_groups(ctx->at<Cell>(l.off_cells), l.cmax, ctx->at<uint32_t>(l.off_gper),
-                                  ctx->at<uint32_t>(l.off_goff), ctx->at<uint32_t>(l.off_gscan_part),
-                                  l.cscan_tiles, ctx->at<int32_t>(l.off_gbeg), ctx->at<int32_t>(l.off_gcnt),
-                                  l.gmax, prm, s));
+        TC_HIP(ctx, launch_tree_groups(ctx->at<Cell>(l.off_cells), l.cmax, ctx->at<uint32_t>(l.off_gper),
+                                       ctx->at<int32_t>(l.off_gbeg), ctx->at<int32_t>(l.off_gcnt), l.gmax, prm, a, s));
+    } else {
+        {
+            StageScope st_(ctx, TC_STAGE_TOPOLOGY, s);
+            TC_HIP(ctx, launch_topology(ctx->at<uint64_t>(l.off_keys_a), n, dim, leaf_cap,
+                                        ctx->at<uint32_t>(l.off_range), ctx->at<uint32_t>(l.off_nper),
+                                        ctx->at<uint32_t>(l.off_cstart), ctx->at<uint32_t>(l.off_scan_part),
+                                        l.scan_tiles, ctx->at<Cell>(l.off_cells),
+                                        l.cmax, prm, big_list(ctx), s));
+        }
+        {
+            StageScope st_(ctx, TC_STAGE_LEVELS, s);
+            // tiles sized for the estimate, not for the slots
+            TC_HIP(ctx, launch_level_order(ctx->at<Cell>(l.off_cells), l.cmax, cells_est, dim, prm,
+                                           ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_lvl_hist),
+                                           ctx->at<uint32_t>(l.off_digit_tot), ctx->at<uint32_t>(l.off_pre2bfs),
+                                           ctx->at<uint32_t>(l.off_lvl_off), s));
+        }
+        {
+            StageScope st_(ctx, TC_STAGE_GROUPS, s);
+            TC_HIP(ctx, launch_groups(ctx->at<Cell>(l.off_cells), l.cmax, ctx->at<uint32_t>(l.off_gper),
+                                      ctx->at<uint32_t>(l.off_goff), ctx->at<uint32_t>(l.off_gscan_part),
+                                      l.cscan_tiles, ctx->at<int32_t>(l.off_gbeg), ctx->at<int32_t>(l.off_gcnt),
+                                      l.gmax, prm, s));
+        }
     }
     ctx->mass = mass;
     ctx->n = n;

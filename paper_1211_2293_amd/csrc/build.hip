@@ -680,9 +680,11 @@ constexpr int kTopoTile = 256;
 
 template <int D>
 __global__ void __launch_bounds__(kTopoTile) k_topo_count(const uint64_t* __restrict__ keys, int64_t n, int leaf_cap,
-                                                          uint32_t* __restrict__ range, uint32_t* __restrict__ nper) {
+                                                          uint32_t* __restrict__ range, uint32_t* __restrict__ nper,
+                                                          uint32_t* __restrict__ tile_tot) {
     constexpr int L = D == 3 ? 21 : 31;
     __shared__ int8_t s_c[kTopoTile + kMaxLeafCap];   // c_j for j = i0 - leaf_cap .. i0 + kTopoTile - 1
+    __shared__ uint32_t s_tot;
     const int t = threadIdx.x;
     for (int64_t i0 = (int64_t)blockIdx.x * kTopoTile; i0 < n; i0 += (int64_t)gridDim.x * kTopoTile) {
         for (int q = t; q < kTopoTile + leaf_cap; q += kTopoTile) {
@@ -691,6 +693,7 @@ __global__ void __launch_bounds__(kTopoTile) k_topo_count(const uint64_t* __rest
         }
         __syncthreads();
         const int64_t i = i0 + t;
+        uint32_t own = 0;
         if (i < n) {
             const int a = (i == 0) ? 0 : common_digits<D>(keys[i - 1], keys[i]) + 1;
             // windows j = i - leaf_cap .. i (those out of range hold -1)
@@ -699,137 +702,381 @@ __global__ void __launch_bounds__(kTopoTile) k_topo_count(const uint64_t* __rest
             int lstar = 0;
             if (deep >= 0) lstar = (deep < L - 1 ? deep : L - 1) + 1;
             range[i] = (uint32_t)a | ((uint32_t)lstar << 8);
-            nper[i] = lstar >= a ? (uint32_t)(lstar - a + 1) : 0u;
+            own = lstar >= a ? (uint32_t)(lstar - a + 1) : 0u;
+            nper[i] = own;
+        }
+        if (tile_tot) {
+            if (t == 0) s_tot = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) own += __shfl_xor(own, o, kWave);
+            if (wave_lane() == 0) atomicAdd(&s_tot, own);
+            __syncthreads();
+            if (t == 0) tile_tot[i0 / kTopoTile] = s_tot;
         }
         __syncthreads();
     }
 }
 
 // The cells that start at body i (levels a_i..l*_i) at their pre-order
-// indices cstart[i] + (l - a_i): prefix, first body, level, parent and the
-// leaf mark.  Their ends (count and skip) come from k_topo_ends, one lane
-// per cell: a body that starts many cells would otherwise run their
-// searches one after another while the other lanes of its wave, most of
-// which start none, wait.
+// indices base + (l - a_i): prefix, first body, level, parent and the leaf
+// mark.  Their ends (count and skip) come from a pass with one lane per cell
+// (topo_end): a body that starts many cells would otherwise run their searches
+// one after another while the other lanes of its wave, most of which start
+// none, wait.
+template <int D>
+__device__ __forceinline__ void emit_cells(int64_t i, uint32_t range, uint32_t base, uint64_t key,
+                                           Cell* __restrict__ cells, int64_t cmax) {
+    constexpr int L = D == 3 ? 21 : 31;
+    const int a = (int)(range & 255u), lstar = (int)(range >> 8);
+    for (int l = a; l <= lstar; ++l) {
+        const int64_t k = (int64_t)base + (l - a);
+        if (k >= cmax) break;
+        Cell c;
+        c.prefix = l == 0 ? 0ull : key >> (D * (L - l));
+        c.begin = (int32_t)i;
+        c.count = 0;                               // topo_end
+        c.skip = 0;
+        c.parent = (l == 0) ? -1 : (l > a ? (int32_t)(k - 1) : -2);
+        c.level = l;
+        c.leaf_nch = (l == lstar) ? (int32_t)0x80000000u : 0;
+        cells[k] = c;
+    }
+}
+
+// The number of cells C, known once the last body's are placed.
+__device__ __forceinline__ void store_ncells(uint32_t C, int64_t cmax, DevParams* prm) {
+    // C never exceeds the bound (internal cells are disjoint per level
+    // and hold > leaf_cap bodies); clamp anyway so no reader can run off
+    prm->ncells = (int64_t)C > cmax ? (uint32_t)cmax : C;
+    if ((int64_t)C > cmax) atomicOr(&prm->status, kFlagOverflow);
+}
+
 template <int D>
 __global__ void __launch_bounds__(256) k_topo_emit(const uint64_t* __restrict__ keys, int64_t n,
                                                    const uint32_t* __restrict__ range,
                                                    const uint32_t* __restrict__ cstart, Cell* __restrict__ cells,
                                                    int64_t cmax, DevParams* prm, BigList big) {
-    constexpr int L = D == 3 ? 21 : 31;
-    const uint32_t C = cstart[n];
     if (blockIdx.x == 0 && threadIdx.x < kLevels) big.count[threadIdx.x * BigList::kStride] = 0u;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        // C never exceeds the bound (internal cells are disjoint per level
-        // and hold > leaf_cap bodies); clamp anyway so no reader can run off
-        prm->ncells = (int64_t)C > cmax ? (uint32_t)cmax : C;
-        if ((int64_t)C > cmax) atomicOr(&prm->status, kFlagOverflow);
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) store_ncells(cstart[n], cmax, prm);
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int a = (int)(range[i] & 255u), lstar = (int)(range[i] >> 8);
-        if (lstar < a) continue;
-        const uint32_t base = cstart[i];
-        const uint64_t key = keys[i];
-        for (int l = a; l <= lstar; ++l) {
-            const int64_t k = (int64_t)base + (l - a);
-            if (k >= cmax) break;
-            Cell c;
-            c.prefix = l == 0 ? 0ull : key >> (D * (L - l));
-            c.begin = (int32_t)i;
-            c.count = 0;                           // k_topo_ends
-            c.skip = 0;
-            c.parent = (l == 0) ? -1 : (l > a ? (int32_t)(k - 1) : -2);
-            c.level = l;
-            c.leaf_nch = (l == lstar) ? (int32_t)0x80000000u : 0;
-            cells[k] = c;
-        }
-    }
+         i += (int64_t)gridDim.x * blockDim.x)
+        emit_cells<D>(i, range[i], cstart[i], keys[i], cells, cmax);
 }
 
-// Each cell's end: the first body after its first whose prefix at the
-// cell's level differs (a galloping search, then bisection over the sorted
-// keys; the root ends at n), giving its body count and its skip (the
-// pre-order index of the cell that starts there).
+// A cell's end: the first body after its first whose prefix at the cell's
+// level differs (a galloping search, then bisection over the sorted keys; the
+// root ends at n), giving its body count and its skip (the pre-order index of
+// the cell that starts there).
+template <int D>
+__device__ __forceinline__ void topo_end(const uint64_t* __restrict__ keys, int64_t n,
+                                         const uint32_t* __restrict__ cstart, const Cell& c,
+                                         Cell* __restrict__ out) {
+    constexpr int L = D == 3 ? 21 : 31;
+    const int64_t i = c.begin;
+    const int l = c.level;
+    int64_t end = n;
+    if (l > 0) {
+        const int shift = D * (L - l);
+        const uint64_t prefix = c.prefix;
+        int64_t lo = i, step = 1, hi = i + 1;
+        while (hi < n && (keys[hi] >> shift) == prefix) {
+            lo = hi;
+            step <<= 1;
+            hi = i + step;
+        }
+        if (hi > n) hi = n;
+        while (hi - lo > 1) {
+            const int64_t mid = lo + ((hi - lo) >> 1);
+            if ((keys[mid] >> shift) == prefix) lo = mid; else hi = mid;
+        }
+        end = hi;
+    }
+    out->count = (int32_t)(end - i);
+    out->skip = (int32_t)cstart[end];
+}
+
 template <int D>
 __global__ void __launch_bounds__(256) k_topo_ends(const uint64_t* __restrict__ keys, int64_t n,
                                                    const uint32_t* __restrict__ cstart, Cell* __restrict__ cells,
                                                    const DevParams* __restrict__ prm, int64_t cmax) {
-    constexpr int L = D == 3 ? 21 : 31;
     int64_t C = prm->ncells;
     if (C > cmax) C = cmax;
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < C;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const Cell c = cells[k];
-        const int64_t i = c.begin;
-        const int l = c.level;
-        int64_t end = n;
-        if (l > 0) {
-            const int shift = D * (L - l);
-            const uint64_t prefix = c.prefix;
-            int64_t lo = i, step = 1, hi = i + 1;
-            while (hi < n && (keys[hi] >> shift) == prefix) {
-                lo = hi;
-                step <<= 1;
-                hi = i + step;
-            }
-            if (hi > n) hi = n;
-            while (hi - lo > 1) {
-                const int64_t mid = lo + ((hi - lo) >> 1);
-                if ((keys[mid] >> shift) == prefix) lo = mid; else hi = mid;
-            }
-            end = hi;
-        }
-        cells[k].count = (int32_t)(end - i);
-        cells[k].skip = (int32_t)cstart[end];
-    }
+         k += (int64_t)gridDim.x * blockDim.x)
+        topo_end<D>(keys, n, cstart, cells[k], &cells[k]);
 }
 
-// Parents and child counts: each internal cell walks over its children (the
-// next one starts where the last one's subtree ends).  Cells with subtrees of
-// more than big.sub cells also go on their level's list in `big` (BigList),
-// for the upper part of the moments pass: a block counts its own per level and takes
-// their places with one add per level (an add per cell would have thousands
-// of adds on one address wait for each other).
+// Parents and child counts: an internal cell walks over its children (the next
+// one starts where the last one's subtree ends); f(child index, child) for
+// each.
+template <typename F>
+__device__ __forceinline__ void link_children(Cell* __restrict__ cells, int64_t k, const Cell& c, int64_t C, F&& f) {
+    int nch = 0;
+    int64_t ch = k + 1;
+    const int64_t end = c.skip < C ? c.skip : C;
+    while (ch < end) {
+        cells[ch].parent = (int32_t)k;
+        ++nch;
+        const Cell cc = cells[ch];
+        f(ch, cc);
+        ch = cc.skip > ch ? (int64_t)cc.skip : end;   // defensive: the skip chain only moves forward
+    }
+    cells[k].leaf_nch = nch;
+}
+
+// Cells with subtrees of more than big.sub cells go on their level's list
+// (BigList), for the upper part of the moments pass: a block counts its own
+// per level and takes their places with one add per level (an add per cell
+// would have thousands of adds on one address wait for each other).  All of
+// the block's threads call this, level < 0 for no cell.
+__device__ __forceinline__ void list_upper(int level, int64_t k, const BigList& big) {
+    __shared__ uint32_t s_n[kLevels], s_at[kLevels];
+    const int t = threadIdx.x;
+    if (t < kLevels) s_n[t] = 0u;
+    __syncthreads();
+    uint32_t at = 0;
+    if (level >= 0) at = atomicAdd(&s_n[level], 1u);
+    __syncthreads();
+    if (t < kLevels && s_n[t]) s_at[t] = atomicAdd(big.count + t * BigList::kStride, s_n[t]);
+    __syncthreads();
+    if (level >= 0 && s_at[level] + at < big.cap) big.cell[(size_t)level * big.cap + s_at[level] + at] = (uint32_t)k;
+    __syncthreads();
+}
+
 constexpr int kLinkThreads = 1024;
 
 __global__ void __launch_bounds__(kLinkThreads) k_topo_link(Cell* __restrict__ cells,
                                                             const DevParams* __restrict__ prm, int64_t cmax,
                                                             BigList big) {
-    __shared__ uint32_t s_n[kLevels], s_at[kLevels];
     int64_t C = prm->ncells;
     if (C > cmax) C = cmax;
-    const int t = threadIdx.x;
     for (int64_t k0 = blockIdx.x * (int64_t)kLinkThreads; k0 < C; k0 += (int64_t)gridDim.x * kLinkThreads) {
-        const int64_t k = k0 + t;
-        if (t < kLevels) s_n[t] = 0u;
-        __syncthreads();
+        const int64_t k = k0 + threadIdx.x;
         int level = -1;
-        uint32_t at = 0;
         if (k < C) {
             const Cell c = cells[k];
             if (c.leaf_nch >= 0) {
-                int nch = 0;
-                int64_t ch = k + 1;
-                const int64_t end = c.skip < C ? c.skip : C;
-                while (ch < end) {
-                    cells[ch].parent = (int32_t)k;
-                    ++nch;
-                    const int64_t nx = cells[ch].skip;
-                    ch = nx > ch ? nx : end;       // defensive: the skip chain only moves forward
-                }
-                cells[k].leaf_nch = nch;
-                if (c.skip - k > big.sub) {
-                    level = c.level;
-                    at = atomicAdd(&s_n[level], 1u);
-                }
+                link_children(cells, k, c, C, [](int64_t, const Cell&) {});
+                if (c.skip - k > big.sub) level = c.level;
             }
         }
-        __syncthreads();
-        if (t < kLevels && s_n[t]) s_at[t] = atomicAdd(big.count + t * BigList::kStride, s_n[t]);
-        __syncthreads();
-        if (level >= 0 && s_at[level] + at < big.cap) big.cell[(size_t)level * big.cap + s_at[level] + at] = (uint32_t)k;
-        __syncthreads();                           // the counts are cleared for the next cells
+        list_upper(level, k, big);
+    }
+}
+
+// ---- topology, level order and walk groups of mid-size trees in five launches
+// (k_topo_count and the four below): the scans and the level sort are folded
+// into the kernels that use them.  Every block adds up the earlier tiles'
+// totals itself, which beats the scans' launches while there are few tiles
+// (fused_tree).  10,000 bodies: ten launches of 51 us in all before, 30 us
+// so; 50,000: 66 and 32; 1M: 86 and 53.
+
+constexpr int kTileThreads = 1024;               // bodies or cells per tile, a thread each
+
+// Sum of v over the block's threads before this one, and over all of them.
+__device__ __forceinline__ uint32_t tile_exscan(uint32_t v, uint32_t* s_w, uint32_t& total) {
+    const int lane = wave_lane(), w = threadIdx.x / kWave;
+    uint32_t x = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, kWave);
+        if (lane >= o) x += y;
+    }
+    if (lane == kWave - 1) s_w[w] = x;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int k = 0; k < kTileThreads / kWave; ++k) {
+        const uint32_t y = s_w[k];
+        if (k < w) before += y;
+        all += y;
+    }
+    __syncthreads();
+    total = all;
+    return before + x - v;
+}
+
+// Cells of the bodies, from the counts per body (nper) and per kTopoTile
+// bodies (tile_tot).
+template <int D>
+__global__ void __launch_bounds__(kTileThreads) k_tree_emit(const uint64_t* __restrict__ keys, int64_t n,
+                                                            const uint32_t* __restrict__ range,
+                                                            const uint32_t* __restrict__ nper,
+                                                            const uint32_t* __restrict__ tile_tot,
+                                                            uint32_t* __restrict__ cstart, Cell* __restrict__ cells,
+                                                            int64_t cmax, DevParams* prm, BigList big) {
+    __shared__ uint32_t s_w[kTileThreads / kWave];
+    const int t = threadIdx.x;
+    if (blockIdx.x == 0 && t < kLevels) big.count[t * BigList::kStride] = 0u;
+    const int64_t i = blockIdx.x * (int64_t)kTileThreads + t;
+    const uint32_t own = i < n ? nper[i] : 0u;
+    const int64_t tiles = blockIdx.x * (int64_t)(kTileThreads / kTopoTile);   // before this block
+    uint32_t part = 0, pre, total;
+    for (int64_t q = t; q < tiles; q += kTileThreads) part += tile_tot[q];
+    tile_exscan(part, s_w, pre);
+    const uint32_t at = pre + tile_exscan(own, s_w, total);
+    if (i < n) {
+        cstart[i] = at;
+        emit_cells<D>(i, range[i], at, keys[i], cells, cmax);
+        if (i == n - 1) {
+            cstart[n] = at + own;
+            store_ncells(at + own, cmax, prm);
+        }
+    }
+}
+
+// The cells' ends, and the tile's cells per level (hist[tile][kLevels]).  Also
+// clears the tile's group count for k_tree_link.
+template <int D>
+__global__ void __launch_bounds__(kTileThreads) k_tree_ends(const uint64_t* __restrict__ keys, int64_t n,
+                                                            const uint32_t* __restrict__ cstart,
+                                                            Cell* __restrict__ cells,
+                                                            const DevParams* __restrict__ prm, int64_t cmax,
+                                                            uint32_t* __restrict__ hist,
+                                                            uint32_t* __restrict__ gtile) {
+    __shared__ uint32_t s_n[kLevels];
+    int64_t C = prm->ncells;
+    if (C > cmax) C = cmax;
+    const int t = threadIdx.x;
+    const int64_t k = blockIdx.x * (int64_t)kTileThreads + t;
+    if (k - t >= C) return;
+    if (t < kLevels) s_n[t] = 0u;
+    __syncthreads();
+    if (k < C) {
+        const Cell c = cells[k];
+        atomicAdd(&s_n[c.level], 1u);
+        topo_end<D>(keys, n, cstart, c, &cells[k]);
+    }
+    __syncthreads();
+    if (t < kLevels) hist[(int64_t)blockIdx.x * kLevels + t] = s_n[t];
+    if (t == 0) gtile[blockIdx.x] = 0u;
+}
+
+__device__ __forceinline__ bool small_cell(const Cell& c) { return c.count <= kCluster || c.leaf_nch < 0; }
+__device__ __forceinline__ uint32_t groups_of(const Cell& c) { return (uint32_t)((c.count + kGroup - 1) / kGroup); }
+
+// Parents and child counts, the upper cells' lists, the level order (a stable
+// pass by level: the places of a tile's cells follow from the counts of all
+// tiles and their ranks within the tile), and the walk groups each cell is cut
+// into (gper, and per tile gtile): those of a cluster cell, which its parent
+// tells.
+__global__ void __launch_bounds__(kTileThreads) k_tree_link(Cell* __restrict__ cells,
+                                                            const DevParams* __restrict__ prm, int64_t cmax,
+                                                            BigList big, const uint32_t* __restrict__ hist,
+                                                            int last_level, uint32_t* __restrict__ bfs2pre,
+                                                            uint32_t* __restrict__ pre2bfs,
+                                                            uint32_t* __restrict__ lvl_off,
+                                                            uint32_t* __restrict__ gper, uint32_t* __restrict__ gtile) {
+    constexpr int kRows = kTileThreads / kLevels, kWaves = kTileThreads / kWave;
+    __shared__ uint32_t s_pre[kRows][kLevels], s_tot[kRows][kLevels];
+    __shared__ uint32_t s_wc[kWaves][kLevels];
+    __shared__ uint32_t s_base[kLevels];
+    int64_t C = prm->ncells;
+    if (C > cmax) C = cmax;
+    const int t = threadIdx.x, lane = wave_lane(), w = t / kWave;
+    const int64_t tile = blockIdx.x, k = tile * kTileThreads + t;
+    if (k - t >= C) return;
+    const Cell c = cells[k < C ? k : C - 1];
+    // cells per level in the earlier tiles and in all, 32 tiles side by side
+    const int tiles = (int)((C + kTileThreads - 1) / kTileThreads);
+    {
+        const int l = t % kLevels, row = t / kLevels;
+        uint32_t pre = 0, tot = 0;
+#pragma unroll 8
+        for (int q = row; q < tiles; q += kRows) {
+            const uint32_t v = hist[(int64_t)q * kLevels + l];
+            tot += v;
+            if (q < tile) pre += v;
+        }
+        s_pre[row][l] = pre;
+        s_tot[row][l] = tot;
+    }
+    if (t < kWaves * kLevels) (&s_wc[0][0])[t] = 0u;
+    __syncthreads();
+    // rank among the wave's cells of the same level, and the wave's counts
+    uint64_t peers = __ballot(k < C);
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+        const bool bit = (c.level >> b) & 1;
+        const uint64_t bb = __ballot(bit);
+        peers &= bit ? bb : ~bb;
+    }
+    const uint32_t rank = (uint32_t)__popcll(peers & (lane == 0 ? 0ull : ~0ull >> (kWave - lane)));
+    if (k < C && rank == 0) s_wc[w][c.level] = (uint32_t)__popcll(peers);
+    if (t < kLevels) {
+        uint32_t pre = 0, tot = 0;
+        for (int r = 0; r < kRows; ++r) {
+            pre += s_pre[r][t];
+            tot += s_tot[r][t];
+        }
+        // where the level starts: an exclusive scan over the 32 lanes
+        uint32_t x = tot;
+#pragma unroll
+        for (int o = 1; o < kLevels; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, kWave);
+            if (t >= o) x += y;
+        }
+        s_base[t] = x - tot + pre;
+        if (tile == 0) {
+            if (t <= last_level + 1) lvl_off[t] = x - tot;
+            if (t == kLevels - 1 && last_level == kLevels - 1) lvl_off[kLevels] = x;
+        }
+    }
+    __syncthreads();
+    int upper = -1;
+    if (k < C) {
+        uint32_t p = s_base[c.level] + rank;
+        for (int q = 0; q < w; ++q) p += s_wc[q][c.level];
+        bfs2pre[p] = (uint32_t)k;
+        pre2bfs[k] = p;
+        if (k == 0) {
+            const uint32_t g = small_cell(c) ? groups_of(c) : 0u;
+            gper[0] = g;
+            if (g) atomicAdd(&gtile[0], g);
+        }
+        if (c.leaf_nch >= 0) {
+            const bool big_parent = !small_cell(c);
+            link_children(cells, k, c, C, [&](int64_t ch, const Cell& cc) {
+                const uint32_t g = big_parent && small_cell(cc) ? groups_of(cc) : 0u;
+                gper[ch] = g;
+                if (g) atomicAdd(&gtile[ch / kTileThreads], g);
+            });
+            if (c.skip - k > big.sub) upper = c.level;
+        }
+    }
+    list_upper(upper, k, big);
+}
+
+// The walk groups, from the counts per cell and per tile.
+__global__ void __launch_bounds__(kTileThreads) k_tree_groups(const Cell* __restrict__ cells,
+                                                              const uint32_t* __restrict__ gper,
+                                                              const uint32_t* __restrict__ gtile, DevParams* prm,
+                                                              int64_t cmax, int32_t* __restrict__ gbeg,
+                                                              int32_t* __restrict__ gcnt, int64_t gmax) {
+    __shared__ uint32_t s_w[kTileThreads / kWave];
+    int64_t C = prm->ncells;
+    if (C > cmax) C = cmax;
+    const int t = threadIdx.x;
+    const int64_t tile = blockIdx.x, k = tile * kTileThreads + t;
+    if (k - t >= C) return;
+    const uint32_t own = k < C ? gper[k] : 0u;
+    uint32_t part = 0, pre, total;
+    for (int64_t q = t; q < tile; q += kTileThreads) part += gtile[q];
+    tile_exscan(part, s_w, pre);
+    const uint32_t g0 = pre + tile_exscan(own, s_w, total);
+    if (own) {
+        const Cell c = cells[k];
+        for (uint32_t g = g0; g < g0 + own && (int64_t)g < gmax; ++g) {
+            const int32_t o = (int32_t)(g - g0) * kGroup;
+            gbeg[g] = c.begin + o;
+            gcnt[g] = min(kGroup, c.count - o);
+        }
+    }
+    if (k == C - 1) {
+        const uint32_t G = g0 + own;
+        prm->ngroups = (int64_t)G > gmax ? (uint32_t)gmax : G;
+        if ((int64_t)G > gmax) atomicOr(&prm->status, kFlagOverflow);
     }
 }
 
@@ -1196,8 +1443,6 @@ __global__ void __launch_bounds__(256) k_mac(const Cell* __restrict__ cells, con
 // space.  Cluster cells are found in pre-order, so groups come out in body
 // order.
 
-__device__ __forceinline__ bool small_cell(const Cell& c) { return c.count <= kCluster || c.leaf_nch < 0; }
-
 __global__ void __launch_bounds__(256) k_group_count(const Cell* __restrict__ cells, const DevParams* __restrict__ prm,
                                                      int64_t cmax, uint32_t* __restrict__ gper) {
     int64_t C = prm->ncells;
@@ -1356,8 +1601,8 @@ hipError_t launch_topology(const uint64_t* keys, int64_t n, int dim, int leaf_ca
                            uint32_t* scan_part, int64_t scan_tiles, Cell* cells,
                            int64_t cmax, DevParams* prm, const BigList& big, hipStream_t s) {
     const unsigned nb = grid_for(n);
-    if (dim == 3) hipLaunchKernelGGL(k_topo_count<3>, dim3(nb), dim3(256), 0, s, keys, n, leaf_cap, range, nper);
-    else hipLaunchKernelGGL(k_topo_count<2>, dim3(nb), dim3(256), 0, s, keys, n, leaf_cap, range, nper);
+    if (dim == 3) hipLaunchKernelGGL(k_topo_count<3>, dim3(nb), dim3(256), 0, s, keys, n, leaf_cap, range, nper, (uint32_t*)nullptr);
+    else hipLaunchKernelGGL(k_topo_count<2>, dim3(nb), dim3(256), 0, s, keys, n, leaf_cap, range, nper, (uint32_t*)nullptr);
     scan_u32(nper, n, nullptr, cstart, scan_part, scan_tiles, s);
     if (dim == 3) hipLaunchKernelGGL(k_topo_emit<3>, dim3(nb), dim3(256), 0, s, keys, n, (const uint32_t*)range, (const uint32_t*)cstart, cells, cmax, prm, big);
     else hipLaunchKernelGGL(k_topo_emit<2>, dim3(nb), dim3(256), 0, s, keys, n, (const uint32_t*)range, (const uint32_t*)cstart, cells, cmax, prm, big);
@@ -1366,6 +1611,42 @@ hipError_t launch_topology(const uint64_t* keys, int64_t n, int dim, int leaf_ca
     else hipLaunchKernelGGL(k_topo_ends<2>, dim3(nc), dim3(256), 0, s, keys, n, (const uint32_t*)cstart, cells, (const DevParams*)prm, cmax);
     hipLaunchKernelGGL(k_topo_link, dim3(grid_for(cmax / 4)), dim3(kLinkThreads), 0, s, cells, (const DevParams*)prm,
                        cmax, big);
+    return hipGetLastError();
+}
+
+template <int D>
+static void tree_cells(const uint64_t* keys, int64_t n, int leaf_cap, uint32_t* range, uint32_t* nper,
+                       uint32_t* cstart, Cell* cells, int64_t cmax, DevParams* prm, const BigList& big,
+                       const TreeScratch& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_topo_count<D>, dim3(grid_for(n)), dim3(256), 0, s, keys, n, leaf_cap, range, nper, a.tile_tot);
+    hipLaunchKernelGGL(k_tree_emit<D>, dim3((unsigned)((n + kTileThreads - 1) / kTileThreads)), dim3(kTileThreads), 0,
+                       s, keys, n, (const uint32_t*)range, (const uint32_t*)nper, (const uint32_t*)a.tile_tot, cstart,
+                       cells, cmax, prm, big);
+    hipLaunchKernelGGL(k_tree_ends<D>, dim3((unsigned)((cmax + kTileThreads - 1) / kTileThreads)), dim3(kTileThreads),
+                       0, s, keys, n, (const uint32_t*)cstart, cells, (const DevParams*)prm, cmax, a.hist, a.gtile);
+}
+
+hipError_t launch_tree_cells(const uint64_t* keys, int64_t n, int dim, int leaf_cap, uint32_t* range, uint32_t* nper,
+                             uint32_t* cstart, Cell* cells, int64_t cmax, DevParams* prm, const BigList& big,
+                             const TreeScratch& a, hipStream_t s) {
+    if (dim == 3) tree_cells<3>(keys, n, leaf_cap, range, nper, cstart, cells, cmax, prm, big, a, s);
+    else tree_cells<2>(keys, n, leaf_cap, range, nper, cstart, cells, cmax, prm, big, a, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_link(Cell* cells, int64_t cmax, int dim, const DevParams* prm, const BigList& big,
+                            uint32_t* bfs2pre, uint32_t* pre2bfs, uint32_t* lvl_off, uint32_t* gper,
+                            const TreeScratch& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_tree_link, dim3((unsigned)((cmax + kTileThreads - 1) / kTileThreads)), dim3(kTileThreads), 0,
+                       s, cells, prm, cmax, big, (const uint32_t*)a.hist, levels_for(dim), bfs2pre, pre2bfs, lvl_off,
+                       gper, a.gtile);
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_groups(const Cell* cells, int64_t cmax, const uint32_t* gper, int32_t* gbeg, int32_t* gcnt,
+                              int64_t gmax, DevParams* prm, const TreeScratch& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_tree_groups, dim3((unsigned)((cmax + kTileThreads - 1) / kTileThreads)), dim3(kTileThreads), 0,
+                       s, cells, gper, (const uint32_t*)a.gtile, prm, cmax, gbeg, gcnt, gmax);
     return hipGetLastError();
 }
 

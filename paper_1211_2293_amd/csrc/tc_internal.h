@@ -166,6 +166,25 @@ hipError_t launch_body_scatter(const void* pos, const void* mass, int64_t n, int
 hipError_t launch_body_sort(const void* pos, const void* mass, int64_t n, int dim, int f64, const double* part,
                             int parts, DevParams* prm, const BodySort& a, Body* bodies, float4* bodies32,
                             hipStream_t s);
+// Mid-size trees: the same topology, level order and walk groups as
+// launch_topology, launch_level_order and launch_groups, with their scans
+// folded in.  Each block of 1024 cells reads the level counts of all of them,
+// so this is for at most a few hundred such tiles, by the host's estimate of
+// the cells.
+inline bool fused_tree(int64_t n, int64_t cells_est) { return n < kBucketMaxN && cells_est <= (int64_t)1 << 19; }
+struct TreeScratch {
+    uint32_t* tile_tot;          // [n / 256 + 1]
+    uint32_t* hist;              // [cmax / 1024 + 1][kLevels]
+    uint32_t* gtile;             // [cmax / 1024 + 1]
+};
+hipError_t launch_tree_cells(const uint64_t* keys, int64_t n, int dim, int leaf_cap, uint32_t* range, uint32_t* nper,
+                             uint32_t* cstart, Cell* cells, int64_t cmax, DevParams* prm, const BigList& big,
+                             const TreeScratch& a, hipStream_t s);
+hipError_t launch_tree_link(Cell* cells, int64_t cmax, int dim, const DevParams* prm, const BigList& big,
+                            uint32_t* bfs2pre, uint32_t* pre2bfs, uint32_t* lvl_off, uint32_t* gper,
+                            const TreeScratch& a, hipStream_t s);
+hipError_t launch_tree_groups(const Cell* cells, int64_t cmax, const uint32_t* gper, int32_t* gbeg, int32_t* gcnt,
+                              int64_t gmax, DevParams* prm, const TreeScratch& a, hipStream_t s);
 hipError_t launch_topology(const uint64_t* keys, int64_t n, int dim, int leaf_cap,
                            uint32_t* range, uint32_t* nper, uint32_t* cstart,
                            uint32_t* scan_part, int64_t scan_tiles, Cell* cells,

@@ -228,12 +228,15 @@ def test_body_order_is_the_stable_order_of_the_keys(name):
 
 
 @pytest.mark.parametrize("dim,n,lc", [(3, 150, 1), (3, 9000, 256), (3, 44_000, 1), (3, 46_000, 1), (3, 250_000, 1),
-                                      (3, 380_000, 1), (2, 60_000, 1), (2, 270_000, 1)])
+                                      (3, 380_000, 1), (2, 60_000, 1), (2, 270_000, 1), (3, 131_071, 1),
+                                      (3, 131_072, 1), (2, 650, 1), (3, 1023, 1), (3, 1025, 2)])
 def test_moments_on_both_sides_of_each_shape(dim, n, lc):
     """Cell moments and topology bit for bit against the oracle where the
     moments pass changes its shape: no cells above the blocks' subtrees, subtrees
     of 128 and of 256 cells, more cells above them than one block looks up in
-    advance, and the levels above in launches of their own."""
+    advance, and the levels above in launches of their own; and where the
+    topology does: its scans folded in (up to 131,071 bodies with leaf_cap 1)
+    and as launches, one tile of cells and a few."""
     pos = (workloads.plummer_sphere(n, seed=62).pos if dim == 3 else workloads.gaussian_disk(n, seed=63).pos)
     mass = np.random.default_rng(64).uniform(0.5, 2.0, n).astype(np.float32)
     g = gpu_tree(pos, mass, lc)
