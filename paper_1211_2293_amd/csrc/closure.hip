@@ -10,8 +10,8 @@
 //   y = (a_exact - a_mono) |x - C|^4 / (M s^2)   (G = 1),
 // where a_exact sums the cell's bodies directly.  The network is
 // 10-64-64-3 with GELU (tanh form); its products run on BF16 matrix-core
-// instructions with FP32 accumulation (training: 16x16x16 tiles through
-// LDS; inference: net_tile in closure.h) with FP32 master weights, trained
+// instructions with FP32 accumulation (training: 16x16x16 tiles;
+// inference: net_tile in closure.h) with FP32 master weights, trained
 // by mean squared error and Adam.
 //
 // This file: residual generation (one wave per target body; the walk is the
@@ -182,101 +182,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {        // round to nearest, 
     return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 
-__device__ __forceinline__ float gelu(float z) { return gelu_f(z); }
-
-__device__ __forceinline__ float gelu_grad(float z) { return gelu_grad_f(z); }
-
-// One 16x16 output tile of a product of BF16 matrices held in LDS:
-//   D(i, j) = sum_k A(i0 + i, k) B(k, j0 + j),  k < K (a multiple of 16),
-// with A(i, k) = A[i*sai + k*sak] and B(k, j) = B[k*sbk + j*sbj].  Lane l
-// supplies A rows l%16, columns 4(l/16)..+3 of each 16-wide k step and the
-// matching B entries, and receives D rows 4(l/16)+q, column l%16 (q < 4).
-__device__ __forceinline__ float4_t mm_tile(const uint16_t* A, int sai, int sak, int i0, const uint16_t* B, int sbk,
-                                            int sbj, int j0, int K) {
-    const int l = threadIdx.x & (kWave - 1);
-    const int r = l & 15, kq = 4 * (l >> 4);
-    float4_t acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        short4_t a, b;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            a[q] = (short)A[(i0 + r) * sai + (k0 + kq + q) * sak];
-            b[q] = (short)B[(k0 + kq + q) * sbk + (j0 + r) * sbj];
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-    }
-    return acc;
-}
-
-struct NetLds {
-    uint16_t w1[16 * kNHid], w2[kNHid * kNHid], w3[kNHid * 16];
-    float b1[kNHid], b2[kNHid], b3[16];
-    uint16_t x[kMlpBlock * 16], h1[kMlpBlock * kNHid], h2[kMlpBlock * kNHid];
-    float z1[kMlpBlock * kNHid], z2[kMlpBlock * kNHid];
-    float yh[kMlpBlock * 16];
-};
-
-__device__ void load_net(const MlpState* __restrict__ st, NetLds& L) {
-    const int l = threadIdx.x;
-    for (int i = l; i < 16 * kNHid; i += kWave) L.w1[i] = st->w1[i];
-    for (int i = l; i < kNHid * kNHid; i += kWave) L.w2[i] = st->w2[i];
-    for (int i = l; i < kNHid * 16; i += kWave) L.w3[i] = st->w3[i];
-    L.b1[l] = st->b1[l];
-    L.b2[l] = st->b2[l];
-    if (l < 16) L.b3[l] = st->b3[l];
-}
-
-// Forward pass for the 64 samples whose BF16 features sit in L.x.
-__device__ void net_forward(NetLds& L) {
-    const int l = threadIdx.x & (kWave - 1);
-    const int col = l & 15, rq = 4 * (l >> 4);
-    for (int rt = 0; rt < 4; ++rt)
-        for (int ct = 0; ct < 4; ++ct) {
-            const float4_t d = mm_tile(L.x, 16, 1, 16 * rt, L.w1, kNHid, 1, 16 * ct, 16);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = 16 * rt + rq + q, c = 16 * ct + col;
-                const float z = d[q] + L.b1[c];
-                L.z1[row * kNHid + c] = z;
-                L.h1[row * kNHid + c] = f2bf(gelu(z));
-            }
-        }
-    __syncthreads();
-    for (int rt = 0; rt < 4; ++rt)
-        for (int ct = 0; ct < 4; ++ct) {
-            const float4_t d = mm_tile(L.h1, kNHid, 1, 16 * rt, L.w2, kNHid, 1, 16 * ct, kNHid);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = 16 * rt + rq + q, c = 16 * ct + col;
-                const float z = d[q] + L.b2[c];
-                L.z2[row * kNHid + c] = z;
-                L.h2[row * kNHid + c] = f2bf(gelu(z));
-            }
-        }
-    __syncthreads();
-    for (int rt = 0; rt < 4; ++rt) {
-        const float4_t d = mm_tile(L.h2, kNHid, 1, 16 * rt, L.w3, 16, 1, 0, kNHid);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) L.yh[(16 * rt + rq + q) * 16 + col] = d[q] + L.b3[col];
-    }
-    __syncthreads();
-}
-
-__device__ void load_features(const float* __restrict__ feat, int64_t nrows, const int32_t* __restrict__ idx,
-                              int64_t nb, int64_t s0, NetLds& L, int64_t& src, bool& valid, uint32_t* status) {
-    const int l = threadIdx.x;
-    const int64_t s = s0 + l;
-    valid = s < nb;
-    src = valid ? (idx ? (int64_t)idx[s] : s) : 0;
-    if (valid && (src < 0 || src >= nrows)) {  // a row outside feat: left out, flagged
-        atomicOr(status, kFlagBadIndex);
-        valid = false;
-        src = 0;
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) L.x[l * 16 + q] = (valid && q < kNIn) ? f2bf(feat[src * kNIn + q]) : (uint16_t)0;
-}
-
 // Inference on rows of stored features, with the matrix-core routine of
 // the learned walk (net_tile): one wave per 64 samples, 16 at a time.
 __global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ feat, int64_t nrows,
@@ -310,103 +215,218 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ f
     }
 }
 
-// One training block: forward, squared error, backward for 64 samples;
-// writes this block's gradient sums (canonical order) and squared error.
-__global__ void __launch_bounds__(64) k_mlp_train(const float* __restrict__ feat, const float* __restrict__ ytrue,
-                                                  int64_t nrows, const int32_t* __restrict__ idx, int64_t nb,
-                                                  MlpState* __restrict__ st, uint32_t* status) {
-    __shared__ NetLds L;
-    __shared__ uint16_t dy[kMlpBlock * 16], dz2[kMlpBlock * kNHid], dz1[kMlpBlock * kNHid];
-    load_net(st, L);
-    int64_t src;
-    bool valid;
-    const int64_t s0 = (int64_t)blockIdx.x * kMlpBlock;
-    load_features(feat, nrows, idx, nb, s0, L, src, valid, status);
-    __syncthreads();
-    net_forward(L);
-    const int l = threadIdx.x;
-    const int col = l & 15, rq = 4 * (l >> 4);
-    float* part = st->partials[blockIdx.x];
-    // loss gradient, one lane per sample
+// One training block: forward, squared error, backward for 64 samples; writes
+// this block's gradient sums (canonical order) and squared error.
+//
+// A wave does 16 samples, and every layer is computed transposed (Z^T = W^T
+// H^T, as in net_tile): lane 16 g + r holds the units 16 t + 4 g + q (q < 4) of
+// sample r for each tile t of 16 units, which is both what a 16x16x16 product
+// gives it and what the next one takes from it as its operand, forward and
+// backward, so activations and their gradients stay in registers.  The
+// weights' gradients are sums over the samples: for those the block's four
+// waves leave their values in LDS by unit, and each takes a quarter of the
+// output tiles.  Bound by latency at the batches in use (64 blocks for 4,096
+// samples).  One wave per 64 samples with every layer going through LDS and
+// the operands read from it two bytes at a time took 28 us for 4,096 samples.
+constexpr int kTrainWaves = 4;
+constexpr int kTrainPad = kMlpBlock + 4;         // samples per unit's row (8-byte aligned rows)
+
+struct __align__(16) TrainLds {
+    uint16_t w2[kNHid][kNHid + 4];
+    uint16_t x[16][kTrainPad], dy[16][kTrainPad];                       // [feature or output][sample]
+    uint16_t h1[kNHid][kTrainPad], h2[kNHid][kTrainPad];                // [unit][sample]
+    uint16_t d1[kNHid][kTrainPad], d2[kNHid][kTrainPad];
+    float f1[kNHid][kMlpBlock + 1], f2[kNHid][kMlpBlock + 1];           // the same gradients, FP32
+    float out[4][kMlpBlock + 1];                                        // output gradients and squared errors
+};
+
+__device__ __forceinline__ float4_t mfma16(short4_t a, short4_t b, float4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+
+// Reads of the network state, whose arrays are only aligned to 4 bytes.
+typedef short short4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef short short8_a4 __attribute__((ext_vector_type(8), aligned(4)));
+typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// Four consecutive samples of a unit.
+__device__ __forceinline__ short4_t row4(const uint16_t* p) { return *reinterpret_cast<const short4_t*>(p); }
+
+// The sum over the 64 samples of A(i, s) B(s, j), rows i0 and j0 of unit-major
+// arrays: samples in order.
+__device__ __forceinline__ float4_t over_samples(const uint16_t (*A)[kTrainPad], int i0, const uint16_t (*B)[kTrainPad],
+                                                 int j0) {
+    const int l = threadIdx.x & (kWave - 1), r = l & 15, kq = 4 * (l >> 4);
+    float4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k0 = 0; k0 < kMlpBlock; k0 += 16) acc = mfma16(row4(&A[i0 + r][k0 + kq]), row4(&B[j0 + r][k0 + kq]), acc);
+    return acc;
+}
+
+__global__ void __launch_bounds__(kTrainWaves * kWave) k_mlp_train(const float* __restrict__ feat,
+                                                                   const float* __restrict__ ytrue, int64_t nrows,
+                                                                   const int32_t* __restrict__ idx, int64_t nb,
+                                                                   MlpState* __restrict__ st, uint32_t* status) {
+    __shared__ TrainLds L;
+    const int t = threadIdx.x, w = t / kWave, l = t & (kWave - 1), g = l >> 4, r = l & 15;
+    const int sl = 16 * w + r;                       // this lane's sample in the block
+    // the sample's row, features 4 g .. 4 g + 3
+    const int64_t s = (int64_t)blockIdx.x * kMlpBlock + sl;
+    bool valid = s < nb;
+    int64_t src = valid ? (idx ? (int64_t)idx[s] : s) : 0;
+    if (valid && (src < 0 || src >= nrows)) {        // a row outside feat: left out, flagged
+        if (g == 0) atomicOr(status, kFlagBadIndex);
+        valid = false;
+        src = 0;
+    }
+    short4_t x = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (valid && 4 * g + j < kNIn) x[j] = (short)f2bf(feat[src * kNIn + 4 * g + j]);
+    float yt[kNOut];
+#pragma unroll
+    for (int q = 0; q < kNOut; ++q) yt[q] = valid && g == 0 ? ytrue[src * kNOut + q] : 0.f;
+    // weights: W2 to LDS (read both ways), the others' operands from memory
+    for (int i = t; i < kNHid * kNHid / 8; i += kTrainWaves * kWave) {
+        const short8_t v = reinterpret_cast<const short8_a4*>(st->w2)[i];
+        const int row = i / (kNHid / 8), c = 8 * (i % (kNHid / 8));
+        *reinterpret_cast<short4_t*>(&L.w2[row][c]) = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+        *reinterpret_cast<short4_t*>(&L.w2[row][c + 4]) = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+    }
+    short4_t a1[4], a3[4], a3t[4];                   // W1^T, W3^T and W3 by tile
+    float4_t b1[4], b2[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            a1[h][j] = (short)st->w1[(4 * g + j) * kNHid + 16 * h + r];
+            a3[h][j] = (short)st->w3[(16 * h + 4 * g + j) * 16 + r];
+        }
+        a3t[h] = *reinterpret_cast<const short4_a4*>(&st->w3[(16 * h + r) * 16 + 4 * g]);
+        b1[h] = *reinterpret_cast<const float4_a4*>(&st->b1[16 * h + 4 * g]);
+        b2[h] = *reinterpret_cast<const float4_a4*>(&st->b2[16 * h + 4 * g]);
+    }
+    const float4_t b3 = *reinterpret_cast<const float4_a4*>(&st->b3[4 * g]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) L.x[4 * g + j][sl] = (uint16_t)x[j];
+    const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+
+    // forward
+    float4_t z1[4], z2[4];
+    short4_t h1[4], h2[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        z1[h] = mfma16(a1[h], x, zero) + b1[h];
+        h1[h] = gelu_pack(z1[h]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) L.h1[16 * h + 4 * g + q][sl] = (uint16_t)h1[h][q];
+    }
+    __syncthreads();                                 // W2
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        float4_t d = zero;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            short4_t a;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[j] = (short)L.w2[16 * k + 4 * g + j][16 * h + r];
+            d = mfma16(a, h1[k], d);
+        }
+        z2[h] = d + b2[h];
+        h2[h] = gelu_pack(z2[h]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) L.h2[16 * h + 4 * g + q][sl] = (uint16_t)h2[h][q];
+    }
+    float4_t y = zero;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) y = mfma16(a3[k], h2[k], y);
+    y = y + b3;
+
+    // loss gradient (outputs 0..2 are in lane group 0)
     const float scale = 2.0f / (float)(nb * kNOut);
-    float se = 0.f;
-    float dyf[kNOut];
+    short4_t dy = {0, 0, 0, 0};
+    if (g == 0) {
+        float se = 0.f;
 #pragma unroll
-    for (int q = 0; q < kNOut; ++q) {
-        const float d = valid ? L.yh[l * 16 + q] - ytrue[src * kNOut + q] : 0.f;
-        se += d * d;
-        dyf[q] = d * scale;
+        for (int q = 0; q < kNOut; ++q) {
+            const float d = valid ? y[q] - yt[q] : 0.f;
+            se += d * d;
+            const float df = d * scale;
+            L.out[q][sl] = df;
+            dy[q] = (short)f2bf(df);
+        }
+        L.out[kNOut][sl] = se;
     }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) dy[l * 16 + q] = q < kNOut ? f2bf(dyf[q]) : (uint16_t)0;
-    __syncthreads();
-    // b3 and the squared error: column sums over the 64 samples, fixed order
-    L.yh[l * 16 + 0] = dyf[0];
-    L.yh[l * 16 + 1] = dyf[1];
-    L.yh[l * 16 + 2] = dyf[2];
-    L.yh[l * 16 + 3] = se;
-    __syncthreads();
-    if (l < kNOut + 1) {
-        float acc = 0.f;
-        for (int s = 0; s < kMlpBlock; ++s) acc += L.yh[s * 16 + l];
-        part[l < kNOut ? kOffB3 + l : kNParam] = acc;
+    for (int q = 0; q < 4; ++q) L.dy[4 * g + q][sl] = (uint16_t)dy[q];
+
+    // backward: dz2 = (dy W3^T) gelu'(z2), dz1 = (dz2 W2^T) gelu'(z1)
+    short4_t d2[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const float4_t d = mfma16(a3t[h], dy, zero);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float v = d[q] * gelu_grad_f(z2[h][q]);
+            const int u = 16 * h + 4 * g + q;
+            L.f2[u][sl] = v;
+            d2[h][q] = (short)f2bf(v);
+            L.d2[u][sl] = (uint16_t)d2[h][q];
+        }
     }
-    // dW3 = h2^T dy  [64 x 3]
-    for (int rt = 0; rt < 4; ++rt) {
-        const float4_t d = mm_tile(L.h2, 1, kNHid, 16 * rt, dy, 16, 1, 0, kMlpBlock);
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        float4_t d = zero;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) d = mfma16(row4(&L.w2[16 * h + r][16 * k + 4 * g]), d2[k], d);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float v = d[q] * gelu_grad_f(z1[h][q]);
+            const int u = 16 * h + 4 * g + q;
+            L.f1[u][sl] = v;
+            L.d1[u][sl] = f2bf(v);
+        }
+    }
+    __syncthreads();
+
+    // gradients over the 64 samples, in sample order
+    float* part = st->partials[blockIdx.x];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {                    // dW2 = h1^T dz2
+        const float4_t d = over_samples(L.h1, 16 * w, L.d2, 16 * c);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) part[kOffW2 + (16 * w + 4 * g + q) * kNHid + 16 * c + r] = d[q];
+    }
+    {                                                // dW3 = h2^T dy
+        const float4_t d = over_samples(L.h2, 16 * w, L.dy, 0);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (col < kNOut) part[kOffW3 + (16 * rt + rq + q) * kNOut + col] = d[q];
+            if (r < kNOut) part[kOffW3 + (16 * w + 4 * g + q) * kNOut + r] = d[q];
     }
-    // dz2 = (dy W3^T) * gelu'(z2)  [64 samples x 64]
-    for (int rt = 0; rt < 4; ++rt)
-        for (int ct = 0; ct < 4; ++ct) {
-            const float4_t d = mm_tile(dy, 16, 1, 16 * rt, L.w3, 1, 16, 16 * ct, 16);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = 16 * rt + rq + q, c = 16 * ct + col;
-                const float g = d[q] * gelu_grad(L.z2[row * kNHid + c]);
-                L.z2[row * kNHid + c] = g;                 // z2 now holds dz2 (FP32)
-                dz2[row * kNHid + c] = f2bf(g);
-            }
-        }
-    __syncthreads();
-    {   // b2: column sums of dz2
-        float acc = 0.f;
-        for (int s = 0; s < kMlpBlock; ++s) acc += L.z2[s * kNHid + l];
-        part[kOffB2 + l] = acc;
-    }
-    // dW2 = h1^T dz2  [64 x 64]
-    for (int rt = 0; rt < 4; ++rt)
-        for (int ct = 0; ct < 4; ++ct) {
-            const float4_t d = mm_tile(L.h1, 1, kNHid, 16 * rt, dz2, kNHid, 1, 16 * ct, kMlpBlock);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) part[kOffW2 + (16 * rt + rq + q) * kNHid + 16 * ct + col] = d[q];
-        }
-    // dz1 = (dz2 W2^T) * gelu'(z1)
-    for (int rt = 0; rt < 4; ++rt)
-        for (int ct = 0; ct < 4; ++ct) {
-            const float4_t d = mm_tile(dz2, kNHid, 1, 16 * rt, L.w2, 1, kNHid, 16 * ct, kNHid);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = 16 * rt + rq + q, c = 16 * ct + col;
-                const float g = d[q] * gelu_grad(L.z1[row * kNHid + c]);
-                L.z1[row * kNHid + c] = g;                 // z1 now holds dz1 (FP32)
-                dz1[row * kNHid + c] = f2bf(g);
-            }
-        }
-    __syncthreads();
-    {   // b1
-        float acc = 0.f;
-        for (int s = 0; s < kMlpBlock; ++s) acc += L.z1[s * kNHid + l];
-        part[kOffB1 + l] = acc;
-    }
-    // dW1 = x^T dz1  [16 (10 used) x 64]
-    for (int ct = 0; ct < 4; ++ct) {
-        const float4_t d = mm_tile(L.x, 1, 16, 0, dz1, kNHid, 1, 16 * ct, kMlpBlock);
+    {                                                // dW1 = x^T dz1
+        const float4_t d = over_samples(L.x, 0, L.d1, 16 * w);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (rq + q < kNIn) part[kOffW1 + (rq + q) * kNHid + 16 * ct + col] = d[q];
+            if (4 * g + q < kNIn) part[kOffW1 + (4 * g + q) * kNHid + 16 * w + r] = d[q];
+    }
+    // biases and the squared error: a thread each
+    const float* row = nullptr;
+    int to = 0;
+    if (t < kNHid) {
+        row = L.f2[t];
+        to = kOffB2 + t;
+    } else if (t < 2 * kNHid) {
+        row = L.f1[t - kNHid];
+        to = kOffB1 + t - kNHid;
+    } else if (t < 2 * kNHid + kNOut + 1) {
+        row = L.out[t - 2 * kNHid];
+        to = t < 2 * kNHid + kNOut ? kOffB3 + t - 2 * kNHid : kNParam;
+    }
+    if (row) {
+        float acc = 0.f;
+#pragma unroll 16
+        for (int k = 0; k < kMlpBlock; ++k) acc += row[k];
+        part[to] = acc;
     }
 }
 
@@ -430,13 +450,25 @@ __device__ void refresh_copy(MlpState* st, int p) {
 }
 
 // Sum the blocks' gradients in block order, then one Adam step on the
-// masters (step counts from 1) and a refresh of the BF16 copies.
-__global__ void __launch_bounds__(256) k_mlp_adam(MlpState* __restrict__ st, int nblocks, int64_t nb, float lr,
-                                                  int step, float* __restrict__ grad_out) {
+// masters (step counts from 1) and a refresh of the BF16 copies.  The
+// partials are read sixteen blocks at a time: one after the other they took
+// 17 us for 64 blocks.
+constexpr int kAdamThreads = 64;
+
+__global__ void __launch_bounds__(kAdamThreads) k_mlp_adam(MlpState* __restrict__ st, int nblocks, int64_t nb, float lr,
+                                                           int step, float* __restrict__ grad_out) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p > kNParam) return;
     float g = 0.f;
-    for (int b = 0; b < nblocks; ++b) g += st->partials[b][p];
+    int b = 0;
+    for (; b + 16 <= nblocks; b += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = st->partials[b + u][p];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) g += v[u];
+    }
+    for (; b < nblocks; ++b) g += st->partials[b][p];
     if (p == kNParam) {
         st->loss = g / (float)(nb * kNOut);
         return;
@@ -519,8 +551,8 @@ hipError_t launch_mlp_forward(const MlpState* st, const float* feat, int64_t nro
 hipError_t launch_mlp_step(MlpState* st, const float* feat, const float* y, int64_t nrows, const int32_t* idx,
                            int64_t nb, float lr, int step, float* grad_out, uint32_t* status, hipStream_t s) {
     const int blocks = (int)((nb + kMlpBlock - 1) / kMlpBlock);
-    hipLaunchKernelGGL(k_mlp_train, dim3(blocks), dim3(kMlpBlock), 0, s, feat, y, nrows, idx, nb, st, status);
-    hipLaunchKernelGGL(k_mlp_adam, dim3((kNParam + 1 + 255) / 256), dim3(256), 0, s, st, blocks, nb, lr, step,
+    hipLaunchKernelGGL(k_mlp_train, dim3(blocks), dim3(kTrainWaves * kWave), 0, s, feat, y, nrows, idx, nb, st, status);
+    hipLaunchKernelGGL(k_mlp_adam, dim3((kNParam + kAdamThreads) / kAdamThreads), dim3(kAdamThreads), 0, s, st, blocks, nb, lr, step,
                        grad_out);
     return hipGetLastError();
 }

@@ -87,6 +87,36 @@ def test_gradient_matches_bf16_oracle(plummer):
     np.testing.assert_array_equal(tc.mlp_get().cpu().numpy(), theta)
 
 
+@pytest.mark.parametrize("nb", [1, 15, 16, 17, 63, 64, 65, 129, 1000, 1025])
+def test_gradient_at_batch_edges(plummer, nb):
+    """Batches that fill a wave's 16 samples, a block's 64 and the sixteen
+    blocks' partials summed at a time, and one sample either side, with rows
+    outside the features dropped (their index flagged): the same bar as above."""
+    _, tc, keep = plummer
+    theta = mlp.init_params(seed=8)
+    tc.mlp_load(to_dev(theta))
+    f, y = _features(1100, seed=96)
+    rng = np.random.default_rng(97)
+    idx = rng.integers(0, len(f), nb).astype(np.int32)
+    grad = torch.empty(mlp.NPARAM, dtype=torch.float32, device="cuda")
+    loss = tc.mlp_step(to_dev(f), to_dev(y), to_dev(idx), lr=0.0, grad=grad)
+    rl, rg = mlp.loss_and_grad(theta, f[idx], y[idx], bf16_ops=True)
+    assert abs(loss - rl) <= 1e-4 * rl
+    assert oracle.rel_l2(grad.cpu().numpy(), rg) < 1e-3
+    if nb == 129:
+        # a dropped sample adds nothing: the sums are over the others, the mean over all
+        bad = idx.copy()
+        bad[[0, 77]] = (-1, len(f))
+        tc.mlp_step(to_dev(f), to_dev(y), to_dev(bad), lr=0.0, grad=grad)
+        ok = np.delete(idx, [0, 77])
+        _, rg = mlp.loss_and_grad(theta, f[ok], y[ok], bf16_ops=True)
+        assert oracle.rel_l2(grad.cpu().numpy(), rg * (len(ok) / nb)) < 1e-2
+        assert tc.status() == treecode.TC_EINVAL
+        tc.build(*keep)                       # clears the flag
+        tc.moments()
+        tc.mlp_load(to_dev(theta))
+
+
 def test_adam_step_matches_oracle(plummer):
     _, tc, _ = plummer
     theta = mlp.init_params(seed=7)
