@@ -1061,15 +1061,16 @@ int tc_residuals(tc_ctx* ctx, double theta, double eps, const int32_t* targets, 
     uint32_t* cnt = ctx->at<uint32_t>(l.off_rcount);
     uint32_t* off = ctx->at<uint32_t>(l.off_roffs);
     TC_HIP(ctx, launch_inverse_perm(ctx->at<uint32_t>(l.off_idx_a), ctx->n, inv, s));
-    for (int pass = 0; pass < 2; ++pass) {
-        TC_HIP(ctx, launch_residuals(pass == 1, ctx->at<WalkCell>(l.off_walk), ctx->at<Body>(l.off_bodies),
-                                     ctx->at<Cell>(l.off_cells), ctx->at<Moments>(l.off_mom),
-                                     ctx->at<uint32_t>(l.off_lvl_idx_b), inv, ctx->prm(), ctx->n, targets, nt,
-                                     eps * eps, cnt, off, cap, feat, y, cell, s));
-        if (pass == 0)
-            TC_HIP(ctx, launch_scan_u32(cnt, nt, off, ctx->at<uint32_t>(l.off_rscan_part),
-                                        (nt + kScanTile - 1) / kScanTile, s));
-    }
+    TC_HIP(ctx, launch_resid_count(ctx->at<WalkCell>(l.off_walk), ctx->at<Body>(l.off_bodies),
+                                   ctx->at<uint32_t>(l.off_lvl_idx_b), inv, ctx->prm(), ctx->n, targets, nt, cnt, s));
+    TC_HIP(ctx, launch_scan_u32(cnt, nt, off, ctx->at<uint32_t>(l.off_rscan_part), (nt + kScanTile - 1) / kScanTile,
+                                s));
+    TC_HIP(ctx, launch_resid_pairs(ctx->at<WalkCell>(l.off_walk), ctx->at<Body>(l.off_bodies),
+                                   ctx->at<Cell>(l.off_cells), ctx->at<Moments>(l.off_mom),
+                                   ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_pre2bfs), inv,
+                                   ctx->prm(), ctx->n, l.cmax, targets, nt, eps * eps, off, cap,
+                                   ctx->at<uint32_t>(l.off_gper), ctx->at<uint32_t>(l.off_goff),
+                                   ctx->at<uint32_t>(l.off_gscan_part), cnt, feat, y, cell, s));
     uint32_t total = 0;
     TC_HIP(ctx, hipMemcpyAsync(&total, off + nt, sizeof(total), hipMemcpyDeviceToHost, s));
     TC_HIP(ctx, hipStreamSynchronize(s));

@@ -14,9 +14,9 @@
 // inference: net_tile in closure.h) with FP32 master weights, trained
 // by mean squared error and Adam.
 //
-// This file: residual generation (one wave per target body; the walk is the
-// batched level-order walk of the force kernel with the box shrunk to the
-// body), the network's forward and backward passes, the Adam update.
+// This file: residual generation (one wave per target body lists its accepted
+// cells by the batched level-order walk of the force kernel with the box shrunk
+// to the body; then the pairs are computed side by side), the network's forward and backward passes, the Adam update.
 #include "tc_internal.h"
 #include "closure.h"
 
@@ -43,11 +43,12 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // Walk for one body (the box shrunk to a point) at the prepared opening
-// radii; on_accept(b) runs with the whole wave for every accepted cell, b
-// its level-order index.  3D.
+// radii; on_round(accept, b) runs with the whole wave once per round: lane j
+// tested the cell at level-order index b, and accept says whether the body is
+// far enough from it.  3D.
 template <typename F>
 __device__ void walk_point(const WalkCell* __restrict__ walk, uint32_t* S, double px, double py, double pz,
-                           F&& on_accept) {
+                           F&& on_round) {
     constexpr int R = 8, RP = kWave / R;
     constexpr int kReserve = (R - 1) * 21 + R;
     static_assert(kStack >= kWave + kReserve + kWave, "stack bound");
@@ -86,89 +87,395 @@ __device__ void walk_point(const WalkCell* __restrict__ walk, uint32_t* S, doubl
         if (opened) S[top + __popcll(O & below)] = ((uint32_t)wc.a << 3) | (uint32_t)(wc.b - 1);
         top += __popcll(O);
         wave_lds_sync();
-        uint64_t A = __ballot(accept);
-        while (A) {
-            const int l = __builtin_ctzll(A);
-            A &= A - 1;
-            on_accept((uint32_t)__builtin_amdgcn_readlane((int)b, l));
-        }
+        on_round(accept, b);
     }
 }
 
-// count pass: pairs per target; write pass: the pairs at the scanned offsets
-template <bool WRITE>
-__global__ void __launch_bounds__(256) k_residuals(const WalkCell* __restrict__ walk, const Body* __restrict__ bodies,
-                                                   const Cell* __restrict__ cells, const Moments* __restrict__ mom,
-                                                   const uint32_t* __restrict__ bfs2pre,
-                                                   const uint32_t* __restrict__ inv_perm,
-                                                   DevParams* __restrict__ prm, int64_t n,
-                                                   const int32_t* __restrict__ targets, int nt, double eps2,
-                                                   uint32_t* __restrict__ counts, const uint32_t* __restrict__ offs,
-                                                   int64_t cap, float* __restrict__ feat, float* __restrict__ yout,
-                                                   int32_t* __restrict__ cell_out) {
+// A pair's key in the order by cell: its cell's level-order index, or for the
+// cells from `hot` on one of kResidColdKeys by its target (only there if there
+// are such cells).
+__device__ __forceinline__ uint32_t pair_key(uint32_t b, uint32_t t, uint32_t hot) {
+    return b < hot ? b : hot + t % kResidColdKeys;
+}
+
+// One wave per target.  Count pass: pairs per target; list pass (LIST): the
+// accepted cells (pre-order) at the scanned offsets, the pairs per key, and in
+// the first two words of the pair's y the target's number and the pair's rank
+// within its key.
+template <bool LIST>
+__global__ void __launch_bounds__(256) k_resid_walk(const WalkCell* __restrict__ walk, const Body* __restrict__ bodies,
+                                                    const uint32_t* __restrict__ bfs2pre,
+                                                    const uint32_t* __restrict__ inv_perm,
+                                                    DevParams* __restrict__ prm, int64_t n,
+                                                    const int32_t* __restrict__ targets, int nt,
+                                                    uint32_t* __restrict__ counts, const uint32_t* __restrict__ offs,
+                                                    int64_t cap, float* __restrict__ yout,
+                                                    int32_t* __restrict__ cell_out, uint32_t* __restrict__ key_count,
+                                                    uint32_t hot) {
     __shared__ uint32_t s_stack[4][kStack];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
     const int t = blockIdx.x * 4 + wv;
     if (t >= nt) return;
     const int64_t o = targets[t];
     if (o < 0 || o >= n) {                     // no pairs for an index outside the bodies
         if (lane == 0) {
             atomicOr(&prm->status, kFlagBadIndex);
-            if (!WRITE) counts[t] = 0u;
+            if (!LIST) counts[t] = 0u;
         }
         return;
     }
-    const int64_t p = inv_perm[o];
-    const Body me = bodies[p];
-    const double mbar = mom[0].M / (double)n;
-    const double size = prm->size;
-    int64_t k = WRITE ? (int64_t)offs[t] : 0;
-    walk_point(walk, s_stack[wv], me.x, me.y, me.z, [&](uint32_t b) {
-        if (WRITE && k < cap) {
-            const int64_t kc = bfs2pre[b];
-            const Cell c = cells[kc];
-            const Moments& mo = mom[kc];
-            // exact softened sum over the cell's bodies, FP64, fixed order
-            double ex = 0.0, ey = 0.0, ez = 0.0;
-            for (int64_t j = c.begin + lane; j < (int64_t)c.begin + c.count; j += kWave) {
-                const Body q = bodies[j];
-                const double dx = q.x - me.x, dy = q.y - me.y, dz = q.z - me.z;
-                const double r2 = ((eps2 + dx * dx) + dy * dy) + dz * dz;
-                const double inv = 1.0 / sqrt(r2);
-                const double w3 = q.m * inv * inv * inv;
-                ex += w3 * dx;
-                ey += w3 * dy;
-                ez += w3 * dz;
+    int64_t k = LIST ? (int64_t)offs[t] : 0;
+    if (LIST && k >= cap) return;
+    const Body me = bodies[inv_perm[o]];
+    walk_point(walk, s_stack[wv], me.x, me.y, me.z, [&](bool accept, uint32_t b) {
+        const uint64_t A = __ballot(accept);
+        if (LIST) {
+            const int64_t at = k + __popcll(A & below);
+            const bool write = accept && at < cap;
+            const uint64_t cold = __ballot(write && b >= hot);
+            uint32_t rank = 0;
+            if (cold) {
+                if (lane == 0) rank = atomicAdd(&key_count[pair_key(hot, (uint32_t)t, hot)], (uint32_t)__popcll(cold));
+                rank = (uint32_t)__builtin_amdgcn_readfirstlane((int)rank) + (uint32_t)__popcll(cold & below);
             }
-            ex = wsum(ex);
-            ey = wsum(ey);
-            ez = wsum(ez);
-            if (lane == 0) {
-                const double M = mo.M;
-                const double dcx = mo.com[0] - me.x, dcy = mo.com[1] - me.y, dcz = mo.com[2] - me.z;
-                const double d2 = (dcx * dcx + dcy * dcy) + dcz * dcz;
-                const double inv = 1.0 / sqrt(d2 + eps2);
-                const double w3 = M * inv * inv * inv;
-                const double s = ldexp(size, -c.level);
-                // residual in units of the quadrupole scale M s^2 / d^4
-                const double nrm = (d2 * d2) / (M * s * s);
-                float* y = yout + k * 3;
-                y[0] = (float)((ex - w3 * dcx) * nrm);
-                y[1] = (float)((ey - w3 * dcy) * nrm);
-                y[2] = (float)((ez - w3 * dcz) * nrm);
-                float* f = feat + k * 10;
-                f[0] = (float)((me.x - mo.com[0]) / s);
-                f[1] = (float)((me.y - mo.com[1]) / s);
-                f[2] = (float)((me.z - mo.com[2]) / s);
-                const double qs = M * s * s;
-                for (int q = 0; q < 6; ++q) f[3 + q] = (float)(mo.Q[q] / qs);
-                f[9] = (float)log(M / mbar);
-                cell_out[k] = (int32_t)kc;
+            if (write) {
+                if (b < hot) rank = atomicAdd(&key_count[b], 1u);
+                cell_out[at] = (int32_t)bfs2pre[b];
+                yout[at * 3] = __int_as_float(t);
+                yout[at * 3 + 1] = __uint_as_float(rank);
             }
         }
-        ++k;
+        k += __popcll(A);
     });
-    if (!WRITE && lane == 0) counts[t] = (uint32_t)k;
+    if (!LIST && lane == 0) counts[t] = (uint32_t)k;
+}
+
+// The pairs by key.  Their order within a key varies from run to run; no
+// pair's result depends on it.
+__global__ void __launch_bounds__(256) k_resid_order(const int32_t* __restrict__ cell, const float* __restrict__ y,
+                                                     const uint32_t* __restrict__ total, int64_t cap,
+                                                     const uint32_t* __restrict__ pre2bfs,
+                                                     const uint32_t* __restrict__ key_off, uint32_t hot,
+                                                     uint32_t* __restrict__ order, uint32_t* __restrict__ ctr) {
+    const int64_t P = (int64_t)*total < cap ? (int64_t)*total : cap;
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < 3) ctr[i] = 0u;
+    for (int64_t k = i; k < P; k += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t b = pre2bfs[cell[k]], t = __float_as_uint(y[k * 3]);
+        order[key_off[pair_key(b, t, hot)] + __float_as_uint(y[k * 3 + 1])] = (uint32_t)k;
+    }
+}
+
+// (r2)^(-1/2) in FP64: the hardware's approximation and one step of third
+// order (relative error 2^-53 or so: the step's own is the cube of 2^-26).
+__device__ __forceinline__ double rsqrt64(double r2) {
+    const double y = __builtin_amdgcn_rsq(r2);
+    const double e = fma(-r2 * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// The sums of the pairs: the exact softened sum over the cell's bodies (FP64,
+// fixed order) against the monopole.  Pairs of one cell are taken up to four at
+// once, each body read once for all of them: those of a cell with more than
+// kPairHuge bodies by a block, of more than kPairLong by a wave; the others go
+// four to a wave on 16 lanes each.  Which way a pair goes, and so the order of
+// its sum, depends on its cell only.  The blocks first take the groups of four
+// in the order by cell that hold pairs of huge cells (k_resid_huge lists them),
+// then their waves take the other pairs, kTake at a time; big cells come first.
+//
+// Bound by the FP64 units, about 25 instructions per body and pair: 5.4e8 bodies
+// of 1.05M pairs (4,096 targets, 262,144 bodies) in 774 us.  One wave per target
+// going through its cells in turn, with sqrt and divide, took 3.1 ms; 16 lanes or
+// a wave per pair 2.1 ms, as one cell of four fifths of the bodies kept a wave
+// busy that long.
+constexpr int kTask = 8;
+constexpr int kTake = 32;
+constexpr int kPairLanes = 16;
+constexpr int kPairLong = 128;
+constexpr int kPairHuge = 2048;
+constexpr int kPairBlock = 512;
+constexpr int kPairGrid = 512;                  // blocks the chip holds at once, two per CU
+
+__global__ void __launch_bounds__(256) k_resid_huge(const Cell* __restrict__ cells, const int32_t* __restrict__ cell,
+                                                    const uint32_t* __restrict__ order,
+                                                    const uint32_t* __restrict__ total, int64_t cap,
+                                                    uint32_t* __restrict__ list, uint32_t* __restrict__ ctr) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t P = (int64_t)*total < cap ? (int64_t)*total : cap;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i0 = blockIdx.x * (int64_t)blockDim.x + (threadIdx.x & ~(kWave - 1)); i0 < P; i0 += stride) {
+        const int64_t i = i0 + lane;
+        const uint64_t H = __ballot(i < P && cells[cell[order[i]]].count > kPairHuge);
+        const bool mine = lane < 16 && ((H >> (4 * lane)) & 15ull);
+        const uint64_t G = __ballot(mine);
+        if (!G) continue;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&ctr[0], (uint32_t)__popcll(G));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(G & ((1ull << lane) - 1ull));
+        if (mine) list[at] = (uint32_t)(i0 / 4 + lane);
+    }
+}
+
+struct Sum3 {
+    double x, y, z;
+};
+
+__device__ __forceinline__ void add_body(Sum3& e, const Body& b, double x, double y, double z, double eps2) {
+    const double dx = b.x - x, dy = b.y - y, dz = b.z - z;
+    const double inv = rsqrt64(fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2))));
+    const double w3 = b.m * inv * inv * inv;
+    e.x = fma(w3, dx, e.x);
+    e.y = fma(w3, dy, e.y);
+    e.z = fma(w3, dz, e.z);
+}
+
+__device__ __forceinline__ Sum3 shfl3(const Sum3& v, int l) {
+    return {__shfl(v.x, l, kWave), __shfl(v.y, l, kWave), __shfl(v.z, l, kWave)};
+}
+
+// One step of the sum over the wave: lanes o apart add up.
+__device__ __forceinline__ void fold(Sum3& v, int o) {
+    v.x += __shfl_xor(v.x, o, kWave);
+    v.y += __shfl_xor(v.y, o, kWave);
+    v.z += __shfl_xor(v.z, o, kWave);
+}
+
+// The same of two sums at once: lanes with bit o keep b, the others a.
+__device__ __forceinline__ Sum3 fold2(const Sum3& a, const Sum3& b, int o, bool hi) {
+    const double x = __shfl_xor(hi ? a.x : b.x, o, kWave), y = __shfl_xor(hi ? a.y : b.y, o, kWave),
+                 z = __shfl_xor(hi ? a.z : b.z, o, kWave);
+    return {(hi ? b.x : a.x) + x, (hi ? b.y : a.y) + y, (hi ? b.z : a.z) + z};
+}
+
+// The whole wave over the bodies [b0, b1) for T targets; afterwards the lanes
+// from m * 64 / T on hold the sum of target m.
+template <int T>
+__device__ __forceinline__ Sum3 wide_sum(const Body* __restrict__ bodies, int64_t b0, int64_t b1, const Sum3 (&at)[T],
+                                         double eps2) {
+    const int lane = threadIdx.x & (kWave - 1);
+    Sum3 e[T];
+#pragma unroll
+    for (int m = 0; m < T; ++m) e[m] = {0.0, 0.0, 0.0};
+    for (int64_t j = b0 + lane; j < b1; j += kWave) {
+        const Body b = bodies[j];
+#pragma unroll
+        for (int m = 0; m < T; ++m) add_body(e[m], b, at[m].x, at[m].y, at[m].z, eps2);
+    }
+    const bool h5 = (lane & 32) != 0, h4 = (lane & 16) != 0;
+    Sum3 v;
+    if constexpr (T == 4) {
+        v = fold2(fold2(e[0], e[2], 32, h5), fold2(e[1], e[3], 32, h5), 16, h4);
+    } else if constexpr (T == 2) {
+        v = fold2(e[0], e[1], 32, h5);
+        fold(v, 16);
+    } else {
+        v = e[0];
+        fold(v, 32);
+        fold(v, 16);
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) fold(v, o);
+    return v;
+}
+
+__device__ __forceinline__ double readlane64(double v, int l) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l),
+                   hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// One lane's pair: its number, cell and target.
+struct Pair {
+    int64_t k;
+    int cell, begin, count, level;
+    Sum3 at;
+};
+
+__device__ __forceinline__ void put_pair(const Pair& p, const Sum3& r, const Moments* __restrict__ mom, double size,
+                                         double eps2, float* yout) {
+    const Moments& mo = mom[p.cell];
+    const double M = mo.M, s = ldexp(size, -p.level);
+    const double dcx = mo.com[0] - p.at.x, dcy = mo.com[1] - p.at.y, dcz = mo.com[2] - p.at.z;
+    const double d2 = (dcx * dcx + dcy * dcy) + dcz * dcz;
+    const double inv = 1.0 / sqrt(d2 + eps2);
+    const double w3 = M * inv * inv * inv;
+    // residual in units of the quadrupole scale M s^2 / d^4
+    const double nrm = (d2 * d2) / (M * s * s);
+    yout[p.k * 3] = (float)((r.x - w3 * dcx) * nrm);
+    yout[p.k * 3 + 1] = (float)((r.y - w3 * dcy) * nrm);
+    yout[p.k * 3 + 2] = (float)((r.z - w3 * dcz) * nrm);
+}
+
+// The wave's part (wave wv of nw) of the sums of `take` pairs from lane i on,
+// all of one cell; the sum of pair i + m is at the returned lane shift m << shift.
+__device__ __forceinline__ Sum3 run_sum(const Body* __restrict__ bodies, const Pair& p, int i, int take, int wv, int nw,
+                                        double eps2, int& shift) {
+    const int64_t c0 = __builtin_amdgcn_readlane(p.begin, i), cn = __builtin_amdgcn_readlane(p.count, i);
+    const int64_t part = (cn + nw - 1) / nw;
+    const int64_t b0 = c0 + min(wv * part, cn), b1 = c0 + min((wv + 1) * part, cn);
+    auto target = [&](int m) {
+        return Sum3{readlane64(p.at.x, m), readlane64(p.at.y, m), readlane64(p.at.z, m)};
+    };
+    if (take >= 3) {
+        const Sum3 a[4] = {target(i), target(i + 1), target(i + 2), target(i + take - 1)};
+        shift = 4;
+        return wide_sum<4>(bodies, b0, b1, a, eps2);
+    }
+    shift = 5;
+    if (take == 2) {
+        const Sum3 a[2] = {target(i), target(i + 1)};
+        return wide_sum<2>(bodies, b0, b1, a, eps2);
+    }
+    const Sum3 a[1] = {target(i)};
+    return wide_sum<1>(bodies, b0, b1, a, eps2);
+}
+
+// Loads the pair at p0 + lane (lane < np) if its cell is on this side of
+// kPairHuge: the other side's y may hold its result already.
+template <bool HUGE>
+__device__ __forceinline__ bool load_pair(Pair& p, int64_t p0, int np, const Body* __restrict__ bodies,
+                                          const Cell* __restrict__ cells, const uint32_t* __restrict__ inv_perm,
+                                          const int32_t* __restrict__ targets, const float* yout,
+                                          const int32_t* __restrict__ cell_out, const uint32_t* __restrict__ order) {
+    const int lane = threadIdx.x & (kWave - 1);
+    p = {0, -1, 0, 0, 0, {0.0, 0.0, 0.0}};
+    if (lane >= np) return false;
+    p.k = order[p0 + lane];
+    const int kc = cell_out[p.k];
+    const Cell c = cells[kc];
+    if ((c.count > kPairHuge) != HUGE) return false;
+    p.cell = kc;
+    p.begin = c.begin;
+    p.count = c.count;
+    p.level = c.level;
+    const Body me = bodies[inv_perm[targets[__float_as_int(yout[p.k * 3])]]];
+    p.at = {me.x, me.y, me.z};
+    return true;
+}
+
+// ctr: groups listed, groups taken, lots of kTake pairs taken.
+__global__ void __launch_bounds__(kPairBlock) k_resid_pairs(const Body* __restrict__ bodies,
+                                                            const Cell* __restrict__ cells,
+                                                            const Moments* __restrict__ mom,
+                                                            const uint32_t* __restrict__ inv_perm,
+                                                            const DevParams* __restrict__ prm,
+                                                            const int32_t* __restrict__ targets, double eps2,
+                                                            const uint32_t* __restrict__ total, int64_t cap,
+                                                            float* yout, const int32_t* __restrict__ cell_out,
+                                                            const uint32_t* __restrict__ order,
+                                                            const uint32_t* __restrict__ list, uint32_t* ctr) {
+    constexpr int kWaves = kPairBlock / kWave;
+    __shared__ Sum3 s_part[kWaves][4];
+    __shared__ uint32_t s_task;
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
+    const int64_t P = (int64_t)*total < cap ? (int64_t)*total : cap;
+    const double size = prm->size;
+    const uint32_t nlist = ctr[0];
+    Pair p;
+    for (;;) {
+        if (threadIdx.x == 0) s_task = atomicAdd(&ctr[1], 1u);
+        __syncthreads();
+        const uint32_t task = s_task;
+        __syncthreads();
+        if (task >= nlist) break;
+        const int64_t p0 = (int64_t)list[task] * 4;
+        uint64_t left = __ballot(load_pair<true>(p, p0, (int)min((int64_t)4, P - p0), bodies, cells, inv_perm, targets,
+                                                 yout, cell_out, order));
+        while (left) {
+            const int i = __builtin_ctzll(left);
+            const int take = __builtin_ctzll(~__ballot(p.cell == __builtin_amdgcn_readlane(p.cell, i)) >> i);
+            int shift;
+            const Sum3 v = run_sum(bodies, p, i, take, wv, kWaves, eps2, shift);
+            if ((lane & ((1 << shift) - 1)) == 0) s_part[wv][lane >> shift] = v;
+            __syncthreads();
+            if (wv == 0 && lane >= i && lane < i + take) {
+                Sum3 r = s_part[0][lane - i];
+                for (int w = 1; w < kWaves; ++w) {
+                    const Sum3& q = s_part[w][lane - i];
+                    r.x += q.x;
+                    r.y += q.y;
+                    r.z += q.z;
+                }
+                put_pair(p, r, mom, size, eps2, yout);
+            }
+            left &= ~(((1ull << take) - 1ull) << i);
+            __syncthreads();
+        }
+    }
+    for (;;) {
+        uint32_t next = 0;
+        if (lane == 0) next = atomicAdd(&ctr[2], 1u);
+        const int64_t t0 = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)next) * kTake;
+        if (t0 >= P) break;
+        for (int64_t p0 = t0; p0 < min(t0 + kTake, P); p0 += kTask) {
+            const int np = (int)min((int64_t)kTask, P - p0);
+            const bool mine = load_pair<false>(p, p0, np, bodies, cells, inv_perm, targets, yout, cell_out, order);
+            const uint32_t mask = (uint32_t)__ballot(mine), wide = (uint32_t)__ballot(mine && p.count > kPairLong);
+            Sum3 r = {0.0, 0.0, 0.0};
+            for (int i = 0; i < np;) {
+                Sum3 v;
+                int take, shift;
+                if (!((mask >> i) & 1u)) {
+                    ++i;
+                    continue;
+                }
+                if ((wide >> i) & 1u) {
+                    const uint32_t other = ~(uint32_t)__ballot(p.cell == __builtin_amdgcn_readlane(p.cell, i)) >> i;
+                    take = min(__builtin_ctz(other), 4);
+                    v = run_sum(bodies, p, i, take, 0, 1, eps2, shift);
+                } else {
+                    constexpr int kPairs = kWave / kPairLanes;
+                    take = min(__builtin_ctz((wide | ~mask) >> i), kPairs);
+                    const int src = i + min(lane / kPairLanes, take - 1);
+                    const Sum3 a = shfl3(p.at, src);
+                    const int64_t b0 = __shfl(p.begin, src, kWave), b1 = b0 + __shfl(p.count, src, kWave);
+                    v = {0.0, 0.0, 0.0};
+                    for (int64_t j = b0 + lane % kPairLanes; j < b1; j += kPairLanes)
+                        add_body(v, bodies[j], a.x, a.y, a.z, eps2);
+#pragma unroll
+                    for (int o = kPairLanes / 2; o > 0; o >>= 1) fold(v, o);
+                    shift = 4;
+                }
+                const Sum3 got = shfl3(v, ((lane - i) << shift) & (kWave - 1));
+                if (lane >= i && lane < i + take) r = got;
+                i += take;
+            }
+            if (mine) put_pair(p, r, mom, size, eps2, yout);
+        }
+    }
+}
+
+// The features, one block per target.
+__global__ void __launch_bounds__(256) k_resid_features(const Body* __restrict__ bodies,
+                                                        const Cell* __restrict__ cells,
+                                                        const Moments* __restrict__ mom,
+                                                        const uint32_t* __restrict__ inv_perm,
+                                                        const DevParams* __restrict__ prm, int64_t n,
+                                                        const int32_t* __restrict__ targets,
+                                                        const uint32_t* __restrict__ offs, int64_t cap,
+                                                        const int32_t* __restrict__ cell_out,
+                                                        float* __restrict__ feat) {
+    const int t = blockIdx.x;
+    const int64_t e = min((int64_t)offs[t + 1], cap);
+    int64_t k = (int64_t)offs[t] + threadIdx.x;
+    if (k >= e) return;
+    const Body me = bodies[inv_perm[targets[t]]];
+    const double mbar = mom[0].M / (double)n;
+    const double size = prm->size;
+    for (; k < e; k += blockDim.x) {
+        const int64_t kc = cell_out[k];
+        const Moments& mo = mom[kc];
+        const double s = ldexp(size, -cells[kc].level);
+        const double M = mo.M;
+        float* f = feat + k * 10;
+        f[0] = (float)((me.x - mo.com[0]) / s);
+        f[1] = (float)((me.y - mo.com[1]) / s);
+        f[2] = (float)((me.z - mo.com[2]) / s);
+        for (int q = 0; q < 6; ++q) f[3 + q] = (float)(mo.Q[q] / (M * s * s));
+        f[9] = (float)log(M / mbar);
+    }
 }
 
 __global__ void k_inverse_perm(const uint32_t* __restrict__ perm, int64_t n, uint32_t* __restrict__ inv) {
@@ -516,18 +823,45 @@ hipError_t launch_inverse_perm(const uint32_t* perm, int64_t n, uint32_t* inv, h
     return hipGetLastError();
 }
 
-hipError_t launch_residuals(bool write, const WalkCell* walk, const Body* bodies, const Cell* cells,
-                            const Moments* mom, const uint32_t* bfs2pre, const uint32_t* inv_perm,
-                            DevParams* prm, int64_t n, const int32_t* targets, int nt, double eps2,
-                            uint32_t* counts, const uint32_t* offs, int64_t cap, float* feat, float* y,
-                            int32_t* cell_out, hipStream_t s) {
-    const unsigned nb = (unsigned)((nt + 3) / 4);
-    if (write)
-        hipLaunchKernelGGL(k_residuals<true>, dim3(nb), dim3(256), 0, s, walk, bodies, cells, mom, bfs2pre, inv_perm,
-                           prm, n, targets, nt, eps2, counts, offs, cap, feat, y, cell_out);
-    else
-        hipLaunchKernelGGL(k_residuals<false>, dim3(nb), dim3(256), 0, s, walk, bodies, cells, mom, bfs2pre, inv_perm,
-                           prm, n, targets, nt, eps2, counts, offs, cap, feat, y, cell_out);
+hipError_t launch_resid_count(const WalkCell* walk, const Body* bodies, const uint32_t* bfs2pre,
+                              const uint32_t* inv_perm, DevParams* prm, int64_t n, const int32_t* targets, int nt,
+                              uint32_t* counts, hipStream_t s) {
+    hipLaunchKernelGGL(k_resid_walk<false>, dim3((unsigned)((nt + 3) / 4)), dim3(256), 0, s, walk, bodies, bfs2pre,
+                       inv_perm, prm, n, targets, nt, counts, (const uint32_t*)nullptr, (int64_t)0, (float*)nullptr,
+                       (int32_t*)nullptr, (uint32_t*)nullptr, 0u);
+    return hipGetLastError();
+}
+
+hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const Cell* cells, const Moments* mom,
+                              const uint32_t* bfs2pre, const uint32_t* pre2bfs, const uint32_t* inv_perm,
+                              DevParams* prm, int64_t n, int64_t cmax, const int32_t* targets, int nt, double eps2,
+                              const uint32_t* offs, int64_t cap, uint32_t* key_count, uint32_t* key_off,
+                              uint32_t* key_part, uint32_t* ctr, float* feat, float* y, int32_t* cell_out,
+                              hipStream_t s) {
+    if (cap <= 0) return hipSuccess;
+    const bool cold = cmax > kResidKeys;
+    const int64_t nkeys = cold ? kResidKeys : cmax;
+    const uint32_t hot = (uint32_t)(cold ? nkeys - kResidColdKeys : nkeys);
+    const uint32_t* total = offs + nt;
+    // The order and the list lie in the features' memory until these are written.
+    uint32_t* order = reinterpret_cast<uint32_t*>(feat);
+    uint32_t* list = order + cap;
+    hipError_t e = launch_fill_u32(key_count, nkeys, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_resid_walk<true>, dim3((unsigned)((nt + 3) / 4)), dim3(256), 0, s, walk, bodies, bfs2pre,
+                       inv_perm, prm, n, targets, nt, (uint32_t*)nullptr, offs, cap, y, cell_out, key_count, hot);
+    e = launch_scan_u32(key_count, nkeys, key_off, key_part, (nkeys + kScanTile - 1) / kScanTile, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_resid_order, dim3(grid_for(cap)), dim3(256), 0, s, (const int32_t*)cell_out, (const float*)y,
+                       total, cap, pre2bfs, (const uint32_t*)key_off, hot, order, ctr);
+    hipLaunchKernelGGL(k_resid_huge, dim3(grid_for(cap)), dim3(256), 0, s, cells, (const int32_t*)cell_out,
+                       (const uint32_t*)order, total, cap, list, ctr);
+    const int64_t groups = (cap + 3) / 4;
+    hipLaunchKernelGGL(k_resid_pairs, dim3((unsigned)(groups < kPairGrid ? groups : kPairGrid)), dim3(kPairBlock), 0, s,
+                       bodies, cells, mom, inv_perm, (const DevParams*)prm, targets, eps2, total, cap, y,
+                       (const int32_t*)cell_out, (const uint32_t*)order, (const uint32_t*)list, ctr);
+    hipLaunchKernelGGL(k_resid_features, dim3((unsigned)nt), dim3(256), 0, s, bodies, cells, mom, inv_perm,
+                       (const DevParams*)prm, n, targets, offs, cap, (const int32_t*)cell_out, feat);
     return hipGetLastError();
 }
 

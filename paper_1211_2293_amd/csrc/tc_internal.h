@@ -279,11 +279,19 @@ hipError_t launch_pb_write_sum(const WalkCell* walk, const Body* bodies, const u
                                const uint64_t* offs, uint32_t* lists, int64_t cap, int64_t cbound, float G,
                                float eps2, float* acc, float* pot, hipStream_t s);
 hipError_t launch_inverse_perm(const uint32_t* perm, int64_t n, uint32_t* inv, hipStream_t s);
-hipError_t launch_residuals(bool write, const WalkCell* walk, const Body* bodies, const Cell* cells,
-                            const Moments* mom, const uint32_t* bfs2pre, const uint32_t* inv_perm,
-                            DevParams* prm, int64_t n, const int32_t* targets, int nt, double eps2,
-                            uint32_t* counts, const uint32_t* offs, int64_t cap, float* feat, float* y,
-                            int32_t* cell_out, hipStream_t s);
+hipError_t launch_resid_count(const WalkCell* walk, const Body* bodies, const uint32_t* bfs2pre,
+                              const uint32_t* inv_perm, DevParams* prm, int64_t n, const int32_t* targets, int nt,
+                              uint32_t* counts, hipStream_t s);
+// Keys of the order by cell: the first cells in level order, which hold nearly
+// all the large ones, have one key each.
+constexpr int64_t kResidKeys = 16384;
+constexpr uint32_t kResidColdKeys = 256;
+hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const Cell* cells, const Moments* mom,
+                              const uint32_t* bfs2pre, const uint32_t* pre2bfs, const uint32_t* inv_perm,
+                              DevParams* prm, int64_t n, int64_t cmax, const int32_t* targets, int nt, double eps2,
+                              const uint32_t* offs, int64_t cap, uint32_t* key_count, uint32_t* key_off,
+                              uint32_t* key_part, uint32_t* ctr, float* feat, float* y, int32_t* cell_out,
+                              hipStream_t s);
 hipError_t launch_mlp_load(MlpState* st, const float* params, hipStream_t s);
 hipError_t launch_mlp_get(const MlpState* st, float* params, hipStream_t s);
 hipError_t launch_mlp_forward(const MlpState* st, const float* feat, int64_t nrows, const int32_t* idx, int64_t nb,

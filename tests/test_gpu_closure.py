@@ -50,6 +50,35 @@ def test_residuals_match_oracle(plummer):
         assert np.all(np.abs(y[a:b][og] - ref) <= 1e-6 * np.abs(ref) + 1e-9)
 
 
+@pytest.mark.parametrize("n,nt,part", [(2, 2, 1.0), (300, 300, 1.0), (300, 1, 1.0), (4000, 4000, 1.0), (4000, 1500, 0.37),
+                                       (40000, 7, 1.0), (40000, 9, 0.01)])
+def test_residual_pairs_at_every_split(n, nt, part):
+    """Cells of one body up to a quarter of the system, met by one to thousands
+    of targets: runs of a cell of every length, and lists that fill the given
+    arrays only in part.  The bounds are the ones of the oracle's test: FP64
+    sums, rounded once."""
+    w = workloads.plummer_sphere(n, seed=300 + n)
+    tc, keep = _ctx(w)
+    targets = np.random.default_rng(n).permutation(n)[:nt].astype(np.int32)
+    full = tc.residuals(0.9, 1e-2, to_dev(targets))
+    cap = int(np.ceil(part * len(full[2])))
+    feat, y, cell = tc.residuals(0.9, 1e-2, to_dev(targets), cap=cap) if part < 1.0 else full
+    feat, y, cell = feat.cpu().numpy(), y.cpu().numpy(), cell.cpu().numpy()
+    r = oracle.Tree(w.pos, w.mass, 16).residuals(0.9, 1e-2, targets)
+    off = np.concatenate([[0], np.cumsum(r["count"])])
+    assert len(full[2]) == off[-1]
+    np.testing.assert_array_equal(cell[:cap], full[2].cpu().numpy()[:cap])
+    for k in range(nt):
+        a, b = off[k], off[k + 1]
+        if b > cap:
+            break
+        og, oo = np.argsort(cell[a:b]), np.argsort(r["cell"][a:b])
+        np.testing.assert_array_equal(cell[a:b][og], r["cell"][a:b][oo])
+        np.testing.assert_allclose(feat[a:b][og], r["feat"][a:b][oo], rtol=1e-6, atol=1e-6)
+        ref = r["y"][a:b][oo]
+        assert np.all(np.abs(y[a:b][og] - ref) <= 1e-6 * np.abs(ref) + 1e-9)
+
+
 def _features(n=3000, seed=91):
     rng = np.random.default_rng(seed)
     f = np.concatenate([rng.normal(size=(n, 9)) * [1, 1, 1, .3, .3, .3, .3, .3, .3],
