@@ -666,6 +666,8 @@ int tc_fmm_plan(tc_ctx* ctx, double theta, void* buf, size_t bytes, int64_t fron
     hipStream_t s = ctx->stream;
     DevParams p;
     TC_HIP(ctx, hipMemcpyAsync(&p, ctx->prm(), sizeof(p), hipMemcpyDeviceToHost, s));
+    TC_HIP(ctx, hipMemcpyAsync(ctx->fmm_lvl_off, ctx->at<uint32_t>(l.off_lvl_off), sizeof(ctx->fmm_lvl_off),
+                               hipMemcpyDeviceToHost, s));
     TC_HIP(ctx, hipStreamSynchronize(s));
     const int64_t C = (int64_t)p.ncells < l.cmax ? (int64_t)p.ncells : l.cmax;
     FmmLayout f;
@@ -683,16 +685,11 @@ int tc_fmm_plan(tc_ctx* ctx, double theta, void* buf, size_t bytes, int64_t fron
     uint64_t* m2l = reinterpret_cast<uint64_t*>(B + f.off_m2l);
     uint64_t* p2p = reinterpret_cast<uint64_t*>(B + f.off_p2p);
     DttCell* dc = reinterpret_cast<DttCell*>(B + f.off_dc);
-    TC_HIP(ctx, launch_fmm_geo(cells, mom, ctx->at<WalkCell>(l.off_walk), ctx->at<uint32_t>(l.off_pre2bfs),
-                               ctx->prm(), C, geo, dc, s));
-    TC_HIP(ctx, hipMemcpyAsync(ctx->fmm_lvl_off, ctx->at<uint32_t>(l.off_lvl_off), sizeof(ctx->fmm_lvl_off),
-                               hipMemcpyDeviceToHost, s));
-    TC_HIP(ctx, hipStreamSynchronize(s));
+    TC_HIP(ctx, launch_fmm_geo(cells, mom, ctx->at<Body>(l.off_bodies), ctx->at<WalkCell>(l.off_walk),
+                               ctx->at<uint32_t>(l.off_pre2bfs), ctx->prm(), C, geo, dc, s));
     for (int lv = levels_for(3); lv >= 0; --lv) {   // level offsets cover levels 0..L and the end
         const int64_t cnt = (int64_t)ctx->fmm_lvl_off[lv + 1] - (int64_t)ctx->fmm_lvl_off[lv];
-        TC_HIP(ctx, launch_fmm_radii(cells, mom, ctx->at<Body>(l.off_bodies), ctx->at<WalkCell>(l.off_walk),
-                                     ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_lvl_off), lv, cnt,
-                                     geo, dc, s));
+        TC_HIP(ctx, launch_fmm_radii(ctx->at<uint32_t>(l.off_lvl_off), lv, cnt, dc, s));
     }
     TC_HIP(ctx, launch_fill_u32(reinterpret_cast<uint32_t*>(ctr), 8, s));
     TC_HIP(ctx, launch_fill_u32(reinterpret_cast<uint32_t*>(fa), 2, s));   // the pair (root, root)

@@ -19,6 +19,7 @@
 // to the body; then the pairs are computed side by side), the network's forward and backward passes, the Adam update.
 #include "tc_internal.h"
 #include "closure.h"
+#include "walk_common.h"
 
 #include <math.h>
 
@@ -167,14 +168,6 @@ __global__ void __launch_bounds__(256) k_resid_order(const int32_t* __restrict__
     }
 }
 
-// (r2)^(-1/2) in FP64: the hardware's approximation and one step of third
-// order (relative error 2^-53 or so: the step's own is the cube of 2^-26).
-__device__ __forceinline__ double rsqrt64(double r2) {
-    const double y = __builtin_amdgcn_rsq(r2);
-    const double e = fma(-r2 * y, y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
 // The sums of the pairs: the exact softened sum over the cell's bodies (FP64,
 // fixed order) against the monopole.  Pairs of one cell are taken up to four at
 // once, each body read once for all of them: those of a cell with more than
@@ -223,7 +216,7 @@ struct Sum3 {
 
 __device__ __forceinline__ void add_body(Sum3& e, const Body& b, double x, double y, double z, double eps2) {
     const double dx = b.x - x, dy = b.y - y, dz = b.z - z;
-    const double inv = rsqrt64(fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2))));
+    const double inv = walk::rsqrt64(fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2))));
     const double w3 = b.m * inv * inv * inv;
     e.x = fma(w3, dx, e.x);
     e.y = fma(w3, dy, e.y);

@@ -20,7 +20,7 @@
 //   * L2L from every parent to its children, level by level;
 //   * per leaf: the expansion at each body (L2P) plus the direct sums over
 //     its partner leaves in FP32 (P2P), coordinates relative to the leaf
-//     centre, compensated as in the treecode force loop.
+//     centre, chunks added in FP64 as in the treecode force loop.
 //
 // The traversal writes its pairs in a fixed order and a stable sort groups
 // them by target, so every sum runs in a fixed order and results are
@@ -29,6 +29,8 @@
 #include "walk_common.h"
 
 #include <math.h>
+
+#include <type_traits>
 
 namespace tc {
 namespace {
@@ -45,15 +47,37 @@ constexpr int kNL = 20;
 __device__ __forceinline__ bool is_leaf(const Cell& c) { return c.leaf_nch < 0; }
 __device__ __forceinline__ int nchildren(const Cell& c) { return c.leaf_nch & 0x7fffffff; }
 
+__device__ __forceinline__ uint64_t pair_key(uint32_t a, uint32_t b) { return ((uint64_t)a << 32) | b; }
+
+__device__ __forceinline__ double dist2(double ax, double ay, double az, double bx, double by, double bz) {
+    const double dx = ax - bx, dy = ay - by, dz = az - bz;
+    return (dx * dx + dy * dy) + dz * dz;
+}
+
+constexpr int kGeoLanes = 8;                // lanes per cell: bodies of a leaf, children of a cell
+
+__device__ __forceinline__ double lanes_max(double v) {
+#pragma unroll
+    for (int o = kGeoLanes / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
+    return v;
+}
+
+// Centres and radii: rho_A bounds the cell's bodies about its centre z, rho_B
+// about its centre of mass; for a leaf the largest distance of one of its
+// bodies (the root of the largest square, which is the same number), for an
+// internal cell the largest (distance between the centres + the child's radius)
+// over its children, from k_fmm_radii; each capped by the geometric bound.
 __global__ void __launch_bounds__(256) k_fmm_geo(const Cell* __restrict__ cells, const Moments* __restrict__ mom,
-                                                 const WalkCell* __restrict__ walk,
+                                                 const Body* __restrict__ bodies, const WalkCell* __restrict__ walk,
                                                  const uint32_t* __restrict__ pre2bfs,
                                                  const DevParams* __restrict__ prm, int64_t cmax,
                                                  FmmGeo* __restrict__ geo, DttCell* __restrict__ dc) {
     int64_t C = prm->ncells;
     if (C > cmax) C = cmax;
     const double size = prm->size;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < C; k += (int64_t)gridDim.x * blockDim.x) {
+    const int sub = threadIdx.x % kGeoLanes;
+    const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kGeoLanes);
+    for (int64_t k = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kGeoLanes; k < C; k += stride) {
         const Cell c = cells[k];
         const int l = c.level;
         const double s = ldexp(size, -l);
@@ -64,26 +88,35 @@ __global__ void __launch_bounds__(256) k_fmm_geo(const Cell* __restrict__ cells,
             for (int a = 0; a < 3; ++a) org[a] = (org[a] << 1) | ((d >> (2 - a)) & 1u);
         }
         FmmGeo g;
-        double d[3];
+        double com[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             g.z[a] = prm->lo[a] + ((double)org[a] + 0.5) * s;
-            d[a] = mom[k].com[a] - g.z[a];
+            com[a] = mom[k].com[a];
         }
-        // geometric bounds; k_fmm_radii tightens them from the bodies
-        g.rhoA = kHalfSqrt3 * s;
-        g.rhoB = kHalfSqrt3 * s + sqrt((d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]);
-        g.pad[0] = g.pad[1] = g.pad[2] = 0.0;
+        double rhoA = kHalfSqrt3 * s;
+        double rhoB = kHalfSqrt3 * s + sqrt(dist2(com[0], com[1], com[2], g.z[0], g.z[1], g.z[2]));
+        if (is_leaf(c)) {
+            double ra = 0.0, rb = 0.0;
+            for (int64_t j = c.begin + sub; j < (int64_t)c.begin + c.count; j += kGeoLanes) {
+                const Body b = bodies[j];
+                ra = fmax(ra, dist2(b.x, b.y, b.z, g.z[0], g.z[1], g.z[2]));
+                rb = fmax(rb, dist2(b.x, b.y, b.z, com[0], com[1], com[2]));
+            }
+            rhoA = fmin(sqrt(lanes_max(ra)), rhoA);
+            rhoB = fmin(sqrt(lanes_max(rb)), rhoB);
+        }
+        if (sub != 0) continue;
         geo[k] = g;
         const uint32_t kb = pre2bfs[k];
         DttCell t;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             t.z[a] = g.z[a];
-            t.com[a] = mom[k].com[a];
+            t.com[a] = com[a];
         }
-        t.rhoA = g.rhoA;
-        t.rhoB = g.rhoB;
+        t.rhoA = rhoA;
+        t.rhoB = rhoB;
         t.child = is_leaf(c) ? -1 : walk[kb].a;
         t.nch_leaf = c.leaf_nch;
         t.level = l;
@@ -92,52 +125,30 @@ __global__ void __launch_bounds__(256) k_fmm_geo(const Cell* __restrict__ cells,
     }
 }
 
-__device__ __forceinline__ uint64_t pair_key(uint32_t a, uint32_t b) { return ((uint64_t)a << 32) | b; }
-
-__device__ __forceinline__ double dist3(double ax, double ay, double az, double bx, double by, double bz) {
-    const double dx = ax - bx, dy = ay - by, dz = az - bz;
-    return sqrt((dx * dx + dy * dy) + dz * dz);
-}
-
-// The radii of the cells of one level (level-order range), deepest level
-// first: rho_A bounds the cell's bodies about its centre z, rho_B about its
-// centre of mass; for a leaf the largest distance of one of its bodies, for
-// an internal cell the largest (distance between the centres + the child's
-// radius) over its children; each capped by the geometric bound.
-__global__ void __launch_bounds__(256) k_fmm_radii(const Cell* __restrict__ cells, const Moments* __restrict__ mom,
-                                                   const Body* __restrict__ bodies, const WalkCell* __restrict__ walk,
-                                                   const uint32_t* __restrict__ bfs2pre,
-                                                   const uint32_t* __restrict__ lvl_off, int level,
-                                                   FmmGeo* __restrict__ geo, DttCell* __restrict__ dc) {
+// The radii of the internal cells of one level (level-order range), deepest
+// level first.  One lane per child: with a thread per cell and the leaves'
+// bodies in the same kernel, a level was one thread's chain of up to 64 loads
+// and roots (285 us for eleven levels of 60,850 cells; now 31, and 14 for
+// k_fmm_geo with the leaves' bodies).
+__global__ void __launch_bounds__(256) k_fmm_radii(const uint32_t* __restrict__ lvl_off, int level, DttCell* dc) {
+    const int sub = threadIdx.x % kGeoLanes;
     const int64_t lo = lvl_off[level], hi = lvl_off[level + 1];
-    for (int64_t k = lo + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < hi;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t c = bfs2pre[k];
-        const Cell cc = cells[c];
-        FmmGeo g = geo[c];
-        const double cx = mom[c].com[0], cy = mom[c].com[1], cz = mom[c].com[2];
+    const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kGeoLanes);
+    for (int64_t k = lo + (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kGeoLanes; k < hi; k += stride) {
+        const DttCell g = dc[k];
+        if (g.nch_leaf < 0) continue;
         double ra = 0.0, rb = 0.0;
-        if (is_leaf(cc)) {
-            for (int64_t j = cc.begin; j < (int64_t)cc.begin + cc.count; ++j) {
-                const Body b = bodies[j];
-                ra = fmax(ra, dist3(b.x, b.y, b.z, g.z[0], g.z[1], g.z[2]));
-                rb = fmax(rb, dist3(b.x, b.y, b.z, cx, cy, cz));
-            }
-        } else {
-            const int32_t first = walk[k].a;
-            const int nch = nchildren(cc);
-            for (int i = 0; i < nch; ++i) {
-                const uint32_t ch = bfs2pre[first + i];
-                const FmmGeo gc = geo[ch];
-                ra = fmax(ra, dist3(gc.z[0], gc.z[1], gc.z[2], g.z[0], g.z[1], g.z[2]) + gc.rhoA);
-                rb = fmax(rb, dist3(mom[ch].com[0], mom[ch].com[1], mom[ch].com[2], cx, cy, cz) + gc.rhoB);
-            }
+        if (sub < g.nch_leaf) {
+            const DttCell ch = dc[g.child + sub];
+            ra = sqrt(dist2(ch.z[0], ch.z[1], ch.z[2], g.z[0], g.z[1], g.z[2])) + ch.rhoA;
+            rb = sqrt(dist2(ch.com[0], ch.com[1], ch.com[2], g.com[0], g.com[1], g.com[2])) + ch.rhoB;
         }
-        g.rhoA = fmin(ra, g.rhoA);
-        g.rhoB = fmin(rb, g.rhoB);
-        geo[c] = g;
-        dc[k].rhoA = g.rhoA;
-        dc[k].rhoB = g.rhoB;
+        ra = lanes_max(ra);
+        rb = lanes_max(rb);
+        if (sub == 0) {
+            dc[k].rhoA = fmin(ra, g.rhoA);
+            dc[k].rhoB = fmin(rb, g.rhoB);
+        }
     }
 }
 
@@ -385,42 +396,43 @@ __global__ void __launch_bounds__(256) k_fmm_offsets(const uint64_t* __restrict_
 // R = centre - source to lam.
 __device__ __forceinline__ void m2l_add(double M, const double* Q, double x, double y, double z, double eps2,
                                         double* lam) {
-    const double r2 = ((x * x + y * y) + z * z) + eps2;
-    const double s = 1.0 / sqrt(r2);
+    const double xx = x * x, yy = y * y, zz = z * z;
+    const double s = rsqrt64(((xx + yy) + zz) + eps2);
     const double s2 = s * s, s3 = s2 * s, s5 = s3 * s2, s7 = s5 * s2;
     const double Qxx = Q[0], Qyy = Q[1], Qzz = Q[2], Qxy = Q[3], Qxz = Q[4], Qyz = Q[5];
-    const double qx = Qxx * x + Qxy * y + Qxz * z;
-    const double qy = Qxy * x + Qyy * y + Qyz * z;
-    const double qz = Qxz * x + Qyz * y + Qzz * z;
-    const double rqr = qx * x + qy * y + qz * z;
+    const double qx = fma(Qxz, z, fma(Qxy, y, Qxx * x));
+    const double qy = fma(Qyz, z, fma(Qyy, y, Qxy * x));
+    const double qz = fma(Qzz, z, fma(Qyz, y, Qxz * x));
+    const double rqr = fma(qz, z, fma(qy, y, qx * x));
     const double trq = Qxx + Qyy + Qzz;
+    const double m3 = M * s3, m5 = 3.0 * M * s5, m7 = -15.0 * M * s7;
     // Lam_0: M D0 + (1/6) Q:D2, with Q:D2 = 3 RQR s^5 - tr(Q) s^3
-    lam[0] += M * s + (3.0 * rqr * s5 - trq * s3) / 6.0;
+    lam[0] += fma(M, s, fma(0.5 * rqr, s5, trq * s3 * (-1.0 / 6.0)));
     // Lam_1: M D1 + (1/6) Q:D3, with (Q:D3)_a = -15 R_a RQR s^7 + 3 (2 (QR)_a + R_a tr Q) s^5
-    const double k7 = -15.0 * rqr * s7, k5 = 3.0 * trq * s5;
-    lam[1] += -M * x * s3 + (x * k7 + 6.0 * qx * s5 + x * k5) / 6.0;
-    lam[2] += -M * y * s3 + (y * k7 + 6.0 * qy * s5 + y * k5) / 6.0;
-    lam[3] += -M * z * s3 + (z * k7 + 6.0 * qz * s5 + z * k5) / 6.0;
+    const double k1 = fma(0.5 * trq, s5, fma(-2.5 * rqr, s7, -m3));
+    lam[1] += fma(x, k1, qx * s5);
+    lam[2] += fma(y, k1, qy * s5);
+    lam[3] += fma(z, k1, qz * s5);
     // Lam_2 = M D2: 3 R_a R_b s^5 - delta_ab s^3
-    const double m5 = 3.0 * M * s5, m3 = M * s3;
-    lam[4] += m5 * x * x - m3;
-    lam[5] += m5 * y * y - m3;
-    lam[6] += m5 * z * z - m3;
-    lam[7] += m5 * x * y;
-    lam[8] += m5 * x * z;
-    lam[9] += m5 * y * z;
+    const double mx = m5 * x, my = m5 * y, mz = m5 * z;
+    lam[4] += fma(mx, x, -m3);
+    lam[5] += fma(my, y, -m3);
+    lam[6] += fma(mz, z, -m3);
+    lam[7] = fma(mx, y, lam[7]);
+    lam[8] = fma(mx, z, lam[8]);
+    lam[9] = fma(my, z, lam[9]);
     // Lam_3 = M D3: -15 R_a R_b R_c s^7 + 3 (delta_ab R_c + delta_ac R_b + delta_bc R_a) s^5
-    const double m7 = -15.0 * M * s7;
-    lam[10] += m7 * x * x * x + 3.0 * m5 * x;
-    lam[11] += m7 * y * y * y + 3.0 * m5 * y;
-    lam[12] += m7 * z * z * z + 3.0 * m5 * z;
-    lam[13] += m7 * x * x * y + m5 * y;
-    lam[14] += m7 * x * x * z + m5 * z;
-    lam[15] += m7 * x * y * y + m5 * x;
-    lam[16] += m7 * y * y * z + m5 * z;
-    lam[17] += m7 * x * z * z + m5 * x;
-    lam[18] += m7 * y * z * z + m5 * y;
-    lam[19] += m7 * x * y * z;
+    const double ax = fma(m7, xx, m5), ay = fma(m7, yy, m5), az = fma(m7, zz, m5);
+    lam[10] = fma(x, fma(2.0, m5, ax), lam[10]);
+    lam[11] = fma(y, fma(2.0, m5, ay), lam[11]);
+    lam[12] = fma(z, fma(2.0, m5, az), lam[12]);
+    lam[13] = fma(y, ax, lam[13]);
+    lam[14] = fma(z, ax, lam[14]);
+    lam[15] = fma(x, ay, lam[15]);
+    lam[16] = fma(z, ay, lam[16]);
+    lam[17] = fma(x, az, lam[17]);
+    lam[18] = fma(y, az, lam[18]);
+    lam[19] = fma(m7 * x, y * z, lam[19]);
 }
 
 // Full-tensor views of the packed coefficients.
@@ -451,19 +463,17 @@ __device__ __forceinline__ void l2p(const double* lam, const double* dl, double*
     p = lam[0];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        double ga = lam[1 + a];
-        p += lam[1 + a] * dl[a];
+        double h = 0.0, t = 0.0;                 // (Lam2 dl)_a and (Lam3[dl, dl])_a
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-            ga += t2(lam, a, b) * dl[b];
-            p += 0.5 * t2(lam, a, b) * dl[a] * dl[b];
+            double u = 0.0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                ga += 0.5 * t3(lam, a, b, c) * dl[b] * dl[c];
-                p += t3(lam, a, b, c) * dl[a] * dl[b] * dl[c] / 6.0;
-            }
+            for (int c = 0; c < 3; ++c) u = fma(t3(lam, a, b, c), dl[c], u);
+            h = fma(t2(lam, a, b), dl[b], h);
+            t = fma(u, dl[b], t);
         }
-        g[a] = ga;
+        g[a] = lam[1 + a] + fma(0.5, t, h);
+        p = fma(dl[a], lam[1 + a] + fma(1.0 / 6.0, t, 0.5 * h), p);
     }
 }
 
@@ -546,7 +556,7 @@ __global__ void __launch_bounds__(256) k_fmm_l2l(const Cell* __restrict__ cells,
 }
 
 constexpr int kFmmList = 256;
-constexpr int kFmmWaves = 4;
+constexpr int kFmmWaves = 1;                // per block: their tasks differ in length
 
 // A target leaf whose partner list is longer than kFmmChunk leaves is cut
 // into chunks of kFmmChunk partners, one task each, so that no single wave
@@ -585,77 +595,96 @@ __global__ void __launch_bounds__(256) k_fmm_tasks_fill(const uint32_t* __restri
 }
 
 // L2P + P2P: one wave per task (a target leaf, or one chunk of a long
-// leaf's partner list).  Lanes are (target body, slice):
-// with nA target bodies, 64/P lanes per slice where P is the smallest power
-// of two >= nA (at most 64), and slice k sums list entries k, k + S, ...
-// (S slices); the slices' sums are added in FP64 in a fixed order.  The
-// partner leaves' bodies are gathered 64 at a time: 64 partner cells are
-// loaded together, their body counts scanned, and each lane finds its
-// body's partner by a binary search over the scan.
-__global__ void __launch_bounds__(256) k_fmm_leaf(const Cell* __restrict__ cells, const Body* __restrict__ bodies,
+// leaf's partner list).  Lanes are (two target bodies t and t + H, slice): with
+// nA target bodies, H = ceil(nA / 2) lanes per slice, and slice k of
+// S = floor(64 / H) sums list entries k, k + S, ...; the slices' sums are added
+// in FP64 in a fixed order.  The partner leaves' bodies are gathered up to 256
+// at a time: 64 partner cells are loaded together, their body counts scanned,
+// and each lane finds its bodies' partners from a bit per partner's first slot,
+// for four bodies at once where there are as many.
+//
+// Bound by the FP32 units, 14 instructions per pair of bodies: 2.9e9 pairs
+// (1,048,576 bodies, leaf size 64, theta 0.5) in 1.6 ms.  Two targets per lane
+// halve the LDS reads per interaction and leave few lanes idle (slices of the
+// next power of two of nA lanes lost a quarter); four entries per lane are read
+// ahead, where one at a time waited for each; chunks are added in FP64 (two
+// instructions, where a compensated FP32 sum took eight); a wave per block, as
+// tasks differ in length.  Before: 2.74 ms.
+__device__ __forceinline__ void two_targets(const float4& q, const float (&x)[2][3], float eps2, float (&a)[2][4]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const float dx = q.x - x[h][0], dy = q.y - x[h][1], dz = q.z - x[h][2];
+        const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
+        const float s = __builtin_amdgcn_rsqf(r2);
+        const float ms = q.w * s;
+        const float ms3 = ms * (s * s);
+        a[h][0] = fmaf(ms3, dx, a[h][0]);
+        a[h][1] = fmaf(ms3, dy, a[h][1]);
+        a[h][2] = fmaf(ms3, dz, a[h][2]);
+        a[h][3] -= ms;
+    }
+}
+
+template <bool F32>
+__global__ void __launch_bounds__(kFmmWaves * kWave, 4) k_fmm_leaf(const Cell* __restrict__ cells, const Body* __restrict__ bodies,
                                                   const float4* __restrict__ bodies32, const uint32_t* __restrict__ perm,
                                                   const FmmGeo* __restrict__ geo, const double* __restrict__ lam,
                                                   const uint64_t* __restrict__ pkeys, const uint32_t* __restrict__ poff,
                                                   const uint32_t* __restrict__ task, const uint32_t* __restrict__ toff,
                                                   const uint32_t* __restrict__ soff, int64_t ntasks, double* __restrict__ part,
                                                   float G, float eps2, float* __restrict__ acc, float* __restrict__ pot) {
+    constexpr int kAhead = 4;               // entries read ahead per lane
+    constexpr int kPlain = 32;              // FP32 terms per lane between additions in FP64
     __shared__ float4 s_list[kFmmWaves][kFmmList];
-    __shared__ uint32_t s_off[kFmmWaves][kWave];
     __shared__ int32_t s_beg[kFmmWaves][kWave];
+    __shared__ uint64_t s_start[kFmmWaves][kFmmList / kWave];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
     float4* L = s_list[wv];
-    uint32_t* SO = s_off[wv];
     int32_t* SB = s_beg[wv];
-    const int64_t nwaves = (int64_t)gridDim.x * kFmmWaves;
-    for (int64_t tk = blockIdx.x * (int64_t)kFmmWaves + wv; tk < ntasks; tk += nwaves) {
+    uint64_t* ST = s_start[wv];
+    const uint64_t upto = ~0ull >> (kWave - 1 - lane);
+    const int64_t tk = blockIdx.x * (int64_t)kFmmWaves + __builtin_amdgcn_readfirstlane(wv);
+    if (tk >= ntasks) return;
+    {
         const uint32_t A = task[tk];
         const uint32_t chunk = (uint32_t)tk - toff[A], nchunks = toff[A + 1] - toff[A];
         const Cell ca = cells[A];
-        const FmmGeo ga = geo[A];
+        const double zx = geo[A].z[0], zy = geo[A].z[1], zz = geo[A].z[2];
         const uint32_t q0 = poff[A] + chunk * kFmmChunk;
         const uint32_t q1 = nchunks > 1 ? min(poff[A + 1], q0 + kFmmChunk) : poff[A + 1];
         for (int t0 = 0; t0 < ca.count; t0 += kWave) {
             const int nA = min(kWave, ca.count - t0);
-            int P = 1;
-            while (P < nA) P <<= 1;
-            const int S = kWave / P;              // slices
-            const int t = lane & (P - 1), sl = lane / P;
-            const bool tv = t < nA;
-            const int64_t i = (int64_t)ca.begin + t0 + (tv ? t : 0);
-            const Body me = bodies[i];
-            // the far field first: the leaf's expansion at the body (a leaf
-            // cut into chunks gets it in k_fmm_leaf_finish)
-            double g[3] = {0.0, 0.0, 0.0}, p = 0.0;
-            if (sl == 0 && tv && nchunks == 1) {
-                double lamA[kNL];
-                for (int k = 0; k < kNL; ++k) lamA[k] = lam[A * kNL + k];
-                const double dl[3] = {me.x - ga.z[0], me.y - ga.z[1], me.z - ga.z[2]};
-                l2p(lamA, dl, g, p);
+            const int H = (nA + 1) / 2, S = kWave / H;
+            const int t = lane % H;
+            const int sl = min(lane / H, S - 1);             // lanes left over repeat the last slice
+            float x[2][3];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const Body me = bodies[(int64_t)ca.begin + t0 + (t + h * H < nA ? t + h * H : t)];
+                x[h][0] = (float)(me.x - zx);
+                x[h][1] = (float)(me.y - zy);
+                x[h][2] = (float)(me.z - zz);
             }
-            const float xi = (float)(me.x - ga.z[0]), yi = (float)(me.y - ga.z[1]), zi = (float)(me.z - ga.z[2]);
-            float sx = 0.f, sy = 0.f, sz = 0.f, sp = 0.f, cx = 0.f, cy = 0.f, cz = 0.f, cp = 0.f;
+            double v[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
             int len = 0;
             auto flush = [&](int cnt) {
                 wave_lds_sync();
-                for (int e = 0; e < cnt; e += kWave) {
-                    const int lim = min(cnt, e + kWave);
-                    float ax = 0.f, ay = 0.f, az = 0.f, ap = 0.f;
-                    for (int k = e + sl; k < lim; k += S) {
-                        const float4 q = L[k];
-                        const float dx = q.x - xi, dy = q.y - yi, dz = q.z - zi;
-                        const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
-                        const float s = __builtin_amdgcn_rsqf(r2);
-                        const float ms = q.w * s;
-                        const float ms3 = ms * (s * s);
-                        ap -= ms;
-                        ax = fmaf(ms3, dx, ax);
-                        ay = fmaf(ms3, dy, ay);
-                        az = fmaf(ms3, dz, az);
+                for (int e = 0; e < cnt; e += kPlain * S) {
+                    const int lim = min(cnt, e + kPlain * S);
+                    float a[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                    int k = e;
+                    for (; k + kAhead * S <= lim; k += kAhead * S) {
+                        float4 q[kAhead];
+#pragma unroll
+                        for (int u = 0; u < kAhead; ++u) q[u] = L[k + u * S + sl];
+#pragma unroll
+                        for (int u = 0; u < kAhead; ++u) two_targets(q[u], x, eps2, a);
                     }
-                    comp_add(sx, cx, ax);
-                    comp_add(sy, cy, ay);
-                    comp_add(sz, cz, az);
-                    comp_add(sp, cp, ap);
+                    for (; k + sl < lim; k += S) two_targets(L[k + sl], x, eps2, a);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) v[h][c] += (double)a[h][c];
                 }
                 wave_lds_sync();
             };
@@ -674,68 +703,104 @@ __global__ void __launch_bounds__(256) k_fmm_leaf(const Cell* __restrict__ cells
                     const uint32_t y = __shfl_up(incl, o, kWave);
                     if (lane >= o) incl += y;
                 }
-                const uint32_t total = __shfl(incl, kWave - 1, kWave);
-                SO[lane] = incl - pc;              // first slot of partner `lane`
-                SB[lane] = pb;
-                wave_lds_sync();
-                for (uint32_t base = 0; base < total; base += kWave) {
-                    const int m = (int)min((uint32_t)kWave, total - base);
-                    if (len + m > kFmmList) {
+                const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+                const uint32_t first = incl - pc;  // slot of the partner's first body
+                SB[lane] = pb - (int32_t)first;
+                for (uint32_t base = 0; base < total;) {
+                    const uint32_t m = min((uint32_t)(kFmmList - len), total - base);
+                    // one bit per slot where a partner starts: a body's partner
+                    // is the number of starts up to its slot, less one
+                    if (lane < kFmmList / kWave) ST[lane] = 0ull;
+                    wave_lds_sync();
+                    if (lane < nq && first - base < m)
+                        atomicOr(reinterpret_cast<uint32_t*>(ST) + (first - base) / 32, 1u << ((first - base) % 32));
+                    int before = __popcll(__ballot(lane < nq && first < base)) - 1;
+                    wave_lds_sync();
+                    auto gather = [&](auto batch, uint32_t from) {
+                        constexpr int B = decltype(batch)::value;
+                        int lo[B];
+                        float4 e[B];
+#pragma unroll
+                        for (int u = 0; u < B; ++u) {
+                            const uint64_t st = ST[from / kWave + u];
+                            lo[u] = before + __popcll(st & upto);
+                            before += __popcll(st);
+                        }
+#pragma unroll
+                        for (int u = 0; u < B; ++u) {
+                            const int64_t j = SB[lo[u]] + (int32_t)(base + min(from + u * kWave + lane, m - 1));
+                            if constexpr (F32) {
+                                e[u] = bodies32[j];
+                            } else {
+                                const Body b = bodies[j];
+                                e[u] = make_float4((float)(b.x - zx), (float)(b.y - zy), (float)(b.z - zz), (float)b.m);
+                            }
+                        }
+#pragma unroll
+                        for (int u = 0; u < B; ++u) {
+                            const uint32_t off = from + u * kWave + lane;
+                            if constexpr (F32)
+                                e[u] = make_float4((float)((double)e[u].x - zx), (float)((double)e[u].y - zy),
+                                                   (float)((double)e[u].z - zz), e[u].w);
+                            if (off < m) L[len + off] = e[u];
+                        }
+                    };
+                    constexpr uint32_t kBatch = kFmmList / kWave;
+                    if (m > kWave * kBatch / 2) gather(std::integral_constant<int, (int)kBatch>{}, 0u);
+                    else
+                        for (uint32_t from = 0; from < m; from += kWave) gather(std::integral_constant<int, 1>{}, from);
+                    len += (int)m;
+                    base += m;
+                    if (len == kFmmList) {
                         flush(len);
                         len = 0;
                     }
-                    if (lane < m) {
-                        const uint32_t slot = base + lane;
-                        int lo = 0, hi = nq - 1;          // last partner whose first slot <= slot
-                        while (lo < hi) {
-                            const int mid = (lo + hi + 1) >> 1;
-                            if (SO[mid] <= slot) lo = mid;
-                            else hi = mid - 1;
-                        }
-                        const int64_t j = (int64_t)SB[lo] + (slot - SO[lo]);
-                        float4 e;
-                        if (bodies32) {
-                            const float4 b = bodies32[j];
-                            e = make_float4((float)((double)b.x - ga.z[0]), (float)((double)b.y - ga.z[1]),
-                                            (float)((double)b.z - ga.z[2]), b.w);
-                        } else {
-                            const Body b = bodies[j];
-                            e = make_float4((float)(b.x - ga.z[0]), (float)(b.y - ga.z[1]), (float)(b.z - ga.z[2]),
-                                            (float)b.m);
-                        }
-                        L[len + lane] = e;
-                    }
-                    len += m;
                 }
                 wave_lds_sync();
             }
             flush(len);
-            // slices' sums in FP64, in slice order
-            double v[4] = {(double)sx + (double)cx, (double)sy + (double)cy, (double)sz + (double)cz,
-                           (double)sp + (double)cp};
-            for (int o = P; o < kWave; o <<= 1) {
+            // slices' sums in FP64, in a fixed order
+            for (int left = S; left > 1;) {
+                const int half = (left + 1) / 2;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const double w = __shfl_down(v[k], o, kWave);
-                    if ((lane & o) == 0) v[k] += w;
-                }
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const double w = __shfl(v[h][c], (lane + half * H) & (kWave - 1), kWave);
+                        if (lane / H + half < left) v[h][c] += w;
+                    }
+                left = half;
             }
-            if (sl == 0 && tv && nchunks > 1) {
-                double* o = part + 4 * ((int64_t)soff[A] + (int64_t)chunk * ca.count + t0 + t);
-                o[0] = v[0];
-                o[1] = v[1];
-                o[2] = v[2];
-                o[3] = v[3];
-            } else if (sl == 0 && tv) {
+            // lane j now takes target j
+            double w[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double lo = __shfl(v[0][c], lane, kWave), hi = __shfl(v[1][c], (lane - H) & (kWave - 1), kWave);
+                w[c] = lane < H ? lo : hi;
+            }
+            if (lane < nA && nchunks > 1) {
+                // the leaf's expansion and the self term: k_fmm_leaf_finish
+                double* o = part + 4 * ((int64_t)soff[A] + (int64_t)chunk * ca.count + t0 + lane);
+                o[0] = w[0];
+                o[1] = w[1];
+                o[2] = w[2];
+                o[3] = w[3];
+            } else if (lane < nA) {
+                const int64_t i = (int64_t)ca.begin + t0 + lane;
+                const Body me = bodies[i];
+                double lamA[kNL], g[3], p;
+                for (int k = 0; k < kNL; ++k) lamA[k] = lam[A * kNL + k];
+                const double dl[3] = {me.x - zx, me.y - zy, me.z - zz};
+                l2p(lamA, dl, g, p);
                 // the body met itself in its own leaf: no force, a -m/eps
                 // potential term removed as it was formed
                 const float mself = (float)me.m;
                 const double self = (double)(mself * __builtin_amdgcn_rsqf(eps2));
                 const int64_t o = perm[i];
-                acc[o * 3 + 0] = (float)((double)G * (g[0] + v[0]));
-                acc[o * 3 + 1] = (float)((double)G * (g[1] + v[1]));
-                acc[o * 3 + 2] = (float)((double)G * (g[2] + v[2]));
-                pot[o] = (float)((double)G * (-p + v[3] + self));
+                acc[o * 3 + 0] = (float)((double)G * (g[0] + w[0]));
+                acc[o * 3 + 1] = (float)((double)G * (g[1] + w[1]));
+                acc[o * 3 + 2] = (float)((double)G * (g[2] + w[2]));
+                pot[o] = (float)((double)G * (-p + w[3] + self));
             }
         }
     }
@@ -804,19 +869,17 @@ __global__ void __launch_bounds__(256) k_fill_u32(uint32_t* __restrict__ p, int6
 
 }  // namespace
 
-hipError_t launch_fmm_geo(const Cell* cells, const Moments* mom, const WalkCell* walk, const uint32_t* pre2bfs,
-                          const DevParams* prm, int64_t cmax, FmmGeo* geo, DttCell* dc, hipStream_t s) {
-    hipLaunchKernelGGL(k_fmm_geo, dim3(grid_for(cmax)), dim3(256), 0, s, cells, mom, walk, pre2bfs, prm, cmax, geo,
-                       dc);
+hipError_t launch_fmm_geo(const Cell* cells, const Moments* mom, const Body* bodies, const WalkCell* walk,
+                          const uint32_t* pre2bfs, const DevParams* prm, int64_t cmax, FmmGeo* geo, DttCell* dc,
+                          hipStream_t s) {
+    hipLaunchKernelGGL(k_fmm_geo, dim3(grid_for(cmax * kGeoLanes)), dim3(256), 0, s, cells, mom, bodies, walk, pre2bfs,
+                       prm, cmax, geo, dc);
     return hipGetLastError();
 }
 
-hipError_t launch_fmm_radii(const Cell* cells, const Moments* mom, const Body* bodies, const WalkCell* walk,
-                            const uint32_t* bfs2pre, const uint32_t* lvl_off, int level, int64_t count, FmmGeo* geo,
-                            DttCell* dc, hipStream_t s) {
+hipError_t launch_fmm_radii(const uint32_t* lvl_off, int level, int64_t count, DttCell* dc, hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fmm_radii, dim3(grid_for(count)), dim3(256), 0, s, cells, mom, bodies, walk, bfs2pre, lvl_off,
-                       level, geo, dc);
+    hipLaunchKernelGGL(k_fmm_radii, dim3(grid_for(count * kGeoLanes)), dim3(256), 0, s, lvl_off, level, dc);
     return hipGetLastError();
 }
 
@@ -876,17 +939,14 @@ hipError_t launch_fmm_leaf(const Cell* cells, const Body* bodies, const float4* 
                            const uint32_t* task, const uint32_t* toff, const uint32_t* soff, int64_t ntasks,
                            double* part, const DevParams* prm, int64_t cmax, float G, float eps2, float* acc,
                            float* pot, hipStream_t s) {
-    int dev = 0, ncu = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
     if (ntasks > 0) {
-        int64_t blocks = (ntasks + kFmmWaves - 1) / kFmmWaves;
-        const int64_t cap = (int64_t)ncu * 16;
-        if (blocks > cap) blocks = cap;
-        hipLaunchKernelGGL(k_fmm_leaf, dim3((unsigned)blocks), dim3(256), 0, s, cells, bodies, bodies32, perm, geo,
-                           lam, pkeys, poff, task, toff, soff, ntasks, part, G, eps2, acc, pot);
+        const dim3 grid((unsigned)((ntasks + kFmmWaves - 1) / kFmmWaves)), block(kFmmWaves * kWave);
+        if (bodies32)
+            hipLaunchKernelGGL(k_fmm_leaf<true>, grid, block, 0, s, cells, bodies, bodies32, perm, geo, lam, pkeys, poff,
+                               task, toff, soff, ntasks, part, G, eps2, acc, pot);
+        else
+            hipLaunchKernelGGL(k_fmm_leaf<false>, grid, block, 0, s, cells, bodies, bodies32, perm, geo, lam, pkeys,
+                               poff, task, toff, soff, ntasks, part, G, eps2, acc, pot);
     }
     int64_t fb = (cmax + 3) / 4;
     if (fb > 65536) fb = 65536;

@@ -307,16 +307,13 @@ hipError_t launch_walk_force_learned(const WalkCell* walk, const double* rcp2, c
                                      const DevParams* prm, float* acc, float* pot, int64_t* m2p, int64_t* p2p,
                                      int64_t* learned, int64_t* fallback, hipStream_t s);
 // fmm.hip
-// Geometry of a cell for the fast multipole method: its geometric centre
-// (the local expansion's centre) and the radii bounding its bodies about
-// that centre (rhoA) and about its centre of mass (rhoB).
+// Geometric centre of a cell, the centre of its local expansion.
 struct __align__(16) FmmGeo {
     double z[3];
-    double rhoA, rhoB;
-    double pad[3];
+    double pad[5];
 };
 // What the traversal reads of a cell, in level order: centre, centre of
-// mass, the two radii, its first child (level order; children are
+// mass, the radii bounding its bodies about the two (rhoA, rhoB), its first child (level order; children are
 // contiguous there), child count with bit 31 set for a leaf, and level.
 constexpr int kFmmMaxBlocks = 4096;   // blocks per traversal launch
 struct __align__(16) DttCell {
@@ -325,11 +322,10 @@ struct __align__(16) DttCell {
     double rhoA, rhoB;
     int32_t child, nch_leaf, level, pre;   // pre: the cell's pre-order index
 };
-hipError_t launch_fmm_geo(const Cell* cells, const Moments* mom, const WalkCell* walk, const uint32_t* pre2bfs,
-                          const DevParams* prm, int64_t cmax, FmmGeo* geo, DttCell* dc, hipStream_t s);
-hipError_t launch_fmm_radii(const Cell* cells, const Moments* mom, const Body* bodies, const WalkCell* walk,
-                            const uint32_t* bfs2pre, const uint32_t* lvl_off, int level, int64_t count, FmmGeo* geo,
-                            DttCell* dc, hipStream_t s);
+hipError_t launch_fmm_geo(const Cell* cells, const Moments* mom, const Body* bodies, const WalkCell* walk,
+                          const uint32_t* pre2bfs, const DevParams* prm, int64_t cmax, FmmGeo* geo, DttCell* dc,
+                          hipStream_t s);
+hipError_t launch_fmm_radii(const uint32_t* lvl_off, int level, int64_t count, DttCell* dc, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, hipStream_t s);
 hipError_t launch_fmm_dtt(const DttCell* dc, double theta, const uint64_t* fin, int64_t nin, uint64_t* fout,
                           int64_t capf, uint64_t* m2l, int64_t capm, uint64_t* p2p, int64_t capp,

@@ -59,6 +59,14 @@ def test_plummer(theta):
     _check(w.pos, w.mass, 16, theta, 1e-2)
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("lc", [1, 2, 5, 33, 64])
+def test_leaf_sums_of_every_width(lc, dtype):
+    # leaves of one body to a full wave's: one lane to 32 per slice, 64 slices to two
+    w = workloads.plummer_sphere(5000, seed=78)
+    _check(w.pos.astype(dtype), w.mass.astype(dtype), lc, 0.6, 1e-2)
+
+
 def test_uniform_cube_fp64_state():
     w = workloads.uniform_cube(4096)
     _check(w.pos, w.mass, w.leaf_cap, 0.5, w.eps)
