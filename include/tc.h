@@ -233,10 +233,10 @@ int tc_set_multipole(tc_ctx *ctx, int order);
 
 /* Per-body accumulation in the force kernel of tc_forces and tc_leapfrog:
  * TC_ACC_COMPENSATED (default) sums each chunk of 64 list entries in FP32
- * and folds the chunk sums into Neumaier-compensated totals;
+ * and adds the chunk sums in FP64;
  * TC_ACC_PLAIN keeps one running FP32 sum per component over the whole
  * list (the uncompensated reference for precision studies).  The learned
- * walk always compensates. */
+ * walk always adds its chunks in FP64. */
 #define TC_ACC_COMPENSATED 0
 #define TC_ACC_PLAIN 1
 int tc_set_accumulation(tc_ctx *ctx, int mode);

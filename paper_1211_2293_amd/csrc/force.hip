@@ -15,7 +15,7 @@
 // own body in FP32, reading each entry as an LDS broadcast.  Coordinates are
 // relative to the group's box centre (FP64 difference, then rounded) so FP32
 // keeps the significant digits; chunks of 64 entries are summed plainly and
-// folded into Neumaier-compensated totals.  Each group's walk also counts
+// added to FP64 totals.  Each group's walk also counts
 // the cells it tests (the root and every child of an opened cell), a
 // measure of the walk's work that is kept per group.
 //
@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
             const double rx = (lox + hix) * 0.5, ry = (loy + hiy) * 0.5, rz = (loz + hiz) * 0.5;
             const float xi = (float)(me.x - rx), yi = (float)(me.y - ry), zi = (float)(me.z - rz);
 
-            Acc a = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            Acc a = {0.0, 0.0, 0.0, 0.0};
             int64_t nm2p = 0, np2p = 0, ntest = 0;
             walk_group<D, PLAIN, QUAD, STEP>(walk, walkq, bodies, bodies32, L, S, LQ, lpl_log2, eps2, lox,
                                                        hix, loy, hiy, loz, hiz, rx, ry, rz, xi, yi, zi, 0u, 1, a, nm2p,
@@ -265,11 +265,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
                 // it was formed
                 const float mself = (float)me.m;
                 const float sself = __builtin_amdgcn_rsqf(eps2);
-                const float ph = (a.sp + a.cp) + mself * sself;
+                const float ph = (float)(a.sp + (double)(mself * sself));
                 const int64_t o = perm[i];
-                acc[o * D + 0] = G * (a.sx + a.cx);
-                acc[o * D + 1] = G * (a.sy + a.cy);
-                if (D == 3) acc[o * D + 2] = G * (a.sz + a.cz);
+                acc[o * D + 0] = G * (float)a.sx;
+                acc[o * D + 1] = G * (float)a.sy;
+                if (D == 3) acc[o * D + 2] = G * (float)a.sz;
                 pot[o] = G * ph;
                 // the list length, for the next evaluation's schedule
                 const int64_t lc = nm2p + np2p;
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu
                 zi = __shfl(zi, own, kWave);
             }
 
-            Acc a = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            Acc a = {0.0, 0.0, 0.0, 0.0};
             int64_t nm2p = 0, np2p = 0, ntest = 0;
             int len = 0, qlen = 0, nleaf = 0, top = 1;
 
@@ -526,10 +526,10 @@ __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu
             // the waves' sums, added in FP64 in wave order: one thread per
             // body and component
             double* part = reinterpret_cast<double*>(L);
-            part[(wv * 4 + 0) * kWave + lane] = (double)a.sx + (double)a.cx;
-            part[(wv * 4 + 1) * kWave + lane] = (double)a.sy + (double)a.cy;
-            part[(wv * 4 + 2) * kWave + lane] = (double)a.sz + (double)a.cz;
-            part[(wv * 4 + 3) * kWave + lane] = (double)a.sp + (double)a.cp;
+            part[(wv * 4 + 0) * kWave + lane] = a.sx;
+            part[(wv * 4 + 1) * kWave + lane] = a.sy;
+            part[(wv * 4 + 2) * kWave + lane] = a.sz;
+            part[(wv * 4 + 3) * kWave + lane] = a.sp;
             if (wv == 0) {
                 const uint32_t nx = order ? sched.pop(xq) : pos + gridDim.x;
                 if (lane == 0) s_next = nx;
@@ -630,13 +630,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
             }
         }
     }
-    Acc a = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    Acc a = {0.0, 0.0, 0.0, 0.0};
     int64_t nm2p = 0, np2p = 0, ntest = 0;   // tested cells are not kept for split walks
     walk_group<D, PLAIN, QUAD>(walk, walkq, bodies, bodies32, s_list[wv], s_stack[wv], s_qlist[wv], lpl_log2, eps2,
                                lox, hix, loy, hiy, loz, hiz, rx, ry, rz, xi, yi, zi, first, first_len, a, nm2p,
                                np2p, ntest);
     if (valid)
-        part[(int64_t)t * n + i] = make_float4(a.sx + a.cx, a.sy + a.cy, a.sz + a.cz, a.sp + a.cp);
+        part[(int64_t)t * n + i] = make_float4((float)a.sx, (float)a.sy, (float)a.sz, (float)a.sp);
     if (lane == 0 && (nm2p | np2p)) {
         atomicAdd(&m2p_out[g], (unsigned long long)nm2p);
         atomicAdd(&p2p_out[g], (unsigned long long)np2p);

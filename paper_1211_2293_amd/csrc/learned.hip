@@ -90,8 +90,8 @@ __global__ void __launch_bounds__(kWPB * 64, 4) k_walk_force_learned(
             const float xi = (float)(me.x - rx), yi = (float)(me.y - ry), zi = (float)(me.z - rz);
             const int ntiles = (gn + 15) >> 4;              // sample tiles holding bodies
 
-            Acc a = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            float kx = 0.f, ky = 0.f, kz = 0.f, ckx = 0.f, cky = 0.f, ckz = 0.f;  // closure corrections
+            Acc a = {0.0, 0.0, 0.0, 0.0};
+            double kx = 0.0, ky = 0.0, kz = 0.0;              // closure corrections
             int len = 0;
             int64_t nm2p = 0, np2p = 0, nlearn = 0, nfall = 0;
             PX[lane] = me.x;
@@ -271,9 +271,9 @@ __global__ void __launch_bounds__(kWPB * 64, 4) k_walk_force_learned(
                             L[len] = make_float4((float)(cx - rx), (float)(cy - ry), (float)(cz - rz), (float)M);
                         len += 1;
                         const float w = (float)(M * s * s / (dd * dd));   // quadrupole scale
-                        comp_add(kx, ckx, w * yo[0]);
-                        comp_add(ky, cky, w * yo[1]);
-                        comp_add(kz, ckz, w * yo[2]);
+                        kx += (double)(w * yo[0]);
+                        ky += (double)(w * yo[1]);
+                        kz += (double)(w * yo[2]);
                     }
                 }
                 wave_lds_sync();
@@ -283,11 +283,11 @@ __global__ void __launch_bounds__(kWPB * 64, 4) k_walk_force_learned(
             if (valid) {
                 const float mself = (float)me.m;
                 const float sself = __builtin_amdgcn_rsqf(eps2);
-                const float ph = (a.sp + a.cp) + mself * sself;
+                const float ph = (float)(a.sp + (double)(mself * sself));
                 const int64_t o = perm[i];
-                acc[o * 3 + 0] = G * ((a.sx + a.cx) + (kx + ckx));
-                acc[o * 3 + 1] = G * ((a.sy + a.cy) + (ky + cky));
-                acc[o * 3 + 2] = G * ((a.sz + a.cz) + (kz + ckz));
+                acc[o * 3 + 0] = G * (float)(a.sx + kx);
+                acc[o * 3 + 1] = G * (float)(a.sy + ky);
+                acc[o * 3 + 2] = G * (float)(a.sz + kz);
                 pot[o] = G * ph;
             }
             if (lane == 0) {

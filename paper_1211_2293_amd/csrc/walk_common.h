@@ -48,22 +48,18 @@ static __device__ __forceinline__ double rsqrt64(double r2) {
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-// Neumaier compensated accumulation of x into (s, c).
-static __device__ __forceinline__ void comp_add(float& s, float& c, float x) {
-    const float t = s + x;
-    if (fabsf(s) >= fabsf(x)) c += (s - t) + x;
-    else c += (x - t) + s;
-    s = t;
-}
-
+// Totals of the FP32 chunk sums, in FP64: two instructions per chunk and
+// component (a conversion and an addition at the FP32 rate), where Neumaier's
+// compensated sum in two FP32 words took eight (a step of 1,048,576 bodies 2.24
+// -> 2.16 ms, forces of 4,194,304 8.72 -> 8.38 ms).
 struct Acc {
-    float sx, sy, sz, sp, cx, cy, cz, cp;
+    double sx, sy, sz, sp;
 };
 
 // Sum the first `cnt` list entries for this lane's body.  cnt is padded up
 // to a multiple of 8 with massless entries, which add exactly zero.  By
-// default each chunk of 64 entries is summed plainly and folded into the
-// Neumaier-compensated totals; with PLAIN the whole list is one running
+// default each chunk of 64 entries is summed plainly in FP32 and added to the
+// FP64 totals; with PLAIN the whole list is one running
 // FP32 sum (the uncompensated reference of the precision study).
 //
 // STAGED takes each half of a batch of 8 entries in three stages
@@ -98,10 +94,10 @@ static __device__ __forceinline__ void flush(float4* L, int cnt, float xi, float
         const int lim = min(kWave, padded - e);
         float ax = 0.f, ay = 0.f, az = 0.f, ap = 0.f;
         if (PLAIN) {
-            ax = a.sx;
-            ay = a.sy;
-            az = a.sz;
-            ap = a.sp;
+            ax = (float)a.sx;
+            ay = (float)a.sy;
+            az = (float)a.sz;
+            ap = (float)a.sp;
         }
         for (int k = 0; k < lim; k += kStep) {
             if (STAGED) {
@@ -164,10 +160,10 @@ static __device__ __forceinline__ void flush(float4* L, int cnt, float xi, float
             a.sz = az;
             a.sp = ap;
         } else {
-            comp_add(a.sx, a.cx, ax);
-            comp_add(a.sy, a.cy, ay);
-            if (D == 3) comp_add(a.sz, a.cz, az);
-            comp_add(a.sp, a.cp, ap);
+            a.sx += (double)ax;
+            a.sy += (double)ay;
+            if (D == 3) a.sz += (double)az;
+            a.sp += (double)ap;
         }
     }
     wave_lds_sync();
@@ -197,10 +193,10 @@ static __device__ __forceinline__ void flush_quad(float4* LQ, int cnt, float xi,
         const int lim = min(kWave, padded - e);
         float ax = 0.f, ay = 0.f, az = 0.f, ap = 0.f;
         if (PLAIN) {
-            ax = a.sx;
-            ay = a.sy;
-            az = a.sz;
-            ap = a.sp;
+            ax = (float)a.sx;
+            ay = (float)a.sy;
+            az = (float)a.sz;
+            ap = (float)a.sp;
         }
         for (int k = 0; k < lim; k += 4) {
 #pragma unroll
@@ -232,10 +228,10 @@ static __device__ __forceinline__ void flush_quad(float4* LQ, int cnt, float xi,
             a.sz = az;
             a.sp = ap;
         } else {
-            comp_add(a.sx, a.cx, ax);
-            comp_add(a.sy, a.cy, ay);
-            comp_add(a.sz, a.cz, az);
-            comp_add(a.sp, a.cp, ap);
+            a.sx += (double)ax;
+            a.sy += (double)ay;
+            a.sz += (double)az;
+            a.sp += (double)ap;
         }
     }
     wave_lds_sync();
