@@ -72,7 +72,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef unsigned int uint2_t __attribute__((ext_vector_type(2)));
 
 // The network's BF16 weights as matrix-core operand fragments, for
-// inference on 16 samples at a time by one wave (net_tile).  Every layer is
+// inference on tiles of 16 samples by one wave (net_tiles).  Every layer is
 // computed transposed, Z^T = W^T H^T: a 16x16 FP32 output tile gives lane l
 // rows 4(l/16)..4(l/16)+3 of sample column l%16, which is what the next
 // layer's B operand needs once the K order of that layer's weights follows
@@ -132,32 +132,46 @@ __device__ __forceinline__ bf16x8_t cat8(short4_t a, short4_t b) {
     return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// The network on 16 samples: lane l = 16 g + r supplies x = the BF16
-// features 4g..4g+3 of sample r (zero beyond the tenth) and receives the
+// The network on K tiles of 16 samples: lane l = 16 g + r supplies x = the
+// BF16 features 4g..4g+3 of sample r (zero beyond the tenth) and receives the
 // outputs 4g..4g+3 of sample r: lanes 0..15 hold yhat (outputs 0..2, b3
-// included) of samples 0..15.  Biases start the FP32 accumulators.
-__device__ __forceinline__ float4_t net_tile(const NetF& N, short4_t x) {
+// included) of samples 0..15.  Biases start the FP32 accumulators.  Tiles share
+// the reads of the weights, which at one tile take half the LDS bandwidth.
+template <int K>
+__device__ __forceinline__ void net_tiles(const NetF& N, const short4_t* x, float4_t* y) {
     const int l = threadIdx.x & 63, g = l >> 4;
-    short4_t h1[4], h2[4];
+    short4_t h1[K][4], h2[K][4];
 #pragma unroll
     for (int ht = 0; ht < 4; ++ht) {
-        float4_t z = *reinterpret_cast<const float4_t*>(&N.b1[16 * ht + 4 * g]);
-        z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(N.f1[ht][l], x, z, 0, 0, 0);
-        h1[ht] = gelu_pack(z);
+        const float4_t b = *reinterpret_cast<const float4_t*>(&N.b1[16 * ht + 4 * g]);
+        const short4_t w = N.f1[ht][l];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            h1[k][ht] = gelu_pack(__builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w, x[k], b, 0, 0, 0));
     }
-    const bf16x8_t k0 = cat8(h1[0], h1[1]), k1 = cat8(h1[2], h1[3]);
 #pragma unroll
     for (int ht = 0; ht < 4; ++ht) {
-        float4_t z = *reinterpret_cast<const float4_t*>(&N.b2[16 * ht + 4 * g]);
-        z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, N.f2[ht][0][l]), k0, z, 0, 0, 0);
-        z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, N.f2[ht][1][l]), k1, z, 0, 0, 0);
-        h2[ht] = gelu_pack(z);
+        const float4_t b = *reinterpret_cast<const float4_t*>(&N.b2[16 * ht + 4 * g]);
+        const bf16x8_t w0 = __builtin_bit_cast(bf16x8_t, N.f2[ht][0][l]), w1 = __builtin_bit_cast(bf16x8_t, N.f2[ht][1][l]);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            float4_t z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, cat8(h1[k][0], h1[k][1]), b, 0, 0, 0);
+            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, cat8(h1[k][2], h1[k][3]), z, 0, 0, 0);
+            h2[k][ht] = gelu_pack(z);
+        }
     }
-    float4_t y = *reinterpret_cast<const float4_t*>(&N.b3[4 * g]);
-    y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, N.f3[0][l]), cat8(h2[0], h2[1]), y, 0, 0,
-                                                0);
-    y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, N.f3[1][l]), cat8(h2[2], h2[3]), y, 0, 0,
-                                                0);
+    const float4_t b = *reinterpret_cast<const float4_t*>(&N.b3[4 * g]);
+    const bf16x8_t w0 = __builtin_bit_cast(bf16x8_t, N.f3[0][l]), w1 = __builtin_bit_cast(bf16x8_t, N.f3[1][l]);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        y[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, cat8(h2[k][0], h2[k][1]), b, 0, 0, 0);
+        y[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, cat8(h2[k][2], h2[k][3]), y[k], 0, 0, 0);
+    }
+}
+
+__device__ __forceinline__ float4_t net_tile(const NetF& N, short4_t x) {
+    float4_t y;
+    net_tiles<1>(N, &x, &y);
     return y;
 }
 

@@ -360,3 +360,44 @@ def test_learned_leapfrog_step_matches_oracle():
     t2 = oracle.Tree(pos.cpu().numpy(), m, 16)
     ref, _ = t2.walk_forces(0.5, eps=eps)
     assert oracle.rel_l2(a_pl.cpu().numpy(), ref) < 1e-5
+
+
+@pytest.mark.parametrize("n,theta_l,theta_p", [(70, 0.9, 0.3), (777, 1.0, 0.4), (9000, 0.3, 0.02)])
+def test_learned_walk_by_blocks(n, theta_l, theta_p):
+    """One or two groups of one to four tiles, and groups with more learned
+    cells than the block's queue holds (512), kept and fallen back; the bounds
+    are those of the walks above."""
+    w = workloads.plummer_sphere(n, seed=500 + n)
+    tc, keep = _ctx(w)
+    p = mlp.unflatten(mlp.init_params(seed=9).astype(np.float64))
+    p["W3"] *= 0.2
+    theta = mlp.flatten(p).astype(np.float32)
+    tc.mlp_load(to_dev(theta))
+    t = oracle.Tree(w.pos, w.mass, 16)
+    # (the oracle's network over the largest case's million pairs takes minutes:
+    # its corrections are left out there)
+    ref = mlp.learned_corrections(t, theta_l, theta_p, theta, G=1.0) if n < 9000 else None
+    gb, gc = t.groups(64, 1024)
+    learned = []
+    for tau, th in ((0.0, theta_p), (float("inf"), theta_l)):
+        acc, pot = tc.forces_learned(theta_l, theta_p, tau, eps=1e-2)
+        m2p, p2p = (v.cpu().numpy() for v in tc.counts())
+        kept, fell = (v.cpu().numpy() for v in tc.learned_counts())
+        rm2p, rp2p = t.walk_counts_groups(th, gb, gc)
+        np.testing.assert_array_equal(m2p, rm2p)
+        np.testing.assert_array_equal(p2p, rp2p)
+        assert np.all((kept if tau == 0.0 else fell) == 0)
+        learned.append(fell if tau == 0.0 else kept)
+        a, ph = t.forces_groups(th, gb, gc, eps=1e-2)
+        ep = oracle.rel_l2(pot.cpu().numpy(), ph)
+        assert ep < 1e-5
+        if tau == 0.0 or ref is not None:
+            size = 0.0 if tau == 0.0 else np.linalg.norm(ref["corr"]) / np.linalg.norm(a)
+            ea = oracle.rel_l2(acc.cpu().numpy(), a if tau == 0.0 else a + ref["corr"])
+            print(f"n={n} tau={tau}: acc {ea:.2e} pot {ep:.2e}, learned up to {learned[-1].max()}", flush=True)
+            assert ea < 1e-5 + 1e-2 * size
+    np.testing.assert_array_equal(learned[0], learned[1])
+    if ref is not None:
+        np.testing.assert_array_equal(learned[0], ref["per_group"])
+    else:
+        assert learned[0].max() > 512
