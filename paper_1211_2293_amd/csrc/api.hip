@@ -615,14 +615,14 @@ bool fmm_layout(int64_t C, int64_t capf, int64_t capm, int64_t capp, FmmLayout* 
     f->off_lam = take(8 * 20 * (size_t)C);
     f->off_moff = take(4 * (size_t)(C + 1));
     f->off_poff = take(4 * (size_t)(C + 1));
-    f->off_ctr = take(8 * 4);
+    f->off_ctr = take(8 * kFmmCounters);
     f->off_fa = take(8 * (size_t)capf);
     f->off_fb = take(8 * (size_t)capf);
     f->off_m2l = take(8 * (size_t)capm);
     f->off_p2p = take(8 * (size_t)capp);
     f->off_keys_b = take(8 * (size_t)f->capk);
-    f->off_bt = take(4 * 3 * (size_t)kFmmMaxBlocks);
-    f->off_base = take(8 * 3 * (size_t)kFmmMaxBlocks);
+    f->off_bt = take(4 * 3 * (size_t)kFmmMaxWaves);
+    f->off_base = take(8 * 3 * (size_t)(kFmmMaxWaves / 4));   // per block of four waves
     f->off_hist = take(4 * 256 * (size_t)f->tiles);
     f->off_digit = take(4 * 256);
     f->ctiles = (C + kScanTile - 1) / kScanTile;
@@ -691,30 +691,37 @@ int tc_fmm_plan(tc_ctx* ctx, double theta, void* buf, size_t bytes, int64_t fron
         const int64_t cnt = (int64_t)ctx->fmm_lvl_off[lv + 1] - (int64_t)ctx->fmm_lvl_off[lv];
         TC_HIP(ctx, launch_fmm_radii(ctx->at<uint32_t>(l.off_lvl_off), lv, cnt, dc, s));
     }
-    TC_HIP(ctx, launch_fill_u32(reinterpret_cast<uint32_t*>(ctr), 8, s));
-    TC_HIP(ctx, launch_fill_u32(reinterpret_cast<uint32_t*>(fa), 2, s));   // the pair (root, root)
-    // one launch per level of pairs; the traversal is at most twice the
-    // tree's depth plus one levels deep
+    TC_HIP(ctx, launch_fmm_dtt_root(ctr, fa, s));
+    // three launches per level of pairs; the traversal is at most twice the
+    // tree's depth plus one levels deep.  The host waits after a batch of
+    // levels: first one and a half times the tree's levels (more than most
+    // trees take; a launch on an empty level costs less than a wait), then four
+    // at a time.
+    int depth = 0;
+    while (depth <= levels_for(3) && ctx->fmm_lvl_off[depth + 1] > ctx->fmm_lvl_off[depth]) ++depth;
     int64_t nin = 1, fmax = 1;
-    unsigned long long hc[3] = {0, 0, 0};
+    unsigned long long hc[kFmmCounters] = {};
     bool overflow = false;
-    for (int it = 0; nin > 0; ++it) {
+    for (int it = 0, batch = std::min(depth + depth / 2, kFmmRing - 1); nin > 0 && !overflow; batch = 4) {
         if (it > 2 * (levels_for(3) + 1) + 1) return internal_fail("FMM traversal deeper than the tree allows");
-        TC_HIP(ctx, launch_fill_u32(reinterpret_cast<uint32_t*>(ctr), 2, s));
-        TC_HIP(ctx, launch_fmm_dtt(dc, theta, fa, nin, fb, f.capf, m2l, f.capm, p2p, f.capp, ctr,
-                                   reinterpret_cast<uint32_t*>(B + f.off_bt),
-                                   reinterpret_cast<unsigned long long*>(B + f.off_base), s));
+        int64_t bound = nin;
+        for (int j = 0; j < batch; ++j) {
+            unsigned long long* size = ctr + kFmmSizes;
+            TC_HIP(ctx, launch_fmm_dtt(dc, ctx->at<uint32_t>(l.off_lvl_idx_b), theta, (it + j) % 2 ? fb : fa, bound,
+                                       size + (it + j) % kFmmRing, size + (it + j + 1) % kFmmRing,
+                                       (it + j) % 2 ? fa : fb, f.capf, m2l, f.capm, p2p, f.capp, ctr,
+                                       reinterpret_cast<uint32_t*>(B + f.off_bt),
+                                       reinterpret_cast<unsigned long long*>(B + f.off_base), s));
+            bound = std::min(bound * 64, f.capf);
+        }
         TC_HIP(ctx, hipMemcpyAsync(hc, ctr, sizeof(hc), hipMemcpyDeviceToHost, s));
         TC_HIP(ctx, hipStreamSynchronize(s));
-        nin = (int64_t)hc[0];
-        if (nin > fmax) fmax = nin;
-        if (nin > f.capf) {
-            overflow = true;
-            break;
+        for (int j = 0; j < batch && nin > 0 && !overflow; ++j) {
+            nin = (int64_t)hc[kFmmSizes + (it + j + 1) % kFmmRing];
+            fmax = std::max(fmax, nin);
+            overflow = nin > f.capf;
         }
-        uint64_t* t = fa;
-        fa = fb;
-        fb = t;
+        it += batch;
     }
     sizes[0] = fmax;
     sizes[1] = (int64_t)hc[1];

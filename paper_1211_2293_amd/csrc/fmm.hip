@@ -154,223 +154,242 @@ __global__ void __launch_bounds__(256) k_fmm_radii(const uint32_t* __restrict__ 
 
 // One level of the traversal, on level-order cell indices: every input
 // pair becomes an M2L pair, a P2P pair, or pairs of the next level.  Three
-// launches per level keep the output order fixed: each block counts the
-// outputs of its contiguous chunk of the input, one block turns the counts
-// into every block's first slots (and advances the running totals), and
-// each block writes its outputs in thread order.  A slot at or beyond a
-// capacity is counted but not written.  M2L and P2P pairs are stored as
-// (source << 32) | target with pre-order indices, ready for the sort by
-// target; pairs of the next level as (A << 32) | B in level order.
+// launches per level keep the output order fixed: each wave counts the
+// outputs of its contiguous chunk of the input and leaves every pair's kind in
+// the pair's two spare bits, one block turns the counts into every wave's first
+// slots (and advances the running totals), and each wave writes its outputs in
+// lane order.  A slot at or beyond a capacity is counted but not written.  M2L
+// and P2P pairs are stored as (source << 32) | target with pre-order indices,
+// ready for the sort by target; pairs of the next level as (A << 32) | B in
+// level order (indices below 2^31).  The levels' sizes stay on the device, so
+// that the host waits once for a batch of levels; a level larger than its
+// buffer counts as empty.
+//
+// Bound by the scattered reads of the cells in the count and by the pairs'
+// traffic in the write.  Classifying again in the write, with up to eight
+// 8-byte stores per lane that each touched another line, and a host wait per
+// level took 243 + 192 + 513 us of kernels for the 17 levels of 1,048,576 bodies
+// (theta 0.5, 27.2M M2L and 5.1M P2P pairs) and 0.9 ms of gaps; now 278 + 112 +
+// 282 and one or two waits.
+// kind 1: M2L, 2: P2P, 3: children x children, 4: children x B, 5: A x children;
+// next: pairs of the next level.  Without branches, so that the loads of
+// several pairs overlap.
 struct DttOut {
-    int kind;          // 0: nothing, 1: M2L, 2: P2P, 3: children x children, 4: children x B, 5: A x children
-    uint32_t A, B;
-    int32_t child, nch;
+    int kind;
+    uint32_t next;
 };
 
-__device__ __forceinline__ DttOut dtt_classify(const DttCell* __restrict__ dc, double theta, uint64_t pr) {
+__device__ __forceinline__ DttOut dtt_classify(const DttCell& ca, const DttCell& cb, bool self, double theta) {
+    const bool la = ca.nch_leaf < 0, lb = cb.nch_leaf < 0;
+    const double dx = ca.z[0] - cb.com[0], dy = ca.z[1] - cb.com[1], dz = ca.z[2] - cb.com[2];
+    const double r = (ca.rhoA + cb.rhoB) / theta;
+    const bool acc = theta != 0.0 && (dx * dx + dy * dy) + dz * dz > r * r;
+    const bool split_a = !la && (lb || ca.level <= cb.level);
+    const uint32_t na = (uint32_t)ca.nch_leaf & 0x7fffffffu, nb = (uint32_t)cb.nch_leaf & 0x7fffffffu;
     DttOut o;
-    o.A = (uint32_t)(pr >> 32);
-    o.B = (uint32_t)pr;
-    o.child = 0;
-    o.nch = 0;
-    const DttCell ca = dc[o.A];
-    const bool la = ca.nch_leaf < 0;
-    if (o.A == o.B) {
-        o.kind = la ? 2 : 3;
-        o.child = ca.child;
-        o.nch = ca.nch_leaf & 0x7fffffff;
-        return o;
-    }
-    const DttCell cb = dc[o.B];
-    bool acc = false;
-    if (theta != 0.0) {
-        double d[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) d[a] = ca.z[a] - cb.com[a];
-        const double d2 = (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2];
-        const double r = (ca.rhoA + cb.rhoB) / theta;
-        acc = d2 > r * r;
-    }
-    const bool lb = cb.nch_leaf < 0;
-    if (acc) {
-        o.kind = 1;
-    } else if (la && lb) {
-        o.kind = 2;
-    } else if (!la && (lb || ca.level <= cb.level)) {
-        o.kind = 4;
-        o.child = ca.child;
-        o.nch = ca.nch_leaf & 0x7fffffff;
-    } else {
-        o.kind = 5;
-        o.child = cb.child;
-        o.nch = cb.nch_leaf & 0x7fffffff;
-    }
+    o.kind = self ? (la ? 2 : 3) : acc ? 1 : la && lb ? 2 : split_a ? 4 : 5;
+    o.next = o.kind < 3 ? 0u : o.kind == 3 ? na * na : o.kind == 4 ? na : nb;
     return o;
-}
-
-__device__ __forceinline__ uint32_t dtt_next(const DttOut& o) {
-    return o.kind == 3 ? (uint32_t)(o.nch * o.nch) : (o.kind >= 4 ? (uint32_t)o.nch : 0u);
 }
 
 constexpr int kDttBlock = 256;
 constexpr int kDttWaves = kDttBlock / kWave;
+constexpr int kScanWaves = kFmmMaxWaves / 1024;
+static_assert(kDttWaves == 4, "the scan takes a block's counts as one uint4");
+constexpr uint64_t kKindA = 1ull << 63, kKindB = 1ull << 31;   // none: M2L; B: P2P; A: split A (or a cell's own pair); both: split B
 
-// The same contiguous chunk of the input for a block in both sweeps.
-__device__ __forceinline__ void dtt_chunk(int64_t nin, int64_t& begin, int64_t& end) {
-    const int64_t chunk = ((nin + gridDim.x - 1) / gridDim.x + kDttBlock - 1) / kDttBlock * kDttBlock;
-    begin = (int64_t)blockIdx.x * chunk;
+// The chunk of the input of one of nw waves, the same in both sweeps.
+__device__ __forceinline__ void dtt_chunk(int64_t nin, int64_t w, int64_t nw, int64_t& begin, int64_t& end) {
+    const int64_t chunk = ((nin + nw - 1) / nw + kWave - 1) / kWave * kWave;
+    begin = min(nin, w * chunk);
     end = min(nin, begin + chunk);
-    if (end < begin) end = begin;
 }
 
-// Exclusive prefix of (a, b, c) over the block's threads in thread order;
-// returns the block totals in tot.  All threads must call it.
-__device__ __forceinline__ void block_scan3(uint32_t a, uint32_t b, uint32_t c, uint32_t* ex, uint32_t* tot,
-                                            uint32_t (*sw)[3]) {
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    uint32_t v[3] = {a, b, c};
+__device__ __forceinline__ int64_t dtt_size(const unsigned long long* size, int64_t capf) {
+    const int64_t n = (int64_t)*size;
+    return n > capf ? 0 : n;
+}
+
+__global__ void k_fmm_dtt_root(unsigned long long* __restrict__ ctr, uint64_t* __restrict__ fin) {
+    if (threadIdx.x < kFmmCounters) ctr[threadIdx.x] = threadIdx.x == kFmmSizes ? 1ull : 0ull;
+    if (threadIdx.x == 0) fin[0] = 0ull;        // the pair (root, root)
+}
+
+// Sweep 1: bt[k * waves + wave] = the wave's M2L (k = 0), P2P (1) and
+// next-level (2) output counts; the kinds go into the pairs.
+__global__ void __launch_bounds__(kDttBlock) k_fmm_dtt_count(const DttCell* __restrict__ dc, double theta,
+                                                             uint64_t* __restrict__ fin,
+                                                             const unsigned long long* __restrict__ size, int64_t capf,
+                                                             uint32_t* __restrict__ bt) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t nw = (int64_t)gridDim.x * kDttWaves, w = (int64_t)blockIdx.x * kDttWaves + (threadIdx.x / kWave);
+    int64_t begin, end;
+    dtt_chunk(dtt_size(size, capf), w, nw, begin, end);
+    uint32_t cm = 0, cp = 0, cn = 0;
+    constexpr int kAhead = 2;
+    for (int64_t i0 = begin + lane; i0 < end; i0 += kAhead * kWave) {
+        uint64_t pr[kAhead];
+        DttCell ca[kAhead], cb[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) pr[u] = fin[min(i0 + u * kWave, end - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            ca[u] = dc[(pr[u] >> 32) & 0x7fffffffu];
+            cb[u] = dc[pr[u] & 0x7fffffffu];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const bool valid = i0 + u * kWave < end;
+            const DttOut o = dtt_classify(ca[u], cb[u], pr[u] >> 32 == (uint32_t)pr[u], theta);
+            cm += valid && o.kind == 1;
+            cp += valid && o.kind == 2;
+            cn += valid ? o.next : 0u;
+            if (valid && o.kind != 1)
+                fin[i0 + u * kWave] = pr[u] | (o.kind == 2 ? kKindB : o.kind == 5 ? kKindA | kKindB : kKindA);
+        }
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        cm += __shfl_xor(cm, o, kWave);
+        cp += __shfl_xor(cp, o, kWave);
+        cn += __shfl_xor(cn, o, kWave);
+    }
+    if (lane < 3) bt[lane * nw + w] = lane == 0 ? cm : lane == 1 ? cp : cn;
+}
+
+// One block: every block's first output slots (M2L and P2P after the running
+// totals ctr[1], ctr[2]; the next level from 0), then the next level's size
+// and ctr[1], ctr[2] advanced.  nw is four per block, at most kScanWaves per
+// thread.
+__global__ void __launch_bounds__(1024) k_fmm_dtt_scan(const uint32_t* __restrict__ bt, int nw,
+                                                       unsigned long long* __restrict__ ctr,
+                                                       unsigned long long* __restrict__ next,
+                                                       unsigned long long* __restrict__ base) {
+    __shared__ unsigned long long s[3][1024 / kWave];
+    const int t = threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
+    uint4 c[3][kScanWaves / 4];
+    unsigned long long mine[3], incl[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
+        mine[k] = 0;
+#pragma unroll
+        for (int j = 0; j < kScanWaves / 4; ++j) {
+            const int w = kScanWaves * t + 4 * j;
+            c[k][j] = w < nw ? *reinterpret_cast<const uint4*>(bt + (int64_t)k * nw + w) : make_uint4(0, 0, 0, 0);
+            mine[k] += (unsigned long long)c[k][j].x + c[k][j].y + c[k][j].z + c[k][j].w;
+        }
+        incl[k] = mine[k];
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t y = __shfl_up(v[k], o, kWave);
-            if (lane >= o) v[k] += y;
+            const unsigned long long y = __shfl_up(incl[k], o, kWave);
+            if (lane >= o) incl[k] += y;
         }
+        if (lane == kWave - 1) s[k][wv] = incl[k];
     }
-    if (lane == kWave - 1) {
-        sw[wv][0] = v[0];
-        sw[wv][1] = v[1];
-        sw[wv][2] = v[2];
-    }
+    const unsigned long long m0 = ctr[1], p0 = ctr[2];
     __syncthreads();
-    uint32_t before[3] = {0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        tot[k] = 0;
-        for (int w = 0; w < kDttWaves; ++w) {
-            if (w < wv) before[k] += sw[w][k];
-            tot[k] += sw[w][k];
+        unsigned long long run = k == 0 ? m0 : k == 1 ? p0 : 0ull;
+        for (int w = 0; w < wv; ++w) run += s[k][w];
+        run += incl[k] - mine[k];
+#pragma unroll
+        for (int j = 0; j < kScanWaves / 4; ++j) {
+            const int w = kScanWaves * t + 4 * j;
+            if (w < nw) base[(int64_t)k * (nw / 4) + w / 4] = run;
+            run += (unsigned long long)c[k][j].x + c[k][j].y + c[k][j].z + c[k][j].w;
         }
-    }
-    ex[0] = before[0] + v[0] - a;
-    ex[1] = before[1] + v[1] - b;
-    ex[2] = before[2] + v[2] - c;
-    __syncthreads();
-}
-
-// Sweep 1: bt[k * gridDim.x + block] = the block's M2L (k = 0), P2P (1)
-// and next-level (2) output counts.
-__global__ void __launch_bounds__(kDttBlock) k_fmm_dtt_count(const DttCell* __restrict__ dc, double theta,
-                                                             const uint64_t* __restrict__ fin, int64_t nin,
-                                                             uint32_t* __restrict__ bt) {
-    __shared__ uint32_t sw[kDttWaves][3];
-    int64_t begin, end;
-    dtt_chunk(nin, begin, end);
-    uint32_t cm = 0, cp = 0, cn = 0;
-    for (int64_t i = begin + threadIdx.x; i < end; i += kDttBlock) {
-        const DttOut o = dtt_classify(dc, theta, fin[i]);
-        cm += o.kind == 1;
-        cp += o.kind == 2;
-        cn += dtt_next(o);
-    }
-    uint32_t ex[3], tot[3];
-    block_scan3(cm, cp, cn, ex, tot, sw);
-    if (threadIdx.x == 0) {
-        bt[blockIdx.x] = tot[0];
-        bt[gridDim.x + blockIdx.x] = tot[1];
-        bt[2 * gridDim.x + blockIdx.x] = tot[2];
+        if (t == 1023) (k == 0 ? ctr[1] : k == 1 ? ctr[2] : *next) = run;
     }
 }
 
-// One block: every block's first output slots (M2L and P2P after the
-// running totals ctr[1], ctr[2]; the next level from 0), then ctr[0] =
-// next-level size and ctr[1], ctr[2] advanced.
-__global__ void __launch_bounds__(1024) k_fmm_dtt_scan(const uint32_t* __restrict__ bt, int nb,
-                                                       unsigned long long* __restrict__ ctr,
-                                                       unsigned long long* __restrict__ base) {
-    __shared__ unsigned long long s[1024];
-    const int t = threadIdx.x;
-    const int per = (nb + 1023) / 1024;    // at most kFmmMaxBlocks / 1024 blocks per thread
-    for (int k = 0; k < 3; ++k) {
-        unsigned long long mine = 0;
-        for (int j = 0; j < per; ++j) {
-            const int b = t * per + j;
-            if (b < nb) mine += bt[k * nb + b];
-        }
-        s[t] = mine;
-        __syncthreads();
-        for (int o = 1; o < 1024; o <<= 1) {     // inclusive Hillis-Steele scan
-            const unsigned long long y = t >= o ? s[t - o] : 0ull;
-            __syncthreads();
-            s[t] += y;
-            __syncthreads();
-        }
-        const unsigned long long start = (k == 2 ? 0ull : ctr[k + 1]) + s[t] - mine;
-        unsigned long long run = start;
-        for (int j = 0; j < per; ++j) {
-            const int b = t * per + j;
-            if (b < nb) {
-                base[k * nb + b] = run;
-                run += bt[k * nb + b];
-            }
-        }
-        const unsigned long long total = s[1023];
-        __syncthreads();
-        if (t == 0) {
-            if (k == 2) ctr[0] = total;
-            else ctr[k + 1] += total;
-        }
-        __syncthreads();
-    }
-}
-
-// Sweep 2: the same classification, written in thread order from the
-// block's first slots.
-__global__ void __launch_bounds__(kDttBlock) k_fmm_dtt_write(const DttCell* __restrict__ dc, double theta,
-                                                             const uint64_t* __restrict__ fin, int64_t nin,
+// Sweep 2: the outputs in lane order from the wave's first slots, those of its
+// block and the counts of the block's waves before it.  The pairs of
+// the next level are written 64 at a time, side by side: a bit per splitting
+// pair's first place tells every lane which pair its place belongs to.
+__global__ void __launch_bounds__(kDttBlock) k_fmm_dtt_write(const DttCell* __restrict__ dc,
+                                                             const uint32_t* __restrict__ bfs2pre,
+                                                             const uint64_t* __restrict__ fin,
+                                                             const unsigned long long* __restrict__ size,
+                                                             const uint32_t* __restrict__ bt,
                                                              const unsigned long long* __restrict__ base,
                                                              uint64_t* __restrict__ fout, int64_t capf,
                                                              uint64_t* __restrict__ m2l, int64_t capm,
                                                              uint64_t* __restrict__ p2p, int64_t capp) {
-    __shared__ uint32_t sw[kDttWaves][3];
+    __shared__ int4 s_split[kDttWaves][kWave];       // first place, A, B, pairs per child of A (bits 24..) and its reciprocal
+    __shared__ uint64_t s_start[kDttWaves][kWave];   // at most 64 places per pair
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const uint64_t below = (1ull << lane) - 1ull, upto = ~0ull >> (kWave - 1 - lane);
+    const int64_t nw = (int64_t)gridDim.x * kDttWaves, w = (int64_t)blockIdx.x * kDttWaves + wv;
     int64_t begin, end;
-    dtt_chunk(nin, begin, end);
-    const int64_t iters = (end - begin + kDttBlock - 1) / kDttBlock;
-    uint64_t om = base[blockIdx.x], op = base[gridDim.x + blockIdx.x], on = base[2 * gridDim.x + blockIdx.x];
-    for (int64_t it = 0; it < iters; ++it) {
-        const int64_t i = begin + it * kDttBlock + threadIdx.x;
-        DttOut o;
-        o.kind = 0;
-        o.nch = 0;
-        if (i < end) o = dtt_classify(dc, theta, fin[i]);
-        uint32_t ex[3], tot[3];
-        block_scan3(o.kind == 1, o.kind == 2, dtt_next(o), ex, tot, sw);
-        if (o.kind == 1 || o.kind == 2) {
-            const uint64_t key = ((uint64_t)(uint32_t)dc[o.B].pre << 32) | (uint32_t)dc[o.A].pre;
-            if (o.kind == 1) {
-                const uint64_t s = om + ex[0];
-                if ((int64_t)s < capm) m2l[s] = key;
-            } else {
-                const uint64_t s = op + ex[1];
-                if ((int64_t)s < capp) p2p[s] = key;
-            }
-        } else if (o.kind == 3) {
-            uint64_t s = on + ex[2];
-            for (int x = 0; x < o.nch; ++x)
-                for (int y = 0; y < o.nch; ++y, ++s)
-                    if ((int64_t)s < capf) fout[s] = pair_key((uint32_t)(o.child + x), (uint32_t)(o.child + y));
-        } else if (o.kind == 4) {
-            const uint64_t s = on + ex[2];
-            for (int j = 0; j < o.nch; ++j)
-                if ((int64_t)(s + j) < capf) fout[s + j] = pair_key((uint32_t)(o.child + j), o.B);
-        } else if (o.kind == 5) {
-            const uint64_t s = on + ex[2];
-            for (int j = 0; j < o.nch; ++j)
-                if ((int64_t)(s + j) < capf) fout[s + j] = pair_key(o.A, (uint32_t)(o.child + j));
+    dtt_chunk(dtt_size(size, capf), w, nw, begin, end);
+    if (begin >= end) return;
+    const int64_t nb = gridDim.x, w0 = (int64_t)blockIdx.x * kDttWaves;
+    int64_t om = (int64_t)base[blockIdx.x], op = (int64_t)base[nb + blockIdx.x], on = (int64_t)base[2 * nb + blockIdx.x];
+    for (int j = 0; j < kDttWaves - 1; ++j)
+        if (j < wv) {
+            om += bt[w0 + j];
+            op += bt[nw + w0 + j];
+            on += bt[2 * nw + w0 + j];
         }
-        om += tot[0];
-        op += tot[1];
-        on += tot[2];
+    uint64_t ahead = fin[min(begin + lane, end - 1)];
+    for (int64_t i0 = begin; i0 < end; i0 += kWave) {
+        const bool valid = i0 + lane < end;
+        const uint64_t pr = ahead;
+        ahead = fin[min(i0 + kWave + lane, end - 1)];
+        const bool ka = (pr & kKindA) != 0, kb = (pr & kKindB) != 0;
+        const uint32_t A = (uint32_t)(pr >> 32) & 0x7fffffffu, B = (uint32_t)pr & 0x7fffffffu;
+        const bool split = valid && ka;
+        const uint64_t M = __ballot(valid && !ka && !kb), P = __ballot(valid && !ka && kb), C = __ballot(split);
+        if (valid && !ka) {
+            const uint64_t key = ((uint64_t)bfs2pre[B] << 32) | bfs2pre[A];
+            if (kb) {
+                const int64_t at = op + __popcll(P & below);
+                if (at < capp) p2p[at] = key;
+            } else {
+                const int64_t at = om + __popcll(M & below);
+                if (at < capm) m2l[at] = key;
+            }
+        }
+        om += __popcll(M);
+        op += __popcll(P);
+        if (!C) continue;
+        int child = 0, nch = 0, per = 1;             // per: pairs per child of A
+        if (split) {
+            const DttCell& c = dc[kb ? B : A];
+            child = c.child;
+            nch = c.nch_leaf & 0x7fffffff;
+            per = A == B ? nch : kb ? kWave : 1;
+        }
+        const int count = A == B ? nch * nch : nch;
+        int incl = count;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int y = __shfl_up(incl, o, kWave);
+            if (lane >= o) incl += y;
+        }
+        const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        s_start[wv][lane] = 0ull;
+        wave_lds_sync();
+        if (split) {
+            const int first = incl - count;
+            s_split[wv][__popcll(C & below)] = make_int4(first, kb ? (int)A : child, kb || A == B ? child : (int)B,
+                                                         per << 24 | (65536 + per - 1) / per);
+            atomicOr(reinterpret_cast<uint32_t*>(s_start[wv]) + first / 32, 1u << (first % 32));
+        }
+        wave_lds_sync();
+        int before = -1;
+        for (int t0 = 0; t0 < total; t0 += kWave) {
+            const uint64_t st = s_start[wv][t0 / kWave];
+            const int4 q = s_split[wv][before + __popcll(st & upto)];
+            before += __popcll(st);
+            const int j = t0 + lane - q.x;
+            const int x = (int)((uint32_t)(j * (q.w & 0xffffff)) >> 16), y = j - x * (q.w >> 24);
+            const int64_t at = on + t0 + lane;
+            if (t0 + lane < total && at < capf) fout[at] = pair_key((uint32_t)(q.y + x), (uint32_t)(q.z + y));
+        }
+        on += total;
+        wave_lds_sync();
     }
 }
 
@@ -478,7 +497,10 @@ __device__ __forceinline__ void l2p(const double* lam, const double* dl, double*
 }
 
 // M2L: one wave per target cell; lane k takes the target's sorted sources
-// k, k + 64, ...; the lanes' sums are added by a fixed butterfly.
+// k, k + 64, ...; the lanes' sums are added by a fixed butterfly, 22 exchanges
+// for the 20 coefficients.  Bound by the gathered moments and the FP64 units:
+// 27.2M pairs in 261 us; with a butterfly of six exchanges per coefficient,
+// divisions and a root it was 374, half of it the exchanges.
 // Overwrites lam.
 __global__ void __launch_bounds__(256) k_fmm_m2l(const Moments* __restrict__ mom, const FmmGeo* __restrict__ geo,
                                                  const DevParams* __restrict__ prm, int64_t cmax,
@@ -493,25 +515,33 @@ __global__ void __launch_bounds__(256) k_fmm_m2l(const Moments* __restrict__ mom
 #pragma unroll
         for (int k = 0; k < kNL; ++k) lam[k] = 0.0;
         const FmmGeo g = geo[t];
-        for (uint32_t q = off[t] + lane; q < off[t + 1]; q += kWave) {
-            const uint32_t b = (uint32_t)(keys[q] >> 32);
-            const Moments& mb = mom[b];
+        const uint32_t q0 = off[t], q1 = off[t + 1];
+        uint64_t ahead = q0 + lane < q1 ? keys[q0 + lane] : 0ull;
+        for (uint32_t q = q0 + lane; q < q1; q += kWave) {
+            const Moments& mb = mom[(uint32_t)(ahead >> 32)];
+            ahead = keys[min(q + kWave, q1 - 1)];
             m2l_add(mb.M, mb.Q, g.z[0] - mb.com[0], g.z[1] - mb.com[1], g.z[2] - mb.com[2], eps2, lam);
         }
+        // the sums over the lanes, xor 32 first: two coefficients share a step
+        // as long as there are two, half the lanes keeping either
+        auto fold = [&](double x, double y, int o) {
+            const bool hi = (lane & o) != 0;
+            return (hi ? y : x) + __shfl_xor(hi ? x : y, o, kWave);
+        };
 #pragma unroll
-        for (int k = 0; k < kNL; ++k) {
-            double v = lam[k];
+        for (int k = 0; k < 10; ++k) lam[k] = fold(lam[k], lam[k + 10], 32);
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-            lam[k] = v;
-        }
-        if (lane < kNL) {
-            double v = lam[0];
-#pragma unroll
-            for (int k = 1; k < kNL; ++k)
-                if (lane == k) v = lam[k];
-            lam_out[t * kNL + lane] = v;
-        }
+        for (int k = 0; k < 5; ++k) lam[k] = fold(lam[k], lam[k + 5], 16);
+        lam[0] = fold(lam[0], lam[3], 8);
+        lam[1] = fold(lam[1], lam[4], 8);
+        lam[2] += __shfl_xor(lam[2], 8, kWave);
+        lam[0] = fold(lam[0], lam[1], 4);
+        lam[2] += __shfl_xor(lam[2], 4, kWave);
+        lam[0] = fold(lam[0], lam[2], 2);
+        lam[0] += __shfl_xor(lam[0], 1, kWave);
+        const bool third = (lane & 2) != 0;
+        const int k = (lane & 32 ? 10 : 0) + (lane & 16 ? 5 : 0) + (third ? 2 : (lane & 8 ? 3 : 0) + (lane & 4 ? 1 : 0));
+        if (!(lane & 1) && !(third && (lane & 12))) lam_out[t * kNL + k] = lam[0];
     }
 }
 
@@ -830,6 +860,7 @@ __global__ void __launch_bounds__(256) k_fmm_leaf_finish(const Cell* __restrict_
             const int64_t i = (int64_t)ca.begin + t;
             const Body me = bodies[i];
             double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
             for (uint32_t j = 0; j < nchunks; ++j) {
                 const double* q = part + 4 * ((int64_t)soff[A] + (int64_t)j * ca.count + t);
                 v[0] += q[0];
@@ -888,15 +919,21 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_fmm_dtt(const DttCell* dc, double theta, const uint64_t* fin, int64_t nin, uint64_t* fout,
-                          int64_t capf, uint64_t* m2l, int64_t capm, uint64_t* p2p, int64_t capp,
-                          unsigned long long* ctr, uint32_t* bt, unsigned long long* base, hipStream_t s) {
-    if (nin <= 0) return hipSuccess;
-    const unsigned nb = grid_for(nin, kFmmMaxBlocks);
-    hipLaunchKernelGGL(k_fmm_dtt_count, dim3(nb), dim3(kDttBlock), 0, s, dc, theta, fin, nin, bt);
-    hipLaunchKernelGGL(k_fmm_dtt_scan, dim3(1), dim3(1024), 0, s, (const uint32_t*)bt, (int)nb, ctr, base);
-    hipLaunchKernelGGL(k_fmm_dtt_write, dim3(nb), dim3(kDttBlock), 0, s, dc, theta, fin, nin,
-                       (const unsigned long long*)base, fout, capf, m2l, capm, p2p, capp);
+hipError_t launch_fmm_dtt_root(unsigned long long* ctr, uint64_t* fin, hipStream_t s) {
+    hipLaunchKernelGGL(k_fmm_dtt_root, dim3(1), dim3(64), 0, s, ctr, fin);
+    return hipGetLastError();
+}
+
+hipError_t launch_fmm_dtt(const DttCell* dc, const uint32_t* bfs2pre, double theta, uint64_t* fin, int64_t bound,
+                          const unsigned long long* size, unsigned long long* next, uint64_t* fout, int64_t capf,
+                          uint64_t* m2l, int64_t capm, uint64_t* p2p, int64_t capp, unsigned long long* ctr,
+                          uint32_t* bt, unsigned long long* base, hipStream_t s) {
+    const unsigned nb = grid_for(bound, kFmmMaxWaves / kDttWaves);
+    const int nw = (int)nb * kDttWaves;
+    hipLaunchKernelGGL(k_fmm_dtt_count, dim3(nb), dim3(kDttBlock), 0, s, dc, theta, fin, size, capf, bt);
+    hipLaunchKernelGGL(k_fmm_dtt_scan, dim3(1), dim3(1024), 0, s, (const uint32_t*)bt, nw, ctr, next, base);
+    hipLaunchKernelGGL(k_fmm_dtt_write, dim3(nb), dim3(kDttBlock), 0, s, dc, bfs2pre, (const uint64_t*)fin, size,
+                       (const uint32_t*)bt, (const unsigned long long*)base, fout, capf, m2l, capm, p2p, capp);
     return hipGetLastError();
 }
 

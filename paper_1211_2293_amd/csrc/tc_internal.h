@@ -315,7 +315,10 @@ struct __align__(16) FmmGeo {
 // What the traversal reads of a cell, in level order: centre, centre of
 // mass, the radii bounding its bodies about the two (rhoA, rhoB), its first child (level order; children are
 // contiguous there), child count with bit 31 set for a leaf, and level.
-constexpr int kFmmMaxBlocks = 4096;   // blocks per traversal launch
+constexpr int kFmmMaxWaves = 8192;      // waves per traversal launch: what the chip holds at once
+// Counters of the traversal: [1], [2] M2L and P2P pairs so far; from kFmmSizes
+// on a ring of level sizes.
+constexpr int kFmmCounters = 32, kFmmSizes = 4, kFmmRing = kFmmCounters - kFmmSizes;
 struct __align__(16) DttCell {
     double z[3];
     double com[3];
@@ -327,9 +330,11 @@ hipError_t launch_fmm_geo(const Cell* cells, const Moments* mom, const Body* bod
                           hipStream_t s);
 hipError_t launch_fmm_radii(const uint32_t* lvl_off, int level, int64_t count, DttCell* dc, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, hipStream_t s);
-hipError_t launch_fmm_dtt(const DttCell* dc, double theta, const uint64_t* fin, int64_t nin, uint64_t* fout,
-                          int64_t capf, uint64_t* m2l, int64_t capm, uint64_t* p2p, int64_t capp,
-                          unsigned long long* ctr, uint32_t* bt, unsigned long long* base, hipStream_t s);
+hipError_t launch_fmm_dtt_root(unsigned long long* ctr, uint64_t* fin, hipStream_t s);
+hipError_t launch_fmm_dtt(const DttCell* dc, const uint32_t* bfs2pre, double theta, uint64_t* fin, int64_t bound,
+                          const unsigned long long* size, unsigned long long* next, uint64_t* fout, int64_t capf,
+                          uint64_t* m2l, int64_t capm, uint64_t* p2p, int64_t capp, unsigned long long* ctr,
+                          uint32_t* bt, unsigned long long* base, hipStream_t s);
 hipError_t launch_fmm_offsets(const uint64_t* keys, int64_t n, int64_t C, uint32_t* off, hipStream_t s);
 hipError_t launch_fmm_m2l(const Moments* mom, const FmmGeo* geo, const DevParams* prm, int64_t cmax,
                           const uint64_t* keys, const uint32_t* off, double eps2, double* lam,
