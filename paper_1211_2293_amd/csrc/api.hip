@@ -462,8 +462,10 @@ int do_forces_learned(tc_ctx* ctx, double G, double eps, double tau) {
     return TC_OK;
 }
 
-int do_forces(tc_ctx* ctx, double G, double eps) {
+// acc, pot: where the caller also wants the results, or null.
+int do_forces(tc_ctx* ctx, double G, double eps, float* acc = nullptr, float* pot = nullptr) {
     const Layout& l = ctx->lay;
+    const ForceOut out{ctx->at<float>(l.off_acc), ctx->at<float>(l.off_pot), acc, pot};
     if (!ctx->radii_plain) {   // a learned walk left its own radii in the walk records
         int rc = do_walk(ctx, ctx->theta, ctx->stream);
         if (rc != TC_OK) return rc;
@@ -488,8 +490,7 @@ int do_forces(tc_ctx* ctx, double G, double eps) {
                                             ctx->at<uint32_t>(l.off_idx_a), ctx->at<int32_t>(l.off_gbeg),
                                             ctx->at<int32_t>(l.off_gcnt), l.gmax, ctx->n, ctx->dim, ctx->leaf_cap,
                                             (float)G, (float)(eps * eps), ctx->prm(), ctx->at<float4>(l.off_split),
-                                            ctx->at<float>(l.off_acc), ctx->at<float>(l.off_pot),
-                                            ctx->at<int64_t>(l.off_m2p), ctx->at<int64_t>(l.off_p2p),
+                                            out, ctx->at<int64_t>(l.off_m2p), ctx->at<int64_t>(l.off_p2p),
                                             ctx->at<int64_t>(l.off_tests), ctx->plain_acc, ctx->stream));
     } else {
         TC_HIP(ctx, launch_walk_force(ctx->at<WalkCell>(l.off_walk), walkq, ctx->at<Body>(l.off_bodies),
@@ -498,8 +499,7 @@ int do_forces(tc_ctx* ctx, double G, double eps) {
                                       ctx->at<int32_t>(l.off_gcnt), l.gmax, ctx->at<uint32_t>(l.off_gorder),
                                       ctx->at<uint32_t>(l.off_queue), ctx->at<uint32_t>(l.off_bcost), ctx->n,
                                       ctx->dim, ctx->leaf_cap,
-                                      (float)G, (float)(eps * eps), ctx->prm(), ctx->at<float>(l.off_acc),
-                                      ctx->at<float>(l.off_pot), ctx->at<int64_t>(l.off_m2p),
+                                      (float)G, (float)(eps * eps), ctx->prm(), out, ctx->at<int64_t>(l.off_m2p),
                                       ctx->at<int64_t>(l.off_p2p), ctx->at<int64_t>(l.off_tests), ctx->plain_acc,
                                       ctx->split != 0, ctx->stream));
     }
@@ -892,16 +892,7 @@ int tc_forces(tc_ctx* ctx, double G, double eps, void* acc, void* pot) {
     if (!(eps > 0.0) || !isfinite(eps) || !isfinite(G)) return TC_EINVAL;
     if ((acc && !aligned(acc, 4)) || (pot && !aligned(pot, 4))) return TC_EINVAL;
     if (ctx->state < kWalked || !ctx->theta_set) return TC_ESTATE;
-    int rc = do_forces(ctx, G, eps);
-    if (rc != TC_OK) return rc;
-    const Layout& l = ctx->lay;
-    if (acc)
-        TC_HIP(ctx, hipMemcpyAsync(acc, ctx->at<float>(l.off_acc), 4 * (size_t)ctx->n * ctx->dim,
-                                   hipMemcpyDeviceToDevice, ctx->stream));
-    if (pot)
-        TC_HIP(ctx, hipMemcpyAsync(pot, ctx->at<float>(l.off_pot), 4 * (size_t)ctx->n,
-                                   hipMemcpyDeviceToDevice, ctx->stream));
-    return TC_OK;
+    return do_forces(ctx, G, eps, (float*)acc, (float*)pot);
 }
 
 int tc_leapfrog(tc_ctx* ctx, double dt, void* pos, void* vel) {
@@ -1204,15 +1195,10 @@ int tc_forces_noalloc(tc_ctx* ctx, const void* pos, const void* mass, int64_t n,
     rc = do_build(ctx, pos, mass, n, leaf_cap, dtype, s);
     if (rc == TC_OK) rc = do_moments(ctx, s);
     if (rc == TC_OK) rc = do_walk(ctx, theta, s);
-    if (rc == TC_OK) rc = do_forces(ctx, G, eps);
+    if (rc == TC_OK) rc = do_forces(ctx, G, eps, (float*)acc, (float*)pot);
     ctx->timing = timing;
     ctx->stage_timing = stage_timing;
-    if (rc != TC_OK) return rc;
-    const Layout& l = ctx->lay;
-    if (acc)
-        TC_HIP(ctx, hipMemcpyAsync(acc, ctx->at<float>(l.off_acc), 4 * (size_t)n * dim, hipMemcpyDeviceToDevice, s));
-    if (pot) TC_HIP(ctx, hipMemcpyAsync(pot, ctx->at<float>(l.off_pot), 4 * (size_t)n, hipMemcpyDeviceToDevice, s));
-    return TC_OK;
+    return rc;
 }
 
 int tc_set_closure(tc_ctx* ctx, double theta_l, double theta_p, double tau) {

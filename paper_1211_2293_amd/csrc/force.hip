@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
                                                     uint32_t* __restrict__ bcost,
                                                     int lpl_log2, float G, float eps2,
                                                     const DevParams* __restrict__ prm,
-                                                    float* __restrict__ acc, float* __restrict__ pot,
+                                                    ForceOut out,
                                                     int64_t* __restrict__ m2p_out,
                                                     int64_t* __restrict__ p2p_out,
                                                     int64_t* __restrict__ tst_out) {
@@ -267,10 +267,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
                 const float sself = __builtin_amdgcn_rsqf(eps2);
                 const float ph = (float)(a.sp + (double)(mself * sself));
                 const int64_t o = perm[i];
-                acc[o * D + 0] = G * (float)a.sx;
-                acc[o * D + 1] = G * (float)a.sy;
-                if (D == 3) acc[o * D + 2] = G * (float)a.sz;
-                pot[o] = G * ph;
+                out.put_acc(o * D + 0, G * (float)a.sx);
+                out.put_acc(o * D + 1, G * (float)a.sy);
+                if (D == 3) out.put_acc(o * D + 2, G * (float)a.sz);
+                out.put_pot(o, G * ph);
                 // the list length, for the next evaluation's schedule
                 const int64_t lc = nm2p + np2p;
                 bcost[o] = lc > 0xffffffffll ? 0xffffffffu : (uint32_t)lc;
@@ -323,7 +323,7 @@ __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu
     const float4* __restrict__ bodies32, const uint32_t* __restrict__ perm, const int32_t* __restrict__ gbeg,
     const int32_t* __restrict__ gcnt, const uint32_t* __restrict__ order, uint32_t* queue,
     uint32_t* __restrict__ bcost, int lpl_log2, float G, float eps2, const DevParams* __restrict__ prm,
-    float* __restrict__ acc, float* __restrict__ pot, int64_t* __restrict__ m2p_out, int64_t* __restrict__ p2p_out,
+    ForceOut out, int64_t* __restrict__ m2p_out, int64_t* __restrict__ p2p_out,
     int64_t* __restrict__ tst_out) {
     using B = BlockWalk<D, QUAD, NW>;
     constexpr int R = B::R, T = B::kThreads;
@@ -541,13 +541,13 @@ __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu
                     for (int w = 0; w < NW; ++w) v += part[(w * 4 + c) * kWave + q * kBodies + lane];
                 const int64_t o = perm[i0 + own];
                 if (c < 3) {
-                    if (c < D) acc[o * D + c] = (float)((double)G * v);
+                    if (c < D) out.put_acc(o * D + c, (float)((double)G * v));
                 } else {
                     // the body met itself once as a direct entry: its -m/eps
                     // potential term is removed as in the one-wave kernel
                     const float mself = (float)bodies[i0 + own].m;
                     v += (double)(mself * __builtin_amdgcn_rsqf(eps2));
-                    pot[o] = (float)((double)G * v);
+                    out.put_pot(o, (float)((double)G * v));
                     const int64_t lc = nm2p + np2p;
                     bcost[o] = lc > 0xffffffffll ? 0xffffffffu : (uint32_t)lc;
                 }
@@ -646,7 +646,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
 template <int D>
 __global__ void __launch_bounds__(256) k_split_reduce(const float4* __restrict__ part, const Body* __restrict__ bodies,
                                                       const uint32_t* __restrict__ perm, int64_t n, float G,
-                                                      float eps2, float* __restrict__ acc, float* __restrict__ pot) {
+                                                      float eps2, ForceOut out) {
     constexpr int T = kSplitTasks<D>;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         double ax = 0.0, ay = 0.0, az = 0.0, ap = 0.0;
@@ -662,10 +662,10 @@ __global__ void __launch_bounds__(256) k_split_reduce(const float4* __restrict__
         const float mself = (float)bodies[i].m;
         ap += (double)(mself * __builtin_amdgcn_rsqf(eps2));
         const int64_t o = perm[i];
-        acc[o * D + 0] = (float)((double)G * ax);
-        acc[o * D + 1] = (float)((double)G * ay);
-        if (D == 3) acc[o * D + 2] = (float)((double)G * az);
-        pot[o] = (float)((double)G * ap);
+        out.put_acc(o * D + 0, (float)((double)G * ax));
+        out.put_acc(o * D + 1, (float)((double)G * ay));
+        if (D == 3) out.put_acc(o * D + 2, (float)((double)G * az));
+        out.put_pot(o, (float)((double)G * ap));
     }
 }
 
@@ -823,7 +823,7 @@ hipError_t launch_quad_pack(const Moments* mom, const uint32_t* pre2bfs, const D
 hipError_t launch_walk_force_split(const WalkCell* walk, const float4* walkq, const Body* bodies,
                                    const float4* bodies32, const uint32_t* perm, const int32_t* gbeg,
                                    const int32_t* gcnt, int64_t gmax, int64_t n, int dim, int leaf_cap, float G,
-                                   float eps2, const DevParams* prm, float4* part, float* acc, float* pot,
+                                   float eps2, const DevParams* prm, float4* part, const ForceOut& out,
                                    int64_t* m2p, int64_t* p2p, int64_t* tests, bool plain, hipStream_t s) {
     int lpl_log2 = 0;
     while ((1 << lpl_log2) < leaf_cap && lpl_log2 < 6) ++lpl_log2;
@@ -849,9 +849,9 @@ hipError_t launch_walk_force_split(const WalkCell* walk, const float4* walkq, co
 #undef TC_LAUNCH_SPLIT
     const unsigned rb = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
     if (dim == 3)
-        hipLaunchKernelGGL(k_split_reduce<3>, dim3(rb), dim3(256), 0, s, part, bodies, perm, n, G, eps2, acc, pot);
+        hipLaunchKernelGGL(k_split_reduce<3>, dim3(rb), dim3(256), 0, s, part, bodies, perm, n, G, eps2, out);
     else
-        hipLaunchKernelGGL(k_split_reduce<2>, dim3(rb), dim3(256), 0, s, part, bodies, perm, n, G, eps2, acc, pot);
+        hipLaunchKernelGGL(k_split_reduce<2>, dim3(rb), dim3(256), 0, s, part, bodies, perm, n, G, eps2, out);
     return hipGetLastError();
 }
 
@@ -881,7 +881,7 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
                              const int32_t* gbeg, const int32_t* gcnt, int64_t gmax, uint32_t* order,
                              uint32_t* queue, uint32_t* bcost,
                              int64_t n, int dim, int leaf_cap, float G, float eps2,
-                             const DevParams* prm, float* acc, float* pot, int64_t* m2p,
+                             const DevParams* prm, const ForceOut& out, int64_t* m2p,
                              int64_t* p2p, int64_t* tests, bool plain, bool share,
                              hipStream_t s) {
     // as many blocks as can be resident at once (the waves are persistent)
@@ -926,8 +926,8 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
         const hipError_t e_ = coop_blocks<k_walk_force_coop<DIM, PL, QU, NW, H>>(NW * kWave, gmax * H, &cb);        \
         if (e_ != hipSuccess) return e_;                                                                            \
         hipLaunchKernelGGL((k_walk_force_coop<DIM, PL, QU, NW, H>), dim3(cb), dim3(NW * kWave), 0, s, walk, walkq,  \
-                           bodies, bodies32, perm, gbeg, gcnt, places, queue, bcost, lpl_log2, G, eps2, prm, acc,   \
-                           pot, m2p, p2p, tests);                                                                   \
+                           bodies, bodies32, perm, gbeg, gcnt, places, queue, bcost, lpl_log2, G, eps2, prm, out,   \
+                           m2p, p2p, tests);                                                                        \
     } while (0)
 #define TC_LAUNCH_COOP(DIM, PL, QU)                                                                                 \
     do {                                                                                                            \
@@ -962,7 +962,7 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
     const bool short_rounds = groups_lo > 2 * waves_all && groups_lo <= 4 * waves_all;
 #define TC_LAUNCH_WF_STEP(DIM, PL, QU, ST)                                                                           \
     hipLaunchKernelGGL((k_walk_force<DIM, PL, QU, ST>), dim3(nb), dim3(256), 0, s, walk, walkq, bodies, bodies32,  \
-                       perm, gbeg, gcnt, order, queue, bcost, lpl_log2, G, eps2, prm, acc, pot, m2p, p2p, tests)
+                       perm, gbeg, gcnt, order, queue, bcost, lpl_log2, G, eps2, prm, out, m2p, p2p, tests)
 #define TC_LAUNCH_WF(DIM, PL, QU)                                                                                \
     do {                                                                                                         \
         if (short_rounds) TC_LAUNCH_WF_STEP(DIM, PL, QU, 4);                                                     \

@@ -211,11 +211,25 @@ hipError_t launch_export(const Cell* cells, const Moments* mom, int dim, int64_t
 // force.hip
 // order: room for 2 gmax uint32 (places, costs) and gmax uint16 keys; bcost:
 // n uint32 per-body list lengths, written for the next call's schedule.
+// Where the force kernels put their results: the copies that the next step and
+// the diagnostics read and, where given, the caller's arrays, which cost a store
+// beside each of these where a copy of them afterwards cost two launches (9 us).
+struct ForceOut {
+    float *acc, *pot, *user_acc, *user_pot;
+    __device__ __forceinline__ void put_acc(int64_t at, float v) const {
+        acc[at] = v;
+        if (user_acc) user_acc[at] = v;
+    }
+    __device__ __forceinline__ void put_pot(int64_t at, float v) const {
+        pot[at] = v;
+        if (user_pot) user_pot[at] = v;
+    }
+};
 hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Body* bodies, const float4* bodies32,
                              const uint32_t* perm,
                              const int32_t* gbeg, const int32_t* gcnt, int64_t gmax, uint32_t* order,
                              uint32_t* queue, uint32_t* bcost, int64_t n, int dim, int leaf_cap, float G, float eps2,
-                             const DevParams* prm, float* acc, float* pot, int64_t* m2p,
+                             const DevParams* prm, const ForceOut& out, int64_t* m2p,
                              int64_t* p2p, int64_t* tests, bool plain, bool share,
                              hipStream_t s);
 hipError_t launch_scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* part, int64_t tiles,
@@ -268,7 +282,7 @@ inline CoopShape coop_shape(int64_t n, int dim) {
 hipError_t launch_walk_force_split(const WalkCell* walk, const float4* walkq, const Body* bodies,
                                    const float4* bodies32, const uint32_t* perm, const int32_t* gbeg,
                                    const int32_t* gcnt, int64_t gmax, int64_t n, int dim, int leaf_cap, float G,
-                                   float eps2, const DevParams* prm, float4* part, float* acc, float* pot,
+                                   float eps2, const DevParams* prm, float4* part, const ForceOut& out,
                                    int64_t* m2p, int64_t* p2p, int64_t* tests, bool plain, hipStream_t s);
 hipError_t launch_quad_pack(const Moments* mom, const uint32_t* pre2bfs, const DevParams* prm, int64_t cmax,
                             float4* walkq, hipStream_t s);
