@@ -272,8 +272,10 @@ BigList big_list(tc_ctx* ctx) {
     return {ctx->at<uint32_t>(l.off_bbox_part), ctx->at<uint32_t>(l.off_big), (uint32_t)(l.cmax / (sub + 1)), sub};
 }
 
-// Everything tc_build enqueues, after its checks.
-int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf_cap, int dtype, hipStream_t s) {
+// Everything tc_build enqueues, after its checks; with kick the bodies are
+// moved first.
+int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf_cap, int dtype, hipStream_t s,
+             const KickDrift* kick = nullptr) {
     const int dim = ctx->dim;
     ctx->lay = make_layout(n, dim, leaf_cap);
     const Layout& l = ctx->lay;
@@ -283,7 +285,8 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
     char* packed = buckets ? nullptr : ctx->at<char>(l.off_recs);
     {
         StageScope st_(ctx, TC_STAGE_BBOX, s);
-        TC_HIP(ctx, launch_bbox(pos, mass, n, dim, f64, ctx->at<double>(l.off_bbox_part), packed, prm, s));
+        TC_HIP(ctx, launch_bbox(const_cast<void*>(pos), mass, n, dim, f64, ctx->at<double>(l.off_bbox_part), packed, kick,
+                                prm, s));
     }
     if (buckets) {
         // the bucket numbers, splitters, totals and starts take the place of
@@ -519,11 +522,12 @@ int do_forces(tc_ctx* ctx, double G, double eps, float* acc = nullptr, float* po
 // moments, opening radii: about 70 short kernels) on stream s.
 int enqueue_pre_force(tc_ctx* ctx, double dt, void* pos, void* vel, hipStream_t s) {
     const int f64 = ctx->dtype == TC_F64;
-    {
+    const KickDrift kick{vel, ctx->at<float>(ctx->lay.off_acc), dt};
+    if (ctx->stage_timing) {   // a launch of its own, to be timed; the same values
         StageScope st_(ctx, TC_STAGE_KICK_DRIFT, s);
-        TC_HIP(ctx, launch_kick_drift(pos, vel, ctx->at<float>(ctx->lay.off_acc), ctx->n, ctx->dim, f64, dt, s));
+        TC_HIP(ctx, launch_kick_drift(pos, vel, kick.acc, ctx->n, ctx->dim, f64, dt, s));
     }
-    int rc = do_build(ctx, pos, ctx->mass, ctx->n, ctx->leaf_cap, ctx->dtype, s);
+    int rc = do_build(ctx, pos, ctx->mass, ctx->n, ctx->leaf_cap, ctx->dtype, s, ctx->stage_timing ? nullptr : &kick);
     if (rc == TC_OK) rc = do_moments(ctx, s);
     if (rc == TC_OK)
         rc = ctx->closure ? do_learned_radii(ctx, ctx->cl_theta_l, ctx->cl_theta_p, s) : do_walk(ctx, ctx->theta, s);

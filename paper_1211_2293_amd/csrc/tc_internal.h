@@ -132,8 +132,15 @@ Layout make_layout(int64_t n, int dim, int leaf_cap);
 // input; n of them) for launch_gather and reduces the boxes to the root cube;
 // without, the kernels of bodysort.hip do that.
 int bbox_parts(int64_t n);
-hipError_t launch_bbox(const void* pos, const void* mass, int64_t n, int dim, int f64,
-                       double* part, void* packed, DevParams* prm, hipStream_t s);
+// A step's half kick and drift, folded into the pass over the bodies' box.
+struct KickDrift {
+    void* vel;
+    const float* acc;
+    double dt;
+};
+// pos is written only with kick.
+hipError_t launch_bbox(void* pos, const void* mass, int64_t n, int dim, int f64, double* part, void* packed,
+                       const KickDrift* kick, DevParams* prm, hipStream_t s);
 hipError_t launch_keys(const void* pos, int64_t n, int dim, int f64, const DevParams* prm,
                        uint64_t* keys, uint32_t* idx, hipStream_t s);
 // LSD radix sort (stable) of the low key_bits bits; idx_a / idx_b may both be
