@@ -1065,6 +1065,7 @@ int tc_residuals(tc_ctx* ctx, double theta, double eps, const int32_t* targets, 
     TC_HIP(ctx, launch_scan_u32(cnt, nt, off, ctx->at<uint32_t>(l.off_rscan_part), (nt + kScanTile - 1) / kScanTile,
                                 s));
     TC_HIP(ctx, launch_resid_pairs(ctx->at<WalkCell>(l.off_walk), ctx->at<Body>(l.off_bodies),
+                                   ctx->dtype == TC_F32 ? ctx->at<float4>(l.off_bodies32) : nullptr,
                                    ctx->at<Cell>(l.off_cells), ctx->at<Moments>(l.off_mom),
                                    ctx->at<uint32_t>(l.off_lvl_idx_b), ctx->at<uint32_t>(l.off_pre2bfs), inv,
                                    ctx->prm(), ctx->n, l.cmax, targets, nt, eps * eps, off, cap,

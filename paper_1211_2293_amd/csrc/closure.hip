@@ -152,6 +152,11 @@ __global__ void __launch_bounds__(256) k_resid_walk(const WalkCell* __restrict__
     if (!LIST && lane == 0) counts[t] = (uint32_t)k;
 }
 
+// Counters of k_resid_pairs, zeroed beforehand: [0] the groups listed, then a
+// line per queue for the groups and for the lots handed out.
+constexpr int kQueues = 16, kLine = 32, kCounters = (1 + 2 * kQueues) * kLine;
+static_assert(kCounters <= kResidMaxTargets, "the counters lie where the targets' counts were");
+
 // The pairs by key.  Their order within a key varies from run to run; no
 // pair's result depends on it.
 __global__ void __launch_bounds__(256) k_resid_order(const int32_t* __restrict__ cell, const float* __restrict__ y,
@@ -161,7 +166,7 @@ __global__ void __launch_bounds__(256) k_resid_order(const int32_t* __restrict__
                                                      uint32_t* __restrict__ order, uint32_t* __restrict__ ctr) {
     const int64_t P = (int64_t)*total < cap ? (int64_t)*total : cap;
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < 3) ctr[i] = 0u;
+    for (int64_t k = i; k < kCounters; k += (int64_t)gridDim.x * blockDim.x) ctr[k] = 0u;
     for (int64_t k = i; k < P; k += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t b = pre2bfs[cell[k]], t = __float_as_uint(y[k * 3]);
         order[key_off[pair_key(b, t, hot)] + __float_as_uint(y[k * 3 + 1])] = (uint32_t)k;
@@ -175,18 +180,21 @@ __global__ void __launch_bounds__(256) k_resid_order(const int32_t* __restrict__
 // four to a wave on 16 lanes each.  Which way a pair goes, and so the order of
 // its sum, depends on its cell only.  The blocks first take the groups of four
 // in the order by cell that hold pairs of huge cells (k_resid_huge lists them),
-// then their waves take the other pairs, kTake at a time; big cells come first.
+// then their waves take the other pairs, kTask at a time; big cells come first.
+// Both are handed out by kQueues counters, each the places of one remainder:
+// from a single one, at some 15 ns a claim, the claims alone took 0.5 ms.
 //
-// Bound by the FP64 units, about 25 instructions per body and pair: 5.4e8 bodies
-// of 1.05M pairs (4,096 targets, 262,144 bodies) in 774 us.  One wave per target
-// going through its cells in turn, with sqrt and divide, took 3.1 ms; 16 lanes or
-// a wave per pair 2.1 ms, as one cell of four fifths of the bodies kept a wave
-// busy that long.
-constexpr int kTask = 8;
-constexpr int kTake = 32;
+// Bound by the FP64 units, about 21 instructions per body and pair, for the
+// large cells and by the latency of their few reads for the small ones: 1.05M
+// pairs of 5.4e8 bodies (4,096 targets, 262,144 bodies) in 0.6 ms.  One wave per
+// target going through its cells in turn, with sqrt and divide, took 3.1 ms; 16
+// lanes or a wave per pair 2.1 ms, as one cell of four fifths of the bodies kept
+// a wave busy that long.  kPairHuge: 4096 and 2048 are alike at 262,144 bodies
+// (852 and 891 us for everything), at 1,000,001 4096 wins (1.96 and 2.11 ms).
+constexpr int kTask = 8;                        // pairs a wave takes at a time
 constexpr int kPairLanes = 16;
 constexpr int kPairLong = 128;
-constexpr int kPairHuge = 2048;
+constexpr int kPairHuge = 4096;
 constexpr int kPairBlock = 512;
 constexpr int kPairGrid = 512;                  // blocks the chip holds at once, two per CU
 
@@ -223,6 +231,20 @@ __device__ __forceinline__ void add_body(Sum3& e, const Body& b, double x, doubl
     e.z = fma(w3, dz, e.z);
 }
 
+// Body j of the sums: FP32 inputs have a copy of 16 bytes a body, exactly the
+// input, which halves what the sums read.
+template <bool F32>
+__device__ __forceinline__ Body sum_body(const Body* __restrict__ bodies, const float4* __restrict__ bodies32, int64_t j) {
+    if (!F32) return bodies[j];
+    const float4 b = bodies32[j];
+    Body o;
+    o.x = b.x;
+    o.y = b.y;
+    o.z = b.z;
+    o.m = b.w;
+    return o;
+}
+
 __device__ __forceinline__ Sum3 shfl3(const Sum3& v, int l) {
     return {__shfl(v.x, l, kWave), __shfl(v.y, l, kWave), __shfl(v.z, l, kWave)};
 }
@@ -243,17 +265,21 @@ __device__ __forceinline__ Sum3 fold2(const Sum3& a, const Sum3& b, int o, bool 
 
 // The whole wave over the bodies [b0, b1) for T targets; afterwards the lanes
 // from m * 64 / T on hold the sum of target m.
-template <int T>
-__device__ __forceinline__ Sum3 wide_sum(const Body* __restrict__ bodies, int64_t b0, int64_t b1, const Sum3 (&at)[T],
+template <bool F32, int T>
+__device__ __forceinline__ Sum3 wide_sum(const Body* __restrict__ bodies, const float4* __restrict__ bodies32, int64_t b0, int64_t b1, const Sum3 (&at)[T],
                                          double eps2) {
     const int lane = threadIdx.x & (kWave - 1);
     Sum3 e[T];
 #pragma unroll
     for (int m = 0; m < T; ++m) e[m] = {0.0, 0.0, 0.0};
-    for (int64_t j = b0 + lane; j < b1; j += kWave) {
-        const Body b = bodies[j];
+    for (int64_t j = b0 + lane; j < b1; j += 2 * kWave) {
+        const Body b = sum_body<F32>(bodies, bodies32, j);
+        Body c = sum_body<F32>(bodies, bodies32, min(j + kWave, b1 - 1));
+        if (j + kWave >= b1) c.m = 0.0;                                      // adds nothing
 #pragma unroll
         for (int m = 0; m < T; ++m) add_body(e[m], b, at[m].x, at[m].y, at[m].z, eps2);
+#pragma unroll
+        for (int m = 0; m < T; ++m) add_body(e[m], c, at[m].x, at[m].y, at[m].z, eps2);
     }
     const bool h5 = (lane & 32) != 0, h4 = (lane & 16) != 0;
     Sum3 v;
@@ -303,7 +329,8 @@ __device__ __forceinline__ void put_pair(const Pair& p, const Sum3& r, const Mom
 
 // The wave's part (wave wv of nw) of the sums of `take` pairs from lane i on,
 // all of one cell; the sum of pair i + m is at the returned lane shift m << shift.
-__device__ __forceinline__ Sum3 run_sum(const Body* __restrict__ bodies, const Pair& p, int i, int take, int wv, int nw,
+template <bool F32>
+__device__ __forceinline__ Sum3 run_sum(const Body* __restrict__ bodies, const float4* __restrict__ bodies32, const Pair& p, int i, int take, int wv, int nw,
                                         double eps2, int& shift) {
     const int64_t c0 = __builtin_amdgcn_readlane(p.begin, i), cn = __builtin_amdgcn_readlane(p.count, i);
     const int64_t part = (cn + nw - 1) / nw;
@@ -314,15 +341,15 @@ __device__ __forceinline__ Sum3 run_sum(const Body* __restrict__ bodies, const P
     if (take >= 3) {
         const Sum3 a[4] = {target(i), target(i + 1), target(i + 2), target(i + take - 1)};
         shift = 4;
-        return wide_sum<4>(bodies, b0, b1, a, eps2);
+        return wide_sum<F32, 4>(bodies, bodies32, b0, b1, a, eps2);
     }
     shift = 5;
     if (take == 2) {
         const Sum3 a[2] = {target(i), target(i + 1)};
-        return wide_sum<2>(bodies, b0, b1, a, eps2);
+        return wide_sum<F32, 2>(bodies, bodies32, b0, b1, a, eps2);
     }
     const Sum3 a[1] = {target(i)};
-    return wide_sum<1>(bodies, b0, b1, a, eps2);
+    return wide_sum<F32, 1>(bodies, bodies32, b0, b1, a, eps2);
 }
 
 // Loads the pair at p0 + lane (lane < np) if its cell is on this side of
@@ -348,8 +375,9 @@ __device__ __forceinline__ bool load_pair(Pair& p, int64_t p0, int np, const Bod
     return true;
 }
 
-// ctr: groups listed, groups taken, lots of kTake pairs taken.
+template <bool F32>
 __global__ void __launch_bounds__(kPairBlock) k_resid_pairs(const Body* __restrict__ bodies,
+                                                            const float4* __restrict__ bodies32,
                                                             const Cell* __restrict__ cells,
                                                             const Moments* __restrict__ mom,
                                                             const uint32_t* __restrict__ inv_perm,
@@ -365,10 +393,11 @@ __global__ void __launch_bounds__(kPairBlock) k_resid_pairs(const Body* __restri
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
     const int64_t P = (int64_t)*total < cap ? (int64_t)*total : cap;
     const double size = prm->size;
-    const uint32_t nlist = ctr[0];
+    const uint32_t nlist = ctr[0], nq = min((uint32_t)kQueues, gridDim.x), queue = blockIdx.x % nq;
+    uint32_t *groups = ctr + (1 + queue) * kLine, *lots = groups + kQueues * kLine;
     Pair p;
     for (;;) {
-        if (threadIdx.x == 0) s_task = atomicAdd(&ctr[1], 1u);
+        if (threadIdx.x == 0) s_task = atomicAdd(groups, 1u) * nq + queue;
         __syncthreads();
         const uint32_t task = s_task;
         __syncthreads();
@@ -380,7 +409,7 @@ __global__ void __launch_bounds__(kPairBlock) k_resid_pairs(const Body* __restri
             const int i = __builtin_ctzll(left);
             const int take = __builtin_ctzll(~__ballot(p.cell == __builtin_amdgcn_readlane(p.cell, i)) >> i);
             int shift;
-            const Sum3 v = run_sum(bodies, p, i, take, wv, kWaves, eps2, shift);
+            const Sum3 v = run_sum<F32>(bodies, bodies32, p, i, take, wv, kWaves, eps2, shift);
             if ((lane & ((1 << shift) - 1)) == 0) s_part[wv][lane >> shift] = v;
             __syncthreads();
             if (wv == 0 && lane >= i && lane < i + take) {
@@ -399,44 +428,53 @@ __global__ void __launch_bounds__(kPairBlock) k_resid_pairs(const Body* __restri
     }
     for (;;) {
         uint32_t next = 0;
-        if (lane == 0) next = atomicAdd(&ctr[2], 1u);
-        const int64_t t0 = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)next) * kTake;
-        if (t0 >= P) break;
-        for (int64_t p0 = t0; p0 < min(t0 + kTake, P); p0 += kTask) {
-            const int np = (int)min((int64_t)kTask, P - p0);
-            const bool mine = load_pair<false>(p, p0, np, bodies, cells, inv_perm, targets, yout, cell_out, order);
-            const uint32_t mask = (uint32_t)__ballot(mine), wide = (uint32_t)__ballot(mine && p.count > kPairLong);
-            Sum3 r = {0.0, 0.0, 0.0};
-            for (int i = 0; i < np;) {
-                Sum3 v;
-                int take, shift;
-                if (!((mask >> i) & 1u)) {
-                    ++i;
-                    continue;
-                }
-                if ((wide >> i) & 1u) {
-                    const uint32_t other = ~(uint32_t)__ballot(p.cell == __builtin_amdgcn_readlane(p.cell, i)) >> i;
-                    take = min(__builtin_ctz(other), 4);
-                    v = run_sum(bodies, p, i, take, 0, 1, eps2, shift);
-                } else {
-                    constexpr int kPairs = kWave / kPairLanes;
-                    take = min(__builtin_ctz((wide | ~mask) >> i), kPairs);
-                    const int src = i + min(lane / kPairLanes, take - 1);
-                    const Sum3 a = shfl3(p.at, src);
-                    const int64_t b0 = __shfl(p.begin, src, kWave), b1 = b0 + __shfl(p.count, src, kWave);
-                    v = {0.0, 0.0, 0.0};
-                    for (int64_t j = b0 + lane % kPairLanes; j < b1; j += kPairLanes)
-                        add_body(v, bodies[j], a.x, a.y, a.z, eps2);
-#pragma unroll
-                    for (int o = kPairLanes / 2; o > 0; o >>= 1) fold(v, o);
-                    shift = 4;
-                }
-                const Sum3 got = shfl3(v, ((lane - i) << shift) & (kWave - 1));
-                if (lane >= i && lane < i + take) r = got;
-                i += take;
+        if (lane == 0) next = atomicAdd(lots, 1u);
+        next = (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
+        const int64_t p0 = ((int64_t)next * nq + queue) * kTask;
+        if (p0 >= P) break;
+        const int np = (int)min((int64_t)kTask, P - p0);
+        const bool mine = load_pair<false>(p, p0, np, bodies, cells, inv_perm, targets, yout, cell_out, order);
+        const uint32_t mask = (uint32_t)__ballot(mine), wide = (uint32_t)__ballot(mine && p.count > kPairLong);
+        Sum3 r = {0.0, 0.0, 0.0};
+        for (int i = 0; i < np;) {
+            Sum3 v;
+            int take, shift;
+            if (!((mask >> i) & 1u)) {
+                ++i;
+                continue;
             }
-            if (mine) put_pair(p, r, mom, size, eps2, yout);
+            if ((wide >> i) & 1u) {
+                const uint32_t other = ~(uint32_t)__ballot(p.cell == __builtin_amdgcn_readlane(p.cell, i)) >> i;
+                take = min(__builtin_ctz(other), 4);
+                v = run_sum<F32>(bodies, bodies32, p, i, take, 0, 1, eps2, shift);
+            } else {
+                constexpr int kPairs = kWave / kPairLanes;
+                take = min(__builtin_ctz((wide | ~mask) >> i), kPairs);
+                const int src = i + min(lane / kPairLanes, take - 1);
+                const Sum3 a = shfl3(p.at, src);
+                const int64_t b0 = __shfl(p.begin, src, kWave), b1 = b0 + __shfl(p.count, src, kWave);
+                v = {0.0, 0.0, 0.0};
+                // four bodies of a lane are read together: one after the
+                // other, the groups waited for each
+                for (int64_t j = b0 + lane % kPairLanes; j < b1; j += 4 * kPairLanes) {
+                    Body b[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        b[u] = sum_body<F32>(bodies, bodies32, min(j + u * kPairLanes, b1 - 1));
+                        if (j + u * kPairLanes >= b1) b[u].m = 0.0;      // adds nothing
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) add_body(v, b[u], a.x, a.y, a.z, eps2);
+                }
+#pragma unroll
+                for (int o = kPairLanes / 2; o > 0; o >>= 1) fold(v, o);
+                shift = 4;
+            }
+            const Sum3 got = shfl3(v, ((lane - i) << shift) & (kWave - 1));
+            if (lane >= i && lane < i + take) r = got;
+            i += take;
         }
+        if (mine) put_pair(p, r, mom, size, eps2, yout);
     }
 }
 
@@ -825,7 +863,7 @@ hipError_t launch_resid_count(const WalkCell* walk, const Body* bodies, const ui
     return hipGetLastError();
 }
 
-hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const Cell* cells, const Moments* mom,
+hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const float4* bodies32, const Cell* cells, const Moments* mom,
                               const uint32_t* bfs2pre, const uint32_t* pre2bfs, const uint32_t* inv_perm,
                               DevParams* prm, int64_t n, int64_t cmax, const int32_t* targets, int nt, double eps2,
                               const uint32_t* offs, int64_t cap, uint32_t* key_count, uint32_t* key_off,
@@ -850,9 +888,11 @@ hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const Ce
     hipLaunchKernelGGL(k_resid_huge, dim3(grid_for(cap)), dim3(256), 0, s, cells, (const int32_t*)cell_out,
                        (const uint32_t*)order, total, cap, list, ctr);
     const int64_t groups = (cap + 3) / 4;
-    hipLaunchKernelGGL(k_resid_pairs, dim3((unsigned)(groups < kPairGrid ? groups : kPairGrid)), dim3(kPairBlock), 0, s,
-                       bodies, cells, mom, inv_perm, (const DevParams*)prm, targets, eps2, total, cap, y,
-                       (const int32_t*)cell_out, (const uint32_t*)order, (const uint32_t*)list, ctr);
+    const dim3 grid((unsigned)(groups < kPairGrid ? groups : kPairGrid));
+    const auto pairs = bodies32 ? k_resid_pairs<true> : k_resid_pairs<false>;
+    hipLaunchKernelGGL(pairs, grid, dim3(kPairBlock), 0, s, bodies, bodies32, cells, mom, inv_perm,
+                       (const DevParams*)prm, targets, eps2, total, cap, y, (const int32_t*)cell_out,
+                       (const uint32_t*)order, (const uint32_t*)list, ctr);
     hipLaunchKernelGGL(k_resid_features, dim3((unsigned)nt), dim3(256), 0, s, bodies, cells, mom, inv_perm,
                        (const DevParams*)prm, n, targets, offs, cap, (const int32_t*)cell_out, feat);
     return hipGetLastError();

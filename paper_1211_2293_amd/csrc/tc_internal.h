@@ -304,10 +304,12 @@ hipError_t launch_resid_count(const WalkCell* walk, const Body* bodies, const ui
                               const uint32_t* inv_perm, DevParams* prm, int64_t n, const int32_t* targets, int nt,
                               uint32_t* counts, hipStream_t s);
 // Keys of the order by cell: the first cells in level order, which hold nearly
-// all the large ones, have one key each.
+// all the large ones, have one key each.  Fewer keys cost fewer atomics in the
+// list pass but lose the pairs side by side (4,096 targets, 1,000,001 bodies: 2.76
+// ms with 2,048 keys, 2.21 with 4,096, 1.98 with 16,384).
 constexpr int64_t kResidKeys = 16384;
 constexpr uint32_t kResidColdKeys = 256;
-hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const Cell* cells, const Moments* mom,
+hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const float4* bodies32, const Cell* cells, const Moments* mom,
                               const uint32_t* bfs2pre, const uint32_t* pre2bfs, const uint32_t* inv_perm,
                               DevParams* prm, int64_t n, int64_t cmax, const int32_t* targets, int nt, double eps2,
                               const uint32_t* offs, int64_t cap, uint32_t* key_count, uint32_t* key_off,

@@ -50,15 +50,20 @@ def test_residuals_match_oracle(plummer):
         assert np.all(np.abs(y[a:b][og] - ref) <= 1e-6 * np.abs(ref) + 1e-9)
 
 
-@pytest.mark.parametrize("n,nt,part", [(2, 2, 1.0), (300, 300, 1.0), (300, 1, 1.0), (4000, 4000, 1.0), (4000, 1500, 0.37),
-                                       (40000, 7, 1.0), (40000, 9, 0.01)])
-def test_residual_pairs_at_every_split(n, nt, part):
+@pytest.mark.parametrize("n,nt,part,dtype", [(2, 2, 1.0, np.float32), (300, 300, 1.0, np.float32),
+                                             (300, 1, 1.0, np.float64), (4000, 4000, 1.0, np.float32),
+                                             (4000, 1500, 0.37, np.float64), (40000, 7, 1.0, np.float32),
+                                             (40000, 9, 0.01, np.float32), (40000, 11, 1.0, np.float64)])
+def test_residual_pairs_at_every_split(n, nt, part, dtype):
     """Cells of one body up to a quarter of the system, met by one to thousands
     of targets: runs of a cell of every length, and lists that fill the given
     arrays only in part.  The bounds are the ones of the oracle's test: FP64
     sums, rounded once."""
     w = workloads.plummer_sphere(n, seed=300 + n)
-    tc, keep = _ctx(w)
+    tc = treecode.Treecode(3, leaf_cap=16)
+    keep = to_dev(w.pos.astype(dtype)), to_dev(w.mass.astype(dtype))
+    tc.build(*keep)
+    tc.moments()
     targets = np.random.default_rng(n).permutation(n)[:nt].astype(np.int32)
     full = tc.residuals(0.9, 1e-2, to_dev(targets))
     cap = int(np.ceil(part * len(full[2])))
