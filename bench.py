@@ -87,7 +87,7 @@ def sources_hash(files, read=None) -> str:
 
 
 FORCE_SOURCES = ("force.hip", "walk_common.h", "tc_internal.h")
-BUILD_SOURCES = ("build.hip", "tc_internal.h")
+BUILD_SOURCES = ("build.hip", "bodysort.hip", "keys.h", "tc_internal.h")
 
 
 def force_kernel_source_hash() -> str:
@@ -230,12 +230,24 @@ def build_bytes(n, dim, f64, ncells, ngroups):
     ncells cells and ngroups walk groups."""
     e = 8 if f64 else 4                              # input element size
     pos = dim * e
-    passes = (dim * (21 if dim == 3 else 31) + 7) // 8   # 8-bit digits of the keys
+    out = 32 + (0 if f64 else 16)                    # FP64 body (+ FP32 copy)
+    if n <= 8192:                                    # ranked in one launch
+        keys, sort, gather = 0, 0, n * (pos + e + 12 + out)
+    elif n < 1 << 21:                                # sample sort: records of 32 (FP64: 48) bytes cross memory once
+        rec = 48 if f64 else 32
+        keys = n * (pos + 2)                         # positions read; bucket written
+        sort = n * (pos + e + 2 + rec)               # position, mass, bucket in; record out
+        gather = n * (rec + 12 + out)                # record in; key, index and body out
+    else:
+        passes = (dim * (21 if dim == 3 else 31) + 7) // 8   # 8-bit digits of the keys
+        keys = n * (pos + 12)                        # positions read; key and index written
+        sort = passes * n * 24                       # each pass: key + index read and written
+        gather = n * (4 + pos + e + out)             # index, position and mass in; body out
     return {
         "bbox": n * (pos + e),                          # positions and masses read
-        "keys": n * (pos + 12),                         # positions read; key and index written
-        "sort": passes * n * 24,                        # each pass: key + index read and written
-        "gather": n * (4 + pos + e + 32 + (0 if f64 else 16)),   # index, position, mass in; FP64 body (+ FP32 copy) out
+        "keys": keys,
+        "sort": sort,
+        "gather": gather,
         "topology": n * 8 + ncells * 32,                # sorted keys read, cells written
         "levels": ncells * 12,                          # levels read, level-order maps written
         "groups": ncells * 12 + ngroups * 8,            # counts and flags read, groups written
