@@ -198,12 +198,13 @@ constexpr int kPairHuge = 4096;
 constexpr int kPairBlock = 512;
 constexpr int kPairGrid = 512;                  // blocks the chip holds at once, two per CU
 
+// The list follows the P pairs of the order.
 __global__ void __launch_bounds__(256) k_resid_huge(const Cell* __restrict__ cells, const int32_t* __restrict__ cell,
-                                                    const uint32_t* __restrict__ order,
-                                                    const uint32_t* __restrict__ total, int64_t cap,
-                                                    uint32_t* __restrict__ list, uint32_t* __restrict__ ctr) {
+                                                    uint32_t* order, const uint32_t* __restrict__ total, int64_t cap,
+                                                    uint32_t* __restrict__ ctr) {
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t P = (int64_t)*total < cap ? (int64_t)*total : cap;
+    uint32_t* list = order + P;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i0 = blockIdx.x * (int64_t)blockDim.x + (threadIdx.x & ~(kWave - 1)); i0 < P; i0 += stride) {
         const int64_t i = i0 + lane;
@@ -385,14 +386,14 @@ __global__ void __launch_bounds__(kPairBlock) k_resid_pairs(const Body* __restri
                                                             const int32_t* __restrict__ targets, double eps2,
                                                             const uint32_t* __restrict__ total, int64_t cap,
                                                             float* yout, const int32_t* __restrict__ cell_out,
-                                                            const uint32_t* __restrict__ order,
-                                                            const uint32_t* __restrict__ list, uint32_t* ctr) {
+                                                            const uint32_t* __restrict__ order, uint32_t* ctr) {
     constexpr int kWaves = kPairBlock / kWave;
     __shared__ Sum3 s_part[kWaves][4];
     __shared__ uint32_t s_task;
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
     const int64_t P = (int64_t)*total < cap ? (int64_t)*total : cap;
     const double size = prm->size;
+    const uint32_t* list = order + P;
     const uint32_t nlist = ctr[0], nq = min((uint32_t)kQueues, gridDim.x), queue = blockIdx.x % nq;
     uint32_t *groups = ctr + (1 + queue) * kLine, *lots = groups + kQueues * kLine;
     Pair p;
@@ -874,9 +875,8 @@ hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const fl
     const int64_t nkeys = cold ? kResidKeys : cmax;
     const uint32_t hot = (uint32_t)(cold ? nkeys - kResidColdKeys : nkeys);
     const uint32_t* total = offs + nt;
-    // The order and the list lie in the features' memory until these are written.
+    // The order and the list lie in the P pairs' features until these are written.
     uint32_t* order = reinterpret_cast<uint32_t*>(feat);
-    uint32_t* list = order + cap;
     hipError_t e = launch_fill_u32(key_count, nkeys, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_resid_walk<true>, dim3((unsigned)((nt + 3) / 4)), dim3(256), 0, s, walk, bodies, bfs2pre,
@@ -886,13 +886,13 @@ hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const fl
     hipLaunchKernelGGL(k_resid_order, dim3(grid_for(cap)), dim3(256), 0, s, (const int32_t*)cell_out, (const float*)y,
                        total, cap, pre2bfs, (const uint32_t*)key_off, hot, order, ctr);
     hipLaunchKernelGGL(k_resid_huge, dim3(grid_for(cap)), dim3(256), 0, s, cells, (const int32_t*)cell_out,
-                       (const uint32_t*)order, total, cap, list, ctr);
+                       order, total, cap, ctr);
     const int64_t groups = (cap + 3) / 4;
     const dim3 grid((unsigned)(groups < kPairGrid ? groups : kPairGrid));
     const auto pairs = bodies32 ? k_resid_pairs<true> : k_resid_pairs<false>;
     hipLaunchKernelGGL(pairs, grid, dim3(kPairBlock), 0, s, bodies, bodies32, cells, mom, inv_perm,
                        (const DevParams*)prm, targets, eps2, total, cap, y, (const int32_t*)cell_out,
-                       (const uint32_t*)order, (const uint32_t*)list, ctr);
+                       (const uint32_t*)order, ctr);
     hipLaunchKernelGGL(k_resid_features, dim3((unsigned)nt), dim3(256), 0, s, bodies, cells, mom, inv_perm,
                        (const DevParams*)prm, n, targets, offs, cap, (const int32_t*)cell_out, feat);
     return hipGetLastError();

@@ -3,6 +3,8 @@ features, normalised residuals), the BF16 matrix-core network's forward
 pass and per-step gradients (against the FP64 oracle with the same bfloat16
 rounding points), the Adam update, and that training on the method's own
 residuals lowers the loss."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -69,6 +71,14 @@ def test_residual_pairs_at_every_split(n, nt, part, dtype):
     cap = int(np.ceil(part * len(full[2])))
     feat, y, cell = tc.residuals(0.9, 1e-2, to_dev(targets), cap=cap) if part < 1.0 else full
     feat, y, cell = feat.cpu().numpy(), y.cpu().numpy(), cell.cpu().numpy()
+    # arrays with room for more: what lies past the pairs is left alone
+    spare = [torch.full((len(full[2]) + 5, *t.shape[1:]), 7, dtype=t.dtype, device="cuda") for t in full]
+    n_out = C.c_int64()
+    assert treecode.lib().tc_residuals(tc._h, 0.9, 1e-2, to_dev(targets).data_ptr(), nt, *(t.data_ptr() for t in spare),
+                                       len(spare[2]), C.byref(n_out)) == 0
+    torch.cuda.synchronize()
+    for t, u in zip(spare, full):
+        assert torch.equal(t[:len(u)], u) and bool((t[len(u):] == 7).all())
     r = oracle.Tree(w.pos, w.mass, 16).residuals(0.9, 1e-2, targets)
     off = np.concatenate([[0], np.cumsum(r["count"])])
     assert len(full[2]) == off[-1]
