@@ -283,7 +283,10 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
     DevParams* prm = ctx->prm();
     const bool buckets = n < kBucketMaxN;
     char* packed = buckets ? nullptr : ctx->at<char>(l.off_recs);
-    {
+    // the smallest systems' order finds the box as well, unless the bodies
+    // are to be moved first or the stages timed
+    const bool boxed = n > kRankMaxN || kick || ctx->stage_timing;
+    if (boxed) {
         StageScope st_(ctx, TC_STAGE_BBOX, s);
         TC_HIP(ctx, launch_bbox(const_cast<void*>(pos), mass, n, dim, f64, ctx->at<double>(l.off_bbox_part), packed, kick,
                                 prm, s));
@@ -305,7 +308,7 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
         a.split_idx = reinterpret_cast<uint32_t*>(nper + 8 * (size_t)nb);
         a.total = a.split_idx + nb;
         a.start = a.total + nb;
-        const double* part = ctx->at<double>(l.off_bbox_part);
+        const double* part = boxed ? ctx->at<double>(l.off_bbox_part) : nullptr;
         const int parts = bbox_parts(n);
         {
             StageScope st_(ctx, TC_STAGE_KEYS, s);

@@ -72,23 +72,14 @@ BucketShape bucket_shape(int64_t n) {
 
 __device__ __forceinline__ int wave_lane() { return threadIdx.x & (kWave - 1); }
 
-// The root cube from the partial boxes of k_bbox_part (7 doubles each), by
-// every block for itself (1024 threads); block 0 also stores it.
-__device__ __forceinline__ Cube block_cube(const double* __restrict__ part, int nb, int dim, DevParams* prm) {
+// The root cube from a block's boxes, one per thread (1024 threads); block 0
+// also stores it.
+__device__ __forceinline__ Cube reduce_cube(double (&lo)[3], double (&hi)[3], int bad, int dim, DevParams* prm) {
     __shared__ double s_box[kRankThreads / kWave][6];
     __shared__ int s_bad;
     __shared__ Cube s_cube;
     const int t = threadIdx.x;
     if (t == 0) s_bad = 0;
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    int bad = 0;
-    for (int b = t; b < nb; b += kRankThreads) {
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = fmin(lo[a], part[b * 7 + a]);
-            hi[a] = fmax(hi[a], part[b * 7 + 3 + a]);
-        }
-        bad |= part[b * 7 + 6] != 0.0;
-    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
 #pragma unroll
@@ -116,6 +107,47 @@ __device__ __forceinline__ Cube block_cube(const double* __restrict__ part, int 
     }
     __syncthreads();
     return s_cube;
+}
+
+// The root cube from the partial boxes of k_bbox_part (7 doubles each), by
+// every block for itself.
+__device__ __forceinline__ Cube block_cube(const double* __restrict__ part, int nb, int dim, DevParams* prm) {
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    int bad = 0;
+    for (int b = threadIdx.x; b < nb; b += kRankThreads) {
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = fmin(lo[a], part[b * 7 + a]);
+            hi[a] = fmax(hi[a], part[b * 7 + 3 + a]);
+        }
+        bad |= part[b * 7 + 6] != 0.0;
+    }
+    return reduce_cube(lo, hi, bad, dim, prm);
+}
+
+// The same from the bodies themselves, where a block reads them all anyway;
+// the masses are checked by the block that stores the cube.
+template <typename T, int D>
+__device__ __forceinline__ Cube bodies_cube(const T* __restrict__ pos, const T* __restrict__ mass, int n,
+                                            DevParams* prm) {
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    int bad = 0;
+    for (int i = threadIdx.x; i < n; i += kRankThreads) {
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            const double v = (double)pos[(int64_t)i * D + a];
+            if (!isfinite(v)) {
+                bad = 1;
+                continue;
+            }
+            lo[a] = fmin(lo[a], v);
+            hi[a] = fmax(hi[a], v);
+        }
+        if (blockIdx.x == 0) {
+            const double m = (double)mass[i];
+            if (!(isfinite(m) && m > 0.0)) bad = 1;
+        }
+    }
+    return reduce_cube(lo, hi, bad, D, prm);
 }
 
 template <typename T, int D>
@@ -161,7 +193,9 @@ constexpr int kSlices = kRankThreads / kRankOwn;
 
 // One launch for the smallest systems: bound by latency (n <= kRankMaxN: at
 // most 256 compares per thread).  Every block computes all keys again, which
-// costs less than the launch that would store them.
+// costs less than the launch that would store them, and, without part, the root
+// cube, which costs less than the launch of k_bbox_part (a force evaluation of
+// 4,096 bodies 93 us with it, 91 without).
 template <typename T, int D>
 __global__ void __launch_bounds__(kRankThreads) k_rank_sort(const T* __restrict__ pos, const T* __restrict__ mass, int n,
                                                             const double* __restrict__ part, int nb, DevParams* prm,
@@ -170,7 +204,7 @@ __global__ void __launch_bounds__(kRankThreads) k_rank_sort(const T* __restrict_
                                                             float4* __restrict__ bodies32) {
     __shared__ uint64_t s_key[kRankChunk];
     __shared__ uint32_t s_rank[kRankOwn];
-    const Cube c = block_cube(part, nb, D, prm);
+    const Cube c = part ? block_cube(part, nb, D, prm) : bodies_cube<T, D>(pos, mass, n, prm);
     const int t = threadIdx.x, own = t % kRankOwn, slice = t / kRankOwn;
     const int i0 = (int)blockIdx.x * kRankOwn, i = i0 + own;
     const uint64_t key = i < n ? key_at<T, D>(pos, i, c.lo, c.scale) : 0ull;
