@@ -167,7 +167,7 @@ struct tc_ctx {
     // the fast multipole plan (tc_fmm_plan) in the caller's buffer
     bool fmm_planned = false;
     uint8_t* fmm_buf = nullptr;
-    int64_t fmm_ncells = 0, fmm_m2l = 0, fmm_p2p = 0, fmm_capf = 0, fmm_capm = 0, fmm_capp = 0, fmm_ntasks = 0;
+    int64_t fmm_ncells = 0, fmm_m2l = 0, fmm_p2p = 0, fmm_capf = 0, fmm_capm = 0, fmm_capp = 0, fmm_ntasks = 0, fmm_nlong = 0;
     uint32_t fmm_lvl_off[64] = {};
     hipStream_t gstream = nullptr;
     hipEvent_t g_in = nullptr, g_out = nullptr;
@@ -744,24 +744,28 @@ int tc_fmm_plan(tc_ctx* ctx, double theta, void* buf, size_t bytes, int64_t fron
     uint32_t* soff = reinterpret_cast<uint32_t*>(B + f.off_soff);
     TC_HIP(ctx, launch_fmm_tasks(cells, reinterpret_cast<const uint32_t*>(B + f.off_poff), ctx->prm(), C,
                                  reinterpret_cast<uint32_t*>(B + f.off_ntask),
-                                 reinterpret_cast<uint32_t*>(B + f.off_nslot), s));
+                                 reinterpret_cast<uint32_t*>(B + f.off_nslot), ctr, s));
     TC_HIP(ctx, launch_scan_u32(reinterpret_cast<const uint32_t*>(B + f.off_ntask), C, toff,
                                 reinterpret_cast<uint32_t*>(B + f.off_tpart), f.ctiles, s));
     TC_HIP(ctx, launch_scan_u32(reinterpret_cast<const uint32_t*>(B + f.off_nslot), C, soff,
                                 reinterpret_cast<uint32_t*>(B + f.off_tpart), f.ctiles, s));
-    uint32_t tot[2] = {0, 0};
-    TC_HIP(ctx, hipMemcpyAsync(&tot[0], toff + C, 4, hipMemcpyDeviceToHost, s));
-    TC_HIP(ctx, hipMemcpyAsync(&tot[1], soff + C, 4, hipMemcpyDeviceToHost, s));
+    TC_HIP(ctx, hipMemcpyAsync(hc, ctr, 4 * sizeof(hc[0]), hipMemcpyDeviceToHost, s));
     TC_HIP(ctx, hipStreamSynchronize(s));
+    const int64_t ntasks = (int64_t)(hc[3] >> 32), nlong = (int64_t)(hc[3] & 0xffffffffull), nslots = (int64_t)hc[0];
     const int64_t part_slots = (int64_t)(f.off_fb + 8 * (size_t)f.capf - f.off_fa) / 32;
-    if ((int64_t)tot[1] > part_slots) {
-        sizes[0] = 2 * (int64_t)tot[1] + 1;          // frontier capacity that holds the partial sums
+    if (nslots > part_slots) {
+        sizes[0] = 2 * nslots + 1;          // frontier capacity that holds the partial sums
         return TC_EWORKSPACE;
     }
-    if ((int64_t)tot[0] > 2 * f.capk)                      // tasks <= leaves + P2P pairs <= 2 capk
+    if (ntasks > 2 * f.capk)                      // tasks <= leaves + P2P pairs <= 2 capk
         return internal_fail("FMM leaf tasks exceed their buffer");
-    TC_HIP(ctx, launch_fmm_tasks_fill(toff, ctx->prm(), C, reinterpret_cast<uint32_t*>(B + f.off_keys_b), s));
-    ctx->fmm_ntasks = (int64_t)tot[0];
+    // long tasks <= P2P pairs / 128: their list fits the pair sort's counts, capk / 4 of them
+    if (nlong > 256 * f.tiles) return internal_fail("FMM long tasks exceed their buffer");
+    TC_HIP(ctx, launch_fmm_tasks_fill(toff, reinterpret_cast<const uint32_t*>(B + f.off_poff), ctx->prm(), C,
+                                      reinterpret_cast<uint32_t*>(B + f.off_keys_b),
+                                      reinterpret_cast<uint32_t*>(B + f.off_hist), ctr, s));
+    ctx->fmm_ntasks = ntasks;
+    ctx->fmm_nlong = nlong;
     TC_HIP(ctx, hipStreamSynchronize(s));
     ctx->fmm_buf = B;
     ctx->fmm_ncells = C;
@@ -804,6 +808,7 @@ int tc_fmm_forces(tc_ctx* ctx, double G, double eps, void* acc, void* pot) {
                                 reinterpret_cast<const uint32_t*>(B + f.off_keys_b),
                                 reinterpret_cast<const uint32_t*>(B + f.off_toff),
                                 reinterpret_cast<const uint32_t*>(B + f.off_soff), ctx->fmm_ntasks,
+                                reinterpret_cast<const uint32_t*>(B + f.off_hist), ctx->fmm_nlong,
                                 reinterpret_cast<double*>(B + f.off_fa), ctx->prm(), f.C,
                                 (float)G, (float)(eps * eps), ctx->at<float>(l.off_acc), ctx->at<float>(l.off_pot), s));
     ctx->G = G;

@@ -594,14 +594,26 @@ constexpr int kFmmWaves = 1;                // per block: their tasks differ in 
 // partial slots and k_fmm_leaf_finish adds them in chunk order.
 constexpr uint32_t kFmmChunk = 256;
 
+// Tasks of more partners than this are started first, so that the others fill
+// the end of the launch: 1,048,576 bodies (leaf size 64, theta 0.5) 3.90 -> 3.67
+// ms for everything, the leaf kernel 1.60 -> 1.37 (a line of 96 or 160 partners
+// was 1% slower).  A task's
+// sums do not depend on when it runs.
+constexpr uint32_t kFmmLong = 128;
+
+__device__ __forceinline__ bool long_task(uint32_t partners) { return partners > kFmmLong; }
+
 // Tasks per cell (leaves: chunks of the partner list; other cells: none)
 // and partial slots (chunks x bodies, for leaves cut into several chunks).
 __global__ void __launch_bounds__(256) k_fmm_tasks_count(const Cell* __restrict__ cells,
                                                          const uint32_t* __restrict__ poff,
                                                          const DevParams* __restrict__ prm, int64_t cmax,
-                                                         uint32_t* __restrict__ ntask, uint32_t* __restrict__ nslot) {
+                                                         uint32_t* __restrict__ ntask, uint32_t* __restrict__ nslot,
+                                                         unsigned long long* __restrict__ ctr) {
+    __shared__ unsigned long long s_slots[4], s_tasks[4];
     int64_t C = prm->ncells;
     if (C > cmax) C = cmax;
+    unsigned long long slots = 0, tasks = 0;          // tasks << 32 | long ones
     for (int64_t A = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; A < C; A += (int64_t)gridDim.x * blockDim.x) {
         const Cell ca = cells[A];
         uint32_t nt = 0, ns = 0;
@@ -609,19 +621,64 @@ __global__ void __launch_bounds__(256) k_fmm_tasks_count(const Cell* __restrict_
             const uint32_t np = poff[A + 1] - poff[A];
             nt = np > kFmmChunk ? (np + kFmmChunk - 1) / kFmmChunk : 1u;
             ns = nt > 1 ? nt * (uint32_t)ca.count : 0u;
+            slots += ns;
+            tasks += (unsigned long long)nt << 32 | (nt - 1 + (long_task(np - (nt - 1) * kFmmChunk) ? 1u : 0u));
         }
         ntask[A] = nt;
         nslot[A] = ns;
     }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        slots += __shfl_xor(slots, o, kWave);
+        tasks += __shfl_xor(tasks, o, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        s_slots[threadIdx.x / kWave] = slots;
+        s_tasks[threadIdx.x / kWave] = tasks;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        tasks = s_tasks[0] + s_tasks[1] + s_tasks[2] + s_tasks[3];
+        slots = s_slots[0] + s_slots[1] + s_slots[2] + s_slots[3];
+        if (tasks) atomicAdd(&ctr[3], tasks);
+        if (slots) atomicAdd(&ctr[0], slots);
+    }
 }
 
+// Every task's leaf, and the list of the long tasks (in any order; left_long:
+// those still to be listed, taken by one claim per wave).
 __global__ void __launch_bounds__(256) k_fmm_tasks_fill(const uint32_t* __restrict__ toff,
+                                                        const uint32_t* __restrict__ poff,
                                                         const DevParams* __restrict__ prm, int64_t cmax,
-                                                        uint32_t* __restrict__ task) {
+                                                        uint32_t* __restrict__ task, uint32_t* __restrict__ longs,
+                                                        uint32_t* __restrict__ left_long) {
     int64_t C = prm->ncells;
     if (C > cmax) C = cmax;
-    for (int64_t A = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; A < C; A += (int64_t)gridDim.x * blockDim.x)
-        for (uint32_t k = toff[A]; k < toff[A + 1]; ++k) task[k] = (uint32_t)A;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t A0 = blockIdx.x * (int64_t)blockDim.x + (threadIdx.x & ~(kWave - 1)); A0 < C; A0 += stride) {
+        const int64_t A = A0 + lane;
+        const uint32_t t0 = A < C ? toff[A] : 0u, t1 = A < C ? toff[A + 1] : 0u;
+        const uint32_t np = t1 > t0 ? poff[A + 1] - poff[A] : 0u;
+        const uint32_t full = t1 > t0 ? t1 - t0 - 1u : 0u;          // whole chunks before the last
+        const uint32_t mine = full + (long_task(np - full * kFmmChunk) ? 1u : 0u);
+        uint32_t incl = mine;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o, kWave);
+            if (lane >= o) incl += y;
+        }
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+        uint32_t at = 0;
+        if (total) {
+            if (lane == 0) at = atomicSub(left_long, total) - total;
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + incl - mine;
+        }
+        for (uint32_t k = t0; k < t1; ++k) {
+            task[k] = (uint32_t)A;
+            if (k - t0 < mine) longs[at + (k - t0)] = k;
+        }
+    }
 }
 
 // L2P + P2P: one wave per task (a target leaf, or one chunk of a long
@@ -634,7 +691,7 @@ __global__ void __launch_bounds__(256) k_fmm_tasks_fill(const uint32_t* __restri
 // for four bodies at once where there are as many.
 //
 // Bound by the FP32 units, 14 instructions per pair of bodies: 2.9e9 pairs
-// (1,048,576 bodies, leaf size 64, theta 0.5) in 1.6 ms.  Two targets per lane
+// (1,048,576 bodies, leaf size 64, theta 0.5) in 1.4 ms.  Two targets per lane
 // halve the LDS reads per interaction and leave few lanes idle (slices of the
 // next power of two of nA lanes lost a quarter); four entries per lane are read
 // ahead, where one at a time waited for each; chunks are added in FP64 (two
@@ -661,7 +718,8 @@ __global__ void __launch_bounds__(kFmmWaves * kWave, 4) k_fmm_leaf(const Cell* _
                                                   const FmmGeo* __restrict__ geo, const double* __restrict__ lam,
                                                   const uint64_t* __restrict__ pkeys, const uint32_t* __restrict__ poff,
                                                   const uint32_t* __restrict__ task, const uint32_t* __restrict__ toff,
-                                                  const uint32_t* __restrict__ soff, int64_t ntasks, double* __restrict__ part,
+                                                  const uint32_t* __restrict__ soff, int64_t ntasks,
+                                                  const uint32_t* __restrict__ longs, int64_t nlong, double* __restrict__ part,
                                                   float G, float eps2, float* __restrict__ acc, float* __restrict__ pot) {
     constexpr int kAhead = 4;               // entries read ahead per lane
     constexpr int kPlain = 32;              // FP32 terms per lane between additions in FP64
@@ -673,8 +731,9 @@ __global__ void __launch_bounds__(kFmmWaves * kWave, 4) k_fmm_leaf(const Cell* _
     int32_t* SB = s_beg[wv];
     uint64_t* ST = s_start[wv];
     const uint64_t upto = ~0ull >> (kWave - 1 - lane);
-    const int64_t tk = blockIdx.x * (int64_t)kFmmWaves + __builtin_amdgcn_readfirstlane(wv);
-    if (tk >= ntasks) return;
+    const int64_t at = blockIdx.x * (int64_t)kFmmWaves + __builtin_amdgcn_readfirstlane(wv);
+    if (at >= nlong + ntasks) return;
+    const int64_t tk = at < nlong ? (int64_t)longs[at] : at - nlong;
     {
         const uint32_t A = task[tk];
         const uint32_t chunk = (uint32_t)tk - toff[A], nchunks = toff[A + 1] - toff[A];
@@ -682,6 +741,7 @@ __global__ void __launch_bounds__(kFmmWaves * kWave, 4) k_fmm_leaf(const Cell* _
         const double zx = geo[A].z[0], zy = geo[A].z[1], zz = geo[A].z[2];
         const uint32_t q0 = poff[A] + chunk * kFmmChunk;
         const uint32_t q1 = nchunks > 1 ? min(poff[A + 1], q0 + kFmmChunk) : poff[A + 1];
+        if (at >= nlong && long_task(q1 - q0)) return;       // done from the list
         for (int t0 = 0; t0 < ca.count; t0 += kWave) {
             const int nA = min(kWave, ca.count - t0);
             const int H = (nA + 1) / 2, S = kWave / H;
@@ -960,30 +1020,32 @@ hipError_t launch_fmm_l2l(const Cell* cells, const FmmGeo* geo, const uint32_t* 
 }
 
 hipError_t launch_fmm_tasks(const Cell* cells, const uint32_t* poff, const DevParams* prm, int64_t cmax,
-                            uint32_t* ntask, uint32_t* nslot, hipStream_t s) {
-    hipLaunchKernelGGL(k_fmm_tasks_count, dim3(grid_for(cmax)), dim3(256), 0, s, cells, poff, prm, cmax, ntask, nslot);
+                            uint32_t* ntask, uint32_t* nslot, unsigned long long* ctr, hipStream_t s) {
+    hipLaunchKernelGGL(k_fmm_tasks_count, dim3(grid_for(cmax)), dim3(256), 0, s, cells, poff, prm, cmax, ntask, nslot,
+                       ctr);
     return hipGetLastError();
 }
 
-hipError_t launch_fmm_tasks_fill(const uint32_t* toff, const DevParams* prm, int64_t cmax, uint32_t* task,
-                                 hipStream_t s) {
-    hipLaunchKernelGGL(k_fmm_tasks_fill, dim3(grid_for(cmax)), dim3(256), 0, s, toff, prm, cmax, task);
+hipError_t launch_fmm_tasks_fill(const uint32_t* toff, const uint32_t* poff, const DevParams* prm, int64_t cmax,
+                                 uint32_t* task, uint32_t* longs, unsigned long long* ctr, hipStream_t s) {
+    hipLaunchKernelGGL(k_fmm_tasks_fill, dim3(grid_for(cmax)), dim3(256), 0, s, toff, poff, prm, cmax, task, longs,
+                       reinterpret_cast<uint32_t*>(ctr + 3));
     return hipGetLastError();
 }
 
 hipError_t launch_fmm_leaf(const Cell* cells, const Body* bodies, const float4* bodies32, const uint32_t* perm,
                            const FmmGeo* geo, const double* lam, const uint64_t* pkeys, const uint32_t* poff,
                            const uint32_t* task, const uint32_t* toff, const uint32_t* soff, int64_t ntasks,
-                           double* part, const DevParams* prm, int64_t cmax, float G, float eps2, float* acc,
-                           float* pot, hipStream_t s) {
+                           const uint32_t* longs, int64_t nlong, double* part, const DevParams* prm, int64_t cmax,
+                           float G, float eps2, float* acc, float* pot, hipStream_t s) {
     if (ntasks > 0) {
-        const dim3 grid((unsigned)((ntasks + kFmmWaves - 1) / kFmmWaves)), block(kFmmWaves * kWave);
+        const dim3 grid((unsigned)((nlong + ntasks + kFmmWaves - 1) / kFmmWaves)), block(kFmmWaves * kWave);
         if (bodies32)
             hipLaunchKernelGGL(k_fmm_leaf<true>, grid, block, 0, s, cells, bodies, bodies32, perm, geo, lam, pkeys, poff,
-                               task, toff, soff, ntasks, part, G, eps2, acc, pot);
+                               task, toff, soff, ntasks, longs, nlong, part, G, eps2, acc, pot);
         else
             hipLaunchKernelGGL(k_fmm_leaf<false>, grid, block, 0, s, cells, bodies, bodies32, perm, geo, lam, pkeys,
-                               poff, task, toff, soff, ntasks, part, G, eps2, acc, pot);
+                               poff, task, toff, soff, ntasks, longs, nlong, part, G, eps2, acc, pot);
     }
     int64_t fb = (cmax + 3) / 4;
     if (fb > 65536) fb = 65536;

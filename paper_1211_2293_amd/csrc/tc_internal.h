@@ -340,7 +340,8 @@ struct __align__(16) FmmGeo {
 // contiguous there), child count with bit 31 set for a leaf, and level.
 constexpr int kFmmMaxWaves = 8192;      // waves per traversal launch: what the chip holds at once
 // Counters of the traversal: [1], [2] M2L and P2P pairs so far; from kFmmSizes
-// on a ring of level sizes.
+// on a ring of level sizes; of the leaf tasks: [3] tasks << 32 | long ones,
+// [0] partial slots.
 constexpr int kFmmCounters = 32, kFmmSizes = 4, kFmmRing = kFmmCounters - kFmmSizes;
 struct __align__(16) DttCell {
     double z[3];
@@ -365,12 +366,13 @@ hipError_t launch_fmm_m2l(const Moments* mom, const FmmGeo* geo, const DevParams
 hipError_t launch_fmm_l2l(const Cell* cells, const FmmGeo* geo, const uint32_t* bfs2pre, const uint32_t* lvl_off,
                           int level, int64_t count, double* lam, hipStream_t s);
 hipError_t launch_fmm_tasks(const Cell* cells, const uint32_t* poff, const DevParams* prm, int64_t cmax,
-                            uint32_t* ntask, uint32_t* nslot, hipStream_t s);
-hipError_t launch_fmm_tasks_fill(const uint32_t* toff, const DevParams* prm, int64_t cmax, uint32_t* task,
-                                 hipStream_t s);
+                            uint32_t* ntask, uint32_t* nslot, unsigned long long* ctr, hipStream_t s);
+hipError_t launch_fmm_tasks_fill(const uint32_t* toff, const uint32_t* poff, const DevParams* prm, int64_t cmax,
+                                 uint32_t* task, uint32_t* longs, unsigned long long* ctr, hipStream_t s);
 hipError_t launch_fmm_leaf(const Cell* cells, const Body* bodies, const float4* bodies32, const uint32_t* perm,
                            const FmmGeo* geo, const double* lam, const uint64_t* pkeys, const uint32_t* poff,
                            const uint32_t* task, const uint32_t* toff, const uint32_t* soff, int64_t ntasks,
+                           const uint32_t* longs, int64_t nlong,
                            double* part, const DevParams* prm, int64_t cmax, float G, float eps2, float* acc,
                            float* pot, hipStream_t s);
 hipError_t launch_fmm_unpack(const uint64_t* keys, int64_t n, int32_t* out, hipStream_t s);
