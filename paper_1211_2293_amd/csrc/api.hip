@@ -61,7 +61,7 @@ Layout make_layout(int64_t n, int dim, int leaf_cap) {
     l.off_nper = take(4 * (size_t)n);
     l.off_cstart = take(4 * (size_t)(n + 1));
     l.off_scan_part = take(4 * (size_t)l.scan_tiles);
-    l.off_hist = take(4 * 256 * (size_t)l.sort_tiles);
+    l.off_hist = take(4 * 256 * (size_t)l.sort_tiles);   // the radix sort's counts
     l.off_digit_tot = take(4 * 256);
     l.off_cells = take(sizeof(Cell) * (size_t)l.cmax);
     l.off_mom = take(sizeof(Moments) * (size_t)l.cmax);
@@ -117,6 +117,25 @@ Layout make_layout(int64_t n, int dim, int leaf_cap) {
     l.off_split = n <= split_max_n(dim) ? take(16 * (size_t)(dim == 3 ? 64 : 16) * (size_t)n) : 0;
     l.total = off;
     return l;
+}
+
+// The bucket numbers, counts, splitters, totals and starts take the place of
+// what the topology writes later (its ranges, cells and counts per body).
+BodySort body_sort_arrays(const Layout& l, uint8_t* ws) {
+    BodySort a;
+    a.keys_a = reinterpret_cast<uint64_t*>(ws + l.off_keys_a);
+    a.keys_b = reinterpret_cast<uint64_t*>(ws + l.off_keys_b);
+    a.idx_a = reinterpret_cast<uint32_t*>(ws + l.off_idx_a);
+    a.idx_b = reinterpret_cast<uint32_t*>(ws + l.off_idx_b);
+    a.bucket = reinterpret_cast<uint16_t*>(ws + l.off_range);
+    a.hist = reinterpret_cast<uint32_t*>(ws + l.off_cells);
+    a.recs = ws + l.off_recs;
+    const int nb = l.n > kRankMaxN ? bucket_shape(l.n).buckets : 0;   // at most n / 32
+    a.split_key = reinterpret_cast<uint64_t*>(ws + l.off_nper);
+    a.split_idx = reinterpret_cast<uint32_t*>(a.split_key + nb);
+    a.total = a.split_idx + nb;
+    a.start = a.total + nb;
+    return a;
 }
 
 }  // namespace tc
@@ -292,22 +311,7 @@ int do_build(tc_ctx* ctx, const void* pos, const void* mass, int64_t n, int leaf
                                 prm, s));
     }
     if (buckets) {
-        // the bucket numbers, splitters, totals and starts take the place of
-        // what the topology writes later
-        char* nper = ctx->at<char>(l.off_nper);
-        BodySort a;
-        a.keys_a = ctx->at<uint64_t>(l.off_keys_a);
-        a.keys_b = ctx->at<uint64_t>(l.off_keys_b);
-        a.idx_a = ctx->at<uint32_t>(l.off_idx_a);
-        a.idx_b = ctx->at<uint32_t>(l.off_idx_b);
-        a.bucket = ctx->at<uint16_t>(l.off_range);
-        a.hist = ctx->at<uint32_t>(l.off_hist);
-        a.recs = ctx->at<char>(l.off_recs);
-        const int nb = body_buckets(n);
-        a.split_key = reinterpret_cast<uint64_t*>(nper);
-        a.split_idx = reinterpret_cast<uint32_t*>(nper + 8 * (size_t)nb);
-        a.total = a.split_idx + nb;
-        a.start = a.total + nb;
+        const BodySort a = body_sort_arrays(l, ctx->ws);
         const double* part = boxed ? ctx->at<double>(l.off_bbox_part) : nullptr;
         const int parts = bbox_parts(n);
         {

@@ -45,31 +45,6 @@ constexpr int kBucketMax = 2048;                 // buckets
 constexpr int kSampleFused = 1024;               // samples up to which k_splitters computes the keys itself
 constexpr int kFoldTiles = 64;                   // tiles whose counts every scatter block adds up itself
 
-// Buckets, samples and tiles for n bodies: about 256 bodies per bucket while
-// few buckets leave CUs idle, at most 1024 (a quarter of what a block can
-// sort in LDS); the tiles grow with the buckets, so a tile's counts are a
-// quarter of its bodies (256 B / 1024, which is what the workspace holds).
-// Eight samples per bucket bound its size by four times the mean but for
-// about 1e-7 of the buckets; four do for smaller means.
-struct BucketShape {
-    int buckets, samples, tile, tiles;
-};
-BucketShape bucket_shape(int64_t n) {
-    BucketShape b;
-    if (n <= 65536) {
-        b.buckets = 32;
-        while (256 * (int64_t)b.buckets < n) b.buckets *= 2;
-        b.tile = 1024;
-    } else {
-        b.buckets = 256;
-        while (1024 * (int64_t)b.buckets < n) b.buckets *= 2;
-        b.tile = 4 * b.buckets;
-    }
-    b.samples = b.buckets * (n > 512 * (int64_t)b.buckets ? 8 : 4);
-    b.tiles = (int)((n + b.tile - 1) / b.tile);
-    return b;
-}
-
 __device__ __forceinline__ int wave_lane() { return threadIdx.x & (kWave - 1); }
 
 // The root cube from a block's boxes, one per thread (1024 threads); block 0
@@ -746,8 +721,6 @@ void bucket_sort(int64_t n, const BodySort& a, Body* bodies, float4* bodies32, h
     } while (0)
 
 }  // namespace
-
-int body_buckets(int64_t n) { return n <= kRankMaxN ? 0 : bucket_shape(n).buckets; }
 
 hipError_t launch_body_keys(const void* pos, int64_t n, int dim, int f64, const double* part, int parts,
                             DevParams* prm, const BodySort& a, hipStream_t s) {

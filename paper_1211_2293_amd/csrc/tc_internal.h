@@ -156,16 +156,41 @@ hipError_t launch_gather(const void* packed, const uint32_t* perm, int64_t n, in
 // keys_a and idx_a receive the sorted keys and the permutation.
 constexpr int64_t kRankMaxN = 8192;
 constexpr int64_t kBucketMaxN = (int64_t)1 << 21;
+// Buckets, samples and tiles for n bodies: about 256 bodies per bucket while
+// few buckets leave CUs idle, at most 1024 (a quarter of what a block can
+// sort in LDS); the tiles grow with the buckets, so a tile's counts are a
+// quarter of a full tile's bodies (the last tile, full or not, has as many).
+// Eight samples per bucket bound its size by four times the mean but for
+// about 1e-7 of the buckets; four do for smaller means.
+struct BucketShape {
+    int buckets, samples, tile, tiles;
+};
+inline BucketShape bucket_shape(int64_t n) {
+    BucketShape b;
+    if (n <= 65536) {
+        b.buckets = 32;
+        while (256 * (int64_t)b.buckets < n) b.buckets *= 2;
+        b.tile = 1024;
+    } else {
+        b.buckets = 256;
+        while (1024 * (int64_t)b.buckets < n) b.buckets *= 2;
+        b.tile = 4 * b.buckets;
+    }
+    b.samples = b.buckets * (n > 512 * (int64_t)b.buckets ? 8 : 4);
+    b.tiles = (int)((n + b.tile - 1) / b.tile);
+    return b;
+}
 struct BodySort {
     uint64_t *keys_a, *keys_b;   // [n]
     uint32_t *idx_a, *idx_b;     // [n]
     uint16_t* bucket;            // [n]
-    uint32_t* hist;              // tiles x buckets, at most 256 per 1024 bodies (rounded up)
+    uint32_t* hist;              // [tiles][buckets]
     void* recs;                  // 48 n bytes
     uint64_t* split_key;         // [buckets]
     uint32_t *split_idx, *total, *start;   // [buckets], [buckets], [buckets + 1]
 };
-int body_buckets(int64_t n);     // at most n / 32
+// Its arrays in the workspace ws (api.hip).
+BodySort body_sort_arrays(const Layout& l, uint8_t* ws);
 hipError_t launch_body_keys(const void* pos, int64_t n, int dim, int f64, const double* part, int parts,
                             DevParams* prm, const BodySort& a, hipStream_t s);
 hipError_t launch_body_scatter(const void* pos, const void* mass, int64_t n, int dim, int f64, const DevParams* prm,
