@@ -778,7 +778,6 @@ int tc_fmm_plan(tc_ctx* ctx, double theta, void* buf, size_t bytes, int64_t fron
     ctx->fmm_capf = f.capf;
     ctx->fmm_capm = f.capm;
     ctx->fmm_capp = f.capp;
-    ctx->theta = theta;
     ctx->fmm_planned = true;
     return TC_OK;
 }

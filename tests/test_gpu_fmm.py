@@ -203,3 +203,29 @@ def test_plan_capacities_and_retry():
     torch.cuda.synchronize()
     np.testing.assert_array_equal(acc.cpu().numpy(), a2.cpu().numpy())
     np.testing.assert_array_equal(pot.cpu().numpy(), p2.cpu().numpy())
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_a_plan_leaves_the_walks_theta_alone(graph):
+    """A leapfrog step walks at the theta of the last walk() whatever a plan
+    made in between (at a theta that a walk would refuse, too): the same bits
+    as without the plan."""
+    w = workloads.plummer_sphere(3000, seed=79)
+    dev = torch.device("cuda:0")
+    out = []
+    for plan in (None, 0.9, 1.7):
+        pos, vel, mass = (torch.from_numpy(a).to(dev) for a in (w.pos, w.vel, w.mass))
+        tc = treecode.Treecode(3, leaf_cap=16)
+        tc.set_graph(graph)
+        tc.build(pos, mass)
+        tc.moments()
+        tc.walk(0.4)
+        tc.forces(1.0, 1e-2)
+        if plan is not None:
+            tc.fmm_plan(plan)
+        for _ in range(3):
+            tc.leapfrog(1e-2, pos, vel)
+        out.append((pos.cpu().numpy(), vel.cpu().numpy(), tc.counts()[0].cpu().numpy()))
+    for got in out[1:]:
+        for a, b in zip(got, out[0]):
+            np.testing.assert_array_equal(a, b)
