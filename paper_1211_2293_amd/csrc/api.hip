@@ -472,7 +472,7 @@ int do_forces_learned(tc_ctx* ctx, double G, double eps, double tau) {
     return TC_OK;
 }
 
-// acc, pot: where the caller also wants the results, or null.
+// acc, pot: where the kernels also put the results, or null.
 int do_forces(tc_ctx* ctx, double G, double eps, float* acc = nullptr, float* pot = nullptr) {
     const Layout& l = ctx->lay;
     const ForceOut out{ctx->at<float>(l.off_acc), ctx->at<float>(l.off_pot), acc, pot};
@@ -522,6 +522,21 @@ int do_forces(tc_ctx* ctx, double G, double eps, float* acc = nullptr, float* po
     ctx->eps = eps;
     ctx->state = kForced;
     ctx->tests_kept = !(ctx->split == 2 && ctx->n <= split_max_n(ctx->dim));
+    return TC_OK;
+}
+
+// Forces for a caller that wants them in acc and pot (each may be null).
+int forces_out(tc_ctx* ctx, double G, double eps, float* acc, float* pot) {
+    if (ctx->n <= kDirectOutMax) return do_forces(ctx, G, eps, acc, pot);
+    const int rc = do_forces(ctx, G, eps);
+    if (rc != TC_OK) return rc;
+    const Layout& l = ctx->lay;
+    if (acc)
+        TC_HIP(ctx, hipMemcpyAsync(acc, ctx->at<float>(l.off_acc), 4 * (size_t)ctx->n * ctx->dim,
+                                   hipMemcpyDeviceToDevice, ctx->stream));
+    if (pot)
+        TC_HIP(ctx, hipMemcpyAsync(pot, ctx->at<float>(l.off_pot), 4 * (size_t)ctx->n, hipMemcpyDeviceToDevice,
+                                   ctx->stream));
     return TC_OK;
 }
 
@@ -907,7 +922,7 @@ int tc_forces(tc_ctx* ctx, double G, double eps, void* acc, void* pot) {
     if (!(eps > 0.0) || !isfinite(eps) || !isfinite(G)) return TC_EINVAL;
     if ((acc && !aligned(acc, 4)) || (pot && !aligned(pot, 4))) return TC_EINVAL;
     if (ctx->state < kWalked || !ctx->theta_set) return TC_ESTATE;
-    return do_forces(ctx, G, eps, (float*)acc, (float*)pot);
+    return forces_out(ctx, G, eps, (float*)acc, (float*)pot);
 }
 
 int tc_leapfrog(tc_ctx* ctx, double dt, void* pos, void* vel) {
@@ -1211,7 +1226,7 @@ int tc_forces_noalloc(tc_ctx* ctx, const void* pos, const void* mass, int64_t n,
     rc = do_build(ctx, pos, mass, n, leaf_cap, dtype, s);
     if (rc == TC_OK) rc = do_moments(ctx, s);
     if (rc == TC_OK) rc = do_walk(ctx, theta, s);
-    if (rc == TC_OK) rc = do_forces(ctx, G, eps, (float*)acc, (float*)pot);
+    if (rc == TC_OK) rc = forces_out(ctx, G, eps, (float*)acc, (float*)pot);
     ctx->timing = timing;
     ctx->stage_timing = stage_timing;
     return rc;

@@ -267,10 +267,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUAD ?
                 const float sself = __builtin_amdgcn_rsqf(eps2);
                 const float ph = (float)(a.sp + (double)(mself * sself));
                 const int64_t o = perm[i];
-                out.put_acc(o * D + 0, G * (float)a.sx);
-                out.put_acc(o * D + 1, G * (float)a.sy);
-                if (D == 3) out.put_acc(o * D + 2, G * (float)a.sz);
-                out.put_pot(o, G * ph);
+                out.put<D>(o, G * (float)a.sx, G * (float)a.sy, G * (float)a.sz, G * ph);
                 // the list length, for the next evaluation's schedule
                 const int64_t lc = nm2p + np2p;
                 bcost[o] = lc > 0xffffffffll ? 0xffffffffu : (uint32_t)lc;
@@ -662,10 +659,8 @@ __global__ void __launch_bounds__(256) k_split_reduce(const float4* __restrict__
         const float mself = (float)bodies[i].m;
         ap += (double)(mself * __builtin_amdgcn_rsqf(eps2));
         const int64_t o = perm[i];
-        out.put_acc(o * D + 0, (float)((double)G * ax));
-        out.put_acc(o * D + 1, (float)((double)G * ay));
-        if (D == 3) out.put_acc(o * D + 2, (float)((double)G * az));
-        out.put_pot(o, (float)((double)G * ap));
+        out.put<D>(o, (float)((double)G * ax), (float)((double)G * ay), (float)((double)G * az),
+                   (float)((double)G * ap));
     }
 }
 

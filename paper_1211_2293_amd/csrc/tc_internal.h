@@ -244,8 +244,7 @@ hipError_t launch_export(const Cell* cells, const Moments* mom, int dim, int64_t
 // order: room for 2 gmax uint32 (places, costs) and gmax uint16 keys; bcost:
 // n uint32 per-body list lengths, written for the next call's schedule.
 // Where the force kernels put their results: the copies that the next step and
-// the diagnostics read and, where given, the caller's arrays, which cost a store
-// beside each of these where a copy of them afterwards cost two launches (9 us).
+// the diagnostics read and, where given, the caller's arrays.
 struct ForceOut {
     float *acc, *pot, *user_acc, *user_pot;
     __device__ __forceinline__ void put_acc(int64_t at, float v) const {
@@ -256,7 +255,29 @@ struct ForceOut {
         pot[at] = v;
         if (user_pot) user_pot[at] = v;
     }
+    // body o's whole result, its components side by side in each array
+    template <int D>
+    __device__ __forceinline__ void put(int64_t o, float x, float y, float z, float p) const {
+        put_vec<D>(acc + o * D, x, y, z);
+        pot[o] = p;
+        if (user_acc) put_vec<D>(user_acc + o * D, x, y, z);
+        if (user_pot) user_pot[o] = p;
+    }
+    template <int D>
+    static __device__ __forceinline__ void put_vec(float* a, float x, float y, float z) {
+        a[0] = x;
+        a[1] = y;
+        if (D == 3) a[2] = z;
+    }
 };
+// Up to kDirectOutMax bodies the kernels store into the caller's arrays too;
+// beyond, the arrays are copied: bodies lie in the caller's order, so the
+// stores go to scattered lines, and a second set of these costs more than two
+// copies once the sets outgrow the caches.  Measured (tc_forces, stores / copies,
+// us): 3D 10,000 bodies 57 / 62, 1,048,576 1,694 / 1,702, 4,000,000 (theta 1)
+// 1,917 / 1,892; 2D 262,144 140 / 142, 1,500,000 591 / 594, 3,000,000 1,070 /
+// 1,057 and at theta 0.8 924 / 877.
+constexpr int64_t kDirectOutMax = 3 << 19;
 hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Body* bodies, const float4* bodies32,
                              const uint32_t* perm,
                              const int32_t* gbeg, const int32_t* gcnt, int64_t gmax, uint32_t* order,

@@ -329,3 +329,40 @@ def test_shared_walk_shapes(dim, n, lc, theta, order):
     # both sum chunks of 64 entries in FP32 (at most 64 x 2^-24 of a chunk,
     # of either sign) and fold them with compensation: 2^-20 covers the two
     assert oracle.rel_l2(out[1][0], out[0][0]) < 2.0 ** -20 and oracle.rel_l2(out[1][1], out[0][1]) < 2.0 ** -20
+
+
+@pytest.mark.parametrize("dim,n", [(2, 3 << 19), (2, (3 << 19) + 1), (3, (3 << 19) + 1), (3, 4097)])
+def test_results_reach_whichever_arrays_are_given(dim, n):
+    """The kernels store into the caller's arrays up to 1,572,864 bodies and
+    the results are copied beyond: the same bits in either array whether both,
+    one or none is given, and in what the diagnostics read."""
+    from paper_1211_2293_amd import treecode
+    from tests.gpu_util import to_dev
+    w = workloads.plummer_sphere(n, seed=93) if dim == 3 else workloads.gaussian_disk(n, seed=94)
+    pos, vel, mass = to_dev(w.pos), to_dev(w.vel), to_dev(w.mass)
+    tc = treecode.Treecode(dim, leaf_cap=64)
+    tc.build(pos, mass)
+    tc.moments()
+    tc.walk(0.9)
+    import torch
+    nan = float("nan")
+    got = []
+    for has_acc, has_pot in ((True, True), (True, False), (False, True), (False, False)):
+        acc = torch.full((n, dim), nan, device="cuda")
+        pot = torch.full((n,), nan, device="cuda")
+        assert treecode.lib().tc_forces(tc._h, 1.0, 1e-2, acc.data_ptr() if has_acc else None,
+                                        pot.data_ptr() if has_pot else None) == 0
+        d = tc.diag(vel)
+        got.append((acc, pot, d))
+        assert bool(torch.isfinite(acc).all()) == has_acc and bool(torch.isnan(acc).all()) != has_acc
+        assert bool(torch.isfinite(pot).all()) == has_pot and bool(torch.isnan(pot).all()) != has_pot
+    both = got[0]
+    assert torch.equal(both[0], got[1][0]) and torch.equal(both[1], got[2][1])
+    for _, _, d in got[1:]:
+        np.testing.assert_array_equal(d, both[2])
+    # what the diagnostics read is what the caller got
+    m = mass.double()
+    assert abs(both[2][1] - 0.5 * float((m * both[1].double()).sum())) <= 1e-12 * abs(both[2][1])
+    mom = (m[:, None] * both[0].double()).sum(0).cpu().numpy()
+    scale = float((m * both[0].double().norm(dim=1)).sum())
+    np.testing.assert_allclose(both[2][5:5 + dim], mom, rtol=0, atol=1e-12 * scale)
