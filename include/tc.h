@@ -212,8 +212,9 @@ int tc_fmm_get_pairs(tc_ctx *ctx, int32_t *m2l, int32_t *p2p);
 
 /* How a group's walk is spread over waves, for sizes with fewer walk groups
  * than the GPU keeps waves resident, where one wave per group leaves a lone,
- * latency-bound walk per SIMD.  mode 1 (the default): for n <= 524288 in 3D
- * and n <= 163840 in 2D a block of 2 to 8 waves (by n and dim) shares each
+ * latency-bound walk per SIMD.  mode 1 (the default): for n <= 163840 in 2D
+ * and n <= min(524288, 262144 / theta) in 3D (196608 / theta with
+ * quadrupoles) a block of 2 to 8 waves (by n, dim and theta) shares each
  * group's walk and list and adds their FP32 partial sums in FP64 in wave
  * order.  mode 2: for n <= 12288 in 3D and n <= 24576 in 2D
  * each group's walk is cut into one task per (level-1 cell, child) (64 in

@@ -511,7 +511,7 @@ int do_forces(tc_ctx* ctx, double G, double eps, float* acc = nullptr, float* po
                                       ctx->dim, ctx->leaf_cap,
                                       (float)G, (float)(eps * eps), ctx->prm(), out, ctx->at<int64_t>(l.off_m2p),
                                       ctx->at<int64_t>(l.off_p2p), ctx->at<int64_t>(l.off_tests), ctx->plain_acc,
-                                      ctx->split != 0, ctx->stream));
+                                      ctx->split != 0, ctx->theta, ctx->stream));
     }
     if (ctx->timing) {
         TC_HIP(ctx, hipEventRecord(e1, ctx->stream));

@@ -878,7 +878,7 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
                              int64_t n, int dim, int leaf_cap, float G, float eps2,
                              const DevParams* prm, const ForceOut& out, int64_t* m2p,
                              int64_t* p2p, int64_t* tests, bool plain, bool share,
-                             hipStream_t s) {
+                             double theta, hipStream_t s) {
     // as many blocks as can be resident at once (the waves are persistent)
     static int resident[3] = {0, 0, 0};                // 2D, 3D, 3D with quadrupoles
     const int kind = dim == 3 ? (walkq ? 2 : 1) : 0;
@@ -908,11 +908,11 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
         hipLaunchKernelGGL(k_group_order, dim3(kXcd), dim3(kOrderThreads), 0, s, (const uint32_t*)bcost, perm, gbeg,
                            gcnt, prm, gcost, ckey, order, queue, (uint32_t)(nb * kWavesPerBlock));
     };
-    if (share && n <= coop_max_n(dim)) {
+    if (share && n <= coop_max_n(dim, theta, walkq != nullptr)) {
         // one block per task at a time, as many blocks as can be resident;
         // with about one task per block (coop_shape) no order is made: it
         // would cost its launch and change nothing
-        const CoopShape shape = coop_shape(n, dim);
+        const CoopShape shape = coop_shape(n, dim, theta);
         if (shape.ordered) make_order();
         const uint32_t* places = shape.ordered ? order : nullptr;
         unsigned cb = 0;

@@ -284,7 +284,7 @@ hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Bo
                              uint32_t* queue, uint32_t* bcost, int64_t n, int dim, int leaf_cap, float G, float eps2,
                              const DevParams* prm, const ForceOut& out, int64_t* m2p,
                              int64_t* p2p, int64_t* tests, bool plain, bool share,
-                             hipStream_t s);
+                             double theta, hipStream_t s);
 hipError_t launch_scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* part, int64_t tiles,
                            hipStream_t s);
 // closure.hip
@@ -300,17 +300,30 @@ hipError_t launch_direct64(const Body* bodies, const uint32_t* inv_perm, int64_t
 constexpr int64_t kSplitMaxN3 = 12288;
 constexpr int64_t kSplitMaxN2 = 24576;
 inline int64_t split_max_n(int dim) { return dim == 3 ? kSplitMaxN3 : kSplitMaxN2; }
-// Up to coop_max_n(dim), one block of waves shares each group's walk and
-// list (k_walk_force_coop); beyond, one wave per group.  Measured (force
-// evaluation, one wave / shared): 3D Plummer 425 / 61 us at 10,000 bodies,
-// 491 / 219 at 100,000, 506 / 371 at 200,000, 788 / 736 at 400,000 and
-// 1,830 / 1,874 at 1,048,576; 2D disk 96 / 43 us at 50,000, 121 / 90 at
-// 160,000, 115 / 143 at 262,144.  tc_set_split(ctx, 0) turns it off;
-// tc_set_split(ctx, 2) uses the split walks (above) for n <=
-// split_max_n(dim) instead.
-constexpr int64_t kCoopMaxN3 = 524288;
+// Up to coop_max_n bodies, one block of waves shares each group's walk and
+// list (k_walk_force_coop); beyond, one wave per group.  Shared walks pay by
+// evening out the lists, the less the shorter these are, so in 3D the line
+// falls as theta rises, and it is lower with quadrupoles, whose sums weigh
+// more.  Measured (tc_forces in us, one wave / shared):
+//   3D Plummer, theta 0.5: 347 / 57 at 10,000 bodies, 544 / 479 at 262,144,
+//     716 / 686 at 400,000, 880 / 879 at 524,288; theta 0.7: 360 / 340 at
+//     330,000, 388 / 405 at 400,000; theta 1: 205 / 208 at 262,144, 341 / 380 at
+//     524,288;
+//   3D cube, theta 0.5: 592 / 593 at 524,288; theta 0.7: 236 / 235 at 330,000,
+//     337 / 369 at 524,288; theta 1: 128 / 124 at 200,000, 246 / 283 at 524,288;
+//   quadrupoles, Plummer and cube, theta 0.3: 4,993 / 4,383 and 2,263 / 2,277 at
+//     524,288; theta 0.5: 1,186 / 1,169 and 646 / 668 at 400,000; theta 0.7: 476 / 451 and 236 / 246 at 262,144; theta 1: 270 / 252
+//     and 170 / 157 at 200,000, 363 / 386 and 230 / 238 at 330,000;
+//   2D disk: 107 / 85 at 163,840 (theta 0.5) and 79 / 68 (theta 1), 115 / 143
+//     at 262,144.
+// tc_set_split(ctx, 0) turns it off; tc_set_split(ctx, 2) uses the split walks
+// (above) for n <= split_max_n(dim) instead.
 constexpr int64_t kCoopMaxN2 = 163840;
-inline int64_t coop_max_n(int dim) { return dim == 3 ? kCoopMaxN3 : kCoopMaxN2; }
+inline int64_t coop_max_n(int dim, double theta, bool quad) {
+    if (dim != 3) return kCoopMaxN2;
+    const double line = quad ? 196608 : 262144;          // theta n up to which sharing pays
+    return theta * 524288 <= line ? 524288 : (int64_t)(line / theta);
+}
 // How a block shares a group: its waves, the tasks (of 64 / parts bodies) a
 // group is cut into, and whether the longest walks are sent first
 // (k_group_order).  More waves shorten one group's walk and sums, where the
@@ -319,18 +332,23 @@ inline int64_t coop_max_n(int dim) { return dim == 3 ? kCoopMaxN3 : kCoopMaxN2; 
 // 10,000 bodies, 8 waves x 2 parts 61, 8 x 1 78, 8 x 4 83, 4 x 1 113, 16 x
 // 1 77; 20,000: 8 x 1 86, 4 x 2 100, 8 x 2 107, 4 x 1 108; 35,000: 8 x 1
 // 108, 4 x 1 122; 50,000: 4 x 1 149, 8 x 1 160, 2 x 1 208; 100,000: 219,
-// 267, 276.  2D disk: 20,000: 8 waves 34, 4 waves 39; 50,000: 4 waves 43,
-// 2 waves 55, 8 waves 57; 160,000: 2 waves 90, 4 waves 103.  Up to 12,288
-// bodies about every task has a block of its own, and skipping the order
-// takes 4,096 bodies (8 x 2) from 31 to 24 us.
+// 267, 276.  2D disk (theta 0.5): 20,000: 8 waves 34, 4 waves 38; 40,000: 4 waves
+// 40, 8 waves 48; 100,000: 2 waves 66, 4 waves 66.  There four waves hold out
+// longer at a small theta, whose lists are long (theta 0.3 / 0.7 / 1, 4 and 2
+// waves: 70,000 bodies 67 43 39 and 81 49 46; 90,000 82 53 51 and 98 52 45;
+// 140,000 113 81 79 and 111 57 51).  While about every task has a block of its
+// own (12,288 bodies of two tasks a group, 30,000 of one in 2D, where the walks
+// differ least) the order is skipped: 4,096 bodies in 3D 31 -> 24 us, 14,000 in
+// 2D 32 -> 23, 30,000 37 -> 29.
 struct CoopShape {
     int waves, parts;
     bool ordered;
 };
-inline CoopShape coop_shape(int64_t n, int dim) {
-    if (n <= 12288) return {8, dim == 3 ? 2 : 1, false};
-    if (dim == 3) return n <= 40000 ? CoopShape{8, 1, true} : CoopShape{4, 1, true};
-    return n <= 30000 ? CoopShape{8, 1, true} : n <= 100000 ? CoopShape{4, 1, true} : CoopShape{2, 1, true};
+inline CoopShape coop_shape(int64_t n, int dim, double theta) {
+    if (dim == 3) return n <= 12288 ? CoopShape{8, 2, false} : CoopShape{n <= 40000 ? 8 : 4, 1, true};
+    if (n <= 30000) return {8, 1, false};
+    const double k = (double)n / 100000;                 // 4 waves up to 100,000 sqrt(0.5 / theta) bodies
+    return {k * k * theta <= 0.5 ? 4 : 2, 1, true};
 }
 hipError_t launch_walk_force_split(const WalkCell* walk, const float4* walkq, const Body* bodies,
                                    const float4* bodies32, const uint32_t* perm, const int32_t* gbeg,

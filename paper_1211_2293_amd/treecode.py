@@ -476,7 +476,7 @@ class Treecode:
 
     def set_split(self, mode):
         """How a group's walk is spread over waves: 1 or True (default) a
-        block of waves shares each group's walk for n <= 524288 (2D: 163840); 2 split
+        block of waves shares each group's walk for small and mid n (see tc.h); 2 split
         walks for n <= 12288 in 3D and n <= 24576 in 2D, else as 1; 0 or
         False one wave per group at any n."""
         mode = int(mode)

@@ -366,3 +366,34 @@ def test_results_reach_whichever_arrays_are_given(dim, n):
     mom = (m[:, None] * both[0].double()).sum(0).cpu().numpy()
     scale = float((m * both[0].double().norm(dim=1)).sum())
     np.testing.assert_allclose(both[2][5:5 + dim], mom, rtol=0, atol=1e-12 * scale)
+
+
+@pytest.mark.parametrize("dim,n,theta,order", [
+    (3, 524288, 0.5, 1), (3, 524289, 0.5, 1), (3, 374491, 0.7, 1), (3, 374492, 0.7, 1), (3, 262144, 1.0, 1),
+    (3, 393216, 0.5, 2), (3, 393217, 0.5, 2), (3, 524288, 0.375, 2), (3, 196608, 1.0, 2), (3, 196609, 1.0, 2),
+    (2, 30000, 0.8, 1), (2, 30001, 0.8, 1), (2, 100000, 0.5, 1), (2, 70710, 1.0, 1), (2, 70711, 1.0, 1),
+    (2, 163840, 0.1, 1), (2, 163841, 0.7, 1), (2, 31000, 0.0, 1)])
+def test_shared_walk_shapes_by_theta(dim, n, theta, order):
+    """Both sides of the sizes where the shared walk begins and changes its
+    shape, which depend on the opening parameter, against one wave per group:
+    equal interactions, counts and tested cells, forces to summation order."""
+    from paper_1211_2293_amd import treecode
+    from tests.gpu_util import to_dev
+    w = workloads.plummer_sphere(n, seed=95) if dim == 3 else workloads.gaussian_disk(n, seed=96)
+    tc = treecode.Treecode(dim, leaf_cap=16)
+    keep = (to_dev(w.pos), to_dev(w.mass))
+    tc.build(*keep)
+    tc.moments()
+    tc.walk(theta)
+    tc.set_multipole(order)
+    out = {}
+    for mode in (0, 1):
+        tc.set_split(mode)
+        acc, pot = tc.forces(1.0, 1e-2)
+        out[mode] = [v.cpu().numpy() for v in (acc, pot, *tc.counts(), tc.tests())]
+    for k in (2, 3, 4):
+        np.testing.assert_array_equal(out[1][k], out[0][k])
+    # both add FP32 sums of at most 64 entries in FP64: each such sum is off by
+    # at most 64 x 2^-24 of its terms, of either sign, so 2^-18 would be the worst
+    # case and 2^-20 leaves room over the random one (sqrt(64) x 2^-24)
+    assert oracle.rel_l2(out[1][0], out[0][0]) < 2.0 ** -20 and oracle.rel_l2(out[1][1], out[0][1]) < 2.0 ** -20
