@@ -1092,6 +1092,12 @@ __global__ void __launch_bounds__(kTileThreads) k_tree_groups(const Cell* __rest
 
 // ------------------------------------------------------------- moments ----
 
+// A leaf's moments by one lane, bodies in order: bound by the latency of its
+// reads, four bodies at a time.  The barrier keeps all four of the quadrupole's
+// ahead of its arithmetic; to save registers the compiler waited for them in two
+// halves (a leaf of 250,000 coincident bodies 58.7 -> 48.7 ms, 4M bodies whose
+// cluster ends in leaves at the deepest level 1.13 -> 0.92 ms for the moments,
+// 16.7M clustered bodies 742 -> 721 us, 1M in leaves of 64 63 -> 59).
 template <int D>
 __device__ void leaf_moments(const Cell& c, const Body* __restrict__ bodies, Moments& mo) {
     double M = 0.0, S0 = 0.0, S1 = 0.0, S2 = 0.0;
@@ -1108,9 +1114,7 @@ __device__ void leaf_moments(const Cell& c, const Body* __restrict__ bodies, Mom
     mo.com[0] = S0 / M; mo.com[1] = S1 / M; mo.com[2] = D == 3 ? S2 / M : 0.0;
     double Q[6] = {0, 0, 0, 0, 0, 0};
     if (D == 3) {
-#pragma unroll 4
-        for (int32_t j = c.begin; j < c.begin + c.count; ++j) {
-            const Body b = bodies[j];
+        auto add = [&](const Body& b) {
             const double d0 = b.x - mo.com[0], d1 = b.y - mo.com[1], d2 = b.z - mo.com[2];
             const double r2 = (d0 * d0 + d1 * d1) + d2 * d2;
             Q[0] = Q[0] + b.m * ((3.0 * d0) * d0 - r2);
@@ -1119,7 +1123,18 @@ __device__ void leaf_moments(const Cell& c, const Body* __restrict__ bodies, Mom
             Q[3] = Q[3] + b.m * ((3.0 * d0) * d1);
             Q[4] = Q[4] + b.m * ((3.0 * d0) * d2);
             Q[5] = Q[5] + b.m * ((3.0 * d1) * d2);
+        };
+        const int32_t end = c.begin + c.count;
+        int32_t j = c.begin;
+        for (; j + 4 <= end; j += 4) {
+            Body b[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) b[u] = bodies[j + u];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add(b[u]);
         }
+        for (; j < end; ++j) add(bodies[j]);
     }
     for (int q = 0; q < 6; ++q) mo.Q[q] = Q[q];
     mo.pad = 0.0;

@@ -242,3 +242,22 @@ def test_moments_on_both_sides_of_each_shape(dim, n, lc):
     g = gpu_tree(pos, mass, lc)
     assert g["status"] == 0
     assert_tree_equal(g, oracle.Tree(pos.astype(np.float64), mass.astype(np.float64), lc))
+
+
+@pytest.mark.parametrize("dim,sizes", [(3, (1, 2, 3, 4, 5, 7, 8, 9, 63, 64, 65, 257, 3001)), (2, (1, 3, 4, 5, 8, 65, 257, 3001))])
+def test_moments_of_leaves_of_every_remainder(dim, sizes):
+    """Leaves of coincident places, each of the given number of bodies (beyond
+    leaf_cap at the deepest level): masses, centres and quadrupoles bit for bit
+    against the oracle, which sums a leaf's bodies in order."""
+    rng = np.random.default_rng(65)
+    at = rng.uniform(-1.0, 1.0, (len(sizes), dim))
+    # a cloud below the resolution of the deepest level around each place
+    pos = np.concatenate([a + rng.uniform(0.0, 2.0 ** -30 if dim == 3 else 2.0 ** -40, (s, dim))
+                          for a, s in zip(at, sizes)])
+    pos = pos[rng.permutation(len(pos))]
+    mass = rng.uniform(0.5, 2.0, len(pos))
+    g = gpu_tree(pos, mass, 1)
+    assert g["status"] == 0
+    t = oracle.Tree(pos, mass, 1)
+    assert_tree_equal(g, t)
+    assert g["cells"]["count"][g["cells"]["leaf"] == 1].max() > 2000
