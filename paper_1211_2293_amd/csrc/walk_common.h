@@ -4,6 +4,7 @@
 
 #include "tc_internal.h"
 
+#include <float.h>
 #include <math.h>
 
 namespace tc {
@@ -42,9 +43,11 @@ static __device__ __forceinline__ double uniform(double v) {
 
 // (r2)^(-1/2) in FP64: the hardware's approximation and one step of third
 // order (relative error 2^-53 or so: the step's own is the cube of 2^-26).
+// 0 for an infinite r2 (a softening whose square overflows), which the step must
+// not multiply by the approximation's 0.
 static __device__ __forceinline__ double rsqrt64(double r2) {
     const double y = __builtin_amdgcn_rsq(r2);
-    const double e = fma(-r2 * y, y, 1.0);
+    const double e = fma(-fmin(r2, DBL_MAX) * y, y, 1.0);
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 

@@ -416,3 +416,19 @@ def test_learned_walk_by_blocks(n, theta_l, theta_p):
         np.testing.assert_array_equal(learned[0], ref["per_group"])
     else:
         assert learned[0].max() > 512
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_residuals_under_a_softening_whose_square_overflows(dtype):
+    """eps is finite, eps^2 is not: the exact sum and the monopole vanish, as
+    1 / sqrt(inf) does, in cells summed by lanes, by a wave and by a block."""
+    w = workloads.plummer_sphere(40000, seed=98)
+    tc = treecode.Treecode(3, leaf_cap=16)
+    keep = to_dev(w.pos.astype(dtype)), to_dev(w.mass.astype(dtype))
+    tc.build(*keep)
+    tc.moments()
+    far = np.argsort(-np.linalg.norm(w.pos, axis=1))[:40].astype(np.int32)
+    feat, y, cell = tc.residuals(1.0, 1e160, to_dev(far))
+    count = tc.cells()["count"][cell.long()]
+    assert int(count.max()) > 4096 and int(count.min()) < 128
+    assert bool((y == 0.0).all()) and bool(torch.isfinite(feat).all())

@@ -229,3 +229,12 @@ def test_a_plan_leaves_the_walks_theta_alone(graph):
     for got in out[1:]:
         for a, b in zip(got, out[0]):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_a_softening_whose_square_overflows(dtype):
+    # eps is finite, eps^2 is not: every term vanishes, as 1 / sqrt(inf) does
+    w = workloads.plummer_sphere(3000, seed=80)
+    for theta in (0.7, 0.0):
+        _, _, acc, pot, _, _ = _gpu_fmm(w.pos.astype(dtype), w.mass.astype(dtype), 16, theta, 1e160)
+        assert np.all(acc == 0.0) and np.all(pot == 0.0)
