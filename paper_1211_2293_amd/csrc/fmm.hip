@@ -30,6 +30,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 namespace tc {
@@ -587,6 +588,10 @@ __global__ void __launch_bounds__(256) k_fmm_l2l(const Cell* __restrict__ cells,
 
 constexpr int kFmmList = 256;
 constexpr int kFmmWaves = 1;                // per block: their tasks differ in length
+// Tasks per launch: a grid holds fewer than 2^32 threads, so one launch for all
+// would be refused from 67M tasks on; a launch costs nothing beside 1M tasks.
+constexpr int64_t kFmmLaunch = (int64_t)1 << 20;
+static_assert(kFmmLaunch * kWave < (int64_t)1 << 32, "a launch's threads must fit its grid");
 
 // A target leaf whose partner list is longer than kFmmChunk leaves is cut
 // into chunks of kFmmChunk partners, one task each, so that no single wave
@@ -718,7 +723,7 @@ __global__ void __launch_bounds__(kFmmWaves * kWave, 4) k_fmm_leaf(const Cell* _
                                                   const FmmGeo* __restrict__ geo, const double* __restrict__ lam,
                                                   const uint64_t* __restrict__ pkeys, const uint32_t* __restrict__ poff,
                                                   const uint32_t* __restrict__ task, const uint32_t* __restrict__ toff,
-                                                  const uint32_t* __restrict__ soff, int64_t ntasks,
+                                                  const uint32_t* __restrict__ soff, int64_t first, int64_t ntasks,
                                                   const uint32_t* __restrict__ longs, int64_t nlong, double* __restrict__ part,
                                                   float G, float eps2, float* __restrict__ acc, float* __restrict__ pot) {
     constexpr int kAhead = 4;               // entries read ahead per lane
@@ -731,7 +736,7 @@ __global__ void __launch_bounds__(kFmmWaves * kWave, 4) k_fmm_leaf(const Cell* _
     int32_t* SB = s_beg[wv];
     uint64_t* ST = s_start[wv];
     const uint64_t upto = ~0ull >> (kWave - 1 - lane);
-    const int64_t at = blockIdx.x * (int64_t)kFmmWaves + __builtin_amdgcn_readfirstlane(wv);
+    const int64_t at = first + blockIdx.x * (int64_t)kFmmWaves + __builtin_amdgcn_readfirstlane(wv);
     if (at >= nlong + ntasks) return;
     const int64_t tk = at < nlong ? (int64_t)longs[at] : at - nlong;
     {
@@ -1038,14 +1043,12 @@ hipError_t launch_fmm_leaf(const Cell* cells, const Body* bodies, const float4* 
                            const uint32_t* task, const uint32_t* toff, const uint32_t* soff, int64_t ntasks,
                            const uint32_t* longs, int64_t nlong, double* part, const DevParams* prm, int64_t cmax,
                            float G, float eps2, float* acc, float* pot, hipStream_t s) {
-    if (ntasks > 0) {
-        const dim3 grid((unsigned)((nlong + ntasks + kFmmWaves - 1) / kFmmWaves)), block(kFmmWaves * kWave);
-        if (bodies32)
-            hipLaunchKernelGGL(k_fmm_leaf<true>, grid, block, 0, s, cells, bodies, bodies32, perm, geo, lam, pkeys, poff,
-                               task, toff, soff, ntasks, longs, nlong, part, G, eps2, acc, pot);
-        else
-            hipLaunchKernelGGL(k_fmm_leaf<false>, grid, block, 0, s, cells, bodies, bodies32, perm, geo, lam, pkeys,
-                               poff, task, toff, soff, ntasks, longs, nlong, part, G, eps2, acc, pot);
+    const auto leaf = bodies32 ? k_fmm_leaf<true> : k_fmm_leaf<false>;
+    for (int64_t first = 0; first < nlong + ntasks; first += kFmmLaunch) {
+        const int64_t tasks = std::min(kFmmLaunch, nlong + ntasks - first);
+        hipLaunchKernelGGL(leaf, dim3((unsigned)((tasks + kFmmWaves - 1) / kFmmWaves)), dim3(kFmmWaves * kWave), 0, s, cells,
+                           bodies, bodies32, perm, geo, lam, pkeys, poff, task, toff, soff, first, ntasks, longs, nlong, part,
+                           G, eps2, acc, pot);
     }
     int64_t fb = (cmax + 3) / 4;
     if (fb > 65536) fb = 65536;

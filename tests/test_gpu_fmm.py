@@ -238,3 +238,27 @@ def test_a_softening_whose_square_overflows(dtype):
     for theta in (0.7, 0.0):
         _, _, acc, pot, _, _ = _gpu_fmm(w.pos.astype(dtype), w.mass.astype(dtype), 16, theta, 1e160)
         assert np.all(acc == 0.0) and np.all(pot == 0.0)
+
+
+def test_more_leaf_tasks_than_a_launch_takes():
+    """1.1M leaves of one body: the leaf tasks go out in two launches, and
+    every body gets its sums (against the FP64 direct sum of a sample; the
+    expansions' truncation is of the order of theta^4, 0.06)."""
+    w = workloads.plummer_sphere(1_100_000, seed=81)
+    dev = torch.device("cuda:0")
+    pos, mass = torch.from_numpy(w.pos).to(dev), torch.from_numpy(w.mass).to(dev)
+    tc = treecode.Treecode(3, leaf_cap=1)
+    tc.build(pos, mass)
+    tc.moments()
+    assert int((tc.cells(moments=False)["leaf"] == 1).sum()) > 1 << 20
+    tc.walk(1.0)
+    acc, _ = tc.forces(0.0, 1e-2)                   # what the library holds is now zero
+    assert not bool(acc.any())
+    tc.fmm_plan(0.5)
+    acc, pot = tc.fmm_forces(1.0, 1e-2)
+    assert bool((acc.abs().sum(1) > 0.0).all()) and bool((pot < 0.0).all())
+    at = torch.from_numpy(workloads.sample_indices(w.n, 2048).astype(np.int32)).to(dev)
+    a, p = tc.direct(at, 1.0, 1e-2)
+    got = acc[at.long()].double()
+    assert float((got - a).norm() / a.norm()) < 0.06
+    assert float((pot[at.long()].double() - p).norm() / p.norm()) < 0.06
