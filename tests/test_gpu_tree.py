@@ -261,3 +261,19 @@ def test_moments_of_leaves_of_every_remainder(dim, sizes):
     t = oracle.Tree(pos, mass, 1)
     assert_tree_equal(g, t)
     assert g["cells"]["count"][g["cells"]["leaf"] == 1].max() > 2000
+
+
+@pytest.mark.parametrize("n,buckets,per,dim,dtype", [
+    (20000, 128, 4, 3, np.float64), (100000, 256, 4, 3, np.float32), (100000, 256, 4, 3, np.float64),
+    (100000, 256, 4, 2, np.float64), (150001, 256, 8, 2, np.float32), (270000, 512, 8, 3, np.float32)])
+def test_a_bucket_beyond_lds_in_every_kernel(n, buckets, per, dim, dtype):
+    """Inputs that the sample misses put nearly all bodies in one bucket, which
+    is sorted in memory: by the kernel of the small and of the large buckets,
+    for records of FP32 and FP64 bodies.  The stable order of the keys, and the
+    bodies themselves (by the leaves' moments)."""
+    pos = _missed_by_the_draw(n, buckets, per, dim).astype(dtype)
+    mass = np.random.default_rng(66).uniform(0.5, 2.0, n).astype(dtype)
+    g = gpu_tree(pos, mass, 16)
+    assert g["status"] == 0
+    t = oracle.Tree(pos.astype(np.float64), mass.astype(np.float64), 16)
+    assert_tree_equal(g, t)
