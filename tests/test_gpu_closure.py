@@ -432,3 +432,35 @@ def test_residuals_under_a_softening_whose_square_overflows(dtype):
     count = tc.cells()["count"][cell.long()]
     assert int(count.max()) > 4096 and int(count.min()) < 128
     assert bool((y == 0.0).all()) and bool(torch.isfinite(feat).all())
+
+
+@pytest.mark.parametrize("nt,dtype", [(600, np.float32), (7, np.float64)])
+def test_residual_pairs_of_cells_that_share_keys(nt, dtype):
+    """Cells past the first 16,128 in level order share 256 keys by target:
+    accepted cells on both sides of that line, more targets than keys and
+    fewer; the bounds are the ones of the oracle's test."""
+    n = 120000
+    w = workloads.plummer_sphere(n, seed=99)
+    tc = treecode.Treecode(3, leaf_cap=4)
+    keep = to_dev(w.pos.astype(dtype)), to_dev(w.mass.astype(dtype))
+    tc.build(*keep)
+    tc.moments()
+    targets = np.random.default_rng(100).permutation(n)[:nt].astype(np.int32)
+    feat, y, cell = (v.cpu().numpy() for v in tc.residuals(0.9, 1e-2, to_dev(targets)))
+    t = oracle.Tree(w.pos, w.mass, 4)
+    # level-order places: by level, pre-order within a level
+    level = tc.cells(moments=False)["level"].cpu().numpy()
+    place = np.empty(len(level), np.int64)
+    place[np.argsort(level, kind="stable")] = np.arange(len(level))
+    past = place[cell] >= 16128
+    assert past.sum() > 3 * nt and (~past).sum() > 3 * nt
+    r = t.residuals(0.9, 1e-2, targets)
+    off = np.concatenate([[0], np.cumsum(r["count"])])
+    assert len(cell) == off[-1]
+    for k in range(nt):
+        a, b = off[k], off[k + 1]
+        og, oo = np.argsort(cell[a:b]), np.argsort(r["cell"][a:b])
+        np.testing.assert_array_equal(cell[a:b][og], r["cell"][a:b][oo])
+        np.testing.assert_allclose(feat[a:b][og], r["feat"][a:b][oo], rtol=1e-6, atol=1e-6)
+        ref = r["y"][a:b][oo]
+        assert np.all(np.abs(y[a:b][og] - ref) <= 1e-6 * np.abs(ref) + 1e-9)
