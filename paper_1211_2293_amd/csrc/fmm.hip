@@ -46,7 +46,6 @@ constexpr double kHalfSqrt3 = 0.8660254037844386;   // sqrt(3)/2, rounded to FP6
 constexpr int kNL = 20;
 
 __device__ __forceinline__ bool is_leaf(const Cell& c) { return c.leaf_nch < 0; }
-__device__ __forceinline__ int nchildren(const Cell& c) { return c.leaf_nch & 0x7fffffff; }
 
 __device__ __forceinline__ uint64_t pair_key(uint32_t a, uint32_t b) { return ((uint64_t)a << 32) | b; }
 
