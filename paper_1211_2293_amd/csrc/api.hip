@@ -527,7 +527,7 @@ int do_forces(tc_ctx* ctx, double G, double eps, float* acc = nullptr, float* po
 
 // Forces for a caller that wants them in acc and pot (each may be null).
 int forces_out(tc_ctx* ctx, double G, double eps, float* acc, float* pot) {
-    if (ctx->n <= kDirectOutMax) return do_forces(ctx, G, eps, acc, pot);
+    if (ctx->n <= direct_out_max(ctx->dim)) return do_forces(ctx, G, eps, acc, pot);
     const int rc = do_forces(ctx, G, eps);
     if (rc != TC_OK) return rc;
     const Layout& l = ctx->lay;

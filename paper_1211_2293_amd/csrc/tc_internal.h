@@ -270,14 +270,16 @@ struct ForceOut {
         if (D == 3) a[2] = z;
     }
 };
-// Up to kDirectOutMax bodies the kernels store into the caller's arrays too;
+// Up to direct_out_max bodies the kernels store into the caller's arrays too;
 // beyond, the arrays are copied: bodies lie in the caller's order, so the
 // stores go to scattered lines, and a second set of these costs more than two
-// copies once the sets outgrow the caches.  Measured (tc_forces, stores / copies,
-// us): 3D 10,000 bodies 57 / 62, 1,048,576 1,694 / 1,702, 4,000,000 (theta 1)
-// 1,917 / 1,892; 2D 262,144 140 / 142, 1,500,000 591 / 594, 3,000,000 1,070 /
-// 1,057 and at theta 0.8 924 / 877.
-constexpr int64_t kDirectOutMax = 3 << 19;
+// copies once the sets outgrow the caches, the sooner the less else the kernel
+// does.  Measured (tc_forces, stores / copies, us): 3D 10,000 bodies 57 / 62,
+// 1,300,000 2,133 / 2,118, 2,000,000 3,262 / 3,234 and at theta 1 1,214 / 1,185,
+// 4,000,000 (theta 1) 1,917 / 1,892; 2D, theta 0.5 and 0.9, 400,000 188 / 192 and
+// 135 / 138, 700,000 289 / 293 and 231 / 231, 1,000,000 420 / 430 and 327 / 316,
+// 2,000,000 758 / 743 and 591 / 570.
+inline int64_t direct_out_max(int dim) { return dim == 3 ? 3 << 19 : 3 << 18; }
 hipError_t launch_walk_force(const WalkCell* walk, const float4* walkq, const Body* bodies, const float4* bodies32,
                              const uint32_t* perm,
                              const int32_t* gbeg, const int32_t* gcnt, int64_t gmax, uint32_t* order,

@@ -331,10 +331,10 @@ def test_shared_walk_shapes(dim, n, lc, theta, order):
     assert oracle.rel_l2(out[1][0], out[0][0]) < 2.0 ** -20 and oracle.rel_l2(out[1][1], out[0][1]) < 2.0 ** -20
 
 
-@pytest.mark.parametrize("dim,n", [(2, 3 << 19), (2, (3 << 19) + 1), (3, (3 << 19) + 1), (3, 4097)])
+@pytest.mark.parametrize("dim,n", [(2, 3 << 18), (2, (3 << 18) + 1), (3, 3 << 19), (3, (3 << 19) + 1), (3, 4097)])
 def test_results_reach_whichever_arrays_are_given(dim, n):
-    """The kernels store into the caller's arrays up to 1,572,864 bodies and
-    the results are copied beyond: the same bits in either array whether both,
+    """The kernels store into the caller's arrays up to 1,572,864 bodies (2D:
+    786,432) and the results are copied beyond: the same bits in either array whether both,
     one or none is given, and in what the diagnostics read."""
     from paper_1211_2293_amd import treecode
     from tests.gpu_util import to_dev
