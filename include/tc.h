@@ -102,7 +102,8 @@ int tc_walk(tc_ctx *ctx, double theta);
  * acceleration G sum m (x_j - x_i) / (|x_j - x_i|^2 + eps^2)^{3/2} and
  * potential -G sum m / (|x_j - x_i|^2 + eps^2)^{1/2} over its group's
  * interaction list (accepted cells as pseudo-bodies, bodies of opened
- * leaves directly, self excluded), FP32 with compensated accumulation.
+ * leaves directly, self excluded): sums of 64 entries in FP32, added in FP64
+ * (tc_set_accumulation).
  * eps > 0 and finite, G finite.  acc ([n][dim] FP32) and pot ([n] FP32)
  * may each be NULL; the results are also kept for tc_leapfrog/tc_diag.
  * Requires tc_walk. */
@@ -116,8 +117,8 @@ int tc_forces(tc_ctx *ctx, double G, double eps, void *acc, void *pot);
  * tc_forces_learned (it supplies a(x), G and eps); the plain walk also
  * requires a tc_walk (its theta), the learned walk a tc_mlp_load, else
  * TC_ESTATE.
- * With tc_set_graph(ctx, 1) everything before the force kernel (about 70
- * short kernels) is recorded once as a HIP graph and replayed: on the
+ * With tc_set_graph(ctx, 1) everything before the force kernel (some 15
+ * short kernels, 55 from 2^21 bodies on) is recorded once as a HIP graph and replayed: on the
  * context's stream if it is a created stream, else (the null stream cannot
  * be recorded) on a stream private to the context, ordered after and before
  * the context's stream by events.  It is recorded again when pos, vel, the
@@ -178,8 +179,8 @@ int tc_lists_forces(tc_ctx *ctx, double G, double eps, uint32_t *lists, int64_t 
  * rho_A and rho_B bounding their bodies about z_A and com_B (a leaf: its
  * farthest body; a cell: the largest centre distance plus radius over its
  * children; capped by the geometric bounds (sqrt 3/2) s and (sqrt 3/2) s +
- * |com - z|); two leaves that are not sum directly (P2P, FP32 with
- * compensated chunks); otherwise the larger cell (smaller level, A on a tie,
+ * |com - z|); two leaves that are not sum directly (P2P, FP32
+ * chunks added in FP64); otherwise the larger cell (smaller level, A on a tie,
  * never a leaf) is split.  Parents pass their expansions down (L2L); each
  * body gets its leaf's expansion (L2P) plus its leaf's direct sums.
  * theta = 0 makes every pair direct: the result is the direct sum. */

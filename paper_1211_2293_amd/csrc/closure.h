@@ -41,7 +41,7 @@ constexpr int kOffB3 = kOffW3 + kNHid * kNOut;       // 5056
 constexpr int kNParam = kOffB3 + kNOut;              // 5059
 
 constexpr int kMlpBatchMax = 65536;                  // samples per training step
-constexpr int kMlpBlock = 64;                        // samples per block (one wave)
+constexpr int kMlpBlock = 64;                        // samples per block (four waves)
 constexpr int kMlpMaxBlocks = kMlpBatchMax / kMlpBlock;
 constexpr int kResidMaxTargets = 65536;
 

@@ -487,7 +487,7 @@ class Treecode:
         _check(lib().tc_set_multipole(self._h, int(order)))
 
     def set_accumulation(self, compensated: bool):
-        """Compensated chunk sums (default) or one plain running FP32 sum."""
+        """Chunk sums added in FP64 (default) or one plain running FP32 sum."""
         _check(lib().tc_set_accumulation(self._h, TC_ACC_COMPENSATED if compensated else TC_ACC_PLAIN))
 
     def set_graph(self, on: bool):
