@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(256) k_resid_order(const int32_t* __restrict__
 // once, each body read once for all of them: those of a cell with more than
 // kPairHuge bodies by a block, of more than kPairLong by a wave; the others go
 // four to a wave on 16 lanes each.  Which way a pair goes, and so the order of
-// its sum, depends on its cell only.  The blocks first take the groups of four
+// its sum, depends on its cell only (and on the system's size: k_resid_small).  The blocks first take the groups of four
 // in the order by cell that hold pairs of huge cells (k_resid_huge lists them),
 // then their waves take the other pairs, kTask at a time; big cells come first.
 // Both are handed out by kQueues counters, each the places of one remainder:
@@ -473,6 +473,18 @@ __global__ void __launch_bounds__(kPairBlock) k_resid_pairs(const Body* __restri
     }
 }
 
+// The features of a pair.
+__device__ __forceinline__ void put_features(float* __restrict__ f, const Sum3& at, const Moments& mo, int level,
+                                             double size, double mbar) {
+    const double s = ldexp(size, -level);
+    const double M = mo.M;
+    f[0] = (float)((at.x - mo.com[0]) / s);
+    f[1] = (float)((at.y - mo.com[1]) / s);
+    f[2] = (float)((at.z - mo.com[2]) / s);
+    for (int q = 0; q < 6; ++q) f[3 + q] = (float)(mo.Q[q] / (M * s * s));
+    f[9] = (float)log(M / mbar);
+}
+
 // The features, one block per target.
 __global__ void __launch_bounds__(256) k_resid_features(const Body* __restrict__ bodies,
                                                         const Cell* __restrict__ cells,
@@ -492,16 +504,47 @@ __global__ void __launch_bounds__(256) k_resid_features(const Body* __restrict__
     const double size = prm->size;
     for (; k < e; k += blockDim.x) {
         const int64_t kc = cell_out[k];
-        const Moments& mo = mom[kc];
-        const double s = ldexp(size, -cells[kc].level);
-        const double M = mo.M;
-        float* f = feat + k * 10;
-        f[0] = (float)((me.x - mo.com[0]) / s);
-        f[1] = (float)((me.y - mo.com[1]) / s);
-        f[2] = (float)((me.z - mo.com[2]) / s);
-        for (int q = 0; q < 6; ++q) f[3 + q] = (float)(mo.Q[q] / (M * s * s));
-        f[9] = (float)log(M / mbar);
+        put_features(feat + k * 10, {me.x, me.y, me.z}, mom[kc], cells[kc].level, size, mbar);
     }
+}
+
+// The smallest systems' pairs in one launch: a wave per target, a lane per
+// accepted cell and its few bodies, in order.  Bound by latency and launches; by
+// way of the order by cell 50 bodies and one target took 95 us, 48 so (kResidSmall).
+__global__ void __launch_bounds__(256) k_resid_small(const WalkCell* __restrict__ walk, const Body* __restrict__ bodies,
+                                                     const Cell* __restrict__ cells, const Moments* __restrict__ mom,
+                                                     const uint32_t* __restrict__ bfs2pre,
+                                                     const uint32_t* __restrict__ inv_perm,
+                                                     const DevParams* __restrict__ prm, int64_t n,
+                                                     const int32_t* __restrict__ targets, int nt, double eps2,
+                                                     const uint32_t* __restrict__ offs, int64_t cap,
+                                                     float* __restrict__ feat, float* __restrict__ yout,
+                                                     int32_t* __restrict__ cell_out) {
+    __shared__ uint32_t s_stack[4][kStack];
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+    const int t = blockIdx.x * 4 + wv;
+    if (t >= nt) return;
+    int64_t k = offs[t];
+    if ((int64_t)offs[t + 1] == k || k >= cap) return;   // no pairs (an index outside the bodies has none)
+    const Body me = bodies[inv_perm[targets[t]]];
+    const double mbar = mom[0].M / (double)n, size = prm->size;
+    walk_point(walk, s_stack[wv], me.x, me.y, me.z, [&](bool accept, uint32_t b) {
+        const uint64_t A = __ballot(accept);
+        const int64_t at = k + __popcll(A & below);
+        if (accept && at < cap) {
+            const int kc = (int)bfs2pre[b];
+            const Cell c = cells[kc];
+            const Pair p = {at, kc, c.begin, c.count, c.level, {me.x, me.y, me.z}};
+            Sum3 r = {0.0, 0.0, 0.0};
+#pragma unroll 4
+            for (int64_t j = c.begin; j < (int64_t)c.begin + c.count; ++j) add_body(r, bodies[j], me.x, me.y, me.z, eps2);
+            put_pair(p, r, mom, size, eps2, yout);
+            put_features(feat + at * 10, p.at, mom[kc], c.level, size, mbar);
+            cell_out[at] = kc;
+        }
+        k += __popcll(A);
+    });
 }
 
 __global__ void k_inverse_perm(const uint32_t* __restrict__ perm, int64_t n, uint32_t* __restrict__ inv) {
@@ -865,6 +908,12 @@ hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const fl
                               uint32_t* key_part, uint32_t* ctr, float* feat, float* y, int32_t* cell_out,
                               hipStream_t s) {
     if (cap <= 0) return hipSuccess;
+    if (n <= kResidSmall) {
+        hipLaunchKernelGGL(k_resid_small, dim3((unsigned)((nt + 3) / 4)), dim3(256), 0, s, walk, bodies, cells, mom,
+                           bfs2pre, inv_perm, (const DevParams*)prm, n, targets, nt, eps2, offs, cap, feat, y,
+                           cell_out);
+        return hipGetLastError();
+    }
     const bool cold = cmax > kResidKeys;
     const int64_t nkeys = cold ? kResidKeys : cmax;
     const uint32_t hot = (uint32_t)(cold ? nkeys - kResidColdKeys : nkeys);

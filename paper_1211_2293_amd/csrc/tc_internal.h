@@ -375,6 +375,11 @@ hipError_t launch_resid_count(const WalkCell* walk, const Body* bodies, const ui
 // ms with 2,048 keys, 2.21 with 4,096, 1.98 with 16,384).
 constexpr int64_t kResidKeys = 16384;
 constexpr uint32_t kResidColdKeys = 256;
+// Up to kResidSmall bodies the pairs are one launch instead of seven (us for a
+// call of 1, 128 and all targets, theta 0.9, seven / one: 100 bodies 94, 99, 99 /
+// 53, 60, 60; 800: 97, 108, 144 / 62, 113, 106; 1,200: 97, 109, 173 / 66, 110, 125;
+// 2,000: 99, 117, 273 / 80, 181, 248).
+constexpr int64_t kResidSmall = 1024;
 hipError_t launch_resid_pairs(const WalkCell* walk, const Body* bodies, const float4* bodies32, const Cell* cells, const Moments* mom,
                               const uint32_t* bfs2pre, const uint32_t* pre2bfs, const uint32_t* inv_perm,
                               DevParams* prm, int64_t n, int64_t cmax, const int32_t* targets, int nt, double eps2,

@@ -464,3 +464,47 @@ def test_residual_pairs_of_cells_that_share_keys(nt, dtype):
         np.testing.assert_allclose(feat[a:b][og], r["feat"][a:b][oo], rtol=1e-6, atol=1e-6)
         ref = r["y"][a:b][oo]
         assert np.all(np.abs(y[a:b][og] - ref) <= 1e-6 * np.abs(ref) + 1e-9)
+
+
+@pytest.mark.parametrize("n", [1, 2, 40, 1023, 1024, 1025])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_residual_pairs_of_the_smallest_systems(n, dtype):
+    """Both sides of the size up to which the pairs take one launch: pairs,
+    features and residuals against the oracle, arrays that hold a part of the
+    pairs, what lies past them, and targets outside the bodies."""
+    w = workloads.plummer_sphere(n, seed=101)
+    tc = treecode.Treecode(3, leaf_cap=2)
+    keep = to_dev(w.pos.astype(dtype)), to_dev(w.mass.astype(dtype))
+    tc.build(*keep)
+    tc.moments()
+    targets = np.random.default_rng(102).integers(0, n, min(n, 70)).astype(np.int32)
+    full = tc.residuals(0.8, 1e-2, to_dev(targets))
+    r = oracle.Tree(w.pos, w.mass, 2).residuals(0.8, 1e-2, targets)
+    off = np.concatenate([[0], np.cumsum(r["count"])])
+    assert len(full[2]) == off[-1]
+    feat, y, cell = (v.cpu().numpy() for v in full)
+    for k in range(len(targets)):
+        a, b = off[k], off[k + 1]
+        og, oo = np.argsort(cell[a:b]), np.argsort(r["cell"][a:b])
+        np.testing.assert_array_equal(cell[a:b][og], r["cell"][a:b][oo])
+        np.testing.assert_allclose(feat[a:b][og], r["feat"][a:b][oo], rtol=1e-6, atol=1e-6)
+        ref = r["y"][a:b][oo]
+        assert np.all(np.abs(y[a:b][og] - ref) <= 1e-6 * np.abs(ref) + 1e-9)
+    if off[-1] < 2:
+        return
+    cap = int(off[-1]) // 2 + 1
+    spare = [torch.full((cap + 7, *t.shape[1:]), 7, dtype=t.dtype, device="cuda") for t in full]
+    n_out = C.c_int64()
+    assert treecode.lib().tc_residuals(tc._h, 0.8, 1e-2, to_dev(targets).data_ptr(), len(targets),
+                                       *(t.data_ptr() for t in spare), cap, C.byref(n_out)) == 0
+    torch.cuda.synchronize()
+    assert n_out.value == off[-1]
+    for t, u in zip(spare, full):
+        assert torch.equal(t[:cap], u[:cap]) and bool((t[cap:] == 7).all())
+    bad = targets.copy()
+    bad[[0, -1]] = (-1, n)
+    got = tc.residuals(0.8, 1e-2, to_dev(bad))
+    assert tc.status() == treecode.TC_EINVAL
+    mid = slice(int(off[1]), int(off[-2]))
+    for t, u in zip(got, full):
+        assert torch.equal(t, u[mid])
