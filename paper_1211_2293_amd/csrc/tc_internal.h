@@ -88,7 +88,11 @@ struct DevParams {
 // cells within a block and the cells above them level by level: smaller
 // subtrees leave more blocks per CU, larger ones fewer cells above (which one
 // block does, except in the largest trees).  Measured (both kernels, 128 / 256
-// cells): 36 / 39 us at 50,000 bodies, 102 / 88 at 1M, 718 / 795 at 16.7M.
+// cells): 36 / 38 us at 50,000 bodies, 38 / 40 at 100,000, 42 / 42 at 200,000, 45 / 43
+// at 230,000 (2^19 slots are 235,000 bodies in leaves of 16), 47 / 50 at 300,000, 61 /
+// 56 at 500,000, 101 / 88 at 1M, 146 / 142 at 1.8M; 135 / 140 at 2M (past 2^22 slots,
+// where the levels above get launches of their own), 169 / 183 at 3M, 726 / 790 at
+// 16.7M; 2D 33 / 31 at 300,000, 81 / 75 at 1.4M, 117 / 123 at 3M.
 inline int subtree_cells(int64_t cmax) {
     return cmax < (int64_t)1 << 19 || cmax >= (int64_t)1 << 22 ? 128 : 256;
 }
