@@ -933,7 +933,11 @@ int tc_leapfrog(tc_ctx* ctx, double dt, void* pos, void* vel) {
     if (ctx->closure ? !ctx->mlp_loaded : !ctx->theta_set) return TC_ESTATE;
     int rc = ctx->use_graph ? pre_force_graph(ctx, dt, pos, vel) : enqueue_pre_force(ctx, dt, pos, vel, ctx->stream);
     if (rc != TC_OK) return rc;
+    // what enqueue_pre_force leaves, also where a graph did its work
     ctx->state = kWalked;
+    ctx->fmm_planned = false;
+    ctx->pb_counted = false;
+    ctx->radii_plain = !ctx->closure;
     rc = ctx->closure ? do_forces_learned(ctx, ctx->G, ctx->eps, ctx->cl_tau) : do_forces(ctx, ctx->G, ctx->eps);
     if (rc != TC_OK) return rc;
     StageScope st_(ctx, TC_STAGE_KICK, ctx->stream);

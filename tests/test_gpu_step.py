@@ -231,3 +231,40 @@ def test_folded_kick_and_drift_equal_the_launch_of_their_own(dim, n, dtype):
     for a, b in zip(folded, own):
         assert torch.equal(a, b)
     assert not np.array_equal(folded[0].cpu().numpy(), w.pos.astype(dtype))
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_a_step_ends_what_was_prepared_for_the_tree_before(graph):
+    """A step rebuilds the tree, also when a recorded graph is replayed: a
+    multipole plan and counted lists are of the tree before and are refused, and
+    forces after learned steps are the plain walk's at its own radii."""
+    from oracle import mlp
+    w = workloads.plummer_sphere(4000, seed=77)
+    pos, vel, mass = to_dev(w.pos), to_dev(w.vel), to_dev(w.mass)
+    tc = treecode.Treecode(3, leaf_cap=16)
+    tc.set_graph(graph)
+    tc.build(pos, mass)
+    tc.moments()
+    tc.mlp_load(to_dev(mlp.init_params(seed=11)))
+    tc.walk(0.5)
+    tc.forces(1.0, 1e-2)
+    tc.leapfrog(1e-3, pos, vel)                   # records the graph
+    tc.fmm_plan(0.6)
+    total, _ = tc.lists_count()
+    lists = torch.empty(2 * total, dtype=torch.int32, device="cuda")
+    tc.leapfrog(1e-3, pos, vel)                   # replays it
+    for stale in (lambda: tc.fmm_forces(), lambda: tc.lists_forces(lists=lists)):
+        with pytest.raises(treecode.TcError):
+            stale()
+    tc.set_closure(0.9, 0.5, 1e9)
+    tc.leapfrog(1e-3, pos, vel)
+    tc.walk(0.5)
+    tc.forces(1.0, 1e-2)
+    tc.leapfrog(1e-3, pos, vel)
+    acc, pot = tc.forces(1.0, 1e-2)
+    fresh = treecode.Treecode(3, leaf_cap=16)
+    fresh.build(pos, mass)
+    fresh.moments()
+    fresh.walk(0.5)
+    ref, rpot = fresh.forces(1.0, 1e-2)
+    assert torch.equal(acc, ref) and torch.equal(pot, rpot)
