@@ -1316,7 +1316,7 @@ __global__ void __launch_bounds__(2 * SUB) __attribute__((amdgpu_waves_per_eu(4,
     }
 }
 
-// The cells above, levels hi down to lo, from their lists, in one block (a
+// The cells above, from their lists: levels hi down to lo in one block (a
 // barrier separates the levels, and the block's waves share one CU's L1), or
 // one level in any number of blocks.  A round takes up to kUpperCells cells of
 // a level: their children's moments are
@@ -1334,21 +1334,54 @@ constexpr int kUpperTable = 640;
 // / 169, 16.7M clustered 1,577 / 723).
 constexpr int64_t kUpperSplit = (int64_t)1 << 22;
 
+// Stages of a large tree: of kUpperWide<D> consecutive levels each has a launch
+// of many blocks (stages 1 ..); the levels below these (stage 0) and above (the last
+// stage) are one block's.  Stage 0 chooses them by the counts: those with the
+// most cells beyond a round's, and the deepest of several such choices, as a level
+// of one round is cheaper in the last stage.  Against levels 12 to 4 (2D 16 to 6)
+// for every tree, us for the moments: 2D, 4M bodies in a compact cluster of a wide
+// square 276 / 183, 10M 646 / 323, 3D 10M 3,350 / 2,726, 16.7M clustered 728 / 715;
+// where the levels stay, 2D 3M 138 / 141, 3D 3M 205 / 205.  Chosen by each launch
+// for itself: 158 and 215.  Stage -1: all levels, in one block.
+template <int D>
+constexpr int kUpperWide = D == 3 ? 9 : 11;
+
 template <int D>
 __global__ void __launch_bounds__(kUpperThreads) k_moments_upper(const Cell* __restrict__ cells,
                                                                  const uint32_t* __restrict__ pre2bfs,
                                                                  const uint32_t* __restrict__ bfs2pre, BigList big,
-                                                                 int hi, int lo, Moments* mom,
+                                                                 int stage, Moments* mom,
                                                                  WalkCell* __restrict__ walk) {
-    constexpr int N = 1 << D;
+    constexpr int N = 1 << D, L = D == 3 ? 21 : 31, W = kUpperWide<D>;
+    static_assert(L < kLevels && kLevels <= 32, "a level's number has five bits");
     __shared__ double s_mom[kUpperCells * N][kMomDoubles];
     __shared__ uint32_t s_ch[kUpperTable][N];
     __shared__ uint32_t s_k[kUpperTable], s_first[kUpperTable], s_at[kUpperTable];
     __shared__ int32_t s_nch[kUpperTable];
-    __shared__ uint32_t s_n[kLevels];
+    __shared__ uint32_t s_n[kLevels], s_wide;
     const uint32_t t = threadIdx.x;
+    int hi = L, lo = 0;
+    if (stage > 0) {
+        const int wide = (int)big.count[BigList::kWide];     // the deepest of them
+        hi = stage <= W ? wide - stage + 1 : wide - W;
+        if (stage <= W) lo = hi;
+        if (hi < 0) return;
+    }
     if (t < kLevels) s_n[t] = min(big.count[t * BigList::kStride], big.cap);
+    if (t == 0) s_wide = 0u;
     __syncthreads();
+    if (stage == 0) {
+        // the cells beyond a round of the W levels up from t (fewer than 2^27), and t
+        if (t <= L) {
+            uint32_t n = 0;
+            for (int l = max(0, (int)t - W + 1); l <= (int)t; ++l) n += s_n[l] - min(s_n[l], (uint32_t)kUpperCells);
+            atomicMax(&s_wide, n << 5 | t);
+        }
+        __syncthreads();
+        lo = (int)(s_wide & 31u) + 1;
+        if (t == 0) big.count[BigList::kWide] = (uint32_t)(lo - 1);
+        if (hi < lo) return;
+    }
     // cell i of level l into the table
     auto look_up = [&](uint32_t slot, int l, uint32_t i) {
         const uint32_t k = big.cell[(size_t)l * big.cap + i];
@@ -1724,7 +1757,6 @@ template <int D>
 static void moments(const Cell* cells, const Body* bodies, int64_t cmax, const uint32_t* bfs2pre,
                     const uint32_t* pre2bfs, const BigList& big, const DevParams* prm, Moments* mom, WalkCell* walk,
                     hipStream_t s) {
-    constexpr int L = D == 3 ? 21 : 31;
     const unsigned nb = (unsigned)std::min<int64_t>((cmax + big.sub - 1) / big.sub, 16384);
     if (big.sub == 128)
         hipLaunchKernelGGL((k_moments_low<D, 128>), dim3(nb), dim3(256), 0, s, cells, bodies, pre2bfs, prm, cmax, mom,
@@ -1732,21 +1764,17 @@ static void moments(const Cell* cells, const Body* bodies, int64_t cmax, const u
     else
         hipLaunchKernelGGL((k_moments_low<D, 256>), dim3(nb), dim3(512), 0, s, cells, bodies, pre2bfs, prm, cmax, mom,
                            walk);
-    auto upper = [&](int hi, int lo, unsigned nb) {
-        hipLaunchKernelGGL(k_moments_upper<D>, dim3(nb), dim3(kUpperThreads), 0, s, cells, pre2bfs, bfs2pre, big, hi,
-                           lo, mom, walk);
+    auto upper = [&](int stage, unsigned nb) {
+        hipLaunchKernelGGL(k_moments_upper<D>, dim3(nb), dim3(kUpperThreads), 0, s, cells, pre2bfs, bfs2pre, big, stage,
+                           mom, walk);
     };
     if (cmax < kUpperSplit) {
-        upper(L, 0, 1);
+        upper(-1, 1);
         return;
     }
-    // large trees: the middle levels, which hold nearly all, by many blocks (a
-    // level less at the deep end and one more at the top: 814 against 723 us for
-    // 16.7M clustered bodies; the other way round 124 against 118 for 3M in 2D)
-    constexpr int kTop = D == 3 ? 3 : 5, kDeep = D == 3 ? 13 : 17;
-    upper(L, kDeep, 1);
-    for (int l = kDeep - 1; l > kTop; --l) upper(l, l, (unsigned)std::min<int64_t>(256, big.cap / kUpperCells + 1));
-    upper(kTop, 0, 1);
+    constexpr int W = kUpperWide<D>;
+    for (int stage = 0; stage <= W + 1; ++stage)
+        upper(stage, stage == 0 || stage > W ? 1u : (unsigned)std::min<int64_t>(256, big.cap / kUpperCells + 1));
 }
 
 hipError_t launch_moments(const Cell* cells, const Body* bodies, int dim, int64_t cmax, const uint32_t* bfs2pre,

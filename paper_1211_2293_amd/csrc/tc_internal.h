@@ -102,6 +102,7 @@ constexpr int kSubtreeMin = 128;
 constexpr int kLevels = 32;                      // levels 0..21 in 3D, 0..31 in 2D
 struct BigList {
     static constexpr int kStride = 32;           // counters 128 B apart (own cache lines)
+    static constexpr int kWide = 1;              // beside the first: the moments' window of levels
     uint32_t* count;                             // [kLevels * kStride]
     uint32_t* cell;                              // [kLevels][cap]: pre-order indices
     uint32_t cap;

@@ -263,6 +263,26 @@ def test_moments_of_leaves_of_every_remainder(dim, sizes):
     assert g["cells"]["count"][g["cells"]["leaf"] == 1].max() > 2000
 
 
+@pytest.mark.parametrize("dim,n", [(3, 380000), (2, 270000)])
+@pytest.mark.parametrize("case", ["shallow", "deep", "deepest", "one place"])
+def test_moments_wherever_the_levels_lie(dim, n, case):
+    """Trees of a size that has the moments of the levels with the most cells
+    in launches of their own (2^22 cell slots and more), with these levels near the
+    root, in the middle, at the deepest level, and with no such level at all."""
+    rng = np.random.default_rng(67)
+    pos = rng.uniform(-1.0, 1.0, (n, dim))
+    if case == "deep":
+        pos[8:] *= 1e-4
+    elif case == "deepest":                           # pairs that no cell parts
+        pos[1::2] = pos[::2]
+    elif case == "one place":
+        pos[8:] = pos[8]
+    mass = rng.uniform(0.5, 2.0, n)
+    g = gpu_tree(pos, mass, 1)
+    assert g["status"] == 0
+    assert_tree_equal(g, oracle.Tree(pos, mass, 1))
+
+
 @pytest.mark.parametrize("n,buckets,per,dim,dtype", [
     (20000, 128, 4, 3, np.float64), (100000, 256, 4, 3, np.float32), (100000, 256, 4, 3, np.float64),
     (100000, 256, 4, 2, np.float64), (150001, 256, 8, 2, np.float32), (270000, 512, 8, 3, np.float32)])
