@@ -319,8 +319,9 @@ inline int64_t split_max_n(int dim) { return dim == 3 ? kSplitMaxN3 : kSplitMaxN
 //   3D cube, theta 0.5: 592 / 593 at 524,288; theta 0.7: 236 / 235 at 330,000,
 //     337 / 369 at 524,288; theta 1: 128 / 124 at 200,000, 246 / 283 at 524,288;
 //   quadrupoles, Plummer and cube, theta 0.3: 4,993 / 4,383 and 2,263 / 2,277 at
-//     524,288; theta 0.5: 1,186 / 1,169 and 646 / 668 at 400,000; theta 0.7: 476 / 451 and 236 / 246 at 262,144; theta 1: 270 / 252
-//     and 170 / 157 at 200,000, 363 / 386 and 230 / 238 at 330,000;
+//     524,288; theta 0.5: 1,186 / 1,169 and 646 / 668 at 400,000; theta 0.7: 476 /
+//     451 and 236 / 246 at 262,144; theta 1: 270 / 252 and 170 / 157 at 200,000,
+//     363 / 386 and 230 / 238 at 330,000;
 //   2D disk: 107 / 85 at 163,840 (theta 0.5) and 79 / 68 (theta 1), 115 / 143
 //     at 262,144.
 // tc_set_split(ctx, 0) turns it off; tc_set_split(ctx, 2) uses the split walks
